@@ -286,16 +286,17 @@ GSBC_API gsbc_status gsbc_encode(gsbc_ctx *ctx, const uint8_t *textures, gsbc_st
 /* Work distribution of gsbc_encode_batch.  Every setting gives the same
  * bits: each block is coded on its own and every decision is a fixed
  * integer computation (results do not depend on launch shapes).
- *   item_rounds  256-block rounds per work item, 1..64
- *   wgs_per_cu   0: one workgroup per item (a plain grid); 1..16: that many
- *                persistent workgroups per compute unit pop items from a
- *                device counter until none are left
+ *   item_rounds  size of a work item, 1..64: 256-block rounds per item (BC1),
+ *                a multiple of the default window of blocks (BC7 search)
+ *   wgs_per_cu   0: one workgroup per item (a plain grid; BC7 search: per
+ *                four items); 1..16: that many persistent workgroups per
+ *                compute unit pop items from a device counter until none are
+ *                left
  *   bc1_lanes    BC1 workgroup size: 64, 128 or 256
  *   bc7_split    BC7 candidate groups per search kernel: 0 = three kernels
  *                (2-subset, 3-subset, 1-subset modes), 1 = two (the 3- and
- *                1-subset modes together), 2 = one kernel running all
- *                groups per block, 3 = one kernel whose work items are
- *                (group, rounds) pairs, heavy groups first
+ *                1-subset modes together), 2 or 3 = one kernel for every
+ *                group, heavy groups first
  *   concurrent   1: the BC1 blocks run on a second stream beside the BC7
  *                blocks; 0: after them on the context's stream */
 typedef struct {

@@ -276,8 +276,8 @@ long rate_units(double rate, uint32_t S)
 }
 
 // Default work split of the single-scene calls: one workgroup per 256-block
-// round, BC1 on 128-lane workgroups, one BC7 search launch whose work items
-// are (candidate group, round) pairs.
+// round, BC1 on 128-lane workgroups, one BC7 search launch over every
+// candidate group.
 constexpr WorkSplit kPlainSplit = {1, 0, nullptr};
 constexpr uint32_t kPlainBc1Lanes = 128;
 constexpr uint32_t kPlainBc7Split = 3;
@@ -710,36 +710,39 @@ gsbc_status gsbc_encode(gsbc_ctx *ctx, const uint8_t *textures, gsbc_stream_desc
     a.mode_mask = p.bc7_mode_mask;
     a.keys = reinterpret_cast<uint32_t *>(arena + front + 2 * kRunTableBytes);
     const WorkSplit w3[3] = {kPlainSplit, kPlainSplit, kPlainSplit};
-    // With both formats: the BC7 search runs alone on the context's stream
-    // (its device time is its own), then the BC1 encoder runs on a side
-    // stream beside the short, latency-bound BC7 bucketing and emit kernels,
-    // joined before anything reads either format's results.  While kernel
-    // timing is on, everything stays on the context's stream, one kernel
-    // after another, so each timed kernel has the GPU to itself.
+    // With both formats the BC1 encoder runs on a side stream beside the BC7
+    // kernels, from the start: each kernel's last, nearly empty wave of
+    // workgroups is then filled by the other format's work.  Joined before
+    // anything reads either format's results.  While kernel timing is on,
+    // everything stays on the context's stream, one kernel after another, so
+    // each timed kernel has the GPU to itself.
     hipStream_t s1 = ctx->stream;
-    const bool both = have1 && have7 && !ctx->profiling;
-    if (both) {
+    if (have1 && have7 && !ctx->profiling) {
         if ((s = ensure_side(ctx))) return s;
         s1 = ctx->side;
+        HIP_TRY(ctx, hipEventRecord(ctx->fork, ctx->stream), "fork");
+        HIP_TRY(ctx, hipStreamWaitEvent(s1, ctx->fork, 0), "fork");
     }
-    if (have7) {
-        a.run = druns7;
-        a.nrun = (uint32_t)r7.v.size();
-        a.total = r7.total;
-        HIP_TRY(ctx, launch_bc7_encode(a, w3, kPlainBc7Split, ctx->stream, both ? ctx->fork : nullptr), "bc7 launch");
-    }
+    hipError_t e1 = hipSuccess, e7 = hipSuccess;
     if (have1) {
         EncodeArgs a1 = a;
         a1.run = druns1;
         a1.nrun = (uint32_t)r1.v.size();
         a1.total = r1.total;
-        if (both) HIP_TRY(ctx, hipStreamWaitEvent(s1, ctx->fork, 0), "fork");
-        HIP_TRY(ctx, launch_bc1_encode(a1, kPlainSplit, kPlainBc1Lanes, s1), "bc1 launch");
+        e1 = launch_bc1_encode(a1, kPlainSplit, kPlainBc1Lanes, s1);
     }
-    if (s1 != ctx->stream) {
+    if (have7 && e1 == hipSuccess) {
+        a.run = druns7;
+        a.nrun = (uint32_t)r7.v.size();
+        a.total = r7.total;
+        e7 = launch_bc7_encode(a, w3, kPlainBc7Split, ctx->stream);
+    }
+    if (s1 != ctx->stream) {   // also after a failed launch: the side stream's work reads this call's buffers
         HIP_TRY(ctx, hipEventRecord(ctx->join, s1), "join");
         HIP_TRY(ctx, hipStreamWaitEvent(ctx->stream, ctx->join, 0), "join");
     }
+    HIP_TRY(ctx, e1, "bc1 launch");
+    HIP_TRY(ctx, e7, "bc7 launch");
     if (autoc) {
         uint64_t *doff1 = reinterpret_cast<uint64_t *>(small_ptr(ctx, kOff1Off));
         uint64_t *doff7 = reinterpret_cast<uint64_t *>(small_ptr(ctx, kOff7Off));

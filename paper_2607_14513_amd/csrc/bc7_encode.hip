@@ -13,11 +13,12 @@
 // (SSE << 9) | candidate, a total order, so the result is independent of how
 // candidates are spread over lanes.
 //
-// Layout on the GPU: one lane per block, all lanes of a wave walk the
-// candidates in the same order, so partition masks, anchors and mode
-// parameters are wave-uniform (scalar registers) and only the texel
-// arithmetic is per lane.  Pass 1 keeps only the best key; pass 2 re-fits
-// each lane's winner (identical arithmetic) to emit its bits.
+// Layout on the GPU: one lane per block, all lanes of a wave work on the same
+// candidate, so partition masks, anchors and mode parameters are wave-uniform
+// (scalar registers) and only the texel arithmetic is per lane.  Pass 1 keeps
+// only the best key, and fits a block's candidate only if a lower bound of
+// its SSE leaves it a chance; pass 2 re-fits each lane's winner (identical
+// arithmetic) to emit its bits.
 #include "gsbc_internal.h"
 #include "bc_format.h"
 
@@ -56,13 +57,17 @@ __host__ __device__ constexpr int ep_value(int code, int p, int cb, int pb)
 __device__ __forceinline__ int bitlen(int x) { return 32 - __clz(x); }
 
 // ---- candidate geometry
-__device__ __forceinline__ uint32_t mask3(int p, int s)
+// Members of subset s of 3-subset partition p: the 2-bit map's low bits (1),
+// high bits (2) or neither (0), brought together from every second bit.
+__host__ __device__ constexpr uint32_t mask3_of(uint32_t map, int s)
 {
-    uint32_t w = kPart3[p], m = 0;
-#pragma unroll
-    for (int i = 0; i < 16; i++) m |= (((w >> (2 * i)) & 3) == (uint32_t)s ? 1u : 0u) << i;
-    return m;
+    uint32_t x = (s == 0 ? ~(map | map >> 1) : s == 1 ? map : map >> 1) & 0x55555555u;
+    x = (x | x >> 1) & 0x33333333u;
+    x = (x | x >> 2) & 0x0F0F0F0Fu;
+    x = (x | x >> 4) & 0x00FF00FFu;
+    return (x | x >> 8) & 0xFFFFu;
 }
+__device__ __forceinline__ uint32_t mask3(int p, int s) { return mask3_of(kPart3[p], s); }
 __device__ __forceinline__ uint32_t mask2(int p, int s)
 {
     uint32_t w = kPart2[p];
@@ -578,9 +583,12 @@ __device__ __forceinline__ PairFit fit_colour(const TexLds &S, uint32_t mask, in
         f.idx = 0;
         f.c0 = f.c1 = 0;
         f.p0 = f.p1 = 0;
+        // (rolled: unrolled, the rows' addresses fill the scalar registers)
+#pragma unroll 1
         for (int pc = 0; pc < NPC; pc++) {
             const int p0 = PB == 2 ? (pc & 1) : PB == 1 ? pc : 0;
             const int p1 = PB == 2 ? (pc >> 1) : PB == 1 ? pc : 0;
+#pragma unroll 1
             for (int k = 0; k < (1 << NB); k++) {
                 const uint32_t *row = sv + ((uint64_t)(cls * 4 + p0 + 2 * p1) * kSlots + slot_of(NB, k)) * 256;
                 uint32_t e = 0, c0 = 0, c1 = 0;
@@ -652,6 +660,7 @@ __device__ __forceinline__ PairFit fit_scalar(const TexLds &S, int rot, const ui
     best.c0 = best.c1 = 0;
     best.p0 = best.p1 = 0;
     if (same) {
+#pragma unroll 1
         for (int k = 0; k < (1 << NB); k++) {
             const uint32_t ent = sv[((uint64_t)(cls * 4) * kSlots + slot_of(NB, k)) * 256 + (-v0)];
             const uint32_t er = ent >> 16;
@@ -723,175 +732,75 @@ __device__ __forceinline__ void anchor_fix(PairFit &f, uint32_t mask, int anchor
     f.idx ^= spread;   // k -> (2^NB - 1) - k on the members
 }
 
-// ---- visiting order of the 3-subset partitions
+// ---- the candidates of one partition shape
 //
-// Of the 192 subset masks of the 64 three-subset partitions only 140 differ
-// (36 of the 48 of partitions 0..15, the ones mode 0 also uses).  The search
-// visits the partitions in the order below; a mask that recurs is fitted
-// once and its SSE kept in an LDS slot of its lane until its last use.  This
-// order (found offline by a local search) needs at most kSlots2 slots for
-// mode 2 and kSlots0 for mode 0; a static check below recomputes both.
-constexpr int kOrder3[64] = {62, 9,  2,  0,  60, 42, 61, 27, 38, 18, 46, 33, 51, 47, 55, 41,
-                             31, 17, 63, 15, 23, 10, 36, 22, 8,  56, 29, 4,  3,  24, 6,  32,
-                             25, 19, 14, 37, 34, 7,  26, 43, 52, 5,  54, 50, 20, 48, 1,  39,
-                             58, 13, 35, 57, 53, 30, 21, 59, 49, 40, 28, 45, 16, 11, 44, 12};
-constexpr int kSlots2 = 6, kSlots0 = 4;
-
-__host__ __device__ constexpr uint32_t mask3_of(int p, int s)
-{
-    uint32_t m = 0;
-    for (int i = 0; i < 16; i++) m |= (((kPart3[p] >> (2 * i)) & 3) == (uint32_t)s ? 1u : 0u) << i;
-    return m;
-}
-
-// What the search does at visit t (partition kOrder3[t]), subset s, per mode:
-//   kFit           fit the subset
-//   kKeep | slot   fit it and keep the SSE in the slot (the mask recurs)
-//   kTake | slot   take the SSE from the slot (fitted at an earlier visit)
-constexpr uint8_t kFit = 0, kKeep = 0x40, kTake = 0x80;
-struct Plan3 {
-    uint8_t act[2][64][3];   // [0]: mode 2 (all partitions), [1]: mode 0 (partitions 0..15)
-    int slots[2];            // slots each mode needs
-};
-
-constexpr Plan3 make_plan3()
-{
-    Plan3 P{};
-    for (int mode = 0; mode < 2; mode++) {
-        // each visit's mask, then its last visit
-        uint32_t mk[192] = {};
-        int pos[192] = {}, n = 0;
-        for (int t = 0; t < 64; t++)
-            for (int s = 0; s < 3; s++)
-                if (mode == 0 || kOrder3[t] < 16) { mk[n] = mask3_of(kOrder3[t], s); pos[n] = t * 3 + s; n++; }
-        bool used[8] = {};
-        uint32_t held[8] = {};
-        int most = 0;
-        for (int q = 0; q < n; q++) {
-            int later = -1, slot = -1;
-            for (int r = q + 1; r < n; r++)
-                if (mk[r] == mk[q]) { later = r; break; }
-            for (int z = 0; z < 8; z++)
-                if (used[z] && held[z] == mk[q]) slot = z;
-            uint8_t a = kFit;
-            if (slot >= 0) {
-                a = (uint8_t)(kTake | slot);
-                if (later < 0) used[slot] = false;   // last use
-            } else if (later >= 0) {
-                int z = 0;
-                while (used[z]) z++;
-                used[z] = true;
-                held[z] = mk[q];
-                a = (uint8_t)(kKeep | z);
-                int live = 0;
-                for (int y = 0; y < 8; y++) live += used[y] ? 1 : 0;
-                most = live > most ? live : most;
-            }
-            P.act[mode][pos[q] / 3][pos[q] % 3] = a;
-        }
-        P.slots[mode] = most;
-    }
-    return P;
-}
-constexpr Plan3 kPlan3 = make_plan3();
-static_assert(kPlan3.slots[0] <= kSlots2 && kPlan3.slots[1] <= kSlots0, "3-subset visiting order needs more slots");
-
-// ---- pass 1: best key over one candidate group
-//
-// The principal axis and the extreme texels of a subset depend only on the
-// partition, so they are found once and shared by every mode with that
-// partition.  The candidates fall into three groups by partition shape; each
-// group is its own kernel (smaller register footprint), and the block's key
-// is the minimum over the groups.
+// Best key of one block over the modes of `mode_mask` that use a partition:
+// the principal axis and the extreme texels of a subset depend only on the
+// partition, so they are found once and shared by its modes.  A wave's lanes
+// hold different blocks; the masks are wave-uniform in the search (scalar
+// member loops) and per lane in the seed pass.
 __device__ __forceinline__ void consider(uint32_t sse, int ci, uint32_t &best)
 {
     best = min(best, (sse << 9) | (uint32_t)ci);
 }
 
-// Per-lane SSE slots of the 3-subset search (kSlots2 for mode 2, then
-// kSlots0 for mode 0), one column per lane.
-typedef uint32_t Cache3[kSlots2 + kSlots0][kWG];
+// 2-subset partition p: modes 1, 3, 7
+__device__ __forceinline__ uint32_t search_2subset(const TexLds &S, int p, uint32_t mode_mask, const uint32_t *sv)
+{
+    uint32_t best = 0xFFFFFFFFu, e1 = 0, e3 = 0, e7 = 0;
+#pragma unroll 1
+    for (int s = 0; s < 2; s++) {
+        const uint32_t m = mask2(p, s);
+        const Prep P = prep_subset(S, m, 0);
+        if (mode_mask & 0x02) e1 += fit_colour<6, 1, 3, true>(S, m, 0, P, sv).sse;
+        if (mode_mask & 0x08) e3 += fit_colour<7, 2, 2, true>(S, m, 0, P, sv).sse;
+        if (mode_mask & 0x80) e7 += fit_colour<5, 2, 2, true>(S, m, 0, P, sv).sse;
+    }
+    if (mode_mask & 0x02) consider(e1, 16 + p, best);
+    if (mode_mask & 0x08) consider(e3, 144 + p, best);
+    if (mode_mask & 0x80) consider(e7, 221 + p, best);
+    return best;
+}
 
-template <int GROUP>
-__device__ __forceinline__ uint32_t search_group(const TexLds &S, Cache3 &cache, uint32_t mode_mask,
-                                                 const uint32_t *sv)
+// 3-subset partition p: mode 2 (MODE 2) or mode 0 (p < 16, MODE 0)
+template <int MODE>
+__device__ __forceinline__ uint32_t search_3subset(const TexLds &S, int p, const uint32_t *sv)
+{
+    uint32_t e = 0;
+#pragma unroll 1
+    for (int s = 0; s < 3; s++) {
+        const uint32_t m = mask3(p, s);
+        const Prep P = prep_subset(S, m, 0);
+        e += MODE == 2 ? fit_colour<5, 0, 2, true>(S, m, 0, P, sv).sse : fit_colour<4, 2, 3, true>(S, m, 0, P, sv).sse;
+    }
+    return (e << 9) | (uint32_t)(MODE == 2 ? 80 + p : p);
+}
+
+// rotation r: modes 4 (both index selections) and 5
+__device__ __forceinline__ uint32_t search_rotation(const TexLds &S, int r, uint32_t mode_mask, const uint32_t *sv)
 {
     uint32_t best = 0xFFFFFFFFu;
-    const Sums tot = GROUP == 0 ? subset_sums(S, 0xFFFFu, 0) : Sums{};
-    if (GROUP == 0) {
-        // 2-subset partitions: modes 1, 3, 7
-        if (mode_mask & 0x8A)
-            for (int p = 0; p < 64; p++) {
-                const uint32_t m0 = mask2(p, 0), m1 = mask2(p, 1);
-                const Sums s0 = subset_sums(S, m0, 0);
-                const Prep P0 = prep_subset(S, m0, 0, s0), P1 = prep_subset(S, m1, 0, sums_minus(tot, s0));
-                if (mode_mask & 0x02)
-                    consider(fit_colour<6, 1, 3, true>(S, m0, 0, P0, sv).sse + fit_colour<6, 1, 3, true>(S, m1, 0, P1, sv).sse,
-                             16 + p, best);
-                if (mode_mask & 0x08)
-                    consider(fit_colour<7, 2, 2, true>(S, m0, 0, P0, sv).sse + fit_colour<7, 2, 2, true>(S, m1, 0, P1, sv).sse,
-                             144 + p, best);
-                if (mode_mask & 0x80)
-                    consider(fit_colour<5, 2, 2, true>(S, m0, 0, P0, sv).sse + fit_colour<5, 2, 2, true>(S, m1, 0, P1, sv).sse,
-                             221 + p, best);
-            }
-    } else if (GROUP == 1) {
-        // 3-subset partitions: mode 0 (partitions 0..15), mode 2; recurring
-        // subset masks are fitted once (see kPlan3)
-        const bool on2 = mode_mask & 0x04, on0 = mode_mask & 0x01;
-        if (on0 || on2)
-            for (int t = 0; t < 64; t++) {
-                const int p = kOrder3[t];
-                if (!on2 && p >= 16) continue;
-                const bool with0 = on0 && p < 16;
-                uint32_t e2 = 0, e0 = 0;
-#pragma unroll 1
-                for (int s = 0; s < 3; s++) {
-                    const uint32_t msk = mask3(p, s);
-                    const int a2 = kPlan3.act[0][t][s], a0 = kPlan3.act[1][t][s];
-                    const bool fit2 = on2 && !(a2 & kTake), fit0 = with0 && !(a0 & kTake);
-                    uint32_t v2 = 0, v0 = 0;
-                    if (on2 && (a2 & kTake)) v2 = cache[a2 & 15][threadIdx.x];
-                    if (with0 && (a0 & kTake)) v0 = cache[kSlots2 + (a0 & 15)][threadIdx.x];
-                    if (fit2 || fit0) {
-                        const Prep P = prep_subset(S, msk, 0);
-                        if (fit2) {
-                            v2 = fit_colour<5, 0, 2, true>(S, msk, 0, P, sv).sse;
-                            if (a2 & kKeep) cache[a2 & 15][threadIdx.x] = v2;
-                        }
-                        if (fit0) {
-                            v0 = fit_colour<4, 2, 3, true>(S, msk, 0, P, sv).sse;
-                            if (a0 & kKeep) cache[kSlots2 + (a0 & 15)][threadIdx.x] = v0;
-                        }
-                    }
-                    e2 += v2;
-                    e0 += v0;
-                }
-                if (on2) consider(e2, 80 + p, best);
-                if (with0) consider(e0, p, best);
-            }
-    } else {
-        // one subset: mode 6, and modes 4 / 5 for every rotation
-        if (mode_mask & 0x70)
-            for (int r = 0; r < 4; r++) {
-                if (r > 0 && !(mode_mask & 0x30)) break;
-                const Prep P = prep_subset(S, 0xFFFFu, r);
-                if (r == 0 && (mode_mask & 0x40)) consider(fit_colour<7, 2, 4, true>(S, 0xFFFFu, 0, P, sv).sse, 220, best);
-                if (mode_mask & 0x10) {
-                    uint32_t s0 = fit_colour<5, 0, 2, true>(S, 0xFFFFu, r, P, sv).sse;
-                    uint32_t s1 = fit_colour<5, 0, 3, true>(S, 0xFFFFu, r, P, sv).sse;
-                    if (r) { s0 += fit_scalar<6, 3, false>(S, r, sv).sse; s1 += fit_scalar<6, 2, false>(S, r, sv).sse; }
-                    consider(s0, 208 + 2 * r, best);
-                    consider(s1, 209 + 2 * r, best);
-                }
-                if (mode_mask & 0x20) {
-                    uint32_t s5 = fit_colour<7, 0, 2, true>(S, 0xFFFFu, r, P, sv).sse;
-                    if (r) s5 += fit_scalar<8, 2, false>(S, r, sv).sse;
-                    consider(s5, 216 + r, best);
-                }
-            }
+    const Prep P = prep_subset(S, 0xFFFFu, r);
+    if (mode_mask & 0x10) {
+        uint32_t s0 = fit_colour<5, 0, 2, true>(S, 0xFFFFu, r, P, sv).sse;
+        uint32_t s1 = fit_colour<5, 0, 3, true>(S, 0xFFFFu, r, P, sv).sse;
+        if (r) { s0 += fit_scalar<6, 3, false>(S, r, sv).sse; s1 += fit_scalar<6, 2, false>(S, r, sv).sse; }
+        consider(s0, 208 + 2 * r, best);
+        consider(s1, 209 + 2 * r, best);
+    }
+    if (mode_mask & 0x20) {
+        uint32_t s5 = fit_colour<7, 0, 2, true>(S, 0xFFFFu, r, P, sv).sse;
+        if (r) s5 += fit_scalar<8, 2, false>(S, r, sv).sse;
+        consider(s5, 216 + r, best);
     }
     return best;
+}
+
+// mode 6
+__device__ __forceinline__ uint32_t search_mode6(const TexLds &S, const uint32_t *sv)
+{
+    const Prep P = prep_subset(S, 0xFFFFu, 0);
+    return (fit_colour<7, 2, 4, true>(S, 0xFFFFu, 0, P, sv).sse << 9) | 220u;
 }
 
 // ---- pass 2: re-fit the winner (same arithmetic) and lay out its bits
@@ -1053,14 +962,14 @@ __device__ __forceinline__ void stage_texels(TexLds &S, const uint8_t *src, bool
     }
 }
 
-// Items of the work split handled by this workgroup: one (its own index)
-// without a queue, else popped from the queue until exhausted.  Every
-// workgroup leaves the loop once the counter passes the last item.
+// Items handled by this workgroup: one (its own index) without a queue,
+// else popped from the queue until exhausted.  Every workgroup leaves the
+// loop once the counter passes the last item.
 struct ItemLoop {
     uint32_t item, n_items;
-    __device__ __forceinline__ ItemLoop(const WorkSplit &w, uint64_t total, uint32_t round, uint32_t *s_item)
+    __device__ __forceinline__ ItemLoop(const WorkSplit &w, uint32_t items, uint32_t *s_item)
     {
-        n_items = (uint32_t)((total + (uint64_t)w.item_rounds * round - 1) / ((uint64_t)w.item_rounds * round));
+        n_items = items;
         item = blockIdx.x;
         if (w.queue) {
             if (threadIdx.x == 0) *s_item = atomicAdd(w.queue, 1u);
@@ -1079,52 +988,432 @@ struct ItemLoop {
     }
 };
 
-// Pass 1: the best key of every block over the candidate groups in GMASK
-// (bit 0: 2-subset modes, bit 1: 3-subset modes, bit 2: 1-subset modes),
-// min-combined into the block's key word (set to all-ones beforehand) with
-// an atomic minimum, so kernels and work items may run in any order.
-// GMASK == 8 makes each (group, rounds) pair a work item of its own, heavy
-// groups first, so one launch covers all groups and ends on light items.
-template <int GMASK>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k_bc7_search(Bc7Launch L)
+// ---- pass 1: search
+//
+// Almost all of the 285 candidates of a block can be ruled out without being
+// fitted.  A palette lies near a line: whatever the endpoints, its entries
+// are within kCheb of some straight line in every channel (the line through
+// the rounded interpolants, see kCheb), so a subset of n texels whose summed
+// squared distance to its own best line is R has
+//     SSE >= (max(0, sqrt(R) - sqrt(3 kCheb^2 n)))^2
+// (the triangle inequality on the members' distances).
+// R is the trace of the subset's scatter matrix less its largest eigenvalue.
+// A candidate whose bound is above the SSE of a candidate already fitted
+// cannot win (nor tie), so it is left out; the others are fitted exactly as
+// before, and the winner is the same.  Three kernels:
+//   bounds  the member sums of every subset of the 64 + 64 partitions as
+//           matrix products (0/1 masks times texel features) on the matrix
+//           cores, from them each candidate's bound (16 bits, rounded down),
+//           and the least bound of the 3-subset partitions and rotations;
+//   seed    fits those two per block (they win or come within 2 % of the
+//           winner on most blocks) and compares every bound with their SSE:
+//           one 64-bit word per (64 blocks, candidate) says which blocks are left;
+//   search  one wave per (candidate, window of blocks): the blocks left are
+//           taken 64 at a time, one per lane, whatever their places in the
+//           window, so the fits run on full waves with wave-uniform masks.
+// On scenes of synthetic SH bands 1-2 of 64 2-subset partitions, 13 of 64
+// 3-subset ones (mode 2), 4 of 16 (mode 0) and 1.7 of 4 rotations are left.
+
+// Largest deviation, in one channel, of a rounded palette from the straight
+// line nearest to it: entry k is e0 + floor((w_k D + 32)/64) with D = e1 - e0,
+// so the deviations depend on D mod 64 only; the minimax line fit over all
+// 64 residues gives 0.3605 (2-bit indices), 0.4474 (3) and 0.4706 (4).
+// sqrt(3) times that, rounded up, is the slack of a member of three channels
+// (sqrt(2): one channel constant, as rotations leave it; modes 1, 3, 7 and
+// modes 4, 5 share the larger slack of 3-bit indices):
+constexpr float kSlack2 = 0.6245f, kSlack3 = 0.7750f, kSlack4 = 0.8152f;
+constexpr float kSlackRot = 0.6328f;
+
+// Candidate words of a slice (64 blocks): 2-subset partitions, 3-subset
+// partitions in mode 2, the 16 of mode 0, rotations (modes 4, 5), mode 6.
+constexpr int kW2 = 0, kW3 = 64, kW0 = 128, kWR = 144, kW6 = 148, kWords = 149;
+constexpr int kTiles = 13;   // 16-row mask tiles: 4 of 2-subset masks, 8 of 3-subset masks, all ones
+
+// Bounds of a chunk of blocks (nc of them, so that the scratch stays at 76 MB
+// and in the last-level cache), 16 bits each:
+//   b2[16][nc] 4 partitions, b3[32][nc] 2 partitions, b0[8][nc] 2, br[nc] 4 rotations,
+//   seed[nc]: least 3-subset partition | least rotation << 8 | mode 6's bound << 16
+struct Bounds {
+    uint2 *b2;
+    uint32_t *b3, *b0;
+    uint2 *br;
+    uint32_t *seed;
+    uint64_t nc;
+};
+
+struct Bc7Search {
+    EncodeArgs a;
+    Tables T;
+    WorkSplit w;
+    uint64_t first;             // bounds, seed: first block of the chunk
+    Bounds B;
+    uint64_t *words;            // [slice][kWords]
+    const uint8_t **src;        // [slice] texels of the slice's first block
+    uint32_t win2, win3, winr;  // search: slices per window
+    uint32_t types;             // search: candidate types of this launch (1: 2-subset, 2: 3-subset, 4: 1-subset)
+};
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// A bound v >= 0 as 16 bits (5 of exponent, 11 of fraction), rounded down;
+// below 1 it is 0.  Monotone, so a candidate is left out only if its bound
+// exceeds the SSE coded the same way.
+__device__ __forceinline__ uint32_t bound16(float v)
+{
+    return (uint32_t)max(__float_as_int(v) - (127 << 23), 0) >> 12;
+}
+
+// sqrt of n R for a subset of n members with sums S = (x, y, z, xx, xy, xz,
+// yy, yz, zz), from below.  n XX - Sx Sx^T is exact in FP32 (integers below
+// 2^24).  Its largest eigenvalue is q + 2 p f with f the largest root of
+// 4 f^3 - 3 f = hr (the trigonometric solution), found by one Newton step
+// from a fit within 0.004; the step lands above the root (the cubic is
+// convex there), and the margins cover the rounding of hr, whose effect on f
+// grows to sqrt(rounding) where the two largest eigenvalues meet.
+__device__ __forceinline__ float residual_root(float n, const float (&S)[9])
+{
+    const float cxx = fmaf(n, S[3], -S[0] * S[0]), cxy = fmaf(n, S[4], -S[0] * S[1]), cxz = fmaf(n, S[5], -S[0] * S[2]);
+    const float cyy = fmaf(n, S[6], -S[1] * S[1]), cyz = fmaf(n, S[7], -S[1] * S[2]), czz = fmaf(n, S[8], -S[2] * S[2]);
+    const float tr = cxx + cyy + czz, q = tr * (1.0f / 3.0f);
+    const float a = cxx - q, b = cyy - q, c = czz - q;
+    const float off = fmaf(cxy, cxy, fmaf(cxz, cxz, cyz * cyz));
+    const float p2 = fmaxf(fmaf(2.0f, off, fmaf(a, a, fmaf(b, b, c * c))) * (1.0f / 6.0f), 1e-3f);
+    const float det = fmaf(a, fmaf(b, c, -cyz * cyz),
+                           fmaf(-cxy, fmaf(cxy, c, -cyz * cxz), cxz * fmaf(cxy, cyz, -b * cxz)));
+    const float ip = __builtin_amdgcn_rsqf(p2), p = p2 * ip;
+    const float hr = fminf(fmaxf(0.5f * det * ip * ip * ip, -1.0f), 1.0f);
+    const float s = __builtin_amdgcn_sqrtf(fmaf(0.5f, hr, 0.5f));
+    const float f0 = fmaf(s, fmaf(s, -0.0774f, 0.5774f), 0.5f);
+    const float f2 = f0 * f0;
+    const float num = fmaf(f0, fmaf(4.0f, f2, -3.0f), -hr), den = fmaxf(fmaf(12.0f, f2, -3.0f), 1e-3f);
+    const float f = fmaf(-num, __builtin_amdgcn_rcpf(den), f0) + 5e-4f;
+    const float lam = fmaf(2.0f * p, f, q * 1.0001f);
+    return __builtin_amdgcn_sqrtf(fmaxf(tr - lam, 0.0f));
+}
+
+// (max(0, sqrt(R) - c sqrt(n)))^2 from root = sqrt(n R)
+__device__ __forceinline__ float bound_term(float root, float n, float rn, float c)
+{
+    const float d = fmaxf(fmaf(-c, n, root), 0.0f);
+    return d * d * rn;
+}
+
+// Row i of mask tile t (see kTiles): 2-subset partition 16 t + i; or of the
+// 3-subset tile t - 4, partition 8 (t - 4) + i/2, subset 1 + i%2 (subset 0 is
+// what the block's total leaves); or all texels.
+__device__ __forceinline__ uint32_t tile_mask(int t, int i)
+{
+    if (t < 4) return kPart2[16 * t + i];
+    if (t < 12) return mask3(8 * (t - 4) + (i >> 1), 1 + (i & 1));
+    return 0xFFFFu;
+}
+
+// Bounds of every candidate.  A wave takes 16 blocks at a time: with
+// v_mfma_f32_16x16x32_bf16, lane l supplies row l%16 of A (a mask) and
+// column l%16 of B (a block's texel feature) for k = 8 (l/16) .. + 7, and
+// receives rows 4 (l/16) .. + 3 of column l%16: four subsets of one block,
+// every feature of them in the same lane.  k < 16 are the texels' values or
+// their products' low bytes, k >= 16 the products' high bytes against masks
+// scaled by 256 (8-bit integers are exact in bf16, the sums in FP32).
+__global__ __launch_bounds__(kWG) void k_bc7_bounds(Bc7Search L)
+{
+    __shared__ uint4 tile[kTiles][64];
+    __shared__ uint32_t count[12][4];      // members of rows 4 g .. 4 g + 3, one byte each
+    for (int e = threadIdx.x; e < kTiles * 64; e += kWG) {
+        const int l = e & 63;
+        const uint32_t m = tile_mask(e >> 6, l & 15) >> (8 * ((l >> 4) & 1)), one = l < 32 ? 0x3F80u : 0x4380u;
+        uint32_t w[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) w[j] = ((m >> (2 * j)) & 1u ? one : 0u) | ((m >> (2 * j + 1)) & 1u ? one << 16 : 0u);
+        tile[e >> 6][l] = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+    if (threadIdx.x < 48) {
+        uint32_t c = 0;
+        for (int r = 0; r < 4; r++) c |= (uint32_t)__popc(tile_mask(threadIdx.x >> 2, 4 * (threadIdx.x & 3) + r)) << (8 * r);
+        count[threadIdx.x >> 2][threadIdx.x & 3] = c;
+    }
+    __syncthreads();
+    const EncodeArgs &a = L.a;
+    const int lane = threadIdx.x & 63, grp = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t g0 = L.first + (uint64_t)blockIdx.x * kWG;          // a workgroup lies in one run
+    const BlockRun run = a.run[find_run(a.run, a.nrun, g0)];
+    const uint64_t b0 = g0 - run.gbase + 64 * wave;                    // the slice's first block in its run
+    if (lane == 0) L.src[(g0 >> 6) + wave] = run.src + b0 * 64;
+    const uint64_t c0 = (uint64_t)blockIdx.x * kWG + 64 * wave;        // ... and in the chunk
+    const uint32_t sh = lane < 32 ? 0u : 8u, lin = lane < 32 ? 0xFFu : 0u;
+    for (int sb = 0; sb < 4; sb++) {
+        const uint64_t b = b0 + 16 * sb + (lane & 15), c = c0 + 16 * sb + (lane & 15);
+        // eight texels of the lane's block (the run's last block stands in past its end)
+        const uint4 *src = reinterpret_cast<const uint4 *>(run.src + min(b, run.nblk - 1) * 64 + 32 * (grp & 1));
+        const uint4 v0 = src[0], v1 = src[1];
+        const uint32_t px[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+        bf16x8 B[9];
+        {
+            uint32_t w[9][4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                uint32_t f[2][9];
+#pragma unroll
+                for (int h = 0; h < 2; h++) {
+                    const uint32_t t = px[2 * j + h], r = t & 255u, g = (t >> 8) & 255u, bl = (t >> 16) & 255u;
+                    const uint32_t pr[6] = {mul_u24(r, r), mul_u24(r, g), mul_u24(r, bl), mul_u24(g, g), mul_u24(g, bl), mul_u24(bl, bl)};
+                    f[h][0] = __float_as_uint((float)(r & lin));
+                    f[h][1] = __float_as_uint((float)(g & lin));
+                    f[h][2] = __float_as_uint((float)(bl & lin));
+#pragma unroll
+                    for (int q = 0; q < 6; q++) f[h][3 + q] = __float_as_uint((float)((pr[q] >> sh) & 255u));
+                }
+                // the top halves of two FP32 values (exact: 8-bit integers)
+#pragma unroll
+                for (int q = 0; q < 9; q++) w[q][j] = __builtin_amdgcn_perm(f[1][q], f[0][q], 0x07060302u);
+            }
+#pragma unroll
+            for (int q = 0; q < 9; q++) B[q] = __builtin_bit_cast(bf16x8, make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]));
+        }
+        auto sums = [&](int t, floatx4 (&D)[9]) {
+            const bf16x8 A = __builtin_bit_cast(bf16x8, tile[t][lane]);
+#pragma unroll
+            for (int q = 0; q < 9; q++)
+                D[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B[q], floatx4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+        };
+        floatx4 D[9];
+        sums(12, D);
+        float tot[9];
+#pragma unroll
+        for (int q = 0; q < 9; q++) tot[q] = D[q][0];
+        // one subset: lane group r takes rotation r (its channel is constant)
+        {
+            float m[9];
+            const float kr = grp == 1 ? 0.0f : 1.0f, kg = grp == 2 ? 0.0f : 1.0f, kb = grp == 3 ? 0.0f : 1.0f;
+            m[0] = tot[0] * kr; m[1] = tot[1] * kg; m[2] = tot[2] * kb;
+            m[3] = tot[3] * kr; m[4] = tot[4] * (kr * kg); m[5] = tot[5] * (kr * kb);
+            m[6] = tot[6] * kg; m[7] = tot[7] * (kg * kb); m[8] = tot[8] * kb;
+            const float root = residual_root(16.0f, m);
+            const uint32_t lb = bound16(bound_term(root, 16.0f, 1.0f / 16.0f, grp ? kSlackRot : kSlack3));
+            reinterpret_cast<uint16_t *>(L.B.br)[4 * c + grp] = (uint16_t)lb;
+            uint32_t least = lb << 8 | (uint32_t)grp;
+            least = min(least, (uint32_t)__shfl_xor((int)least, 16));
+            least = min(least, (uint32_t)__shfl_xor((int)least, 32));
+            // (mode 6 is rotation 0's subset: lane group 0)
+            const uint32_t lb6 = bound16(bound_term(root, 16.0f, 1.0f / 16.0f, kSlack4));
+            if (grp == 0) L.B.seed[c] = (least & 255u) << 8 | lb6 << 16;
+        }
+        // 2-subset partitions: rows are subset 1, the total less them subset 0
+#pragma unroll 1
+        for (int t = 0; t < 4; t++) {
+            sums(t, D);
+            const uint32_t cnt = count[t][grp];
+            uint32_t lb[4];
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const float n1 = (float)((cnt >> (8 * r)) & 255u), n0 = 16.0f - n1;
+                float s1[9], s0[9];
+#pragma unroll
+                for (int q = 0; q < 9; q++) { s1[q] = D[q][r]; s0[q] = tot[q] - s1[q]; }
+                lb[r] = bound16(bound_term(residual_root(n1, s1), n1, __builtin_amdgcn_rcpf(n1), kSlack3) +
+                                bound_term(residual_root(n0, s0), n0, __builtin_amdgcn_rcpf(n0), kSlack3));
+            }
+            L.B.b2[(uint64_t)(4 * t + grp) * L.B.nc + c] = make_uint2(lb[0] | lb[1] << 16, lb[2] | lb[3] << 16);
+        }
+        // 3-subset partitions: two rows each
+        uint32_t least = ~0u;
+#pragma unroll 1
+        for (int t = 0; t < 8; t++) {
+            sums(4 + t, D);
+            const uint32_t cnt = count[4 + t][grp];
+            uint32_t lb[2], lb0[2];
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                const float n1 = (float)((cnt >> (16 * h)) & 255u), n2 = (float)((cnt >> (16 * h + 8)) & 255u);
+                const float n0 = 16.0f - n1 - n2;
+                float s0[9], s1[9], s2[9];
+#pragma unroll
+                for (int q = 0; q < 9; q++) { s1[q] = D[q][2 * h]; s2[q] = D[q][2 * h + 1]; s0[q] = tot[q] - s1[q] - s2[q]; }
+                const float r0 = residual_root(n0, s0), r1 = residual_root(n1, s1), r2 = residual_root(n2, s2);
+                const float q0 = __builtin_amdgcn_rcpf(n0), q1 = __builtin_amdgcn_rcpf(n1), q2 = __builtin_amdgcn_rcpf(n2);
+                lb[h] = bound16(bound_term(r0, n0, q0, kSlack2) + bound_term(r1, n1, q1, kSlack2) + bound_term(r2, n2, q2, kSlack2));
+                lb0[h] = bound16(bound_term(r0, n0, q0, kSlack3) + bound_term(r1, n1, q1, kSlack3) + bound_term(r2, n2, q2, kSlack3));
+                least = min(least, lb[h] << 8 | (uint32_t)(8 * t + 2 * grp + h));
+            }
+            L.B.b3[(uint64_t)(4 * t + grp) * L.B.nc + c] = lb[0] | lb[1] << 16;
+            if (t < 2) L.B.b0[(uint64_t)(4 * t + grp) * L.B.nc + c] = lb0[0] | lb0[1] << 16;
+        }
+        least = min(least, (uint32_t)__shfl_xor((int)least, 16));
+        least = min(least, (uint32_t)__shfl_xor((int)least, 32));
+        if (grp == 0) L.B.seed[c] |= least & 255u;
+    }
+}
+
+// Seeds, and the words of the blocks each candidate is left with: lane =
+// block.  The seeds' own bits are cleared (they are fitted here).
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k_bc7_seed(Bc7Search L)
 {
     __shared__ TexLds S;
-    __shared__ Cache3 cache;
-    __shared__ uint32_t s_item;
-    constexpr bool kItems = GMASK == 8;
     const EncodeArgs &a = L.a;
-    const uint64_t rounds = a.total / kWG;
-    const uint64_t per_group = (rounds + L.w.item_rounds - 1) / L.w.item_rounds;   // items per group
+    const int lane = threadIdx.x & 63;
+    const uint64_t g0 = L.first + (uint64_t)blockIdx.x * kWG, g = g0 + threadIdx.x, c = (uint64_t)blockIdx.x * kWG + threadIdx.x;
+    const BlockRun run = a.run[find_run(a.run, a.nrun, g0)];
+    const uint64_t b = g0 - run.gbase + threadIdx.x;
+    const bool live = b < run.nblk;
     stage_table(S, L.T.near64);
-    ItemLoop it(L.w, kItems ? 3 * per_group * L.w.item_rounds * kWG : a.total, kWG, &s_item);
+    stage_texels(S, run.src + b * 64, live);
+    __syncthreads();
+    const uint32_t seed = L.B.seed[c];
+    const int p3 = (int)(seed & 255u), rot = (int)((seed >> 8) & 255u);
+    uint32_t key = ~0u;
+    if (live) {
+        if (a.mode_mask & 0x04) key = min(key, search_3subset<2>(S, p3, L.T.sv));
+        if (a.mode_mask & 0x30) key = min(key, search_rotation(S, rot, a.mode_mask, L.T.sv));
+    }
+    a.keys[g] = key;
+    // 0 .. thr: bounds that may still win (with no seed, all of them; past the run, none)
+    const int thr = !live ? -1 : key == ~0u ? 0xFFFF : (int)bound16((float)(key >> 9));
+    uint64_t w2 = 0, w3 = 0, w1 = 0;   // lane p's words
+    auto put = [&](uint64_t &w, int at, bool keep) {
+        const uint64_t m = __ballot(keep);
+        if (lane == at) w = m;
+    };
+#pragma unroll 4
+    for (int q = 0; q < 16; q++) {
+        const uint2 v = L.B.b2[q * L.B.nc + c];
+        put(w2, 4 * q, (int)(v.x & 0xFFFFu) <= thr);
+        put(w2, 4 * q + 1, (int)(v.x >> 16) <= thr);
+        put(w2, 4 * q + 2, (int)(v.y & 0xFFFFu) <= thr);
+        put(w2, 4 * q + 3, (int)(v.y >> 16) <= thr);
+    }
+#pragma unroll 4
+    for (int q = 0; q < 32; q++) {
+        const uint32_t v = L.B.b3[q * L.B.nc + c];
+        put(w3, 2 * q, (int)(v & 0xFFFFu) <= thr && p3 != 2 * q);
+        put(w3, 2 * q + 1, (int)(v >> 16) <= thr && p3 != 2 * q + 1);
+    }
+#pragma unroll 4
+    for (int q = 0; q < 8; q++) {
+        const uint32_t v = L.B.b0[q * L.B.nc + c];
+        put(w1, 2 * q, (int)(v & 0xFFFFu) <= thr);
+        put(w1, 2 * q + 1, (int)(v >> 16) <= thr);
+    }
+    const uint2 vr = L.B.br[c];
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+        put(w1, 16 + r, (int)(((r < 2 ? vr.x : vr.y) >> (16 * (r & 1))) & 0xFFFFu) <= thr && rot != r);
+    put(w1, 20, (int)(seed >> 16) <= thr);
+    uint64_t *words = L.words + (g >> 6) * kWords;
+    words[kW2 + lane] = w2;
+    words[kW3 + lane] = w3;
+    if (lane < kWords - kW0) words[kW0 + lane] = w1;
+}
+
+// Bit k (from 0) among the set bits of w.
+__device__ __forceinline__ int nth_bit(uint64_t w, int k)
+{
+    uint32_t x = (uint32_t)w;
+    int at = 0, n = __popc(x);
+    if (k >= n) { k -= n; x = (uint32_t)(w >> 32); at = 32; }
+#pragma unroll
+    for (int s = 16; s; s >>= 1) {
+        n = __popc(x & ((1u << s) - 1u));
+        if (k >= n) { k -= n; x >>= s; at += s; }
+    }
+    return at;
+}
+
+// Items of a search launch, heavy types first: (window, candidate) pairs of
+// one type, a window's candidates next to each other (its texels stay in L2).
+struct Items {
+    uint32_t n[5], win[5];
+    uint32_t total;
+};
+__host__ __device__ inline Items search_items(uint64_t slices, uint32_t types, uint32_t mode_mask, uint32_t win2,
+                                              uint32_t win3, uint32_t winr)
+{
+    Items I;
+    const uint32_t per[5] = {64, 16, 1, 4, 64};   // 2-subset, mode 0, mode 6, rotations, mode 2
+    const uint32_t win[5] = {win2, win3, winr, winr, win3};
+    const bool on[5] = {(types & 1) && (mode_mask & 0x8A), (types & 2) && (mode_mask & 0x01), (types & 4) && (mode_mask & 0x40),
+                        (types & 4) && (mode_mask & 0x30), (types & 2) && (mode_mask & 0x04)};
+    I.total = 0;
+    for (int q = 0; q < 5; q++) {
+        I.win[q] = win[q];
+        I.n[q] = on[q] ? per[q] * (uint32_t)((slices + win[q] - 1) / win[q]) : 0u;
+        I.total += I.n[q];
+    }
+    return I;
+}
+
+constexpr int kMaxWin = 128;   // slices per window, at most
+
+// The candidates left, one item per wave (the workgroup shares the code
+// table only, so its waves run apart between the barriers of the queue).
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k_bc7_search(Bc7Search L)
+{
+    __shared__ TexLds S;
+    __shared__ uint64_t s_word[4][kMaxWin];
+    __shared__ uint32_t s_end[4][kMaxWin];
+    __shared__ uint32_t s_item;
+    const EncodeArgs &a = L.a;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t slices = (uint32_t)(a.total >> 6);
+    const Items I = search_items(slices, L.types, a.mode_mask, L.win2, L.win3, L.winr);
+    stage_table(S, L.T.near64);
+    ItemLoop it(L.w, (I.total + 3) / 4, &s_item);
+    __syncthreads();
     if (it.item >= it.n_items) return;
     do {
-        const uint32_t group = kItems ? (uint32_t)(it.item / per_group) : 0u;
-        const uint64_t first = kItems ? (it.item % per_group) * L.w.item_rounds : (uint64_t)it.item * L.w.item_rounds;
-        for (uint32_t r = 0; r < L.w.item_rounds; r++) {
-            const uint64_t g0 = (first + r) * kWG;
-            if (g0 >= a.total) break;
-            const BlockRun run = a.run[find_run(a.run, a.nrun, g0)];
-            const uint64_t b = g0 - run.gbase + threadIdx.x;
-            const bool live = b < run.nblk;
-            __syncthreads();   // the previous round's LDS reads are done
-            stage_texels(S, run.src + b * 64, live);
-            __syncthreads();
-            if (__ballot(live) == 0) continue;
+        uint32_t q = it.item * 4 + wave;
+        if (q >= I.total) continue;
+        int type = 0;
+        while (q >= I.n[type]) q -= I.n[type++];
+        const uint32_t per = type == 0 || type == 4 ? 64u : type == 1 ? 16u : type == 3 ? 4u : 1u;
+        const int word0 = type == 0 ? kW2 : type == 1 ? kW0 : type == 2 ? kW6 : type == 3 ? kWR : kW3;
+        const uint32_t win = I.win[type], w = q / per, s0 = w * win, ns = min(win, slices - s0);
+        const int p = (int)(q % per);
+        // the window's words of this candidate and the running count of their bits
+        uint32_t n = 0;
+        for (uint32_t h = 0; h < ns; h += 64) {
+            const uint32_t i = h + lane;
+            const uint64_t x = i < ns ? L.words[(uint64_t)(s0 + i) * kWords + word0 + p] : 0ull;
+            uint32_t e = (uint32_t)__popcll(x);
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t o = (uint32_t)__shfl_up((int)e, d);
+                if (lane >= d) e += o;
+            }
+            if (i < ns) {
+                s_word[wave][i] = x;
+                s_end[wave][i] = n + e;
+            }
+            n += (uint32_t)__builtin_amdgcn_readlane((int)e, 63);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (uint32_t t0 = 0; t0 < n; t0 += 64) {
+            // lane's block: bit t - (bits before its slice) of the slice's word
+            const uint32_t t = t0 + lane;
+            const bool live = t < n;
+            uint32_t lo = 0, hi = ns - 1;
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (s_end[wave][mid] > t) hi = mid;
+                else lo = mid + 1;
+            }
+            const uint64_t x = s_word[wave][lo];
+            const int bit = live ? nth_bit(x, (int)(t - (s_end[wave][lo] - (uint32_t)__popcll(x)))) : 0;
+            stage_texels(S, live ? L.src[s0 + lo] + 64 * bit : nullptr, live);
             if (live) {
-                uint32_t key = ~0u;
-                if (kItems) {
-                    key = group == 0 ? search_group<0>(S, cache, a.mode_mask, L.T.sv)
-                                     : group == 1 ? search_group<1>(S, cache, a.mode_mask, L.T.sv)
-                                                  : search_group<2>(S, cache, a.mode_mask, L.T.sv);
-                } else {
-                    if (GMASK & 1) key = min(key, search_group<0>(S, cache, a.mode_mask, L.T.sv));
-                    if (GMASK & 2) key = min(key, search_group<1>(S, cache, a.mode_mask, L.T.sv));
-                    if (GMASK & 4) key = min(key, search_group<2>(S, cache, a.mode_mask, L.T.sv));
-                }
-                atomicMin(a.keys + g0 + threadIdx.x, key);
+                const uint32_t key = type == 0 ? search_2subset(S, p, a.mode_mask, L.T.sv)
+                                   : type == 1 ? search_3subset<0>(S, p, L.T.sv)
+                                   : type == 2 ? search_mode6(S, L.T.sv)
+                                   : type == 3 ? search_rotation(S, p, a.mode_mask, L.T.sv)
+                                               : search_3subset<2>(S, p, L.T.sv);
+                atomicMin(a.keys + (uint64_t)(s0 + lo) * 64 + bit, key);
             }
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     } while (it.next(L.w, &s_item));
 }
 
@@ -1362,8 +1651,7 @@ hipError_t upload_bc7_tables(int device, hipStream_t st)
     return hipSuccess;
 }
 
-hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t split, hipStream_t st,
-                             hipEvent_t searched)
+hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t split, hipStream_t st)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -1378,34 +1666,63 @@ hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t 
     L.T.sv = reinterpret_cast<const uint32_t *>(L.T.near64 + kQEntries);
     const uint32_t nwg = (uint32_t)(a.total / kWG);
     const dim3 sgrid(nwg);
-    // every key word starts all-ones (padding indices keep it)
-    if ((e = launch_fill_u64(reinterpret_cast<unsigned long long *>(a.keys), a.total / 2, ~0ull, st)) != hipSuccess)
-        return e;
-    auto launch = [&](int q, auto kernel, const char *name) -> hipError_t {
-        L.w = w3[q];
-        const uint32_t per = (uint32_t)((nwg + L.w.item_rounds - 1) / L.w.item_rounds);
-        dim3 grid(L.w.queue ? L.w.grid : (split == 3 ? 3 * per : per));
-        if (L.w.queue) {
-            hipError_t f = launch_fill_u64(reinterpret_cast<unsigned long long *>(L.w.queue), 1, 0, st);
+    // scratch: keys[total] | list[total] | count[8] start[8] | wgcount[nwg][8] |
+    // slice texels | candidate words | bounds of one chunk
+    Bc7Search Q;
+    Q.a = a;
+    Q.T = L.T;
+    const uint64_t slices = a.total / 64;
+    uint8_t *s = reinterpret_cast<uint8_t *>(a.keys) + 8 * a.total + 64 + 32 * (uint64_t)nwg;
+    auto take = [&](size_t bytes) { uint8_t *r = s; s += (bytes + 15) & ~(size_t)15; return r; };
+    Q.src = reinterpret_cast<const uint8_t **>(take(8 * slices));
+    Q.words = reinterpret_cast<uint64_t *>(take(8 * kWords * slices));
+    const uint64_t nc = a.total < kBc7Chunk ? a.total : kBc7Chunk;
+    Q.B.nc = nc;
+    Q.B.b2 = reinterpret_cast<uint2 *>(take(16 * 8 * nc));
+    Q.B.b3 = reinterpret_cast<uint32_t *>(take(32 * 4 * nc));
+    Q.B.b0 = reinterpret_cast<uint32_t *>(take(8 * 4 * nc));
+    Q.B.br = reinterpret_cast<uint2 *>(take(8 * nc));
+    Q.B.seed = reinterpret_cast<uint32_t *>(take(4 * nc));
+    for (uint64_t first = 0; first < a.total; first += nc) {
+        Q.first = first;
+        const dim3 grid((uint32_t)(((a.total - first < nc ? a.total - first : nc)) / kWG));
+        GSBC_LAUNCH("bc7_bounds", k_bc7_bounds, grid, dim3(kWG), 0, st, Q);
+        GSBC_LAUNCH("bc7_seed", k_bc7_seed, grid, dim3(kWG), 0, st, Q);
+    }
+    // Windows: long enough that a candidate's blocks fill waves (about 1 in
+    // 40 blocks is left of a 2-subset partition, 1 in 5 of a 3-subset one, 1
+    // in 3 of a rotation), short enough that a small scene spreads over the chip.
+    auto window = [&](uint64_t split, uint32_t most) {
+        const uint64_t n = slices / split;
+        return (uint32_t)(n < 4 ? 4 : n > most ? most : n);
+    };
+    auto launch = [&](int q, uint32_t types, const char *name) -> hipError_t {
+        Q.w = w3[q];
+        Q.types = types;
+        const uint32_t r = Q.w.item_rounds;
+        auto widen = [&](uint32_t n) { return n * r > (uint32_t)kMaxWin ? (uint32_t)kMaxWin : n * r; };
+        Q.win2 = widen(window(32, kMaxWin));
+        Q.win3 = widen(window(64, 64));
+        Q.winr = widen(window(512, 16));
+        const Items I = search_items(slices, types, a.mode_mask, Q.win2, Q.win3, Q.winr);
+        if (I.total == 0) return hipSuccess;
+        if (Q.w.queue) {
+            hipError_t f = launch_fill_u64(reinterpret_cast<unsigned long long *>(Q.w.queue), 1, 0, st);
             if (f != hipSuccess) return f;
         }
-        GSBC_LAUNCH(name, kernel, grid, dim3(kWG), 0, st, L);
+        GSBC_LAUNCH(name, k_bc7_search, dim3(Q.w.queue ? Q.w.grid : (I.total + 3) / 4), dim3(kWG), 0, st, Q);
         return hipGetLastError();
     };
     if (split == 0) {
-        if ((e = launch(0, k_bc7_search<1>, "bc7_search_2subset")) != hipSuccess) return e;
-        if ((e = launch(1, k_bc7_search<2>, "bc7_search_3subset")) != hipSuccess) return e;
-        if ((e = launch(2, k_bc7_search<4>, "bc7_search_1subset")) != hipSuccess) return e;
+        if ((e = launch(0, 1, "bc7_search_2subset")) != hipSuccess) return e;
+        if ((e = launch(1, 2, "bc7_search_3subset")) != hipSuccess) return e;
+        if ((e = launch(2, 4, "bc7_search_1subset")) != hipSuccess) return e;
     } else if (split == 1) {
-        if ((e = launch(0, k_bc7_search<1>, "bc7_search_2subset")) != hipSuccess) return e;
-        if ((e = launch(1, k_bc7_search<6>, "bc7_search_3subset_1subset")) != hipSuccess) return e;
-    } else if (split == 2) {
-        if ((e = launch(0, k_bc7_search<7>, "bc7_search_all")) != hipSuccess) return e;
+        if ((e = launch(0, 1, "bc7_search_2subset")) != hipSuccess) return e;
+        if ((e = launch(1, 6, "bc7_search_3subset_1subset")) != hipSuccess) return e;
     } else {
-        if ((e = launch(0, k_bc7_search<8>, "bc7_search_items")) != hipSuccess) return e;
+        if ((e = launch(0, 7, "bc7_search_items")) != hipSuccess) return e;
     }
-    if (searched && (e = hipEventRecord(searched, st)) != hipSuccess) return e;
-    // key scratch: keys[total] | list[total] | count[8] start[8] | wgcount[nwg][8]
     uint32_t *count = a.keys + 2 * a.total, *wgcount = count + 16;
     GSBC_LAUNCH("bc7_bucket", k_bc7_bucket_count, sgrid, dim3(kWG), 0, st, a, wgcount);
     GSBC_LAUNCH("bc7_bucket", k_bc7_bucket_scan, dim3(1), dim3(256), 0, st, wgcount, nwg, count);

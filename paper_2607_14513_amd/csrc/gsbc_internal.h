@@ -161,19 +161,23 @@ struct EncodeArgs {
     uint32_t mode_mask;
     uint32_t *keys;                 // BC7 only: scratch of bc7_scratch_bytes(total)
 };
-// Scratch bytes the BC7 encoder needs for `blocks` global indices: a key and
-// a bucket-list word per index, plus per-mode counters.
-inline size_t bc7_scratch_bytes(uint64_t blocks) { return (size_t)blocks * 8 + 64 + ((blocks + 255) / 256) * 32; }
+// Scratch bytes the BC7 encoder needs for `blocks` global indices (a
+// multiple of 256): a key and a bucket-list word per index, per-mode
+// counters, per 64 indices a texel pointer and the 149 candidate words, and
+// 300 bytes of candidate bounds per index of one chunk.
+constexpr uint64_t kBc7Chunk = 1u << 18;
+inline size_t bc7_scratch_bytes(uint64_t blocks)
+{
+    return (size_t)blocks * 8 + 64 + ((blocks + 255) / 256) * 32 + (blocks / 64) * 150 * 8 +
+           (blocks < kBc7Chunk ? blocks : kBc7Chunk) * 300 + 128;
+}
 // How the BC7 candidate search is split over kernels: 0 -> three kernels
 // (2-subset, 3-subset, 1-subset modes), 1 -> two (the 1-subset modes folded
-// into the 3-subset kernel), 2 -> one kernel for all modes, 3 -> one kernel
-// with (group, rounds) work items.  Every split gives the same bits (the
-// winner is a minimum over a total order, combined with atomic minima).
+// into the 3-subset kernel), 2 and 3 -> one kernel for all modes.  Every
+// split gives the same bits (the winner is a minimum over a total order,
+// combined with atomic minima).
 hipError_t launch_bc1_encode(const EncodeArgs &a, const WorkSplit &w, uint32_t lanes, hipStream_t st);
-// `searched`, when given, is recorded on st once the search kernels are
-// enqueued (before the bucketing and emit kernels).
-hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t split, hipStream_t st,
-                             hipEvent_t searched = nullptr);
+hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t split, hipStream_t st);
 hipError_t upload_bc1_tables(int device, hipStream_t st);
 hipError_t upload_bc7_tables(int device, hipStream_t st);
 
