@@ -2,18 +2,17 @@
 // colours and 2-bit indices, Sec. III-A; the paper codes each 4x4 band block
 // this way, Sec. V).
 //
-// One lane codes one block, so the whole split enumeration of the cluster
-// fit runs in wave-uniform order: the split bounds, cluster weights and
-// normal-equation determinants are scalar, and each lane only evaluates its
-// own numerators, quantised endpoints and SSE.  Per-lane prefix sums of the
-// ordered texels live in LDS, one column per lane (conflict-free reads at a
-// uniform row), and so does the nearest-code table.  Every decision is
-// integer; ties take the first candidate in the fixed enumeration order.
+// One lane codes one block.  A lower bound of every split's SSE is tested in
+// wave-uniform order; the splits that pass are queued and scored 64 at a
+// time, any lane for any block of its wave.  Per-lane prefix sums of the
+// ordered texels live in LDS, one column per lane, and so does the
+// nearest-code table.  Every decision is integer; ties take the first
+// candidate in the fixed enumeration order.
 //
 // Steps: constant block -> per-channel endpoint tables; otherwise principal
-// axis by integer power iteration, texels ordered by projection, every
-// 4-cluster and 3-cluster split fitted by least squares and scored by its
-// exact SSE, the best canonicalised and re-indexed, then `refine_steps`
+// axis by integer power iteration, texels ordered by projection, the best
+// 4-cluster or 3-cluster split by exact SSE after a least-squares fit, that
+// split canonicalised and re-indexed, then `refine_steps`
 // rounds of +-1 moves of the six endpoint channels.
 #include "gsbc_internal.h"
 #include "bc_format.h"
@@ -29,14 +28,18 @@ namespace {
 // Constant-colour endpoint tables per channel width (0: 5 bits, 1: 6 bits),
 // the nearest-code table of the cluster fit (code[w][h] is the number of
 // codes c < max with E(c) + E(c+1) < h), and for every split of the 4- and
-// 3-cluster lists, in enumeration order, the division multiplier
-// ceil(2^36 / det) of its determinant (0 where det = 0).
+// 3-cluster lists, in enumeration order, its bounds (s1 | s2 << 5 | s3 << 10)
+// and the division multiplier ceil(2^36 / det) of its determinant (0 where
+// det = 0).  For the splits' bounds: the spread of a split's weights,
+// sum a^2 - (sum a)^2 / 16, for every (s1, s2) and s3, or s1 and s2.
 constexpr int kSplits4 = 969, kSplits3 = 153;
 struct Bc1Tables {
     uint8_t a4[2][256], b4[2][256], e4[2][256];
     uint8_t a3[2][256], b3[2][256], e3[2][256];
     uint8_t code[2][512];
-    uint32_t magic4[kSplits4], magic3[kSplits3];
+    uint4 split4[kSplits4], split3[kSplits3];
+    float spread4[17 * 17][17], spread3[17][17];
+    uint32_t first4[17 * 17], first3[17];   // number of the split with the least s3 (s2)
 };
 __constant__ Bc1Tables kTab;
 
@@ -49,6 +52,9 @@ struct Bc1Lds {
     short m2P[17 * 3][LANES];
     uint8_t code[2][512];
     uint8_t val[2][512];
+    int Q[LANES];                     // sum of |x|^2 of each lane's block
+    unsigned long long best[LANES];   // least SSE << 16 | split order so far
+    uint32_t queue[LANES / 64][128];  // per wave: (block's lane << 11 | split) waiting to be scored
 };
 
 __host__ __device__ inline int e5(int c) { return (c << 3) | (c >> 2); }
@@ -157,7 +163,8 @@ __device__ inline uint32_t canon_index(uint32_t &c0, uint32_t &c1, bool four, co
     return acc >> 6;
 }
 
-// Cluster fit over one split list in enumeration order (4-colour: s1 <= s2 <=
+// Cluster fit over every split of one list in enumeration order, for waves
+// most of whose splits have to be scored (4-colour: s1 <= s2 <=
 // s3; 3-colour: s1 <= s2, s3 = 16).  The split bounds, weights and
 // determinant are wave-uniform; each lane forms its numerators from the
 // prefix sums, quantises, and scores the exact SSE of the split
@@ -172,7 +179,7 @@ __device__ __forceinline__ void split_list(const Lds &L, int lane, const int (&t
                                            int Q, uint32_t &best, uint32_t &best_split)
 {
     constexpr int F = FOUR ? 3 : 2;
-    const uint32_t *magic = FOUR ? kTab.magic4 : kTab.magic3;
+    const uint4 *split = FOUR ? kTab.split4 : kTab.split3;
     int si = 0;   // split number in enumeration order
     for (int s1 = 0; s1 <= 16; s1++) {
         int a[3];
@@ -192,7 +199,7 @@ __device__ __forceinline__ void split_list(const Lds &L, int lane, const int (&t
                 bm[c] = short2_t{(short)(-bq[c]), (short)m2tot[c]};
             }
             for (int s3 = FOUR ? s2 : 16; s3 <= 16; s3++) {
-                const uint32_t M = magic[si++];
+                const uint32_t M = split[si++].y;
                 const int n0 = s1, n1 = s2 - s1, n2 = s3 - s2, n3 = 16 - s3;
                 const int A = FOUR ? 9 * n0 + 4 * n1 + n2 : 4 * n0 + n1;
                 const int B = FOUR ? n1 + 4 * n2 + 9 * n3 : n1 + 4 * n2;
@@ -239,6 +246,221 @@ __device__ __forceinline__ void split_list(const Lds &L, int lane, const int (&t
     }
 }
 
+// ---- the splits worth scoring
+//
+// With the texels centred on their mean, the real least-squares endpoints of
+// a split leave E = Q' - |u|^2 / V, where Q' is the scatter about the mean, u
+// the weighted sum P'(s1) + P'(s2) + P'(s3) of the centred prefix sums (three
+// clusters: P'(s1) + P'(s2)) and V the spread of the weights, which depends on
+// the split only.  The quantised palette is a line in the weights up to the
+// rounding of its interpolants, which stay within 1/4 of some line in every
+// channel ((0, -1/3, 1/3, 0) or (0, 1/2, 0) less its best linear fit), so
+//     SSE >= (max(0, sqrt(E) - sqrt(3)))^2
+// over 16 texels of three channels.  A split whose bound exceeds an SSE
+// already reached cannot win: |u|^2 >= V (Q' - (sqrt(best) + sqrt(3))^2) is
+// the test, eight instructions where scoring a split takes about 85.
+//
+// The splits that pass are queued with their block's lane and scored 64 at a
+// time, any lane for any block, so that scoring runs on full waves; the
+// first score comes from cutting the projections at 1/6, 1/2 and 5/6 of their
+// range (4 % above the best on average), then the splits with even bounds
+// are tested before the others, so that most are tested against nearly
+// the final SSE.  About 190 of the 1,122 splits of a block of synthetic SH
+// bands are scored; a wave issues 57 k VALU instructions where scoring every
+// split took 105 k, and 1,048,576 blocks take 1.77 ms (2.95 before).  Bound by
+// VALU issue (85 %): scoring 27 k, the tests 11 k, refinement 7 k.
+
+// Score the queued splits e (lane: one entry, or none).  The same arithmetic
+// as split_list, with the split per lane.
+template <bool FOUR, class Lds>
+__device__ __forceinline__ void score(Lds &L, uint32_t e, int wave0, bool live)
+{
+    const uint4 sp = (FOUR ? kTab.split4 : kTab.split3)[live ? e & 2047u : 0u];
+    const int col = wave0 + (int)((e >> 11) & 63u);
+    const int s1 = (int)(sp.x & 31u), s2 = (int)((sp.x >> 5) & 31u), s3 = (int)((sp.x >> 10) & 31u);
+    const int det = (int)(sp.x >> 16);
+    const uint32_t M = sp.y;
+    const short2_t k01 = __builtin_bit_cast(short2_t, sp.z), k23 = __builtin_bit_cast(short2_t, sp.w);
+    const int n2 = s3 - s2;
+    const short2_t n01 = {(short)s1, (short)(s2 - s1)}, n23 = {(short)n2, (short)(16 - s3)};
+    int sse = L.Q[col];
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        const int wide = c == 1;
+        const int a = L.m2P[s1 * 3 + c][col], bq = L.m2P[s2 * 3 + c][col], m2t = L.m2P[48 + c][col];
+        const int cq = FOUR ? L.m2P[s3 * 3 + c][col] : m2t;
+        // (-2 SA, tot): |-2 SA| <= 3 * 8160 fits 16 bits
+        const short2_t st = {(short)(FOUR ? a + bq + cq : a + bq), (short)(-(m2t >> 1))};
+        const int y0 = __builtin_amdgcn_sdot2(st, k01, 0, false), y1 = __builtin_amdgcn_sdot2(st, k23, 0, false);
+        const int e0 = L.val[wide][quant_h_int(y0, det, M)];
+        const int e1 = L.val[wide][quant_h_int(y1, det, M)];
+        const short2_t d01 = {(short)a, (short)(bq - a)};
+        if (FOUR) {
+            const int p1 = (int)((mul_u24((uint32_t)(2 * e0 + e1), 43691u) + 43691u) >> 17);
+            const int p2 = (int)((mul_u24((uint32_t)(e0 + 2 * e1), 43691u) + 43691u) >> 17);
+            const short2_t pe01 = __builtin_bit_cast(short2_t, (uint32_t)e0 | ((uint32_t)p1 << 16));
+            const short2_t pe23 = __builtin_bit_cast(short2_t, (uint32_t)p2 | ((uint32_t)e1 << 16));
+            const short2_t d23 = {(short)(cq - bq), (short)(m2t - cq)};
+            sse = __builtin_amdgcn_sdot2(pe01, n01 * pe01 + d01, sse, false);
+            sse = __builtin_amdgcn_sdot2(pe23, n23 * pe23 + d23, sse, false);
+        } else {
+            const int p1 = (e0 + e1 + 1) >> 1;
+            const short2_t pe01 = __builtin_bit_cast(short2_t, (uint32_t)e0 | ((uint32_t)p1 << 16));
+            sse = __builtin_amdgcn_sdot2(pe01, n01 * pe01 + d01, sse, false);
+            sse += mul_i24(e1, mul_i24(n2, e1) + (m2t - bq));
+        }
+    }
+    // ties go to the first split of the enumeration: the four-cluster list,
+    // then the lower (s1, s2, s3)
+    const uint32_t order = (FOUR ? 0u : 1u << 15) | (uint32_t)s1 << 10 | (uint32_t)s2 << 5 | (uint32_t)s3;
+    if (live && det != 0) atomicMin(&L.best[col], (unsigned long long)(uint32_t)sse << 16 | order);
+}
+
+// Orders this wave's LDS writes before its reads of other lanes' data.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+struct Sweep {
+    float scatter;   // Q'
+    float mean[3];
+    int q;           // entries in the wave's queue
+    uint32_t tested; // splits queued so far by the wave
+    uint32_t lanes;  // all ones, or 0 on a lane whose block needs no split (constant colour)
+};
+
+// Q' - (sqrt(best) + sqrt(3))^2, less what FP32 rounding could hide.
+__device__ __forceinline__ float need(float scatter, unsigned long long best)
+{
+    const float r = __builtin_amdgcn_sqrtf((float)(uint32_t)(best >> 16)) + 1.74f;
+    return fmaf(scatter, 1.0f - 2e-5f, -r * r) - 0.05f;
+}
+
+// Test the splits of one list in enumeration order, those with even bounds
+// only (step 2) or, in the four-cluster list, all the others (step 1).  A row
+// is the splits of one (s1, s2) (three clusters: s1) and every last bound s;
+// R holds the centred prefix rows (0 and 16 are zero).  Misses collect bit by
+// bit over rows, as their numbers follow each other; every 32 splits at most,
+// the hits are queued, and scored whenever 64 are waiting.
+template <bool FOUR, class Lds>
+__device__ __forceinline__ void sweep(Lds &L, int lane, int wave, const float (&R)[15][3], int step, Sweep &w, float &T)
+{
+    uint32_t miss = 0, wanted = 0, bits = 0, next = 0;   // the row's splits are number next - bits ..
+    int s1 = 0, s2 = 0;
+    float a[3] = {0.0f, 0.0f, 0.0f};
+    while (true) {
+        const bool end = s1 > 16;
+        const int lo = FOUR ? s2 : s1;
+        if (end || bits + 17 - lo > 32 || (FOUR && step == 2)) {
+            uint32_t hits = ~miss & wanted & w.lanes;
+            uint64_t any;
+            while ((any = __ballot(hits != 0)) != 0) {
+                if (hits) {
+                    const uint32_t at = (uint32_t)w.q + __builtin_amdgcn_mbcnt_hi((uint32_t)(any >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)any, 0u));
+                    L.queue[wave][at] = (uint32_t)(lane & 63) << 11 | (next - (uint32_t)__ffs(hits));
+                    hits &= hits - 1;
+                }
+                const int k = __popcll(any);
+                w.q += k;
+                w.tested += (uint32_t)k;
+                if (w.q >= 64) {
+                    wave_lds_fence();
+                    w.q -= 64;
+                    score<FOUR>(L, L.queue[wave][w.q + (lane & 63)], 64 * wave, true);
+                    wave_lds_fence();
+                    T = need(w.scatter, L.best[lane]);
+                }
+            }
+            wanted = bits = 0;
+            if (end) break;
+        }
+        if (s2 == s1 || !FOUR) {
+#pragma unroll
+            for (int c = 0; c < 3; c++) a[c] = fmaf(-0.5f, (float)L.m2P[3 * s1 + c][lane], -w.mean[c] * (float)s1);
+        }
+        float u[3];
+#pragma unroll
+        for (int c = 0; c < 3; c++)
+            u[c] = FOUR ? a[c] + fmaf(-0.5f, (float)L.m2P[3 * s2 + c][lane], -w.mean[c] * (float)s2) : a[c];
+        const float *spread = FOUR ? kTab.spread4[17 * s1 + s2] : kTab.spread3[s1];
+        float V[17];
+#pragma unroll
+        for (int s = 0; s <= 16; s++) V[s] = spread[s];   // scalar, one wide load
+#pragma unroll
+        for (int s = 0; s <= 16; s++) {
+            if (s >= lo) {
+                const bool zero = s == 0 || s == 16;
+                const float x = zero ? u[0] : u[0] + R[zero ? 0 : s - 1][0], y = zero ? u[1] : u[1] + R[zero ? 0 : s - 1][1];
+                const float z = zero ? u[2] : u[2] + R[zero ? 0 : s - 1][2];
+                const float d = fmaf(x, x, fmaf(y, y, fmaf(z, z, -T * V[s])));
+                miss = __builtin_amdgcn_alignbit(miss, __float_as_uint(d), 31);   // its sign enters from below
+            }
+        }
+        const uint32_t n = (uint32_t)(17 - lo);
+        // bit 16 - s of the row: even s in the first sweep, what it left in the second
+        const uint32_t row = !FOUR ? ~0u : step == 2 ? 0x15555u : ((s1 | s2) & 1) ? ~0u : ~0x15555u;
+        wanted = wanted << n | (row & ((1u << n) - 1u));
+        bits += n;
+        next = (FOUR ? kTab.first4[17 * s1 + s2] : kTab.first3[s1]) + n;
+        if (FOUR) s2 += step;
+        if (!FOUR || s2 > 16) {
+            s1 += step;
+            s2 = s1;
+        }
+    }
+}
+
+template <bool FOUR, class Lds>
+__device__ __forceinline__ void score_rest(Lds &L, int lane, int wave, Sweep &w)
+{
+    wave_lds_fence();
+    score<FOUR>(L, L.queue[wave][lane & 63], 64 * wave, (lane & 63) < w.q);
+    wave_lds_fence();
+    w.q = 0;
+}
+
+// Best split of every block of the wave (in L.best): false if so many of the
+// even splits pass the test that scoring every split in uniform order is
+// cheaper (smooth blocks, whose SSE is mostly endpoint quantisation).
+template <class Lds>
+__device__ __forceinline__ bool find_split(Lds &L, int lane, int wave, const int (&tot)[3], int Q, const int (&cut)[3],
+                                           bool constant)
+{
+    Sweep w;
+    w.lanes = constant ? 0u : ~0u;
+    w.scatter = (float)(16 * Q - (tot[0] * tot[0] + tot[1] * tot[1] + tot[2] * tot[2])) * (1.0f / 16.0f);
+    w.q = 0;
+    w.tested = 0;
+    float R[15][3];
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        w.mean[c] = (float)tot[c] * (1.0f / 16.0f);
+#pragma unroll
+        for (int s = 1; s <= 15; s++) R[s - 1][c] = fmaf(-0.5f, (float)L.m2P[3 * s + c][lane], -w.mean[c] * (float)s);
+    }
+    L.Q[lane] = Q;
+    L.best[lane] = ~0ull;
+    // the first score: one split per lane, its own block's
+    wave_lds_fence();
+    score<true>(L, (uint32_t)(lane & 63) << 11 | (kTab.first4[17 * cut[0] + cut[1]] + (uint32_t)(cut[2] - cut[1])),
+                64 * wave, true);
+    wave_lds_fence();
+    float T = need(w.scatter, L.best[lane]);
+#pragma unroll 1
+    for (int step = 2; step >= 1; step--) {
+        sweep<true>(L, lane, wave, R, step, w, T);
+        if (step == 2 && w.tested > 64u * 132u) return false;   // above 4 in 5 of the 165
+    }
+    score_rest<true>(L, lane, wave, w);
+    T = need(w.scatter, L.best[lane]);
+    sweep<false>(L, lane, wave, R, 1, w, T);
+    score_rest<false>(L, lane, wave, w);
+    return true;
+}
+
 // Endpoint codes of one split (the same arithmetic as split_list).
 template <class Lds>
 __device__ __forceinline__ void split_codes(const Lds &L, int lane, const int (&tot)[3], const int (&m2tot)[3], uint32_t split,
@@ -266,10 +488,42 @@ __device__ __forceinline__ void split_codes(const Lds &L, int lane, const int (&
     }
 }
 
-template <class Lds>
-__device__ __forceinline__ void encode_block(const uint32_t (&t)[16], uint32_t refine_steps, Lds &L, int lane, uint32_t &w0,
-                             uint32_t &w1, uint32_t &sse_out)
+__device__ __forceinline__ void load_texels(const uint4 *src, uint32_t (&t)[16])
 {
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const uint4 v = src[q];
+        t[4 * q] = v.x; t[4 * q + 1] = v.y; t[4 * q + 2] = v.z; t[4 * q + 3] = v.w;
+    }
+}
+
+// Constant block: per-channel endpoint tables; the mode with the smaller
+// error (4-colour on ties).
+__device__ __forceinline__ void encode_constant(const uint32_t (&t)[16], int Q, uint32_t &w0, uint32_t &w1, uint32_t &sse)
+{
+    int a4[3], b4[3], a3[3], b3[3], err4 = 0, err3 = 0;
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        int wide = c == 1, v = (int)((t[0] >> (8 * c)) & 255u);
+        a4[c] = kTab.a4[wide][v]; b4[c] = kTab.b4[wide][v];
+        a3[c] = kTab.a3[wide][v]; b3[c] = kTab.b3[wide][v];
+        int e4 = kTab.e4[wide][v], e3 = kTab.e3[wide][v];
+        err4 += e4 * e4;
+        err3 += e3 * e3;
+    }
+    const bool four = err4 <= err3;
+    uint32_t c0 = four ? pack565(a4[0], a4[1], a4[2]) : pack565(a3[0], a3[1], a3[2]);
+    uint32_t c1 = four ? pack565(b4[0], b4[1], b4[2]) : pack565(b3[0], b3[1], b3[2]);
+    sse = canon_index(c0, c1, four, t, Q, w1);
+    w0 = c0 | (c1 << 16);
+}
+
+template <class Lds>
+__device__ __forceinline__ void encode_block(const uint4 *src, uint32_t refine_steps, Lds &L, int lane, int wave,
+                             uint32_t &w0, uint32_t &w1, uint32_t &sse_out)
+{
+    uint32_t t[16];
+    load_texels(src, t);
     // sum of |x|^2 over the texels (the palette-independent part of the SSE)
     int Q = 0;
 #pragma unroll
@@ -281,25 +535,8 @@ __device__ __forceinline__ void encode_block(const uint32_t (&t)[16], uint32_t r
 #pragma unroll
     for (int i = 1; i < 16; i++) constant &= ((t[i] ^ t[0]) & 0xFFFFFFu) == 0;
 
-    uint32_t c0, c1, idx, sse;
-    if (constant) {
-        int a4[3], b4[3], a3[3], b3[3], err4 = 0, err3 = 0;
-#pragma unroll
-        for (int c = 0; c < 3; c++) {
-            int wide = c == 1, v = (int)((t[0] >> (8 * c)) & 255u);
-            a4[c] = kTab.a4[wide][v]; b4[c] = kTab.b4[wide][v];
-            a3[c] = kTab.a3[wide][v]; b3[c] = kTab.b3[wide][v];
-            int e4 = kTab.e4[wide][v], e3 = kTab.e3[wide][v];
-            err4 += e4 * e4;
-            err3 += e3 * e3;
-        }
-        bool four = err4 <= err3;
-        c0 = four ? pack565(a4[0], a4[1], a4[2]) : pack565(a3[0], a3[1], a3[2]);
-        c1 = four ? pack565(b4[0], b4[1], b4[2]) : pack565(b3[0], b3[1], b3[2]);
-        sse = canon_index(c0, c1, four, t, Q, idx);
-        w0 = c0 | (c1 << 16);
-        w1 = idx;
-        sse_out = sse;
+    if (__all(constant)) {
+        encode_constant(t, Q, w0, w1, sse_out);
         return;
     }
 
@@ -360,6 +597,21 @@ __device__ __forceinline__ void encode_block(const uint32_t (&t)[16], uint32_t r
     for (int i = 0; i < 16; i++)
         proj[i] = __builtin_amdgcn_sdot2(__builtin_bit_cast(short2_t, __builtin_amdgcn_perm(0u, t[i], 0x0C010C00u)), v01,
                                          __mul24((int)__builtin_amdgcn_ubfe(t[i], 16, 8), v[2]), false);
+    // texels below 1/6, 1/2 and 5/6 of the projections' range (|proj| < 2^25)
+    int cut[3] = {0, 0, 0};
+    {
+        int plo = proj[0], phi = proj[0];
+#pragma unroll
+        for (int i = 1; i < 16; i++) { plo = min(plo, proj[i]); phi = max(phi, proj[i]); }
+        const int range = phi - plo;
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const int x = proj[i] - plo;
+            cut[0] += 6 * x < range ? 1 : 0;
+            cut[1] += 2 * x < range ? 1 : 0;
+            cut[2] += 6 * x < 5 * range ? 1 : 0;
+        }
+    }
 #pragma unroll
     for (int i = 0; i < 16; i++) {
         int r = 0;
@@ -385,15 +637,25 @@ __device__ __forceinline__ void encode_block(const uint32_t (&t)[16], uint32_t r
     const int m2tot[3] = {-2 * run[0], -2 * run[1], -2 * run[2]};
 
     // ---- cluster fit over every split (4-colour list, then 3-colour list)
-    uint32_t best = 0xFFFFFFFFu, best_split = 1u << 15;
-    split_list<true>(L, lane, tot, m2tot, Q, best, best_split);
-    split_list<false>(L, lane, tot, m2tot, Q, best, best_split);
+    uint32_t best_split;
+    if (find_split(L, lane, wave, tot, Q, cut, constant)) {
+        const uint32_t o = (uint32_t)L.best[lane] & 0xFFFFu;   // three << 15 | s1 << 10 | s2 << 5 | s3
+        best_split = (o >> 10 & 31u) | (o & 0x3E0u) | (o & 31u) << 10 | (o & 0x8000u ? 0u : 1u << 15);
+    } else {
+        uint32_t best = 0xFFFFFFFFu;
+        best_split = 1u << 15;
+        split_list<true>(L, lane, tot, m2tot, Q, best, best_split);
+        split_list<false>(L, lane, tot, m2tot, Q, best, best_split);
+    }
     int bq0[3], bq1[3];
     split_codes(L, lane, tot, m2tot, best_split, bq0, bq1);
 
-    c0 = pack565(bq0[0], bq0[1], bq0[2]);
-    c1 = pack565(bq1[0], bq1[1], bq1[2]);
-    sse = canon_index(c0, c1, (best_split >> 15) & 1, t, Q, idx);
+    // the texels again (cached): held across the split search, their 16
+    // registers would spill (the empty asm keeps the loads apart)
+    asm volatile("" : "+v"(src));
+    load_texels(src, t);
+    uint32_t c0 = pack565(bq0[0], bq0[1], bq0[2]), c1 = pack565(bq1[0], bq1[1], bq1[2]), idx;
+    uint32_t sse = canon_index(c0, c1, (best_split >> 15) & 1, t, Q, idx);
 
     // ---- refinement: best of the 12 one-step moves, taken if strictly better
     for (uint32_t step = 0; step < refine_steps; step++) {
@@ -419,6 +681,7 @@ __device__ __forceinline__ void encode_block(const uint32_t (&t)[16], uint32_t r
     w0 = c0 | (c1 << 16);
     w1 = idx;
     sse_out = sse;
+    if (constant) encode_constant(t, Q, w0, w1, sse_out);
 }
 
 // One lane per block over the run map; rounds of LANES blocks (a run never
@@ -428,6 +691,7 @@ __global__ __launch_bounds__(LANES) __attribute__((amdgpu_waves_per_eu(4))) void
 {
     __shared__ Bc1Lds<LANES> L;
     __shared__ uint32_t s_item;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (int e = threadIdx.x; e < 2 * 512; e += LANES) {
         const int wide = e >> 9, c = kTab.code[wide][e & 511];
         L.code[wide][e & 511] = (uint8_t)c;
@@ -451,14 +715,8 @@ __global__ __launch_bounds__(LANES) __attribute__((amdgpu_waves_per_eu(4))) void
             if (__ballot(live) == 0) continue;   // padding (per wave; no barriers below)
             const uint64_t bl = live ? b : run.nblk - 1;   // dead lanes redo the last block, write nothing
             const uint4 *src = reinterpret_cast<const uint4 *>(run.src + bl * 64);
-            uint32_t t[16];
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                uint4 v = src[q];
-                t[4 * q] = v.x; t[4 * q + 1] = v.y; t[4 * q + 2] = v.z; t[4 * q + 3] = v.w;
-            }
             uint32_t w0, w1, sse;
-            encode_block(t, a.refine_steps, L, threadIdx.x, w0, w1, sse);
+            encode_block(src, a.refine_steps, L, threadIdx.x, wave, w0, w1, sse);
             if (live) {
                 uint2 *dst = reinterpret_cast<uint2 *>(run.dst + b * 8);
                 *dst = make_uint2(w0, w1);
@@ -513,21 +771,32 @@ void build_tables(Bc1Tables &T)
             T.code[wide][h] = (uint8_t)n;
         }
     }
-    // split multipliers, enumerated as the device's split lists are
+    // splits, enumerated as the device's split lists are
     for (int four = 0; four < 2; four++) {
-        uint32_t *M = four ? T.magic4 : T.magic3;
+        uint4 *S = four ? T.split4 : T.split3;
+        const int F = four ? 3 : 2;
         int si = 0;
-        for (int s1 = 0; s1 <= 16; s1++)
-            for (int s2 = s1; s2 <= 16; s2++)
+        for (int s1 = 0; s1 <= 16; s1++) {
+            if (!four) T.first3[s1] = (uint32_t)si;
+            for (int s2 = s1; s2 <= 16; s2++) {
+                if (four) T.first4[17 * s1 + s2] = (uint32_t)si;
                 for (int s3 = four ? s2 : 16; s3 <= 16; s3++) {
                     const int n0 = s1, n1 = s2 - s1, n2 = s3 - s2, n3 = 16 - s3;
                     const int A = four ? 9 * n0 + 4 * n1 + n2 : 4 * n0 + n1;
                     const int B = four ? n1 + 4 * n2 + 9 * n3 : n1 + 4 * n2;
                     const int AB = four ? 2 * (n1 + n2) : n1;
                     const long long det = (long long)A * B - (long long)AB * AB;
-                    M[si++] = det > 0 ? (uint32_t)(((1ull << 36) + (unsigned long long)det - 1) / (unsigned long long)det)
-                                      : 0u;
+                    auto pair16 = [](int lo, int hi) { return (uint32_t)(uint16_t)lo | (uint32_t)(uint16_t)hi << 16; };
+                    S[si].x = (uint32_t)(s1 | s2 << 5 | s3 << 10) | (uint32_t)det << 16;
+                    S[si].z = pair16(-F * (B + AB), -2 * F * F * AB);
+                    S[si].w = pair16(F * (A + AB), 2 * F * F * A);
+                    S[si++].y = det > 0 ? (uint32_t)(((1ull << 36) + (unsigned long long)det - 1) / (unsigned long long)det)
+                                        : 0u;
+                    const int w = four ? s1 + s2 + s3 : s1 + s2;   // sum of the weights; A is the sum of their squares
+                    (four ? T.spread4[17 * s1 + s2][s3] : T.spread3[s1][s2]) = (float)(16 * A - w * w) / 16.0f;
                 }
+            }
+        }
         if (si != (four ? kSplits4 : kSplits3)) abort();
     }
 }
