@@ -91,7 +91,7 @@ __device__ __forceinline__ void candidate(int ci, int &m, int &p, int &r, int &s
 // ---- texels in LDS
 //
 // Texels sit in LDS, one column per lane, scaled by -8: rg holds -8 R and
-// -8 G as 16-bit halves, bx holds -8 B.  Because |x|^2 is the same for every
+// -8 G as 16-bit halves, bx holds -8 B (16 bits).  Because |x|^2 is the same for every
 // palette entry, the least-SSE entry is the least 256 (|p|^2 - 2 x.p) + k.
 // Each entry is held as E = (64 pR, 64 pG) in 16-bit halves, Eb = 64 pB and
 // C = 256 |p|^2 + k, so one texel x entry evaluation is
@@ -112,7 +112,7 @@ constexpr int kScaleNeg = -8;          // texel scale in LDS
 
 struct TexLds {
     uint32_t rg[16][kWG];
-    int32_t bx[16][kWG];
+    int16_t bx[16][kWG];
     uint16_t q[kQEntries];        // search: near64; emit: nearest
 };
 
@@ -648,6 +648,9 @@ __device__ __forceinline__ PairFit fit_scalar(const TexLds &S, int rot, const ui
     const int v0 = nvalue(0);
     int nlo = v0, nhi = v0;
     bool same = true;
+    // (member loops partly rolled: unrolled, the 16 values stay in registers
+    // from pass to pass, which spills in the search)
+#pragma unroll 3
     for (int i = 1; i < 16; i++) {
         int v = nvalue(i);
         same &= v == v0;
@@ -689,6 +692,7 @@ __device__ __forceinline__ PairFit fit_scalar(const TexLds &S, int rot, const ui
         uint32_t sse = 0;
         uint64_t idx = 0;
         int A = 0, B = 0, AB2 = 0, nSA = 0, nSB = 0;
+#pragma unroll 2
         for (int i = 0; i < 16; i++) {
             const int x = nvalue(i);
             int kmin = 0x7FFFFFFF;
@@ -734,62 +738,76 @@ __device__ __forceinline__ void anchor_fix(PairFit &f, uint32_t mask, int anchor
 
 // ---- the candidates of one partition shape
 //
-// Best key of one block over the modes of `mode_mask` that use a partition:
-// the principal axis and the extreme texels of a subset depend only on the
-// partition, so they are found once and shared by its modes.  A wave's lanes
-// hold different blocks; the masks are wave-uniform in the search (scalar
-// member loops) and per lane in the seed pass.
+// The principal axis and the extreme texels of a subset depend only on its
+// members, so they are found once and shared by the modes with that
+// partition.  A wave's lanes hold different blocks; the masks are
+// wave-uniform in the search (scalar member loops) and per lane in the seed
+// pass.
 __device__ __forceinline__ void consider(uint32_t sse, int ci, uint32_t &best)
 {
     best = min(best, (sse << 9) | (uint32_t)ci);
 }
 
-// 2-subset partition p: modes 1, 3, 7
-__device__ __forceinline__ uint32_t search_2subset(const TexLds &S, int p, uint32_t mode_mask, const uint32_t *sv)
+// Candidate types of the search: 2-subset partitions (modes 1, 3, 7),
+// 3-subset ones in mode 0 and in mode 2, rotations (modes 4, 5), mode 6.
+enum { kTwo = 0, kThree0 = 1, kThree2 = 2, kRot = 3, kSix = 4, kTypes = 5 };
+constexpr uint32_t kGone = 0xFFFFFFFFu;   // a mode that is out of the race
+
+// Add the subset's SSE to each of the type's modes still in the race (e[0]
+// only, except for modes 1, 3, 7).
+template <int TYPE>
+__device__ __forceinline__ void add_subset(const TexLds &S, uint32_t m, const Sums &sums, const uint32_t *sv, uint32_t (&e)[3])
 {
-    uint32_t best = 0xFFFFFFFFu, e1 = 0, e3 = 0, e7 = 0;
-#pragma unroll 1
-    for (int s = 0; s < 2; s++) {
-        const uint32_t m = mask2(p, s);
-        const Prep P = prep_subset(S, m, 0);
-        if (mode_mask & 0x02) e1 += fit_colour<6, 1, 3, true>(S, m, 0, P, sv).sse;
-        if (mode_mask & 0x08) e3 += fit_colour<7, 2, 2, true>(S, m, 0, P, sv).sse;
-        if (mode_mask & 0x80) e7 += fit_colour<5, 2, 2, true>(S, m, 0, P, sv).sse;
+    const Prep P = prep_subset(S, m, 0, sums);
+    auto add = [&](int q, auto fit) {
+        if (__any(e[q] != kGone)) {
+            const uint32_t v = fit();
+            e[q] = e[q] == kGone ? kGone : e[q] + v;
+        }
+    };
+    if (TYPE == kTwo) {
+        add(0, [&] { return fit_colour<6, 1, 3, true>(S, m, 0, P, sv).sse; });
+        add(1, [&] { return fit_colour<7, 2, 2, true>(S, m, 0, P, sv).sse; });
+        add(2, [&] { return fit_colour<5, 2, 2, true>(S, m, 0, P, sv).sse; });
+    } else if (TYPE == kThree0) {
+        e[0] += fit_colour<4, 2, 3, true>(S, m, 0, P, sv).sse;
+    } else {
+        e[0] += fit_colour<5, 0, 2, true>(S, m, 0, P, sv).sse;
     }
-    if (mode_mask & 0x02) consider(e1, 16 + p, best);
-    if (mode_mask & 0x08) consider(e3, 144 + p, best);
-    if (mode_mask & 0x80) consider(e7, 221 + p, best);
+}
+
+// Key of a partition whose subsets are all added.
+template <int TYPE>
+__device__ __forceinline__ uint32_t partition_key(int p, const uint32_t (&e)[3])
+{
+    if (TYPE == kThree0) return (e[0] << 9) | (uint32_t)p;
+    if (TYPE == kThree2) return (e[0] << 9) | (uint32_t)(80 + p);
+    uint32_t best = 0xFFFFFFFFu;
+    if (e[0] != kGone) consider(e[0], 16 + p, best);
+    if (e[1] != kGone) consider(e[1], 144 + p, best);
+    if (e[2] != kGone) consider(e[2], 221 + p, best);
     return best;
 }
 
-// 3-subset partition p: mode 2 (MODE 2) or mode 0 (p < 16, MODE 0)
-template <int MODE>
-__device__ __forceinline__ uint32_t search_3subset(const TexLds &S, int p, const uint32_t *sv)
-{
-    uint32_t e = 0;
-#pragma unroll 1
-    for (int s = 0; s < 3; s++) {
-        const uint32_t m = mask3(p, s);
-        const Prep P = prep_subset(S, m, 0);
-        e += MODE == 2 ? fit_colour<5, 0, 2, true>(S, m, 0, P, sv).sse : fit_colour<4, 2, 3, true>(S, m, 0, P, sv).sse;
-    }
-    return (e << 9) | (uint32_t)(MODE == 2 ? 80 + p : p);
-}
+// The full mask, not a constant to the compiler: with one it unrolls the
+// member loops and keeps all texels in registers, which spill.
+__device__ __forceinline__ uint32_t all_texels() { return 0xFFFFu + g_bc7_opaque_zero; }
 
 // rotation r: modes 4 (both index selections) and 5
 __device__ __forceinline__ uint32_t search_rotation(const TexLds &S, int r, uint32_t mode_mask, const uint32_t *sv)
 {
     uint32_t best = 0xFFFFFFFFu;
-    const Prep P = prep_subset(S, 0xFFFFu, r);
+    const uint32_t full = all_texels();
+    const Prep P = prep_subset(S, full, r);
     if (mode_mask & 0x10) {
-        uint32_t s0 = fit_colour<5, 0, 2, true>(S, 0xFFFFu, r, P, sv).sse;
-        uint32_t s1 = fit_colour<5, 0, 3, true>(S, 0xFFFFu, r, P, sv).sse;
+        uint32_t s0 = fit_colour<5, 0, 2, true>(S, full, r, P, sv).sse;
+        uint32_t s1 = fit_colour<5, 0, 3, true>(S, full, r, P, sv).sse;
         if (r) { s0 += fit_scalar<6, 3, false>(S, r, sv).sse; s1 += fit_scalar<6, 2, false>(S, r, sv).sse; }
         consider(s0, 208 + 2 * r, best);
         consider(s1, 209 + 2 * r, best);
     }
     if (mode_mask & 0x20) {
-        uint32_t s5 = fit_colour<7, 0, 2, true>(S, 0xFFFFu, r, P, sv).sse;
+        uint32_t s5 = fit_colour<7, 0, 2, true>(S, full, r, P, sv).sse;
         if (r) s5 += fit_scalar<8, 2, false>(S, r, sv).sse;
         consider(s5, 216 + r, best);
     }
@@ -799,8 +817,9 @@ __device__ __forceinline__ uint32_t search_rotation(const TexLds &S, int r, uint
 // mode 6
 __device__ __forceinline__ uint32_t search_mode6(const TexLds &S, const uint32_t *sv)
 {
-    const Prep P = prep_subset(S, 0xFFFFu, 0);
-    return (fit_colour<7, 2, 4, true>(S, 0xFFFFu, 0, P, sv).sse << 9) | 220u;
+    const uint32_t full = all_texels();
+    const Prep P = prep_subset(S, full, 0);
+    return (fit_colour<7, 2, 4, true>(S, full, 0, P, sv).sse << 9) | 220u;
 }
 
 // ---- pass 2: re-fit the winner (same arithmetic) and lay out its bits
@@ -958,7 +977,7 @@ __device__ __forceinline__ void stage_texels(TexLds &S, const uint8_t *src, bool
     for (int i = 0; i < 16; i++) {
         const int r = (int)(t[i] & 255u), g = (int)((t[i] >> 8) & 255u), bb = (int)((t[i] >> 16) & 255u);
         S.rg[i][threadIdx.x] = ((uint32_t)(kScaleNeg * r) & 0xFFFFu) | ((uint32_t)(kScaleNeg * g) << 16);
-        S.bx[i][threadIdx.x] = kScaleNeg * bb;
+        S.bx[i][threadIdx.x] = (int16_t)(kScaleNeg * bb);
     }
 }
 
@@ -1011,8 +1030,16 @@ struct ItemLoop {
 //   search  one wave per (candidate, window of blocks): the blocks left are
 //           taken 64 at a time, one per lane, whatever their places in the
 //           window, so the fits run on full waves with wave-uniform masks.
-// On scenes of synthetic SH bands 1-2 of 64 2-subset partitions, 13 of 64
-// 3-subset ones (mode 2), 4 of 16 (mode 0) and 1.7 of 4 rotations are left.
+//           Each is tested again against the block's best so far, and once
+//           more when the partition's largest subset is fitted (its SSE and
+//           the bounds of the others); the blocks still left are gathered to
+//           full waves again for the other subsets.
+// On 1,048,576 primitives of synthetic SH bands 2-3 of 64 2-subset
+// partitions, 20 of 64 3-subset ones (mode 2), 6 of 16 (mode 0) and 2 of 4
+// rotations are left in bands 1-15, twice to eight times as many in the
+// smooth band 0; half to 85 % of those stop at their largest subset.  VALU
+// instructions per 64 blocks: bounds 28 k, seeds 13 k, search 79 k (735 k for
+// an exhaustive search); 1,048,576 blocks: 16.5 ms exhaustive, 4.2 ms now.
 
 // Largest deviation, in one channel, of a rounded palette from the straight
 // line nearest to it: entry k is e0 + floor((w_k D + 32)/64) with D = e1 - e0,
@@ -1024,13 +1051,13 @@ struct ItemLoop {
 constexpr float kSlack2 = 0.6245f, kSlack3 = 0.7750f, kSlack4 = 0.8152f;
 constexpr float kSlackRot = 0.6328f;
 
-// Candidate words of a slice (64 blocks): 2-subset partitions, 3-subset
-// partitions in mode 2, the 16 of mode 0, rotations (modes 4, 5), mode 6.
-constexpr int kW2 = 0, kW3 = 64, kW0 = 128, kWR = 144, kW6 = 148, kWords = 149;
+// Candidate words of a slice (64 blocks), per type.
+constexpr int kWordAt[kTypes + 1] = {0, 64, 80, 144, 148, 149};
+constexpr int kWords = 149;
 constexpr int kTiles = 13;   // 16-row mask tiles: 4 of 2-subset masks, 8 of 3-subset masks, all ones
 
-// Bounds of a chunk of blocks (nc of them, so that the scratch stays at 76 MB
-// and in the last-level cache), 16 bits each:
+// Bounds of a chunk of blocks (nc of them: the scratch of a large encode stays
+// at 167 MB), 16 bits each:
 //   b2[16][nc] 4 partitions, b3[32][nc] 2 partitions, b0[8][nc] 2, br[nc] 4 rotations,
 //   seed[nc]: least 3-subset partition | least rotation << 8 | mode 6's bound << 16
 struct Bounds {
@@ -1045,12 +1072,13 @@ struct Bc7Search {
     EncodeArgs a;
     Tables T;
     WorkSplit w;
-    uint64_t first;             // bounds, seed: first block of the chunk
+    uint64_t first;             // first block of the chunk
+    uint32_t slices;            // slices of the chunk
     Bounds B;
     uint64_t *words;            // [slice][kWords]
     const uint8_t **src;        // [slice] texels of the slice's first block
-    uint32_t win2, win3, winr;  // search: slices per window
-    uint32_t types;             // search: candidate types of this launch (1: 2-subset, 2: 3-subset, 4: 1-subset)
+    uint32_t win[kTypes];       // search: slices per window, per type
+    uint32_t types;             // search: candidate types of this launch, bit per type
 };
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -1063,6 +1091,7 @@ __device__ __forceinline__ uint32_t bound16(float v)
 {
     return (uint32_t)max(__float_as_int(v) - (127 << 23), 0) >> 12;
 }
+__device__ __forceinline__ float bound_value(uint32_t b) { return b ? __int_as_float((int)(b << 12) + (127 << 23)) : 0.0f; }
 
 // sqrt of n R for a subset of n members with sums S = (x, y, z, xx, xy, xz,
 // yy, yz, zz), from below.  n XX - Sx Sx^T is exact in FP32 (integers below
@@ -1140,8 +1169,8 @@ __global__ __launch_bounds__(kWG) void k_bc7_bounds(Bc7Search L)
     const uint64_t g0 = L.first + (uint64_t)blockIdx.x * kWG;          // a workgroup lies in one run
     const BlockRun run = a.run[find_run(a.run, a.nrun, g0)];
     const uint64_t b0 = g0 - run.gbase + 64 * wave;                    // the slice's first block in its run
-    if (lane == 0) L.src[(g0 >> 6) + wave] = run.src + b0 * 64;
     const uint64_t c0 = (uint64_t)blockIdx.x * kWG + 64 * wave;        // ... and in the chunk
+    if (lane == 0) L.src[c0 >> 6] = run.src + b0 * 64;
     const uint32_t sh = lane < 32 ? 0u : 8u, lin = lane < 32 ? 0xFFu : 0u;
     for (int sb = 0; sb < 4; sb++) {
         const uint64_t b = b0 + 16 * sb + (lane & 15), c = c0 + 16 * sb + (lane & 15);
@@ -1264,7 +1293,15 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
     const int p3 = (int)(seed & 255u), rot = (int)((seed >> 8) & 255u);
     uint32_t key = ~0u;
     if (live) {
-        if (a.mode_mask & 0x04) key = min(key, search_3subset<2>(S, p3, L.T.sv));
+        if (a.mode_mask & 0x04) {
+            uint32_t e[3] = {0, 0, 0};
+#pragma unroll 1
+            for (int s = 0; s < 3; s++) {
+                const uint32_t m = mask3(p3, s);
+                add_subset<kThree2>(S, m, subset_sums(S, m, 0), L.T.sv, e);
+            }
+            key = partition_key<kThree2>(p3, e);
+        }
         if (a.mode_mask & 0x30) key = min(key, search_rotation(S, rot, a.mode_mask, L.T.sv));
     }
     a.keys[g] = key;
@@ -1300,10 +1337,12 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
     for (int r = 0; r < 4; r++)
         put(w1, 16 + r, (int)(((r < 2 ? vr.x : vr.y) >> (16 * (r & 1))) & 0xFFFFu) <= thr && rot != r);
     put(w1, 20, (int)(seed >> 16) <= thr);
-    uint64_t *words = L.words + (g >> 6) * kWords;
-    words[kW2 + lane] = w2;
-    words[kW3 + lane] = w3;
-    if (lane < kWords - kW0) words[kW0 + lane] = w1;
+    uint64_t *words = L.words + (c >> 6) * kWords;
+    words[kWordAt[kTwo] + lane] = w2;
+    words[kWordAt[kThree2] + lane] = w3;
+    // w1: the 16 of mode 0, 4 rotations, mode 6
+    if (lane < 16) words[kWordAt[kThree0] + lane] = w1;
+    else if (lane < 21) words[kWordAt[kRot] + lane - 16] = w1;
 }
 
 // Bit k (from 0) among the set bits of w.
@@ -1320,44 +1359,205 @@ __device__ __forceinline__ int nth_bit(uint64_t w, int k)
     return at;
 }
 
-// Items of a search launch, heavy types first: (window, candidate) pairs of
-// one type, a window's candidates next to each other (its texels stay in L2).
+// Items of a search launch, type after type: (window, candidate) pairs, a
+// window's candidates next to each other (its texels stay in L2).  The
+// longest items come first: with mode 2 first, which lowers most blocks' best
+// for the types after it, the launch ended on the 2-subset items of a dense
+// window (5.41 ms at 1,048,576 blocks against 4.52).
 struct Items {
-    uint32_t n[5], win[5];
+    uint32_t n[kTypes];
     uint32_t total;
 };
-__host__ __device__ inline Items search_items(uint64_t slices, uint32_t types, uint32_t mode_mask, uint32_t win2,
-                                              uint32_t win3, uint32_t winr)
+template <int T>
+struct Type { static constexpr int value = T; };
+__host__ __device__ constexpr uint32_t per_window(int type) { return (uint32_t)(kWordAt[type + 1] - kWordAt[type]); }
+__host__ __device__ inline Items search_items(const Bc7Search &L)
 {
+    constexpr uint32_t modes[kTypes] = {0x8A, 0x01, 0x04, 0x30, 0x40};
     Items I;
-    const uint32_t per[5] = {64, 16, 1, 4, 64};   // 2-subset, mode 0, mode 6, rotations, mode 2
-    const uint32_t win[5] = {win2, win3, winr, winr, win3};
-    const bool on[5] = {(types & 1) && (mode_mask & 0x8A), (types & 2) && (mode_mask & 0x01), (types & 4) && (mode_mask & 0x40),
-                        (types & 4) && (mode_mask & 0x30), (types & 2) && (mode_mask & 0x04)};
     I.total = 0;
-    for (int q = 0; q < 5; q++) {
-        I.win[q] = win[q];
-        I.n[q] = on[q] ? per[q] * (uint32_t)((slices + win[q] - 1) / win[q]) : 0u;
-        I.total += I.n[q];
+    for (int t = 0; t < kTypes; t++) {
+        const bool on = (L.types >> t & 1) && (L.a.mode_mask & modes[t]);
+        I.n[t] = on ? per_window(t) * ((L.slices + L.win[t] - 1) / L.win[t]) : 0u;
+        I.total += I.n[t];
     }
     return I;
 }
 
 constexpr int kMaxWin = 128;   // slices per window, at most
 
-// The candidates left, one item per wave (the workgroup shares the code
-// table only, so its waves run apart between the barriers of the queue).
+// One wave's LDS.  Blocks are held by their place in the window.
+struct WaveLds {
+    uint64_t word[kMaxWin];    // the candidate's words
+    uint16_t end[kMaxWin];     // running count of their bits
+    uint16_t q1[128];          // blocks to fit
+    uint16_t q2[128];          // blocks whose largest subset is fitted ...
+    uint32_t e[3][128];        // ... and its SSEs
+};
+
+// Orders a wave's LDS writes before its reads of other lanes' data.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// The candidates left of one window, for one candidate p of the type.
+template <int TYPE>
+__device__ __forceinline__ void search_item(const Bc7Search &L, TexLds &S, WaveLds &W, uint32_t s0, uint32_t ns, int p)
+{
+    const EncodeArgs &a = L.a;
+    const int lane = threadIdx.x & 63;
+    constexpr bool kParts = TYPE == kTwo || TYPE == kThree0 || TYPE == kThree2;
+    constexpr int NS = TYPE == kTwo ? 2 : 3;
+    // the candidate's bound of chunk block c
+    const uint64_t nc = L.B.nc;
+    const uint16_t *lb = TYPE == kTwo ? reinterpret_cast<const uint16_t *>(L.B.b2) + (p >> 2) * nc * 4 + (p & 3)
+                       : TYPE == kThree2 ? reinterpret_cast<const uint16_t *>(L.B.b3) + (p >> 1) * nc * 2 + (p & 1)
+                       : TYPE == kThree0 ? reinterpret_cast<const uint16_t *>(L.B.b0) + (p >> 1) * nc * 2 + (p & 1)
+                       : TYPE == kRot ? reinterpret_cast<const uint16_t *>(L.B.br) + p
+                                      : reinterpret_cast<const uint16_t *>(L.B.seed) + 1;
+    constexpr int kStep = TYPE == kTwo || TYPE == kRot ? 4 : 2;
+    uint32_t *const keys = a.keys + L.first + (uint64_t)s0 * 64;   // of the window
+    lb += (uint64_t)s0 * 64 * kStep;
+    // the window's words and the running count of their bits
+    uint32_t n = 0;
+    for (uint32_t h = 0; h < ns; h += 64) {
+        const uint32_t i = h + lane;
+        const uint64_t x = i < ns ? L.words[(uint64_t)(s0 + i) * kWords + kWordAt[TYPE] + p] : 0ull;
+        uint32_t e = (uint32_t)__popcll(x);
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t o = (uint32_t)__shfl_up((int)e, d);
+            if (lane >= d) e += o;
+        }
+        if (i < ns) {
+            W.word[i] = x;
+            W.end[i] = (uint16_t)(n + e);
+        }
+        n += (uint32_t)__builtin_amdgcn_readlane((int)e, 63);
+    }
+    if (n == 0) return;
+    wave_lds_fence();
+    // partitions: the largest subset first (one stage for the other types)
+    uint32_t first = 0xFFFFu;
+    int s_first = 0;
+    if (kParts) {
+        const uint32_t m0 = NS == 2 ? mask2(p, 0) : mask3(p, 0), m1 = NS == 2 ? mask2(p, 1) : mask3(p, 1);
+        const uint32_t m2 = NS == 2 ? 0u : mask3(p, 2);
+        const int c0 = __popc(m0), c1 = __popc(m1), c2 = __popc(m2);
+        s_first = c0 >= c1 && c0 >= c2 ? 0 : c1 >= c2 ? 1 : 2;
+        first = s_first == 0 ? m0 : s_first == 1 ? m1 : m2;
+    }
+    constexpr float kSlack = TYPE == kThree2 ? kSlack2 : kSlack3;
+    const float members = (float)__popc(first), inv = __builtin_amdgcn_rcpf(members);
+    auto stage = [&](uint32_t at, bool live) { stage_texels(S, live ? L.src[s0 + (at >> 6)] + 64 * (at & 63u) : nullptr, live); };
+    // the other subsets of `count` blocks at the top of q2
+    auto finish = [&](uint32_t q2, uint32_t count) {
+        wave_lds_fence();
+        const bool live = (uint32_t)lane < count;
+        const uint32_t at = live ? W.q2[q2 + lane] : 0u;
+        stage(at, live);
+        if (live) {
+            uint32_t e[3];
+            e[0] = W.e[0][q2 + lane];
+            if (TYPE == kTwo) { e[1] = W.e[1][q2 + lane]; e[2] = W.e[2][q2 + lane]; }
+#pragma unroll 1
+            for (int s = 0; s < NS; s++) {
+                if (s == s_first) continue;
+                const uint32_t m = NS == 2 ? mask2(p, s) : mask3(p, s);
+                add_subset<TYPE>(S, m, subset_sums(S, m, 0), L.T.sv, e);
+            }
+            atomicMin(keys + at, partition_key<TYPE>(p, e));
+        }
+        wave_lds_fence();
+    };
+    uint32_t t = 0, q1 = 0, q2 = 0;
+    while (true) {
+        // gather 64 blocks whose best so far still leaves the candidate a chance
+        while (q1 < 64 && t < n) {
+            const uint32_t i = t + lane;
+            uint32_t lo = 0, hi = ns - 1;
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (W.end[mid] > i) hi = mid;
+                else lo = mid + 1;
+            }
+            const uint64_t x = W.word[lo];
+            bool keep = i < n;
+            uint32_t at = 0;
+            if (keep) {
+                at = lo * 64 + (uint32_t)nth_bit(x, (int)(i - ((uint32_t)W.end[lo] - (uint32_t)__popcll(x))));
+                const uint32_t key = keys[at];
+                keep = key == ~0u || (uint32_t)lb[(uint64_t)at * kStep] <= bound16((float)(key >> 9));
+            }
+            const uint64_t m = __ballot(keep);
+            if (keep) W.q1[q1 + lanes_below(m)] = (uint16_t)at;
+            q1 += (uint32_t)__popcll(m);
+            t += 64;
+        }
+        if (q1 == 0) break;
+        wave_lds_fence();
+        const uint32_t count = q1 < 64 ? q1 : 64;
+        q1 -= count;
+        const bool live = (uint32_t)lane < count;
+        const uint32_t at = live ? W.q1[q1 + lane] : 0u;
+        stage(at, live);
+        uint32_t key = ~0u, e[3] = {kGone, kGone, kGone};
+        if (live) {
+            if (TYPE == kRot) key = search_rotation(S, p, a.mode_mask, L.T.sv);
+            if (TYPE == kSix) key = search_mode6(S, L.T.sv);
+            if (kParts) {
+                const Sums sums = subset_sums(S, first, 0);
+                const float f[9] = {(float)sums.nSx[0], (float)sums.nSx[1], (float)sums.nSx[2], (float)sums.XX[0], (float)sums.XX[1],
+                                    (float)sums.XX[2], (float)sums.XX[3], (float)sums.XX[4], (float)sums.XX[5]};
+                // what the bounds leave for the other subsets (the same arithmetic as the bounds')
+                const float rest = fmaf(bound_value(lb[(uint64_t)at * kStep]), 1.0f - 2e-6f,
+                                        -bound_term(residual_root(members, f), members, inv, kSlack));
+                if (TYPE == kTwo) {
+                    if (a.mode_mask & 0x02) e[0] = 0;
+                    if (a.mode_mask & 0x08) e[1] = 0;
+                    if (a.mode_mask & 0x80) e[2] = 0;
+                } else e[0] = 0;
+                add_subset<TYPE>(S, first, sums, L.T.sv, e);
+                const uint32_t best = keys[at];
+                const float room = best == ~0u ? 1e9f : (float)(best >> 9) * (1.0f + 2e-6f) - fmaxf(rest, 0.0f);
+#pragma unroll
+                for (int q = 0; q < (TYPE == kTwo ? 3 : 1); q++)
+                    if ((float)e[q] > room) e[q] = kGone;
+            } else atomicMin(keys + at, key);
+        }
+        if (kParts) {
+            const bool keep = live && (e[0] & e[1] & e[2]) != kGone;
+            const uint64_t m = __ballot(keep);
+            if (keep) {
+                const uint32_t to = q2 + lanes_below(m);
+                W.q2[to] = (uint16_t)at;
+                W.e[0][to] = e[0];
+                if (TYPE == kTwo) { W.e[1][to] = e[1]; W.e[2][to] = e[2]; }
+            }
+            q2 += (uint32_t)__popcll(m);
+            if (q2 >= 64) { q2 -= 64; finish(q2, 64); }
+        }
+    }
+    if (kParts && q2) finish(0, q2);
+    wave_lds_fence();
+}
+
+// One item per wave (the workgroup shares the code table only, so its waves
+// run apart between the barriers of the queue).
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k_bc7_search(Bc7Search L)
 {
     __shared__ TexLds S;
-    __shared__ uint64_t s_word[4][kMaxWin];
-    __shared__ uint32_t s_end[4][kMaxWin];
+    __shared__ WaveLds W[4];
     __shared__ uint32_t s_item;
-    const EncodeArgs &a = L.a;
-    const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t slices = (uint32_t)(a.total >> 6);
-    const Items I = search_items(slices, L.types, a.mode_mask, L.win2, L.win3, L.winr);
+    const Items I = search_items(L);
     stage_table(S, L.T.near64);
     ItemLoop it(L.w, (I.total + 3) / 4, &s_item);
     __syncthreads();
@@ -1365,55 +1565,16 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
     do {
         uint32_t q = it.item * 4 + wave;
         if (q >= I.total) continue;
-        int type = 0;
-        while (q >= I.n[type]) q -= I.n[type++];
-        const uint32_t per = type == 0 || type == 4 ? 64u : type == 1 ? 16u : type == 3 ? 4u : 1u;
-        const int word0 = type == 0 ? kW2 : type == 1 ? kW0 : type == 2 ? kW6 : type == 3 ? kWR : kW3;
-        const uint32_t win = I.win[type], w = q / per, s0 = w * win, ns = min(win, slices - s0);
-        const int p = (int)(q % per);
-        // the window's words of this candidate and the running count of their bits
-        uint32_t n = 0;
-        for (uint32_t h = 0; h < ns; h += 64) {
-            const uint32_t i = h + lane;
-            const uint64_t x = i < ns ? L.words[(uint64_t)(s0 + i) * kWords + word0 + p] : 0ull;
-            uint32_t e = (uint32_t)__popcll(x);
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const uint32_t o = (uint32_t)__shfl_up((int)e, d);
-                if (lane >= d) e += o;
-            }
-            if (i < ns) {
-                s_word[wave][i] = x;
-                s_end[wave][i] = n + e;
-            }
-            n += (uint32_t)__builtin_amdgcn_readlane((int)e, 63);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        for (uint32_t t0 = 0; t0 < n; t0 += 64) {
-            // lane's block: bit t - (bits before its slice) of the slice's word
-            const uint32_t t = t0 + lane;
-            const bool live = t < n;
-            uint32_t lo = 0, hi = ns - 1;
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (s_end[wave][mid] > t) hi = mid;
-                else lo = mid + 1;
-            }
-            const uint64_t x = s_word[wave][lo];
-            const int bit = live ? nth_bit(x, (int)(t - (s_end[wave][lo] - (uint32_t)__popcll(x)))) : 0;
-            stage_texels(S, live ? L.src[s0 + lo] + 64 * bit : nullptr, live);
-            if (live) {
-                const uint32_t key = type == 0 ? search_2subset(S, p, a.mode_mask, L.T.sv)
-                                   : type == 1 ? search_3subset<0>(S, p, L.T.sv)
-                                   : type == 2 ? search_mode6(S, L.T.sv)
-                                   : type == 3 ? search_rotation(S, p, a.mode_mask, L.T.sv)
-                                               : search_3subset<2>(S, p, L.T.sv);
-                atomicMin(a.keys + (uint64_t)(s0 + lo) * 64 + bit, key);
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        // the item's type (the first whose items reach past q), its window and candidate
+        auto item = [&](auto type) {
+            constexpr int T = decltype(type)::value;
+            if (q >= I.n[T]) { q -= I.n[T]; return false; }
+            const uint32_t s0 = q / per_window(T) * L.win[T], ns = min(L.win[T], L.slices - s0);
+            search_item<T>(L, S, W[wave], s0, ns, (int)(q % per_window(T)));
+            return true;
+        };
+        if (!item(Type<kTwo>()) && !item(Type<kThree0>()) && !item(Type<kRot>()) && !item(Type<kThree2>()))
+            item(Type<kSix>());
     } while (it.next(L.w, &s_item));
 }
 
@@ -1667,44 +1828,38 @@ hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t 
     const uint32_t nwg = (uint32_t)(a.total / kWG);
     const dim3 sgrid(nwg);
     // scratch: keys[total] | list[total] | count[8] start[8] | wgcount[nwg][8] |
-    // slice texels | candidate words | bounds of one chunk
+    // then for one chunk: slice texels | candidate words | bounds
     Bc7Search Q;
     Q.a = a;
     Q.T = L.T;
-    const uint64_t slices = a.total / 64;
     uint8_t *s = reinterpret_cast<uint8_t *>(a.keys) + 8 * a.total + 64 + 32 * (uint64_t)nwg;
     auto take = [&](size_t bytes) { uint8_t *r = s; s += (bytes + 15) & ~(size_t)15; return r; };
-    Q.src = reinterpret_cast<const uint8_t **>(take(8 * slices));
-    Q.words = reinterpret_cast<uint64_t *>(take(8 * kWords * slices));
     const uint64_t nc = a.total < kBc7Chunk ? a.total : kBc7Chunk;
+    Q.src = reinterpret_cast<const uint8_t **>(take(8 * (nc / 64)));
+    Q.words = reinterpret_cast<uint64_t *>(take(8 * kWords * (nc / 64)));
     Q.B.nc = nc;
     Q.B.b2 = reinterpret_cast<uint2 *>(take(16 * 8 * nc));
     Q.B.b3 = reinterpret_cast<uint32_t *>(take(32 * 4 * nc));
     Q.B.b0 = reinterpret_cast<uint32_t *>(take(8 * 4 * nc));
     Q.B.br = reinterpret_cast<uint2 *>(take(8 * nc));
     Q.B.seed = reinterpret_cast<uint32_t *>(take(4 * nc));
-    for (uint64_t first = 0; first < a.total; first += nc) {
-        Q.first = first;
-        const dim3 grid((uint32_t)(((a.total - first < nc ? a.total - first : nc)) / kWG));
-        GSBC_LAUNCH("bc7_bounds", k_bc7_bounds, grid, dim3(kWG), 0, st, Q);
-        GSBC_LAUNCH("bc7_seed", k_bc7_seed, grid, dim3(kWG), 0, st, Q);
-    }
-    // Windows: long enough that a candidate's blocks fill waves (about 1 in
-    // 40 blocks is left of a 2-subset partition, 1 in 5 of a 3-subset one, 1
-    // in 3 of a rotation), short enough that a small scene spreads over the chip.
-    auto window = [&](uint64_t split, uint32_t most) {
-        const uint64_t n = slices / split;
-        return (uint32_t)(n < 4 ? 4 : n > most ? most : n);
-    };
     auto launch = [&](int q, uint32_t types, const char *name) -> hipError_t {
         Q.w = w3[q];
         Q.types = types;
-        const uint32_t r = Q.w.item_rounds;
-        auto widen = [&](uint32_t n) { return n * r > (uint32_t)kMaxWin ? (uint32_t)kMaxWin : n * r; };
-        Q.win2 = widen(window(32, kMaxWin));
-        Q.win3 = widen(window(64, 64));
-        Q.winr = widen(window(512, 16));
-        const Items I = search_items(slices, types, a.mode_mask, Q.win2, Q.win3, Q.winr);
+        // Windows: long enough that a candidate's blocks fill waves (about 1
+        // in 20 blocks is left of a 2-subset partition, 1 in 3 of a 3-subset
+        // one or a rotation), short enough that a small scene spreads over
+        // the chip.
+        auto window = [&](uint32_t split, uint32_t most) {
+            uint32_t n = Q.slices / split;
+            n = n < 4 ? 4 : n > most ? most : n;
+            n *= Q.w.item_rounds;
+            return n > (uint32_t)kMaxWin ? (uint32_t)kMaxWin : n;
+        };
+        Q.win[kTwo] = window(32, kMaxWin);
+        Q.win[kThree0] = Q.win[kThree2] = window(64, 64);
+        Q.win[kRot] = Q.win[kSix] = window(512, 16);
+        const Items I = search_items(Q);
         if (I.total == 0) return hipSuccess;
         if (Q.w.queue) {
             hipError_t f = launch_fill_u64(reinterpret_cast<unsigned long long *>(Q.w.queue), 1, 0, st);
@@ -1713,15 +1868,24 @@ hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t 
         GSBC_LAUNCH(name, k_bc7_search, dim3(Q.w.queue ? Q.w.grid : (I.total + 3) / 4), dim3(kWG), 0, st, Q);
         return hipGetLastError();
     };
-    if (split == 0) {
-        if ((e = launch(0, 1, "bc7_search_2subset")) != hipSuccess) return e;
-        if ((e = launch(1, 2, "bc7_search_3subset")) != hipSuccess) return e;
-        if ((e = launch(2, 4, "bc7_search_1subset")) != hipSuccess) return e;
-    } else if (split == 1) {
-        if ((e = launch(0, 1, "bc7_search_2subset")) != hipSuccess) return e;
-        if ((e = launch(1, 6, "bc7_search_3subset_1subset")) != hipSuccess) return e;
-    } else {
-        if ((e = launch(0, 7, "bc7_search_items")) != hipSuccess) return e;
+    constexpr uint32_t kType2 = 1u << kTwo, kType3 = 1u << kThree0 | 1u << kThree2, kType1 = 1u << kRot | 1u << kSix;
+    for (uint64_t first = 0; first < a.total; first += nc) {
+        const uint64_t left = a.total - first < nc ? a.total - first : nc;
+        Q.first = first;
+        Q.slices = (uint32_t)(left / 64);
+        const dim3 grid((uint32_t)(left / kWG));
+        GSBC_LAUNCH("bc7_bounds", k_bc7_bounds, grid, dim3(kWG), 0, st, Q);
+        GSBC_LAUNCH("bc7_seed", k_bc7_seed, grid, dim3(kWG), 0, st, Q);
+        if (split == 0) {
+            if ((e = launch(0, kType3, "bc7_search_3subset")) != hipSuccess) return e;
+            if ((e = launch(1, kType1, "bc7_search_1subset")) != hipSuccess) return e;
+            if ((e = launch(2, kType2, "bc7_search_2subset")) != hipSuccess) return e;
+        } else if (split == 1) {
+            if ((e = launch(0, kType3 | kType1, "bc7_search_3subset_1subset")) != hipSuccess) return e;
+            if ((e = launch(1, kType2, "bc7_search_2subset")) != hipSuccess) return e;
+        } else {
+            if ((e = launch(0, kType3 | kType1 | kType2, "bc7_search_items")) != hipSuccess) return e;
+        }
     }
     uint32_t *count = a.keys + 2 * a.total, *wgcount = count + 16;
     GSBC_LAUNCH("bc7_bucket", k_bc7_bucket_count, sgrid, dim3(kWG), 0, st, a, wgcount);

@@ -163,13 +163,13 @@ struct EncodeArgs {
 };
 // Scratch bytes the BC7 encoder needs for `blocks` global indices (a
 // multiple of 256): a key and a bucket-list word per index, per-mode
-// counters, per 64 indices a texel pointer and the 149 candidate words, and
-// 300 bytes of candidate bounds per index of one chunk.
-constexpr uint64_t kBc7Chunk = 1u << 18;
+// counters, and for the indices of one chunk 300 bytes of candidate bounds
+// each, a texel pointer and 149 candidate words per 64.
+constexpr uint64_t kBc7Chunk = 1u << 19;
 inline size_t bc7_scratch_bytes(uint64_t blocks)
 {
-    return (size_t)blocks * 8 + 64 + ((blocks + 255) / 256) * 32 + (blocks / 64) * 150 * 8 +
-           (blocks < kBc7Chunk ? blocks : kBc7Chunk) * 300 + 128;
+    const uint64_t nc = blocks < kBc7Chunk ? blocks : kBc7Chunk;
+    return (size_t)blocks * 8 + 64 + ((blocks + 255) / 256) * 32 + (nc / 64) * 150 * 8 + nc * 300 + 128;
 }
 // How the BC7 candidate search is split over kernels: 0 -> three kernels
 // (2-subset, 3-subset, 1-subset modes), 1 -> two (the 1-subset modes folded

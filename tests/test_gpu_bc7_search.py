@@ -59,9 +59,9 @@ def test_search_equals_exhaustive(kind, nblk):
 def test_search_past_one_chunk():
     import torch
     from paper_2607_14513_amd import gsbc
-    nblk = (1 << 18) + 528     # one chunk of bounds and a ragged piece of the next
+    nblk = (1 << 19) + 528     # one chunk of bounds and a ragged piece of the next
     t = _blocks("random", nblk, 12)
-    pick = np.r_[0:32, (1 << 18) - 32:(1 << 18) + 32, nblk - 32:nblk]
+    pick = np.r_[0:32, (1 << 19) - 32:(1 << 19) + 32, nblk - 32:nblk]
     want, _ = O.bc7_encode(t[pick])
     with gsbc.Context(0) as ctx:
         out, _, _ = ctx.encode(torch.from_numpy(t[None]).cuda(), _prim_desc(gsbc, nblk), fmt=gsbc.FMT_BC7)
