@@ -65,8 +65,6 @@ constexpr size_t kRangeOff = 0;                  // RangeRec
 constexpr size_t kSelOff = 512;                  // RateSel
 constexpr size_t kSse1Off = 1024;                // 16 x u64
 constexpr size_t kSse7Off = 1152;                // 16 x u64
-constexpr size_t kOff1Off = 1280;                // 16 x u64
-constexpr size_t kOff7Off = 1408;                // 16 x u64
 constexpr size_t kClassOff = 1536;               // 4 x u32 degree-class counts
 constexpr size_t kSmallBytes = 2048;
 static_assert(sizeof(gsbc::RangeRec) <= kSelOff, "RangeRec must fit before RateSel (and before the class counts read back beside it)");
@@ -282,7 +280,6 @@ constexpr WorkSplit kPlainSplit = {1, 0, nullptr};
 constexpr uint32_t kPlainBc1Lanes = 128;
 constexpr uint32_t kPlainBc7Split = 3;
 constexpr size_t kRunTableBytes = 16 * sizeof(BlockRun);   // one scene, one format
-constexpr size_t kRunStageOff = 2048;                        // in ctx->pinned
 
 // The second stream (default priority) and its fork/join events.
 gsbc_status ensure_side(gsbc_ctx *ctx)
@@ -639,7 +636,6 @@ gsbc_status gsbc_encode(gsbc_ctx *ctx, const uint8_t *textures, gsbc_stream_desc
     bool have1 = false, have7 = false;
     Runs r1, r7;
     uint8_t *buf1 = nullptr, *buf7 = nullptr;
-    uint64_t off1[16], off7[16];
     size_t front = 0;
     if (!autoc) {
         for (uint32_t k = 0; k < 16; k++)
@@ -686,24 +682,20 @@ gsbc_status gsbc_encode(gsbc_ctx *ctx, const uint8_t *textures, gsbc_stream_desc
     if (autoc) {
         buf1 = arena;
         buf7 = buf1 + 16 * align16(8 * nblk);
-        for (int q = 0; q < 16; q++) {
-            off1[q] = q * align16(8 * nblk);
-            off7[q] = q * 16 * nblk;
-        }
         for (uint32_t q = 0; q < S; q++) {
-            r7.add(textures + q * tex_band, buf7 + off7[q], sse7 + q, nblk);
-            r1.add(textures + q * tex_band, buf1 + off1[q], sse1 + q, nblk);   // band 0 too: its BC1 SSE is reported
+            r7.add(textures + q * tex_band, buf7 + q * 16 * nblk, sse7 + q, nblk);
+            r1.add(textures + q * tex_band, buf1 + q * align16(8 * nblk), sse1 + q, nblk);   // band 0 too: its BC1 SSE is reported
         }
     }
     BlockRun *druns7 = reinterpret_cast<BlockRun *>(arena + front);
     BlockRun *druns1 = druns7 + 16;
     have1 = !r1.v.empty();
     have7 = !r7.v.empty();
-    char *stage = static_cast<char *>(ctx->pinned) + kRunStageOff;
-    memcpy(stage, r7.v.data(), r7.v.size() * sizeof(BlockRun));
-    memcpy(stage + kRunTableBytes, r1.v.data(), r1.v.size() * sizeof(BlockRun));
-    HIP_TRY(ctx, hipMemcpyAsync(druns7, stage, 2 * kRunTableBytes, hipMemcpyHostToDevice, ctx->stream), "run tables");
-    HIP_TRY(ctx, launch_fill_u64(sse1, 32, 0, ctx->stream), "clear");
+    RunTables tables;
+    memset(&tables, 0, sizeof tables);
+    std::copy(r7.v.begin(), r7.v.end(), tables.run);
+    std::copy(r1.v.begin(), r1.v.end(), tables.run + 16);
+    HIP_TRY(ctx, launch_encode_setup(tables, druns7, sse1, ctx->stream), "run tables");
     EncodeArgs a;
     memset(&a, 0, sizeof a);
     a.refine_steps = p.refine_steps;
@@ -724,7 +716,12 @@ gsbc_status gsbc_encode(gsbc_ctx *ctx, const uint8_t *textures, gsbc_stream_desc
         HIP_TRY(ctx, hipStreamWaitEvent(s1, ctx->fork, 0), "fork");
     }
     hipError_t e1 = hipSuccess, e7 = hipSuccess;
-    if (have1) {
+    unsigned long long *hist = reinterpret_cast<unsigned long long *>(arena + hist_off);
+    if (format == GSBC_FMT_AUTO_ZERO) {   // the code histograms need the textures only
+        e1 = launch_fill_u64(hist, 16 * 256, 0, s1);
+        if (e1 == hipSuccess) e1 = launch_band_hist(textures, S, nblk, hist, s1);
+    }
+    if (have1 && e1 == hipSuccess) {
         EncodeArgs a1 = a;
         a1.run = druns1;
         a1.nrun = (uint32_t)r1.v.size();
@@ -743,28 +740,20 @@ gsbc_status gsbc_encode(gsbc_ctx *ctx, const uint8_t *textures, gsbc_stream_desc
     }
     HIP_TRY(ctx, e1, "bc1 launch");
     HIP_TRY(ctx, e7, "bc7 launch");
+    unsigned long long *host_sse = reinterpret_cast<unsigned long long *>(static_cast<char *>(ctx->pinned) + 1024);
     if (autoc) {
-        uint64_t *doff1 = reinterpret_cast<uint64_t *>(small_ptr(ctx, kOff1Off));
-        uint64_t *doff7 = reinterpret_cast<uint64_t *>(small_ptr(ctx, kOff7Off));
-        uint64_t *ostage = reinterpret_cast<uint64_t *>(static_cast<char *>(ctx->pinned) + kRunStageOff + 2 * kRunTableBytes);
-        memcpy(ostage, off1, sizeof off1);
-        memcpy(ostage + 16, off7, sizeof off7);
-        HIP_TRY(ctx, hipMemcpyAsync(doff1, ostage, 2 * sizeof off1, hipMemcpyHostToDevice, ctx->stream), "offsets");
-        RateSel *sel = reinterpret_cast<RateSel *>(small_ptr(ctx, kSelOff));
+        RateSel *sel = reinterpret_cast<RateSel *>(small_ptr(ctx, kSelOff)), *host_sel = static_cast<RateSel *>(ctx->pinned);
         if (format == GSBC_FMT_AUTO_ZERO) {
-            unsigned long long *hist = reinterpret_cast<unsigned long long *>(arena + hist_off);
-            HIP_TRY(ctx, launch_fill_u64(hist, 16 * 256, 0, ctx->stream), "clear");
-            HIP_TRY(ctx, launch_band_hist(textures, S, nblk, hist, ctx->stream), "band histograms");
-            HIP_TRY(ctx, launch_rate_select_zero(sse1, sse7, hist, band_args(desc), S, k_auto, nblk, sel, ctx->stream),
+            HIP_TRY(ctx, launch_rate_select_zero(sse1, hist, band_args(desc), S, k_auto, nblk, sel, host_sel, host_sse, ctx->stream),
                     "rate select");
         } else {
-            HIP_TRY(ctx, launch_rate_select(sse1, sse7, band_args(desc), S, k_auto, nblk, sel, ctx->stream), "rate select");
+            HIP_TRY(ctx, launch_rate_select(sse1, band_args(desc), S, k_auto, nblk, sel, host_sel, host_sse, ctx->stream),
+                    "rate select");
         }
-        HIP_TRY(ctx, launch_copy_streams(buf1, doff1, buf7, doff7, sel, S, nblk, blocks, ctx->stream), "stream copy");
-        HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned, sel, sizeof(RateSel), hipMemcpyDeviceToHost, ctx->stream), "selection read-back");
+        HIP_TRY(ctx, launch_copy_streams(buf1, buf7, sel, S, nblk, blocks, ctx->stream), "stream copy");
+    } else if (band_sse) {
+        HIP_TRY(ctx, hipMemcpyAsync(host_sse, sse1, 32 * sizeof(uint64_t), hipMemcpyDeviceToHost, ctx->stream), "sse read-back");
     }
-    char *sstage = static_cast<char *>(ctx->pinned) + 1024;
-    HIP_TRY(ctx, hipMemcpyAsync(sstage, sse1, 32 * sizeof(uint64_t), hipMemcpyDeviceToHost, ctx->stream), "sse read-back");
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream), "encode");
     if (autoc) {
         const RateSel *r = static_cast<const RateSel *>(ctx->pinned);
@@ -774,7 +763,7 @@ gsbc_status gsbc_encode(gsbc_ctx *ctx, const uint8_t *textures, gsbc_stream_desc
         payload = r->payload_bytes;
     }
     if (band_sse) {
-        const uint64_t *h = reinterpret_cast<const uint64_t *>(sstage);
+        const unsigned long long *h = host_sse;
         for (uint32_t q = 0; q < 16; q++) {
             const bool c1 = q < S && (autoc || (have1 && host_fmt[q] == GSBC_FMT_BC1));
             const bool c7 = q < S && (autoc || (have7 && host_fmt[q] == GSBC_FMT_BC7));

@@ -182,26 +182,31 @@ hipError_t upload_bc1_tables(int device, hipStream_t st);
 hipError_t upload_bc7_tables(int device, hipStream_t st);
 
 // ---- rate control (rate.hip)
-// sse1/sse7: [16] int64 band SSEs; writes format[16] and offsets[16] plus the
-// payload size into sel (device), then copies the chosen streams from the
-// two candidate payloads into `out`.
+// sse: [32] int64 band SSEs, BC1 then BC7; writes format[16], offsets[16] and
+// the payload size into sel (device) and host_sel, and the SSEs into host_sse
+// (both pinned host memory); the chosen streams are then copied from the two
+// candidate payloads (stream q of BC1 at q * align16(8 nblk), of BC7 at
+// q * 16 nblk) into `out`.
 struct RateSel {
     uint32_t format[16];
     uint64_t offset[16];
     uint64_t payload_bytes;
 };
-hipError_t launch_rate_select(const unsigned long long *sse1, const unsigned long long *sse7,
-                              const BandArgs &b, uint32_t S, uint32_t k, uint64_t nblk, RateSel *sel,
-                              hipStream_t st);
+hipError_t launch_rate_select(const unsigned long long *sse, const BandArgs &b, uint32_t S, uint32_t k, uint64_t nblk,
+                              RateSel *sel, RateSel *host_sel, unsigned long long *host_sse, hipStream_t st);
 // Code histograms of the R, G, B channels of each of the S band streams
 // into hist[S][256] (which the caller clears).
 hipError_t launch_band_hist(const uint8_t *tex, uint32_t S, uint64_t nblk, unsigned long long *hist, hipStream_t st);
-hipError_t launch_rate_select_zero(const unsigned long long *sse1, const unsigned long long *sse7,
-                                   const unsigned long long *hist, const BandArgs &b, uint32_t S, uint32_t U,
-                                   uint64_t nblk, RateSel *sel, hipStream_t st);
-hipError_t launch_copy_streams(const uint8_t *src1, const uint64_t *off1, const uint8_t *src7,
-                               const uint64_t *off7, const RateSel *sel, uint32_t S, uint64_t nblk, uint8_t *out,
-                               hipStream_t st);
+hipError_t launch_rate_select_zero(const unsigned long long *sse, const unsigned long long *hist, const BandArgs &b,
+                                   uint32_t S, uint32_t U, uint64_t nblk, RateSel *sel, RateSel *host_sel,
+                                   unsigned long long *host_sse, hipStream_t st);
+hipError_t launch_copy_streams(const uint8_t *src1, const uint8_t *src7, const RateSel *sel, uint32_t S, uint64_t nblk,
+                               uint8_t *out, hipStream_t st);
+// One scene's run tables (BC7, then BC1) as a kernel argument.
+struct RunTables {
+    BlockRun run[32];
+};
+hipError_t launch_encode_setup(const RunTables &t, BlockRun *runs, unsigned long long *sse, hipStream_t st);
 hipError_t launch_fill_u64(unsigned long long *p, uint64_t n, unsigned long long v, hipStream_t st);
 
 // ---- decoders (decode.hip)
