@@ -292,7 +292,9 @@ GSBC_API gsbc_status gsbc_encode(gsbc_ctx *ctx, const uint8_t *textures, gsbc_st
  *                four items); 1..16: that many persistent workgroups per
  *                compute unit pop items from a device counter until none are
  *                left
- *   bc1_lanes    BC1 workgroup size: 64, 128 or 256
+ *   bc1_lanes    BC1 workgroup size: 64, 128 or 256 (fewer than 524,288 blocks
+ *                at one round per item and no queue: four waves share 64
+ *                blocks instead)
  *   bc7_split    BC7 candidate groups per search kernel: 0 = three kernels
  *                (2-subset, 3-subset, 1-subset modes), 1 = two (the 3- and
  *                1-subset modes together), 2 or 3 = one kernel for every

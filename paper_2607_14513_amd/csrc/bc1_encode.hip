@@ -47,14 +47,15 @@ __constant__ Bc1Tables kTab;
 // |-2 P| <= 8160), row 3 s + c holding channel c of the sum over the first s
 // texels, one column per lane; and the nearest-code table with its expanded
 // values.
-template <int LANES>
+template <int LANES, int WAVES>
 struct Bc1Lds {
     short m2P[17 * 3][LANES];
     uint8_t code[2][512];
     uint8_t val[2][512];
     int Q[LANES];                     // sum of |x|^2 of each lane's block
     unsigned long long best[LANES];   // least SSE << 16 | split order so far
-    uint32_t queue[LANES / 64][128];  // per wave: (block's lane << 11 | split) waiting to be scored
+    uint32_t queue[WAVES][128];       // per wave: (block's lane << 11 | split) waiting to be scored
+    uint32_t moved[WAVES > LANES / 64 ? LANES : 1];   // shared blocks: least SSE << 4 | neighbour of the refinement
 };
 
 __host__ __device__ inline int e5(int c) { return (c << 3) | (c >> 2); }
@@ -172,16 +173,19 @@ __device__ inline uint32_t canon_index(uint32_t &c0, uint32_t &c1, bool four, co
 // per channel.  With SA + SB = F tot, the numerators are
 //   2 num0 = -F (B + AB) (-2 SA) - 2 F AB F tot
 //   2 num1 =  F (A + AB) (-2 SA) + 2 F A F tot.
-// The best split (strictly less SSE, so the first on ties) is kept by its
-// packed bounds.
+// The best split (strictly less SSE, so the first on ties) joins the block's
+// key, SSE << 16 | order; rows: the first bounds s1 to try, a bit each.
 template <bool FOUR, class Lds>
-__device__ __forceinline__ void split_list(const Lds &L, int lane, const int (&tot)[3], const int (&m2tot)[3],
-                                           int Q, uint32_t &best, uint32_t &best_split)
+__device__ __forceinline__ void split_list(const Lds &L, int lane, const int (&tot)[3], int Q, uint32_t rows,
+                                           unsigned long long &key)
 {
+    const int m2tot[3] = {-2 * tot[0], -2 * tot[1], -2 * tot[2]};
+    uint32_t best = 0xFFFFFFFFu, order = 0;
     constexpr int F = FOUR ? 3 : 2;
     const uint4 *split = FOUR ? kTab.split4 : kTab.split3;
-    int si = 0;   // split number in enumeration order
-    for (int s1 = 0; s1 <= 16; s1++) {
+    for (; rows; rows &= rows - 1) {
+        const int s1 = __ffs(rows) - 1;
+        uint32_t si = FOUR ? kTab.first4[18 * s1] : kTab.first3[s1];   // split number in enumeration order
         int a[3];
 #pragma unroll
         for (int c = 0; c < 3; c++) a[c] = L.m2P[s1 * 3 + c][lane];
@@ -239,11 +243,13 @@ __device__ __forceinline__ void split_list(const Lds &L, int lane, const int (&t
                 }
                 if ((uint32_t)sse < best) {
                     best = (uint32_t)sse;
-                    best_split = (uint32_t)s1 | ((uint32_t)s2 << 5) | ((uint32_t)s3 << 10) | (FOUR ? 1u << 15 : 0u);
+                    order = (uint32_t)s1 << 10 | (uint32_t)s2 << 5 | (uint32_t)s3;
                 }
             }
         }
     }
+    if (!FOUR) order |= 1u << 15;
+    if (best != 0xFFFFFFFFu) key = min(key, (unsigned long long)best << 16 | order);
 }
 
 // ---- the splits worth scoring
@@ -327,7 +333,6 @@ struct Sweep {
     float scatter;   // Q'
     float mean[3];
     int q;           // entries in the wave's queue
-    uint32_t tested; // splits queued so far by the wave
     uint32_t lanes;  // all ones, or 0 on a lane whose block needs no split (constant colour)
 };
 
@@ -338,22 +343,47 @@ __device__ __forceinline__ float need(float scatter, unsigned long long best)
     return fmaf(scatter, 1.0f - 2e-5f, -r * r) - 0.05f;
 }
 
-// Test the splits of one list in enumeration order, those with even bounds
-// only (step 2) or, in the four-cluster list, all the others (step 1).  A row
-// is the splits of one (s1, s2) (three clusters: s1) and every last bound s;
-// R holds the centred prefix rows (0 and 16 are zero).  Misses collect bit by
-// bit over rows, as their numbers follow each other; every 32 splits at most,
-// the hits are queued, and scored whenever 64 are waiting.
-template <bool FOUR, class Lds>
-__device__ __forceinline__ void sweep(Lds &L, int lane, int wave, const float (&R)[15][3], int step, Sweep &w, float &T)
+// Test one row, the splits of one (s1, s2) (three clusters: s1) and every last
+// bound s from lo: u is the sum of the earlier bounds' prefix values, R the
+// centred prefix rows (0 and 16 are zero).  The misses enter `miss` from
+// below, bit by bit.
+__device__ __forceinline__ void test_row(const float (&R)[15][3], const float (&u)[3], int lo, const float *spread, float T,
+                                         uint32_t &miss)
 {
-    uint32_t miss = 0, wanted = 0, bits = 0, next = 0;   // the row's splits are number next - bits ..
-    int s1 = 0, s2 = 0;
+    float V[17];
+#pragma unroll
+    for (int s = 0; s <= 16; s++) V[s] = spread[s];   // scalar, one wide load
+#pragma unroll
+    for (int s = 0; s <= 16; s++) {
+        if (s >= lo) {
+            const bool zero = s == 0 || s == 16;
+            const float x = zero ? u[0] : u[0] + R[zero ? 0 : s - 1][0], y = zero ? u[1] : u[1] + R[zero ? 0 : s - 1][1];
+            const float z = zero ? u[2] : u[2] + R[zero ? 0 : s - 1][2];
+            const float d = fmaf(x, x, fmaf(y, y, fmaf(z, z, -T * V[s])));
+            miss = __builtin_amdgcn_alignbit(miss, __float_as_uint(d), 31);   // its sign
+        }
+    }
+}
+
+// Test the splits of one list in enumeration order, those with even bounds
+// only (step 2) or, in the four-cluster list, all the others (step 1).  Misses
+// collect over rows while their numbers follow each other; every 32 splits at most,
+// the hits are queued, and scored whenever 64 are waiting.  rows: the first
+// bounds s1 to test, a bit each.
+template <bool FOUR, class Lds>
+__device__ __forceinline__ void sweep(Lds &L, int lane, int wave, const float (&R)[15][3], int step, uint32_t rows, Sweep &w,
+                                      float &T)
+{
+    const int lane0 = __builtin_amdgcn_readfirstlane(lane);   // the wave's first block
+    uint32_t miss = 0, wanted = 0, bits = 0, next = 0;        // the row's splits are number next - bits ..
+    if (step == 2) rows &= 0x15555u;
+    int s1 = __ffs(rows) - 1, s2 = s1;
     float a[3] = {0.0f, 0.0f, 0.0f};
     while (true) {
-        const bool end = s1 > 16;
+        const bool end = rows == 0;
         const int lo = FOUR ? s2 : s1;
-        if (end || bits + 17 - lo > 32 || (FOUR && step == 2)) {
+        const uint32_t number = end ? 0u : FOUR ? kTab.first4[17 * s1 + s2] : kTab.first3[s1];   // of the row's first split
+        if (end || bits + 17 - lo > 32 || number != next) {
             uint32_t hits = ~miss & wanted & w.lanes;
             uint64_t any;
             while ((any = __ballot(hits != 0)) != 0) {
@@ -365,11 +395,10 @@ __device__ __forceinline__ void sweep(Lds &L, int lane, int wave, const float (&
                 }
                 const int k = __popcll(any);
                 w.q += k;
-                w.tested += (uint32_t)k;
                 if (w.q >= 64) {
                     wave_lds_fence();
                     w.q -= 64;
-                    score<FOUR>(L, L.queue[wave][w.q + (lane & 63)], 64 * wave, true);
+                    score<FOUR>(L, L.queue[wave][w.q + (lane & 63)], lane0, true);
                     wave_lds_fence();
                     T = need(w.scatter, L.best[lane]);
                 }
@@ -385,30 +414,17 @@ __device__ __forceinline__ void sweep(Lds &L, int lane, int wave, const float (&
 #pragma unroll
         for (int c = 0; c < 3; c++)
             u[c] = FOUR ? a[c] + fmaf(-0.5f, (float)L.m2P[3 * s2 + c][lane], -w.mean[c] * (float)s2) : a[c];
-        const float *spread = FOUR ? kTab.spread4[17 * s1 + s2] : kTab.spread3[s1];
-        float V[17];
-#pragma unroll
-        for (int s = 0; s <= 16; s++) V[s] = spread[s];   // scalar, one wide load
-#pragma unroll
-        for (int s = 0; s <= 16; s++) {
-            if (s >= lo) {
-                const bool zero = s == 0 || s == 16;
-                const float x = zero ? u[0] : u[0] + R[zero ? 0 : s - 1][0], y = zero ? u[1] : u[1] + R[zero ? 0 : s - 1][1];
-                const float z = zero ? u[2] : u[2] + R[zero ? 0 : s - 1][2];
-                const float d = fmaf(x, x, fmaf(y, y, fmaf(z, z, -T * V[s])));
-                miss = __builtin_amdgcn_alignbit(miss, __float_as_uint(d), 31);   // its sign enters from below
-            }
-        }
+        test_row(R, u, lo, FOUR ? kTab.spread4[17 * s1 + s2] : kTab.spread3[s1], T, miss);
         const uint32_t n = (uint32_t)(17 - lo);
         // bit 16 - s of the row: even s in the first sweep, what it left in the second
         const uint32_t row = !FOUR ? ~0u : step == 2 ? 0x15555u : ((s1 | s2) & 1) ? ~0u : ~0x15555u;
         wanted = wanted << n | (row & ((1u << n) - 1u));
         bits += n;
-        next = (FOUR ? kTab.first4[17 * s1 + s2] : kTab.first3[s1]) + n;
+        next = number + n;
         if (FOUR) s2 += step;
         if (!FOUR || s2 > 16) {
-            s1 += step;
-            s2 = s1;
+            rows &= rows - 1;
+            s1 = s2 = __ffs(rows) - 1;
         }
     }
 }
@@ -416,24 +432,39 @@ __device__ __forceinline__ void sweep(Lds &L, int lane, int wave, const float (&
 template <bool FOUR, class Lds>
 __device__ __forceinline__ void score_rest(Lds &L, int lane, int wave, Sweep &w)
 {
+    const int lane0 = __builtin_amdgcn_readfirstlane(lane);
     wave_lds_fence();
-    score<FOUR>(L, L.queue[wave][lane & 63], 64 * wave, (lane & 63) < w.q);
+    score<FOUR>(L, L.queue[wave][lane & 63], lane0, (lane & 63) < w.q);
     wave_lds_fence();
     w.q = 0;
 }
 
-// Best split of every block of the wave (in L.best): false if so many of the
-// even splits pass the test that scoring every split in uniform order is
-// cheaper (smooth blocks, whose SSE is mostly endpoint quantisation).
-template <class Lds>
-__device__ __forceinline__ bool find_split(Lds &L, int lane, int wave, const int (&tot)[3], int Q, const int (&cut)[3],
+// First bounds s1 of each of four waves that share their blocks: 240 to 247
+// of the 969 four-cluster splits (17 - s1 rows of 17 - s2 splits each).
+constexpr uint32_t kShare4[4] = {1u << 0 | 1u << 6 | 1u << 11, 1u << 1 | 1u << 5 | 1u << 10, 1u << 2 | 1u << 4 | 1u << 9,
+                                 1u << 3 | 1u << 7 | 1u << 8 | 0x1F000u};
+constexpr uint32_t kShare3[4] = {0x11111u, 0x02222u, 0x04444u, 0x08888u};
+static_assert((kShare4[0] ^ kShare4[1] ^ kShare4[2] ^ kShare4[3]) == 0x1FFFFu &&
+              (kShare3[0] ^ kShare3[1] ^ kShare3[2] ^ kShare3[3]) == 0x1FFFFu, "every first bound has one wave");
+
+// Rows that stand for all when the wave decides how to score: s1 | s2 << 8.
+constexpr int kSample[4] = {1 | 4 << 8, 3 | 9 << 8, 6 | 10 << 8, 0 | 7 << 8};
+constexpr int kSampleSplits = 13 + 8 + 7 + 10;
+
+// Best split of every block of the wave (in L.best).  Where most splits pass
+// the test (smooth blocks, whose SSE is mostly endpoint quantisation), every
+// split is scored in uniform order instead, at about 85 instructions a split
+// for 64 blocks against 140: cheaper from 500 scored splits a block on, which
+// is where about 72 % of the sample's splits pass the first test.
+// SHARED: four waves hold the same blocks and take a share of the splits each.
+template <bool SHARED, class Lds>
+__device__ __forceinline__ void find_split(Lds &L, int lane, int wave, const int (&tot)[3], int Q, const int (&cut)[3],
                                            bool constant)
 {
     Sweep w;
     w.lanes = constant ? 0u : ~0u;
     w.scatter = (float)(16 * Q - (tot[0] * tot[0] + tot[1] * tot[1] + tot[2] * tot[2])) * (1.0f / 16.0f);
     w.q = 0;
-    w.tested = 0;
     float R[15][3];
 #pragma unroll
     for (int c = 0; c < 3; c++) {
@@ -441,24 +472,51 @@ __device__ __forceinline__ bool find_split(Lds &L, int lane, int wave, const int
 #pragma unroll
         for (int s = 1; s <= 15; s++) R[s - 1][c] = fmaf(-0.5f, (float)L.m2P[3 * s + c][lane], -w.mean[c] * (float)s);
     }
-    L.Q[lane] = Q;
-    L.best[lane] = ~0ull;
-    // the first score: one split per lane, its own block's
-    wave_lds_fence();
-    score<true>(L, (uint32_t)(lane & 63) << 11 | (kTab.first4[17 * cut[0] + cut[1]] + (uint32_t)(cut[2] - cut[1])),
-                64 * wave, true);
-    wave_lds_fence();
+    if (!SHARED || wave == 0) {
+        L.Q[lane] = Q;
+        L.best[lane] = ~0ull;
+        // the first score: one split per lane, its own block's
+        wave_lds_fence();
+        score<true>(L, (uint32_t)(lane & 63) << 11 | (kTab.first4[17 * cut[0] + cut[1]] + (uint32_t)(cut[2] - cut[1])),
+                    __builtin_amdgcn_readfirstlane(lane), true);
+    }
+    if (SHARED) __syncthreads();
+    else wave_lds_fence();
     float T = need(w.scatter, L.best[lane]);
+    const uint32_t rows4 = SHARED ? kShare4[wave] : 0x1FFFFu, rows3 = SHARED ? kShare3[wave] : 0x1FFFFu;
+    uint32_t pass = 0;
+#pragma unroll 1
+    for (int k = 0; k < 4; k++) {
+        const int s1 = kSample[k] & 255, s2 = kSample[k] >> 8;
+        float u[3];
+#pragma unroll
+        for (int c = 0; c < 3; c++)
+            u[c] = fmaf(-0.5f, (float)(L.m2P[3 * s1 + c][lane] + L.m2P[3 * s2 + c][lane]), -w.mean[c] * (float)(s1 + s2));
+        uint32_t miss = 0;
+        test_row(R, u, s2, kTab.spread4[17 * s1 + s2], T, miss);
+        pass += (uint32_t)__popc(~miss & w.lanes & ((1u << (17 - s2)) - 1u));
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) pass += (uint32_t)__shfl_xor((int)pass, d);
+    if (pass * 100u > 64u * kSampleSplits * 72u) {
+        unsigned long long key = ~0ull;
+        split_list<true>(L, lane, tot, Q, rows4, key);
+        split_list<false>(L, lane, tot, Q, rows3, key);
+        atomicMin(&L.best[lane], key);
+        if (SHARED) __syncthreads();
+        else wave_lds_fence();
+        return;
+    }
 #pragma unroll 1
     for (int step = 2; step >= 1; step--) {
-        sweep<true>(L, lane, wave, R, step, w, T);
-        if (step == 2 && w.tested > 64u * 132u) return false;   // above 4 in 5 of the 165
+        sweep<true>(L, lane, wave, R, step, rows4, w, T);
+        if (SHARED) T = need(w.scatter, L.best[lane]);   // the other waves' scores too
     }
     score_rest<true>(L, lane, wave, w);
     T = need(w.scatter, L.best[lane]);
-    sweep<false>(L, lane, wave, R, 1, w, T);
+    sweep<false>(L, lane, wave, R, 1, rows3, w, T);
     score_rest<false>(L, lane, wave, w);
-    return true;
+    if (SHARED) __syncthreads();
 }
 
 // Endpoint codes of one split (the same arithmetic as split_list).
@@ -518,7 +576,9 @@ __device__ __forceinline__ void encode_constant(const uint32_t (&t)[16], int Q, 
     w0 = c0 | (c1 << 16);
 }
 
-template <class Lds>
+// SHARED: four waves hold the same 64 blocks; they order the texels and test
+// the splits in shares, and take three of the refinement's neighbours each.
+template <bool SHARED, class Lds>
 __device__ __forceinline__ void encode_block(const uint4 *src, uint32_t refine_steps, Lds &L, int lane, int wave,
                              uint32_t &w0, uint32_t &w1, uint32_t &sse_out)
 {
@@ -614,6 +674,7 @@ __device__ __forceinline__ void encode_block(const uint4 *src, uint32_t refine_s
     }
 #pragma unroll
     for (int i = 0; i < 16; i++) {
+        if (SHARED && (i >> 2) != wave) continue;
         int r = 0;
 #pragma unroll
         for (int k = 0; k < 16; k++)
@@ -623,30 +684,28 @@ __device__ __forceinline__ void encode_block(const uint4 *src, uint32_t refine_s
         L.m2P[3 * r + 1][lane] = (short)((t[i] >> 16) & 255u);
     }
     // rows 3 k and 3 k + 1 still hold the texel of rank k when the prefix rows of k are written
-    int run[3] = {0, 0, 0};
+    if (SHARED) __syncthreads();
+    if (!SHARED || wave == 0) {
+        int run[3] = {0, 0, 0};
 #pragma unroll
-    for (int k = 0; k <= 16; k++) {
-        const uint32_t x = k < 16 ? ((uint32_t)(uint16_t)L.m2P[3 * k][lane] | ((uint32_t)L.m2P[3 * k + 1][lane] << 16)) : 0u;
+        for (int k = 0; k <= 16; k++) {
+            const uint32_t x = k < 16 ? ((uint32_t)(uint16_t)L.m2P[3 * k][lane] | ((uint32_t)L.m2P[3 * k + 1][lane] << 16)) : 0u;
 #pragma unroll
-        for (int c = 0; c < 3; c++) L.m2P[3 * k + c][lane] = (short)(-2 * run[c]);
-        run[0] += (int)(x & 255u);
-        run[1] += (int)((x >> 8) & 255u);
-        run[2] += (int)((x >> 16) & 255u);
+            for (int c = 0; c < 3; c++) L.m2P[3 * k + c][lane] = (short)(-2 * run[c]);
+            run[0] += (int)(x & 255u);
+            run[1] += (int)((x >> 8) & 255u);
+            run[2] += (int)((x >> 16) & 255u);
+        }
     }
-    const int tot[3] = {run[0], run[1], run[2]};
-    const int m2tot[3] = {-2 * run[0], -2 * run[1], -2 * run[2]};
+    if (SHARED) __syncthreads();
+    const int tot[3] = {S[0], S[1], S[2]};
+    const int m2tot[3] = {-2 * S[0], -2 * S[1], -2 * S[2]};
 
     // ---- cluster fit over every split (4-colour list, then 3-colour list)
-    uint32_t best_split;
-    if (find_split(L, lane, wave, tot, Q, cut, constant)) {
-        const uint32_t o = (uint32_t)L.best[lane] & 0xFFFFu;   // three << 15 | s1 << 10 | s2 << 5 | s3
-        best_split = (o >> 10 & 31u) | (o & 0x3E0u) | (o & 31u) << 10 | (o & 0x8000u ? 0u : 1u << 15);
-    } else {
-        uint32_t best = 0xFFFFFFFFu;
-        best_split = 1u << 15;
-        split_list<true>(L, lane, tot, m2tot, Q, best, best_split);
-        split_list<false>(L, lane, tot, m2tot, Q, best, best_split);
-    }
+    find_split<SHARED>(L, lane, wave, tot, Q, cut, constant);
+    // three << 15 | s1 << 10 | s2 << 5 | s3 (a constant block has no best: any split that can be fitted)
+    const uint32_t o = constant ? 8u << 10 | 8u << 5 | 8u : (uint32_t)L.best[lane] & 0xFFFFu;
+    const uint32_t best_split = (o >> 10 & 31u) | (o & 0x3E0u) | (o & 31u) << 10 | (o & 0x8000u ? 0u : 1u << 15);
     int bq0[3], bq1[3];
     split_codes(L, lane, tot, m2tot, best_split, bq0, bq1);
 
@@ -658,25 +717,47 @@ __device__ __forceinline__ void encode_block(const uint4 *src, uint32_t refine_s
     uint32_t sse = canon_index(c0, c1, (best_split >> 15) & 1, t, Q, idx);
 
     // ---- refinement: best of the 12 one-step moves, taken if strictly better
+    // neighbour q moves channel q/2 (R0, G0, B0, R1, G1, B1) by -1 (q even) or
+    // +1, clamped
+    auto neighbour = [&](int q, bool four, uint32_t &a, uint32_t &b, uint32_t &ii) {
+        const int ch = q >> 1, c = ch >= 3 ? ch - 3 : ch;
+        const int shift = c == 0 ? 11 : c == 1 ? 5 : 0, maxc = c == 1 ? 63 : 31;
+        const uint32_t word = ch < 3 ? c0 : c1;
+        const int f = (int)((word >> shift) & (uint32_t)maxc) + ((q & 1) ? 1 : -1);
+        const uint32_t moved = (word & ~((uint32_t)maxc << shift)) | ((uint32_t)min(max(f, 0), maxc) << shift);
+        a = ch < 3 ? moved : c0;
+        b = ch < 3 ? c1 : moved;
+        return canon_index(a, b, four, t, Q, ii);
+    };
     for (uint32_t step = 0; step < refine_steps; step++) {
         const bool four = c0 > c1;
         uint32_t nb_sse = 0xFFFFFFFFu, nb0 = 0, nb1 = 0, nbi = 0;
-        // neighbour q moves channel q/2 (R0, G0, B0, R1, G1, B1) by -1 (q
-        // even) or +1, clamped; one neighbour at a time (a rolled loop, so
-        // that only one palette is live)
+        if (SHARED) {
+            // each wave's three, the least (first on ties) through LDS, that
+            // one again in every wave
+            L.moved[lane] = ~0u;
+            __syncthreads();
+            uint32_t least = ~0u;
 #pragma unroll 1
-        for (int q = 0; q < 12; q++) {
-            const int ch = q >> 1, c = ch % 3;
-            const int shift = c == 0 ? 11 : c == 1 ? 5 : 0, maxc = c == 1 ? 63 : 31;
-            const uint32_t word = ch < 3 ? c0 : c1;
-            const int f = (int)((word >> shift) & (uint32_t)maxc) + ((q & 1) ? 1 : -1);
-            const uint32_t moved = (word & ~((uint32_t)maxc << shift)) | ((uint32_t)min(max(f, 0), maxc) << shift);
-            uint32_t a = ch < 3 ? moved : c0, b = ch < 3 ? c1 : moved, ii;
-            const uint32_t s = canon_index(a, b, four, t, Q, ii);
-            if (s < nb_sse) { nb_sse = s; nb0 = a; nb1 = b; nbi = ii; }
+            for (int q = 3 * wave; q < 3 * wave + 3; q++) {
+                uint32_t a, b, ii;
+                least = min(least, neighbour(q, four, a, b, ii) << 4 | (uint32_t)q);
+            }
+            atomicMin(&L.moved[lane], least);
+            __syncthreads();
+            nb_sse = neighbour((int)(L.moved[lane] & 15u), four, nb0, nb1, nbi);
+            __syncthreads();
+        } else {
+            // one neighbour at a time (a rolled loop, so that only one palette is live)
+#pragma unroll 1
+            for (int q = 0; q < 12; q++) {
+                uint32_t a, b, ii;
+                const uint32_t s = neighbour(q, four, a, b, ii);
+                if (s < nb_sse) { nb_sse = s; nb0 = a; nb1 = b; nbi = ii; }
+            }
         }
         if (nb_sse < sse) { sse = nb_sse; c0 = nb0; c1 = nb1; idx = nbi; }
-        else break;
+        else if (!SHARED) break;   // (a shared block's further steps change nothing)
     }
     w0 = c0 | (c1 << 16);
     w1 = idx;
@@ -685,14 +766,17 @@ __device__ __forceinline__ void encode_block(const uint4 *src, uint32_t refine_s
 }
 
 // One lane per block over the run map; rounds of LANES blocks (a run never
-// straddles a round since runs start at multiples of 256).
-template <int LANES>
-__global__ __launch_bounds__(LANES) __attribute__((amdgpu_waves_per_eu(4))) void k_bc1_encode(EncodeArgs a, WorkSplit w)
+// straddles a round since runs start at multiples of 256).  SHARED: four
+// waves per 64 blocks, for encodes whose blocks would not fill the chip.
+template <int LANES, bool SHARED>
+__global__ __launch_bounds__(SHARED ? 256 : LANES) __attribute__((amdgpu_waves_per_eu(4))) void k_bc1_encode(EncodeArgs a, WorkSplit w)
 {
-    __shared__ Bc1Lds<LANES> L;
+    static_assert(!SHARED || LANES == 64, "four waves on the same lanes");
+    constexpr int kThreads = SHARED ? 256 : LANES;
+    __shared__ Bc1Lds<LANES, kThreads / 64> L;
     __shared__ uint32_t s_item;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    for (int e = threadIdx.x; e < 2 * 512; e += LANES) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = SHARED ? (int)(threadIdx.x & 63u) : (int)threadIdx.x;
+    for (int e = threadIdx.x; e < 2 * 512; e += kThreads) {
         const int wide = e >> 9, c = kTab.code[wide][e & 511];
         L.code[wide][e & 511] = (uint8_t)c;
         L.val[wide][e & 511] = (uint8_t)ew(c, wide);
@@ -710,13 +794,18 @@ __global__ __launch_bounds__(LANES) __attribute__((amdgpu_waves_per_eu(4))) void
             const uint64_t g0 = ((uint64_t)item * w.item_rounds + r) * LANES;
             if (g0 >= a.total) break;
             const BlockRun run = a.run[find_run(a.run, a.nrun, g0)];
-            const uint64_t b = g0 - run.gbase + threadIdx.x;
+            const uint64_t b = g0 - run.gbase + (uint64_t)lane;
             const bool live = b < run.nblk;
-            if (__ballot(live) == 0) continue;   // padding (per wave; no barriers below)
+            // padding (per wave: without SHARED no barriers below, with it the same in all four)
+            if (__ballot(live) == 0) continue;
             const uint64_t bl = live ? b : run.nblk - 1;   // dead lanes redo the last block, write nothing
             const uint4 *src = reinterpret_cast<const uint4 *>(run.src + bl * 64);
             uint32_t w0, w1, sse;
-            encode_block(src, a.refine_steps, L, threadIdx.x, wave, w0, w1, sse);
+            encode_block<SHARED>(src, a.refine_steps, L, lane, wave, w0, w1, sse);
+            if (SHARED) {
+                __syncthreads();   // every wave is done with the blocks' LDS
+                if (wave) continue;
+            }
             if (live) {
                 uint2 *dst = reinterpret_cast<uint2 *>(run.dst + b * 8);
                 *dst = make_uint2(w0, w1);
@@ -822,6 +911,11 @@ hipError_t upload_bc1_tables(int device, hipStream_t st)
     return e;
 }
 
+// Encodes of fewer blocks than this take the kernel whose four waves share
+// their blocks: 4,112 blocks 264 -> 102 us, 65,536 339 -> 154, 200,003 511 ->
+// 406, 400,000 816 -> 758; at 1,048,576, where the chip is full either way, its
+// repeated set-up costs more, 1,918 against 1,814 us.
+constexpr uint64_t kBc1SharedBelow = 1u << 19;
 hipError_t launch_bc1_encode(const EncodeArgs &a, const WorkSplit &w, uint32_t lanes, hipStream_t st)
 {
     if (a.total == 0) return hipSuccess;
@@ -830,11 +924,15 @@ hipError_t launch_bc1_encode(const EncodeArgs &a, const WorkSplit &w, uint32_t l
         hipError_t f = launch_fill_u64(reinterpret_cast<unsigned long long *>(w.queue), 1, 0, st);
         if (f != hipSuccess) return f;
     }
+    if (!w.queue && w.item_rounds == 1 && a.total < kBc1SharedBelow) {
+        GSBC_LAUNCH("bc1_encode", (k_bc1_encode<64, true>), dim3((uint32_t)(a.total / 64)), dim3(256), 0, st, a, w);
+        return hipGetLastError();
+    }
     const uint64_t rounds = a.total / lanes;
     const dim3 grid(w.queue ? w.grid : (uint32_t)((rounds + w.item_rounds - 1) / w.item_rounds));
-    if (lanes == 64) GSBC_LAUNCH("bc1_encode", k_bc1_encode<64>, grid, dim3(64), 0, st, a, w);
-    else if (lanes == 128) GSBC_LAUNCH("bc1_encode", k_bc1_encode<128>, grid, dim3(128), 0, st, a, w);
-    else GSBC_LAUNCH("bc1_encode", k_bc1_encode<256>, grid, dim3(256), 0, st, a, w);
+    if (lanes == 64) GSBC_LAUNCH("bc1_encode", (k_bc1_encode<64, false>), grid, dim3(64), 0, st, a, w);
+    else if (lanes == 128) GSBC_LAUNCH("bc1_encode", (k_bc1_encode<128, false>), grid, dim3(128), 0, st, a, w);
+    else GSBC_LAUNCH("bc1_encode", (k_bc1_encode<256, false>), grid, dim3(256), 0, st, a, w);
     return hipGetLastError();
 }
 
