@@ -1299,8 +1299,12 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
     stage_table(S, L.T.near64);
     stage_texels(S, run.src + b * 64, live);
     __syncthreads();
+    // a block of one colour has the same SSE in every partition of a mode
+    bool one = live;
+#pragma unroll
+    for (int i = 1; i < 16; i++) one &= S.rg[i][threadIdx.x] == S.rg[0][threadIdx.x] && S.bx[i][threadIdx.x] == S.bx[0][threadIdx.x];
     const uint32_t seed = L.B.seed[c];
-    const int p3 = (int)(seed & 255u), rot = (int)((seed >> 8) & 255u);
+    const int p3 = one ? 0 : (int)(seed & 255u), rot = (int)((seed >> 8) & 255u);
     uint32_t key = ~0u;
     if (live) {
         if (parts) {
@@ -1322,9 +1326,11 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
         key = min(key, s_key[wave ^ 1][lane]);
     }
     if (parts) a.keys[g] = key;
-    // 0 .. thr: bounds that may still win (with no seed, all of them; past the run, none)
+    // 0 .. thr: bounds that may still win (with no seed, all of them; past the
+    // run, none; only partition 0 of a block of one colour)
     const int thr = !live ? -1 : key == ~0u ? 0xFFFF : (int)bound16((float)(key >> 9));
-    uint64_t w0 = 0, w1 = 0;   // lane p's words
+    const int thrp = one ? -1 : thr;   // of partitions from 1
+    uint64_t w0 = 0, w1 = 0;           // lane p's words
     auto put = [&](uint64_t &w, int at, bool keep) {
         const uint64_t m = __ballot(keep);
         if (lane == at) w = m;
@@ -1334,14 +1340,14 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
 #pragma unroll 4
         for (int q = 0; q < 32; q++) {
             const uint32_t v = L.B.b3[q * L.B.nc + c];
-            put(w0, 2 * q, (int)(v & 0xFFFFu) <= thr && p3 != 2 * q);
-            put(w0, 2 * q + 1, (int)(v >> 16) <= thr && p3 != 2 * q + 1);
+            put(w0, 2 * q, (int)(v & 0xFFFFu) <= (q ? thrp : thr) && p3 != 2 * q);
+            put(w0, 2 * q + 1, (int)(v >> 16) <= thrp && p3 != 2 * q + 1);
         }
 #pragma unroll 4
         for (int q = 0; q < 8; q++) {
             const uint32_t v = L.B.b0[q * L.B.nc + c];
-            put(w1, 2 * q, (int)(v & 0xFFFFu) <= thr);
-            put(w1, 2 * q + 1, (int)(v >> 16) <= thr);
+            put(w1, 2 * q, (int)(v & 0xFFFFu) <= (q ? thrp : thr));
+            put(w1, 2 * q + 1, (int)(v >> 16) <= thrp);
         }
         words[kWordAt[kThree2] + lane] = w0;
         if (lane < 16) words[kWordAt[kThree0] + lane] = w1;
@@ -1350,10 +1356,10 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
 #pragma unroll 4
         for (int q = 0; q < 16; q++) {
             const uint2 v = L.B.b2[q * L.B.nc + c];
-            put(w0, 4 * q, (int)(v.x & 0xFFFFu) <= thr);
-            put(w0, 4 * q + 1, (int)(v.x >> 16) <= thr);
-            put(w0, 4 * q + 2, (int)(v.y & 0xFFFFu) <= thr);
-            put(w0, 4 * q + 3, (int)(v.y >> 16) <= thr);
+            put(w0, 4 * q, (int)(v.x & 0xFFFFu) <= (q ? thrp : thr));
+            put(w0, 4 * q + 1, (int)(v.x >> 16) <= thrp);
+            put(w0, 4 * q + 2, (int)(v.y & 0xFFFFu) <= thrp);
+            put(w0, 4 * q + 3, (int)(v.y >> 16) <= thrp);
         }
         const uint2 vr = L.B.br[c];
 #pragma unroll
@@ -1381,9 +1387,11 @@ __device__ __forceinline__ int nth_bit(uint64_t w, int k)
 
 // Items of a search launch, type after type: (window, candidate) pairs, a
 // window's candidates next to each other (its texels stay in L2).  The
-// longest items come first: with mode 2 first, which lowers most blocks' best
+// longest items come early: with mode 2 first, which lowers most blocks' best
 // for the types after it, the launch ended on the 2-subset items of a dense
-// window (5.41 ms at 1,048,576 blocks against 4.52).
+// window (5.41 ms at 1,048,576 blocks against 4.52).  Before them only mode 6,
+// which few blocks keep unless their colours lie along a line, where it
+// lowers the best at once (1,048,576 such blocks 19.6 -> 15.4 ms).
 struct Items {
     uint32_t n[kTypes];
     uint32_t total;
@@ -1593,8 +1601,8 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
             search_item<T>(L, S, W[wave], s0, ns, (int)(q % per_window(T)));
             return true;
         };
-        if (!item(Type<kTwo>()) && !item(Type<kThree0>()) && !item(Type<kRot>()) && !item(Type<kThree2>()))
-            item(Type<kSix>());
+        if (!item(Type<kSix>()) && !item(Type<kTwo>()) && !item(Type<kThree0>()) && !item(Type<kRot>()))
+            item(Type<kThree2>());
     } while (it.next(L.w, &s_item));
 }
 

@@ -27,6 +27,8 @@ def _blocks(kind, n, seed):
         c = rng.integers(0, 3, n)
         x[np.arange(n), :, c] = rng.integers(0, 256, (n, 16))
         return rgba(x)
+    if kind == "constant":        # every partition of a mode ties
+        return rgba(np.repeat(base, 16, 1))
     if kind == "corners":         # the largest sums and covariances
         return rgba(255 * rng.integers(0, 2, (n, 16, 3)))
     return random_blocks(n, seed)
@@ -43,7 +45,7 @@ def _prim_desc(gsbc, nblk):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("kind,nblk", [("gradient", 1040), ("near_constant", 272), ("two_level", 272), ("one_channel", 272),
-                                       ("corners", 272), ("random", 16), ("random", 80), ("random", 4112)])
+                                       ("corners", 272), ("constant", 272), ("random", 16), ("random", 80), ("random", 4112)])
 def test_search_equals_exhaustive(kind, nblk):
     import torch
     from paper_2607_14513_amd import gsbc
