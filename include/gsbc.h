@@ -138,7 +138,7 @@ GSBC_API const char *gsbc_last_error(const gsbc_ctx *ctx);
 GSBC_API gsbc_status gsbc_sync(gsbc_ctx *ctx);
 
 /* Size the context's scratch arena once for scenes of up to n_max primitives
- * and decode_evals of up to n_dirs_max directions, so that calls within those
+ * (decode_eval needs no scratch, whatever n_dirs_max is), so that calls within those
  * sizes allocate nothing (a serving slot reserves its largest admissible
  * request up front instead of growing mid-stream).  Outgrown arenas are kept
  * until gsbc_destroy, since queued kernels may still read them and freeing
@@ -365,16 +365,11 @@ GSBC_API gsbc_status gsbc_decode_eval(gsbc_ctx *ctx, const uint8_t *blocks, cons
 
 /* gsbc_decode_eval for callers that cannot allocate (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): the same
- * arguments, checks, kernels and results, but the per-call scratch (16 basis
- * floats per direction) is a file-scope device array of the library instead
- * of the context's arena, so the call allocates nothing (no device, host or
- * event allocation; kernel timing is not recorded for it).
- *   n_dirs   at most 1024 (GSBC_E_ARG above: the array's fixed size)
- * Every call on one GPU shares that GPU's array (the library keeps it until
- * the process ends; gsbc_create looks its address up): calls that overlap on
- * one GPU, e.g. from two contexts on different streams, race on it and must
- * be serialised by the caller.  Each call writes the rows it reads before
- * reading them, so nothing needs clearing between calls. */
+ * arguments, checks, kernels and results.  gsbc_decode_eval needs no scratch;
+ * this call allocates nothing else either (no host or event allocation;
+ * kernel timing is not recorded for it).  Calls on different contexts and
+ * streams share nothing and may overlap.
+ *   n_dirs   at most 1024 (GSBC_E_ARG above) */
 GSBC_API gsbc_status gsbc_decode_eval_noalloc(gsbc_ctx *ctx, const uint8_t *blocks, const gsbc_stream_desc *desc,
                                      const float *dirs, uint32_t n_dirs, const uint32_t *prim_idx,
                                      uint64_t m, float *out);

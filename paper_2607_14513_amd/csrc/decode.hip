@@ -10,9 +10,6 @@
 #include "gsbc_internal.h"
 #include "bc_format.h"
 
-#include <atomic>
-#include <mutex>
-
 namespace gsbc {
 namespace {
 
@@ -159,17 +156,13 @@ __global__ __launch_bounds__(256) void k_decode(const uint8_t *blocks, BandArgs 
 }
 
 // Real SH basis of degree <= 3 in FP32 (3DGS sign convention, k = l^2+l+m).
-__global__ void k_sh_basis(const float *dirs, uint32_t n, float *basis)
+__device__ __forceinline__ void sh_basis(float x, float y, float z, float (&Y)[16])
 {
-    const uint32_t v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= n) return;
-    const float x = dirs[3 * v], y = dirs[3 * v + 1], z = dirs[3 * v + 2];
     const float c0 = 0.28209479177387814f, c1 = 0.4886025119029199f;
     const float c2a = 1.0925484305920792f, c2b = 0.31539156525252005f, c2c = 0.5462742152960396f;
     const float c3a = 0.5900435899266435f, c3b = 2.890611442640554f, c3c = 0.4570457994644658f;
     const float c3d = 0.3731763325901154f, c3e = 1.445305721320277f;
     const float xx = x * x, yy = y * y, zz = z * z;
-    float *Y = basis + 16 * (uint64_t)v;
     Y[0] = c0;
     Y[1] = -c1 * y;
     Y[2] = c1 * z;
@@ -198,7 +191,8 @@ __global__ void k_sh_basis(const float *dirs, uint32_t n, float *basis)
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr int kSlots = 256;                 // slots per workgroup
 constexpr int kCols = 3 * kSlots;           // output floats per direction
-constexpr int kDirChunk = 256;              // directions per workgroup (grid.y); their basis rows sit in LDS
+constexpr int kDirChunk = 256;              // directions per workgroup (grid.y), one per thread; their basis rows sit in LDS
+static_assert(kDirChunk == kEvalBlock, "a thread makes one direction's basis row");
 constexpr int kBasStride = 17;              // padded basis row in LDS
 constexpr int kStageStride = 196;           // padded staging row (192 columns per wave)
 // SR staging rows per wave: 16 (all rows of a 16-direction tile at once;
@@ -216,7 +210,7 @@ constexpr int lds_floats()
 
 template <int SR>
 __device__ __forceinline__ void decode_eval_body(const uint8_t *blocks, const BandArgs &b, const uint32_t *prim_idx,
-                                                 uint64_t m, uint64_t n_prims, const float *basis, uint32_t n_dirs,
+                                                 uint64_t m, uint64_t n_prims, const float *dirs, uint32_t n_dirs,
                                                  float *out)
 {
     __shared__ __align__(16) float lds[lds_floats<SR>()];
@@ -224,6 +218,14 @@ __device__ __forceinline__ void decode_eval_body(const uint8_t *blocks, const Ba
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);   // wave-uniform: row addresses stay scalar
     const uint64_t j0 = (uint64_t)blockIdx.x * kSlots;
+    const uint32_t vc0 = blockIdx.y * kDirChunk;
+    const uint32_t v_end = min(n_dirs, vc0 + kDirChunk);
+    // this thread's direction, loaded with the slot's index (each workgroup
+    // makes its basis rows: with a launch of their own and their read-back,
+    // 1,003 slots x 9 directions took 11.8 us instead of 9.2, 1,048,576 x 64
+    // 189 instead of 182)
+    const uint32_t vd = min(vc0 + (uint32_t)t, n_dirs - 1);
+    const float dir[3] = {dirs[3 * (uint64_t)vd], dirs[3 * (uint64_t)vd + 1], dirs[3 * (uint64_t)vd + 2]};
     // ---- decode: lane t -> slot j0 + t
     {
         const uint64_t j = j0 + t;
@@ -282,13 +284,11 @@ __device__ __forceinline__ void decode_eval_body(const uint8_t *blocks, const Ba
     // also wait for every store issued before it.
     float *bas = lds;                                                  // [kDirChunk][kBasStride]
     float(*stage)[kStageStride] = reinterpret_cast<float(*)[kStageStride]>(lds + kDirChunk * kBasStride) + SR * wave;
-    const uint32_t vc0 = blockIdx.y * kDirChunk;
-    const uint32_t v_end = min(n_dirs, vc0 + kDirChunk);
+    float Y[16];
+    sh_basis(dir[0], dir[1], dir[2], Y);
     __syncthreads();           // every wave holds its B operands
-    for (uint32_t e = t; e < kDirChunk * 16; e += kEvalBlock) {
-        const uint32_t v = vc0 + e / 16;
-        bas[(e / 16) * kBasStride + e % 16] = v < v_end ? basis[16 * (uint64_t)v + e % 16] : 0.0f;
-    }
+#pragma unroll
+    for (int k = 0; k < 16; k++) bas[t * kBasStride + k] = vc0 + t < v_end ? Y[k] : 0.0f;
     __syncthreads();
     if constexpr (SR == 16) {
         for (uint32_t v0 = vc0; v0 < v_end; v0 += 16) {
@@ -406,17 +406,17 @@ __device__ __forceinline__ void decode_eval_body(const uint8_t *blocks, const Ba
 
 __global__ __launch_bounds__(kEvalBlock) void k_decode_eval(const uint8_t *blocks, BandArgs b,
                                                             const uint32_t *prim_idx, uint64_t m,
-                                                            uint64_t n_prims, const float *basis,
+                                                            uint64_t n_prims, const float *dirs,
                                                             uint32_t n_dirs, float *out)
 {
-    decode_eval_body<16>(blocks, b, prim_idx, m, n_prims, basis, n_dirs, out);
+    decode_eval_body<16>(blocks, b, prim_idx, m, n_prims, dirs, n_dirs, out);
 }
 
 __global__ __launch_bounds__(kEvalBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_decode_eval_small(
-    const uint8_t *blocks, BandArgs b, const uint32_t *prim_idx, uint64_t m, uint64_t n_prims, const float *basis,
+    const uint8_t *blocks, BandArgs b, const uint32_t *prim_idx, uint64_t m, uint64_t n_prims, const float *dirs,
     uint32_t n_dirs, float *out)
 {
-    decode_eval_body<8>(blocks, b, prim_idx, m, n_prims, basis, n_dirs, out);
+    decode_eval_body<8>(blocks, b, prim_idx, m, n_prims, dirs, n_dirs, out);
 }
 
 // Colour of slot s seen from view position f (Sec. II, c(f) = H w(f - p)):
@@ -435,28 +435,8 @@ __device__ __forceinline__ void view_colour(const uint8_t *blocks, const BandArg
     x *= inv;
     y *= inv;
     z *= inv;
-    const float c0 = 0.28209479177387814f, c1 = 0.4886025119029199f;
-    const float c2a = 1.0925484305920792f, c2b = 0.31539156525252005f, c2c = 0.5462742152960396f;
-    const float c3a = 0.5900435899266435f, c3b = 2.890611442640554f, c3c = 0.4570457994644658f;
-    const float c3d = 0.3731763325901154f, c3e = 1.445305721320277f;
-    const float xx = x * x, yy = y * y, zz = z * z;
     float Y[16];
-    Y[0] = c0;
-    Y[1] = -c1 * y;
-    Y[2] = c1 * z;
-    Y[3] = -c1 * x;
-    Y[4] = c2a * x * y;
-    Y[5] = -c2a * y * z;
-    Y[6] = c2b * (2.0f * zz - xx - yy);
-    Y[7] = -c2a * x * z;
-    Y[8] = c2c * (xx - yy);
-    Y[9] = -c3a * y * (3.0f * xx - yy);
-    Y[10] = c3b * x * y * z;
-    Y[11] = -c3c * y * (4.0f * zz - xx - yy);
-    Y[12] = c3d * z * (2.0f * zz - 3.0f * xx - 3.0f * yy);
-    Y[13] = -c3c * x * (4.0f * zz - xx - yy);
-    Y[14] = c3e * z * (xx - yy);
-    Y[15] = -c3a * x * (xx - 3.0f * yy);
+    sh_basis(x, y, z, Y);
     uint32_t px[16];
     slot_texels(blocks, b, s, px, lut);
     c[0] = c[1] = c[2] = 0.0f;
@@ -643,46 +623,17 @@ hipError_t launch_decode(const uint8_t *blocks, const BandArgs &b, uint64_t nblk
     return hipGetLastError();
 }
 
-// ---- scratch of the allocation-free decode_eval
-// The basis rows (16 floats per direction) of gsbc_decode_eval_noalloc live
-// in this file-scope device array: the library holds one copy on each GPU it
-// runs on until the process ends.  Host code never uses the array's name as
-// an address (on the host it is only a stand-in for the symbol); each
-// device's address is looked up once, with that device current, and kept.
-static __device__ __align__(256) float scratch[kStaticScratchDirs * 16];
-static std::atomic<float *> g_scratch_ptr[kMaxDevices];
-static std::mutex g_scratch_lock;
-
-hipError_t init_static_scratch(int device)
-{
-    if (device < 0 || device >= kMaxDevices) return hipErrorInvalidDevice;
-    std::lock_guard<std::mutex> guard(g_scratch_lock);
-    if (g_scratch_ptr[device].load()) return hipSuccess;
-    void *ptr = nullptr;
-    const hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
-    if (e != hipSuccess) return e;
-    g_scratch_ptr[device].store(static_cast<float *>(ptr));
-    return hipSuccess;
-}
-
-float *static_scratch(int device)
-{
-    return device >= 0 && device < kMaxDevices ? g_scratch_ptr[device].load() : nullptr;
-}
-
 hipError_t launch_decode_eval(const uint8_t *blocks, const BandArgs &b, uint64_t n_prims, const float *dirs,
-                              uint32_t n_dirs, const uint32_t *prim_idx, uint64_t m, float *out,
-                              float *basis, hipStream_t st)
+                              uint32_t n_dirs, const uint32_t *prim_idx, uint64_t m, float *out, hipStream_t st)
 {
     if (m == 0 || n_dirs == 0) return hipSuccess;
-    GSBC_LAUNCH("sh_basis", k_sh_basis, dim3((n_dirs + 255) / 256), dim3(256), 0, st, dirs, n_dirs, basis);
     dim3 grid((uint32_t)((m + kSlots - 1) / kSlots), (n_dirs + kDirChunk - 1) / kDirChunk);
     if (n_dirs <= (uint32_t)kDirChunk)   // one direction chunk per workgroup: three workgroups per CU
         GSBC_LAUNCH("decode_eval", k_decode_eval_small, grid, dim3(kEvalBlock), 0, st, blocks, b, prim_idx, m,
-                    n_prims, basis, n_dirs, out);
+                    n_prims, dirs, n_dirs, out);
     else
         GSBC_LAUNCH("decode_eval", k_decode_eval, grid, dim3(kEvalBlock), 0, st, blocks, b, prim_idx, m, n_prims,
-                    basis, n_dirs, out);
+                    dirs, n_dirs, out);
     return hipGetLastError();
 }
 

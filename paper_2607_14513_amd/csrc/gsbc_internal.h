@@ -181,6 +181,9 @@ hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t 
 hipError_t upload_bc1_tables(int device, hipStream_t st);
 hipError_t upload_bc7_tables(int device, hipStream_t st);
 
+// Devices the encoders keep tables on, at most.
+constexpr int kMaxDevices = 64;
+
 // ---- rate control (rate.hip)
 // sse: [32] int64 band SSEs, BC1 then BC7; writes format[16], offsets[16] and
 // the payload size into sel (device) and host_sel, and the SSEs into host_sse
@@ -215,16 +218,7 @@ hipError_t launch_decode(const uint8_t *blocks, const BandArgs &b, uint64_t nblk
 // Slots listed in prim_idx at or beyond n_prims give NaN outputs.
 hipError_t launch_decode_eval(const uint8_t *blocks, const BandArgs &b, uint64_t n_prims,
                               const float *dirs, uint32_t n_dirs, const uint32_t *prim_idx,
-                              uint64_t m, float *out, float *basis_scratch, hipStream_t st);
-
-// The allocation-free decode_eval's basis scratch: a file-scope device
-// array of kStaticScratchDirs x 16 floats in decode.hip.  init_static_scratch
-// looks its address up on `device` (which must be current) once; after that
-// static_scratch returns it (null before).
-constexpr uint32_t kStaticScratchDirs = 1024;
-constexpr int kMaxDevices = 64;
-hipError_t init_static_scratch(int device);
-float *static_scratch(int device);
+                              uint64_t m, float *out, hipStream_t st);
 
 // One view position: out[j] = colour of slot prim_idx[j] (or j) at the
 // direction from its primitive (pos[perm[slot]]) towards `view`.
