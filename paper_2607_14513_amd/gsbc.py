@@ -7,6 +7,7 @@ it, or calling it without a GPU, raises -- there is no CPU fallback.
 """
 import ctypes
 import os
+import threading
 
 import numpy as np
 import torch
@@ -209,9 +210,48 @@ def _sizes(desc):
     return r if r is not None else (None, None, None, None)
 
 
+# Blocking HIP streams of closed contexts, per device, for the next ones (a
+# stream's handle names a pool of torch's allocator: reusing handles keeps
+# those pools few).  At most _SPARE_STREAMS a device; the others are destroyed.
+_SPARE_STREAMS = 8
+_spare_streams = {}
+_spare_lock = threading.Lock()
+
+
+def _take_stream(device):
+    """A blocking stream of `device` that no open context uses."""
+    with _spare_lock:
+        spare = _spare_streams.get(device)
+        if spare:
+            return spare.pop()
+    h = ctypes.c_void_p()
+    with torch.cuda.device(device):
+        st = load().hipStreamCreate(ctypes.byref(h))
+    if st != 0:
+        raise GsbcError(E_DEVICE, "hipStreamCreate failed")
+    return h.value
+
+
+def _give_stream(device, handle):
+    """The stream of a closed context (idle: gsbc_destroy waits for it)."""
+    with _spare_lock:
+        spare = _spare_streams.setdefault(device, [])
+        if len(spare) < _SPARE_STREAMS:
+            spare.append(handle)
+            return
+    load().hipStreamDestroy(ctypes.c_void_p(handle))
+
+
 class Context:
     """One library context: device, stream (torch's current stream by default)
-    and scratch arena."""
+    and scratch arena.
+
+    On torch's default stream a context works on a blocking stream of its own,
+    which HIP keeps in order with the default stream but not with the streams
+    of other contexts.  The outputs that it makes therefore come from that
+    stream's pool of torch's allocator: memory that is freed while the context
+    may still write it goes to its own later calls only, not to another
+    context's."""
 
     def __init__(self, device=0, stream=None):
         lib = load()
@@ -222,8 +262,14 @@ class Context:
             stream = torch.cuda.current_stream(self.device)
         self.stream = stream
         h = ctypes.c_void_p()
-        st = lib.gsbc_create(ctypes.byref(h), int(device), ctypes.c_void_p(stream.cuda_stream))
+        self._own, self._pool = None, None
+        if not stream.cuda_stream and 0 <= int(device) < torch.cuda.device_count():
+            self._own = _take_stream(int(device))
+            self._pool = torch.cuda.ExternalStream(self._own, device=self.device)
+        st = lib.gsbc_create(ctypes.byref(h), int(device), ctypes.c_void_p(self._own or stream.cuda_stream))
         if st != OK:
+            if self._own:
+                _give_stream(int(device), self._own)
             raise GsbcError(st, "gsbc_create failed")
         self._h = h
 
@@ -231,6 +277,9 @@ class Context:
         if getattr(self, "_h", None):
             load().gsbc_destroy(self._h)
             self._h = None
+            if self._own:
+                _give_stream(self.device.index, self._own)
+                self._own = None
 
     def __del__(self):
         try:
@@ -243,6 +292,21 @@ class Context:
 
     def __exit__(self, *a):
         self.close()
+
+    def _empty(self, shape, dtype):
+        """A new output tensor, from the pool of the stream that writes it."""
+        if self._pool is None:
+            return torch.empty(shape, dtype=dtype, device=self.device)
+        if torch._C._cuda_getDevice() != self.device.index:
+            with torch.cuda.stream(self._pool):
+                return torch.empty(shape, dtype=dtype, device=self.device)
+        # the same without the context manager's 6 us a call
+        now = torch._C._cuda_getCurrentStream(self.device.index)
+        torch._C._cuda_setStream(self._pool.stream_id, self._pool.device_index, self._pool.device_type)
+        try:
+            return torch.empty(shape, dtype=dtype, device=self.device)
+        finally:
+            torch._C._cuda_setStream(*now)
 
     def _check(self, st):
         if st != OK:
@@ -294,8 +358,8 @@ class Context:
         S = N_STREAMS.get(int(p.arrangement), 16)
         npad = (n + 15) // 16 * 16
         if out is None:
-            perm = torch.empty(n, dtype=torch.int32, device=self.device)
-            tex = torch.empty((S, npad // S, 16, 4), dtype=torch.uint8, device=self.device)
+            perm = self._empty(n, torch.int32)
+            tex = self._empty((S, npad // S, 16, 4), torch.uint8)
         else:
             perm, tex = out
             _check(perm, torch.int32, "perm", shape=(n,))
@@ -328,8 +392,8 @@ class Context:
         _on_device(("pos", pos), ("sh", sh), ("opacity", opacity))
         p = params if params is not None else default_params()
         cap = (n + 15) // 16 * 16 * 64 + 1800
-        buf = torch.empty(cap, dtype=torch.uint8, device=self.device)
-        perm = torch.empty(n, dtype=torch.int32, device=self.device)
+        buf = self._empty(cap, torch.uint8)
+        perm = self._empty(n, torch.int32)
         counts = (ctypes.c_uint64 * 4)()
         offs = (ctypes.c_uint64 * 4)()
         descs = (StreamDesc * 4)()
@@ -358,7 +422,7 @@ class Context:
         desc = desc.copy()
         if blocks is None:
             _, cap, _ = query_sizes(desc.n_prims)
-            blocks = torch.empty(cap, dtype=torch.uint8, device=self.device)
+            blocks = self._empty(cap, torch.uint8)
         _check(blocks, torch.uint8, "blocks")
         _on_device(("textures", textures), ("blocks", blocks))
         sse = np.zeros(32, np.int64) if want_sse else None
@@ -410,7 +474,7 @@ class Context:
         if prim_idx is not None:
             _check(prim_idx, torch.int32, "prim_idx", shape=(m,))
         if out is None:
-            out = torch.empty((m, 3), dtype=torch.float32, device=self.device)
+            out = self._empty((m, 3), torch.float32)
         _check(out, torch.float32, "out", shape=(m, 3))
         _on_device(("blocks", blocks), ("pos", pos), ("perm", perm), ("prim_idx", prim_idx), ("out", out))
         f = (ctypes.c_float * 3)(*[float(x) for x in view])
@@ -439,10 +503,10 @@ class Context:
         _check(lst, torch.int32, "lst")
         H, W = 16 * int(tiles_y), 16 * int(tiles_x)
         if image is None:
-            image = torch.empty((H, W, 3), dtype=torch.float32, device=self.device)
+            image = self._empty((H, W, 3), torch.float32)
         _check(image, torch.float32, "image", shape=(H, W, 3))
         if transmittance is None and want_transmittance:
-            transmittance = torch.empty((H, W), dtype=torch.float32, device=self.device)
+            transmittance = self._empty((H, W), torch.float32)
         if transmittance is not None:
             _check(transmittance, torch.float32, "transmittance", shape=(H, W))
         _on_device(("blocks", blocks), ("pos", pos), ("perm", perm), ("opacity", opacity), ("footprint", footprint),
@@ -473,10 +537,10 @@ class Context:
         _check(lst, torch.int32, "lst")
         H, W = 16 * int(tiles_y), 16 * int(tiles_x)
         if image is None:
-            image = torch.empty((H, W, 3), dtype=torch.float32, device=self.device)
+            image = self._empty((H, W, 3), torch.float32)
         _check(image, torch.float32, "image", shape=(H, W, 3))
         if transmittance is None and want_transmittance:
-            transmittance = torch.empty((H, W), dtype=torch.float32, device=self.device)
+            transmittance = self._empty((H, W), torch.float32)
         if transmittance is not None:
             _check(transmittance, torch.float32, "transmittance", shape=(H, W))
         _on_device(("colours", colours), ("perm", perm), ("opacity", opacity), ("footprint", footprint),
@@ -494,7 +558,7 @@ class Context:
     def load(self, path):
         """Read a container file -> (device blocks tensor, desc)."""
         d = load_header(path)
-        blocks = torch.empty(d.payload_bytes, dtype=torch.uint8, device=self.device)
+        blocks = self._empty(d.payload_bytes, torch.uint8)
         self._check(load().gsbc_load(self._h, os.fsencode(path), ctypes.byref(d), _ptr(blocks), blocks.numel()))
         return blocks, d
 
@@ -503,8 +567,7 @@ class Context:
         S, nblk, payload, _ = _sizes(desc)
         _check(blocks, torch.uint8, "blocks", min_numel=payload)
         if out is None:
-            out = torch.empty((int(desc.n_streams), int(desc.blocks_per_stream), 16, 4), dtype=torch.uint8,
-                              device=self.device)
+            out = self._empty((int(desc.n_streams), int(desc.blocks_per_stream), 16, 4), torch.uint8)
         _check(out, torch.uint8, "out", shape=(S, nblk, 16, 4) if S else None)
         _on_device(("blocks", blocks), ("out", out))
         self._check(load().gsbc_decode(self._h, _ptr(blocks), ctypes.byref(desc), _ptr(out)))
@@ -524,7 +587,7 @@ class Context:
         if prim_idx is not None:
             _check(prim_idx, torch.int32, "prim_idx", shape=(m,))
         if out is None:
-            out = torch.empty((V, m, 3), dtype=torch.float32, device=self.device)
+            out = self._empty((V, m, 3), torch.float32)
         _check(out, torch.float32, "out", shape=(V, m, 3))
         _on_device(("blocks", blocks), ("dirs", dirs), ("prim_idx", prim_idx), ("out", out))
         fn = load().gsbc_decode_eval_noalloc if noalloc else load().gsbc_decode_eval
