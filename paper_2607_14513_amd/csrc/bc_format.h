@@ -44,24 +44,18 @@ __host__ __device__ constexpr int bc7_weight(int n, int i)
     return (128 * i + ((1 << n) - 1)) / (2 * ((1 << n) - 1));
 }
 
-// The same weights for n and i known only at run time (the decoders): the
-// table bytes, little end first, taken by one 64-bit shift instead of a
-// division by 2 (2^n - 1).
-__host__ __device__ constexpr int bc7_weight_packed(int n, int i)
-{
-    const uint64_t lo = n == 2 ? 0x402B1500ull : n == 3 ? 0x40372E251B120900ull : 0x1E1A15110D090400ull;
-    const uint64_t hi = 0x403C37332F2B2622ull;   // n = 4, indices 8..15
-    return (int)(((i < 8 ? lo : hi) >> (8 * (i & 7))) & 255u);
-}
+// The same weights for n and i known only at run time (the decoders), by one
+// multiply-add and a shift: (i * bc7_weight_step(n) + 128) >> 8.
+__host__ __device__ constexpr uint32_t bc7_weight_step(int n) { return n == 2 ? 5461u : n == 3 ? 2341u : 1092u; }
 
-__host__ __device__ constexpr bool bc7_weights_packed_ok()
+__host__ __device__ constexpr bool bc7_weight_steps_ok()
 {
     for (int n = 2; n <= 4; n++)
-        for (int i = 0; i < (1 << n); i++)
-            if (bc7_weight_packed(n, i) != bc7_weight(n, i)) return false;
+        for (uint32_t i = 0; i < (1u << n); i++)
+            if ((int)((i * bc7_weight_step(n) + 128u) >> 8) != bc7_weight(n, (int)i)) return false;
     return true;
 }
-static_assert(bc7_weights_packed_ok(), "packed BC7 weight tables");
+static_assert(bc7_weight_steps_ok(), "BC7 weights by one multiply-add");
 
 __host__ __device__ constexpr int interp64(int e0, int e1, int w)
 {
@@ -75,7 +69,7 @@ __host__ __device__ constexpr int expand_bits(int v, int n)
 }
 
 // ------------------------------------------------------------ partition maps
-static __constant__ uint16_t kPart2[64] = {
+constexpr uint16_t kPart2[64] = {
     0xCCCC, 0x8888, 0xEEEE, 0xECC8, 0xC880, 0xFEEC, 0xFEC8, 0xEC80,
     0xC800, 0xFFEC, 0xFE80, 0xE800, 0xFFE8, 0xFF00, 0xFFF0, 0xF000,
     0xF710, 0x008E, 0x7100, 0x08CE, 0x008C, 0x7310, 0x3100, 0x8CCE,
@@ -121,92 +115,73 @@ constexpr uint32_t kPart3[64] = {
 
 // Anchor texel of the second subset (2-subset partitions), and of the second
 // and third subsets (3-subset partitions).  Subset 0's anchor is texel 0.
-static __constant__ uint8_t kAnchor2[64] = {
+constexpr uint8_t kAnchor2[64] = {
     15, 15, 15, 15, 15, 15, 15, 15, 15, 15, 15, 15, 15, 15, 15, 15,
     15, 2, 8, 2, 2, 8, 8, 15, 2, 8, 2, 2, 8, 8, 2, 2,
     15, 15, 6, 8, 2, 8, 15, 15, 2, 8, 2, 2, 2, 15, 15, 6,
     6, 2, 6, 8, 15, 15, 2, 2, 15, 15, 15, 15, 15, 2, 2, 15,
 };
-static __constant__ uint8_t kAnchor3b[64] = {
+constexpr uint8_t kAnchor3b[64] = {
     3, 3, 15, 15, 8, 3, 15, 15, 8, 8, 6, 6, 6, 5, 3, 3,
     3, 3, 8, 15, 3, 3, 6, 10, 5, 8, 8, 6, 8, 5, 15, 15,
     8, 15, 3, 5, 6, 10, 8, 15, 15, 3, 15, 5, 15, 15, 15, 15,
     3, 15, 5, 5, 5, 8, 5, 10, 5, 10, 8, 13, 15, 12, 3, 3,
 };
-static __constant__ uint8_t kAnchor3c[64] = {
+constexpr uint8_t kAnchor3c[64] = {
     15, 8, 8, 3, 15, 15, 3, 8, 15, 15, 15, 15, 15, 15, 15, 8,
     15, 8, 15, 3, 15, 8, 15, 8, 3, 15, 6, 10, 15, 15, 10, 8,
     15, 3, 15, 10, 10, 8, 9, 10, 6, 15, 8, 15, 3, 6, 6, 8,
     15, 3, 15, 15, 15, 15, 15, 15, 15, 15, 15, 15, 3, 15, 15, 8,
 };
 
-// Partition-map and anchor access for the texel decoder.  The default reads
-// the constant-memory tables above; a kernel can hand it a copy of them in
-// LDS (Bc7PackedLut) so that its per-lane lookups wait on LDS instead of on
-// the vector-memory counter its loads and stores share.
+// One row of the decoders' partition table: the subset of each texel at 2
+// bits a texel and a bit for each anchor texel.  Rows 0..63 are the 2-subset
+// partitions, 64..127 the 3-subset ones, 128 the single subset.
+struct Bc7Part {
+    uint32_t map, anchors;
+};
+constexpr int kBc7PartRows = 129;
+struct Bc7PartTable {
+    Bc7Part row[kBc7PartRows];
+};
+
+constexpr Bc7PartTable bc7_part_table()
+{
+    Bc7PartTable t{};
+    for (int p = 0; p < 64; p++) {
+        for (int i = 0; i < 16; i++) t.row[p].map |= (uint32_t)((kPart2[p] >> i) & 1) << (2 * i);
+        t.row[p].anchors = 1u | 1u << kAnchor2[p];
+        t.row[64 + p] = Bc7Part{kPart3[p], 1u | 1u << kAnchor3b[p] | 1u << kAnchor3c[p]};
+    }
+    t.row[128] = Bc7Part{0u, 1u};
+    return t;
+}
+static __constant__ __align__(8) Bc7PartTable kBc7Parts = bc7_part_table();
+
+// Access to the table for the decoders: in constant memory, or a workgroup's
+// copy in LDS (Bc7LdsLut), whose per-lane lookups wait on LDS instead of on
+// the vector-memory counter that loads and stores share.
 struct Bc7ConstLut {
-    __device__ uint32_t part2(int p) const { return kPart2[p]; }
-    __device__ uint32_t part3(int p) const { return kPart3[p]; }
-    __device__ int anchor2(int p) const { return kAnchor2[p]; }
-    __device__ int anchor3b(int p) const { return kAnchor3b[p]; }
-    __device__ int anchor3c(int p) const { return kAnchor3c[p]; }
+    __device__ Bc7Part row(uint32_t e) const { return kBc7Parts.row[e]; }
 };
 
-// The same tables as 128 words: word p (p < 64) = 2-subset mask | 2-subset
-// anchor << 16 | 3-subset anchors << 20 and << 24; word 64 + p = 3-subset map.
-constexpr int kBc7LutWords = 128;
-__device__ inline uint32_t bc7_lut_word(int e)
-{
-    if (e >= 64) return kPart3[e - 64];
-    return (uint32_t)kPart2[e] | (uint32_t)kAnchor2[e] << 16 | (uint32_t)kAnchor3b[e] << 20 |
-           (uint32_t)kAnchor3c[e] << 24;
-}
-
-struct Bc7PackedLut {
-    const uint32_t *w;   // kBc7LutWords words of bc7_lut_word
-    __device__ uint32_t part2(int p) const { return w[p] & 0xFFFFu; }
-    __device__ uint32_t part3(int p) const { return w[64 + p]; }
-    __device__ int anchor2(int p) const { return (int)(w[p] >> 16) & 15; }
-    __device__ int anchor3b(int p) const { return (int)(w[p] >> 20) & 15; }
-    __device__ int anchor3c(int p) const { return (int)(w[p] >> 24) & 15; }
+struct Bc7LdsLut {
+    const Bc7Part *rows;   // kBc7PartRows of them
+    __device__ Bc7Part row(uint32_t e) const { return rows[e]; }
 };
-
-// Subset of texel i in partition p of an ns-subset mode.
-template <class Lut>
-__device__ inline int bc7_subset(int ns, int p, int i, const Lut &lut)
-{
-    if (ns == 1) return 0;
-    if (ns == 2) return (lut.part2(p) >> i) & 1;
-    return (lut.part3(p) >> (2 * i)) & 3;
-}
-__device__ inline int bc7_subset(int ns, int p, int i) { return bc7_subset(ns, p, i, Bc7ConstLut{}); }
 
 // Anchor texel of subset s.
-template <class Lut>
-__device__ inline int bc7_anchor(int ns, int p, int s, const Lut &lut)
+__device__ inline int bc7_anchor(int ns, int p, int s)
 {
     if (s == 0) return 0;
-    if (ns == 2) return lut.anchor2(p);
-    return s == 1 ? lut.anchor3b(p) : lut.anchor3c(p);
+    if (ns == 2) return kAnchor2[p];
+    return s == 1 ? kAnchor3b[p] : kAnchor3c[p];
 }
-__device__ inline int bc7_anchor(int ns, int p, int s) { return bc7_anchor(ns, p, s, Bc7ConstLut{}); }
 
-// ------------------------------------------------------------- bit access
 // A 128-bit block held as two little-endian 64-bit halves.
 struct Blk128 {
     uint64_t lo, hi;
 };
-
-// Bits pos .. pos + n - 1 of the block (0 <= pos < 128, 1 <= n <= 31):
-// a funnel shift of the two halves, without branches (positions differ
-// from lane to lane).  (hi << 1) << (63 - p) is hi << (64 - p), zero at p = 0.
-__device__ inline uint32_t get_field(const Blk128 &b, int pos, int n)
-{
-    const int p = pos & 63;
-    const uint64_t below = (b.lo >> p) | ((b.hi << 1) << (63 - p));
-    const uint64_t v = pos >= 64 ? b.hi >> p : below;
-    return (uint32_t)v & ((1u << n) - 1u);
-}
 
 // ------------------------------------------------------------- BC1 decode
 __device__ inline void bc1_expand(uint32_t c, int e[3])
@@ -217,96 +192,302 @@ __device__ inline void bc1_expand(uint32_t c, int e[3])
     e[2] = (b5 << 3) | (b5 >> 2);
 }
 
+// The decoders' arithmetic is bound by instruction issue (a colour of one
+// primitive takes 16 texels), so it is written for the instructions that do
+// several steps at once: a byte permute looks up a per-mode constant or packs
+// channels, a funnel shift cuts a field at a position that differs from lane
+// to lane, and a two-way 16-bit dot product interpolates a channel.  The
+// gathers of 1,003 listed slots and of the fused colour stage took 26 and 1,248
+// us by shifts and masks of 64 bits, by these 19 and 909.
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+// Low word of (hi:lo) >> n, 0 <= n < 32.
+__device__ inline uint32_t funnel(uint32_t hi, uint32_t lo, uint32_t n) { return __builtin_amdgcn_alignbit(hi, lo, n); }
+
+// n bits of x from bit `at` (both below 32).
+__device__ inline uint32_t bits(uint32_t x, uint32_t at, uint32_t n) { return __builtin_amdgcn_ubfe(x, at, n); }
+
+// Halves of e times halves of w, summed, plus c.
+__device__ inline uint32_t dot2(uint32_t e, uint32_t w, uint32_t c)
+{
+    return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, e), __builtin_bit_cast(u16x2, w), c, false);
+}
+
+// Four bytes of (hi:lo), one per selector byte: 0..3 of lo, 4..7 of hi, 0x0C zero.
+__device__ inline uint32_t bytes(uint32_t hi, uint32_t lo, uint32_t sel) { return __builtin_amdgcn_perm(hi, lo, sel); }
+
+// ------------------------------------------------------------- BC1 palette
+// A block's endpoints as pairs (first | second << 16) per channel, and the
+// weights of its four colours: colour = (pair . weights + 1) mult >> 16, with
+// mult 1/3 or 1/2 (exact for the sums that occur, below 767; the pure
+// endpoints come out as (3 e + 1) / 3 and (2 e + 1) / 2, rounded down).
+struct Bc1Head {
+    uint32_t r, g, b, first, second, mult;
+    bool three;
+};
+
+__device__ inline Bc1Head bc1_head(uint32_t w0)
+{
+    Bc1Head h;
+    const uint32_t r5 = (w0 >> 11) & 0x001F001Fu, g6 = (w0 >> 5) & 0x003F003Fu, b5 = w0 & 0x001F001Fu;
+    h.r = r5 << 3 | ((r5 >> 2) & 0x00070007u);
+    h.g = g6 << 2 | ((g6 >> 4) & 0x00030003u);
+    h.b = b5 << 3 | ((b5 >> 2) & 0x00070007u);
+    h.three = (w0 & 0xFFFFu) <= (w0 >> 16);   // two endpoints, their mean and transparent black
+    h.first = h.three ? 0x00010002u : 0x01020003u;    // byte k: weight of the first endpoint in colour k
+    h.second = h.three ? 0x00010200u : 0x02010300u;
+    h.mult = h.three ? 32768u : 21846u;
+    return h;
+}
+
+__device__ inline uint32_t bc1_colour(const Bc1Head &h, uint32_t k)
+{
+    const uint32_t w = bytes(h.second, h.first, __umul24(k, 0x00010001u) + 0x0C040C00u);
+    const uint32_t r = __umul24(dot2(h.r, w, 1u), h.mult), g = __umul24(dot2(h.g, w, 1u), h.mult),
+                   b = __umul24(dot2(h.b, w, 1u), h.mult);
+    // each channel in byte 2 of its product; alpha 255, or 0 for transparent black
+    const uint32_t alpha = h.three && k == 3u ? 0u : 0xFF000000u;
+    return bytes(g, r, 0x0C0C0602u) | (b & 0x00FF0000u) | alpha;
+}
+
 // Texel i of a BC1 block given as two 32-bit words; RGBA packed in a uint32
 // (R in the low byte).
 __device__ inline uint32_t bc1_texel(uint32_t w0, uint32_t w1, int i)
 {
-    uint32_t c0 = w0 & 0xFFFF, c1 = w0 >> 16;
-    int k = (w1 >> (2 * i)) & 3;
-    int e0[3], e1[3];
-    bc1_expand(c0, e0);
-    bc1_expand(c1, e1);
-    int px[3];
-    uint32_t a = 255;
-    if (k == 0) { px[0] = e0[0]; px[1] = e0[1]; px[2] = e0[2]; }
-    else if (k == 1) { px[0] = e1[0]; px[1] = e1[1]; px[2] = e1[2]; }
-    else if (c0 > c1) {
-        for (int c = 0; c < 3; c++)
-            px[c] = k == 2 ? (2 * e0[c] + e1[c] + 1) / 3 : (e0[c] + 2 * e1[c] + 1) / 3;
-    } else if (k == 2) {
-        for (int c = 0; c < 3; c++) px[c] = (e0[c] + e1[c] + 1) >> 1;
-    } else {
-        px[0] = px[1] = px[2] = 0;
-        a = 0;
+    return bc1_colour(bc1_head(w0), (w1 >> (2 * i)) & 3u);
+}
+
+// All 16 texels.
+__device__ inline void bc1_block(uint32_t w0, uint32_t w1, uint32_t (&px)[16])
+{
+    const Bc1Head h = bc1_head(w0);
+    uint32_t pal[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4; k++) pal[k] = bc1_colour(h, k);
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const bool b0 = (w1 >> (2 * i)) & 1u, b1 = (w1 >> (2 * i + 1)) & 1u;
+        const uint32_t lo = b0 ? pal[1] : pal[0], hi = b0 ? pal[3] : pal[2];
+        px[i] = b1 ? hi : lo;
     }
-    return (uint32_t)px[0] | ((uint32_t)px[1] << 8) | ((uint32_t)px[2] << 16) | (a << 24);
 }
 
 // ------------------------------------------------------------- BC7 decode
+// Bit positions of a mode's fields: colour endpoints (channel by channel,
+// each all its endpoints in order), alpha endpoints, p-bits, first and second
+// index.
+struct Bc7Layout {
+    int colour, alpha, pbits, index, index2;
+};
+
+constexpr Bc7Layout bc7_layout(int m)
+{
+    const Bc7Mode d = bc7_mode(m);
+    const int colour = m + 1 + d.partbits + d.rotbits + d.selbits;
+    const int alpha = colour + 6 * d.ns * d.cb;
+    const int pbits = alpha + 2 * d.ns * d.ab;
+    const int index = pbits + d.pb * d.ns;
+    return Bc7Layout{colour, alpha, pbits, index, index + 16 * d.ib - d.ns};
+}
+
+// One constant per mode, mode m in byte m.
+template <class F>
+constexpr uint64_t bc7_by_mode(F f)
+{
+    uint64_t v = 0;
+    for (int m = 0; m < 8; m++) v |= (uint64_t)(uint8_t)f(m) << (8 * m);
+    return v;
+}
+
+// What the decoders below rely on.
+constexpr bool bc7_layout_ok()
+{
+    for (int m = 0; m < 8; m++) {
+        const Bc7Mode d = bc7_mode(m);
+        const Bc7Layout l = bc7_layout(m);
+        // the first channel of any subset starts in the first word, a channel's endpoints span at most 30 bits
+        if (l.colour + 2 * (d.ns - 1) * d.cb >= 32 || 2 * d.ns * d.cb > 30) return false;
+        // alpha endpoints: within words 1 and 2, in mode 7 within words 2 and 3
+        if (d.ab && (l.alpha < (m == 7 ? 64 : 32) || l.alpha >= (m == 7 ? 96 : 64) || 2 * d.ns * d.ab > 20)) return false;
+        // p-bits within words 2 and 3, in mode 6 the last bit of word 1 and the first of word 2
+        if (d.pb && (m == 6 ? l.pbits != 63 : (l.pbits < 64 || l.pbits >= 96))) return false;
+        // indices within the upper half, in mode 4 the first within words 1 and 2
+        if (m == 4 ? (l.index < 32 || l.index2 > 96) : l.index < 64) return false;
+        if (d.ib2 && (l.index2 < 64 || l.index2 + 16 * d.ib2 - 1 != 128)) return false;
+        if (!d.ib2 && l.index2 != 128) return false;
+    }
+    return true;
+}
+static_assert(bc7_layout_ok(), "BC7 field positions");
+
+// A block's mode and the fields that all its texels share.
+struct Bc7Head {
+    uint32_t sel;              // byte-permute selector of the mode: m in the low byte, the others zero
+    uint32_t m;
+    uint32_t cb, ab, hp;       // endpoint bits; 1 with p-bits
+    uint32_t up, down, aup, adown;   // an n-bit code's expansion to 8 bits: << 8 - n, | >> 2 n - 8
+    uint32_t amask;            // 255 in both halves without stored alpha
+    uint32_t rot;              // the last permute: (B, A):(R, G) to the rotated texel, all zero in the reserved mode
+    uint32_t ib, ib2, step, step2;   // index bits and weight steps
+    uint32_t ibase, ibase2;    // first bit of the indices in iw:iv and w3:w2
+    uint32_t iv, iw;
+    bool swap, second;         // colour takes the second index; alpha takes the second index
+    Bc7Part part;
+};
+
+#define GSBC_BY_MODE(expr) [&] { constexpr uint64_t t = bc7_by_mode([](int m) { \
+        [[maybe_unused]] const Bc7Mode d = bc7_mode(m); \
+        [[maybe_unused]] const Bc7Layout l = bc7_layout(m); \
+        return (expr); }); \
+        return bytes((uint32_t)(t >> 32), (uint32_t)t, h.sel); }()
+
+template <class Lut>
+__device__ inline Bc7Head bc7_head(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, const Lut &lut)
+{
+    Bc7Head h;
+    const bool reserved = (w0 & 255u) == 0u;   // no mode bit: every texel zero (the fields are read as mode 7's)
+    h.m = (uint32_t)__builtin_ctz(w0 | 0x80u);
+    h.sel = h.m | 0x0C0C0C00u;
+    const uint32_t after = w0 >> (h.m + 1u);
+    // row of the partition table
+    const uint32_t row = GSBC_BY_MODE(d.ns == 1 ? 128 : d.ns == 3 ? 64 : 0) + (after & GSBC_BY_MODE((1 << d.partbits) - 1));
+    h.part = lut.row(row);
+    const uint32_t rot = after & GSBC_BY_MODE(d.rotbits ? 3 : 0);
+    h.rot = rot == 0u ? 0x05040100u : rot == 1u ? 0x00040105u : rot == 2u ? 0x01040500u : 0x04050100u;
+    if (reserved) h.rot = 0x0C0C0C0Cu;
+    h.cb = GSBC_BY_MODE(d.cb);
+    h.ab = GSBC_BY_MODE(d.ab);
+    h.hp = GSBC_BY_MODE(d.pb ? 1 : 0);
+    const uint32_t n = h.cb + h.hp, an = h.ab + h.hp;
+    h.up = 8u - n;
+    h.down = 2u * n - 8u;
+    h.amask = h.ab ? 0u : 0x00FF00FFu;
+    h.aup = h.ab ? 8u - an : 0u;
+    h.adown = h.ab ? 2u * an - 8u : 0u;
+    const bool four = h.m == 4u;
+    h.ib = GSBC_BY_MODE(d.ib);
+    h.ib2 = GSBC_BY_MODE(d.ib2);
+    h.step = h.m == 6u ? bc7_weight_step(4) : h.m < 2u ? bc7_weight_step(3) : bc7_weight_step(2);
+    h.step2 = four ? bc7_weight_step(3) : bc7_weight_step(2);
+    h.ibase = GSBC_BY_MODE(m == 4 ? l.index - 32 : l.index - 64);
+    h.ibase2 = GSBC_BY_MODE(d.ib2 ? l.index2 - 64 : 0);
+    h.iv = four ? w1 : w2;
+    h.iw = four ? w2 : w3;
+    h.swap = four && (w0 & 0x80u);             // mode 4's index selection bit
+    h.second = h.ib2 != 0u && !h.swap;
+    return h;
+}
+
+// Two stored codes of n bits, the first in the low bits, as endpoints of 8
+// bits in the halves of a word; pp holds their p-bits.
+__device__ inline uint32_t bc7_endpoints(uint32_t code0, uint32_t code1, uint32_t pp, uint32_t hp, uint32_t up,
+                                         uint32_t down)
+{
+    const uint32_t v = (code0 | code1 << 16) << hp | pp;
+    return v << up | ((v >> down) & 0x00FF00FFu);
+}
+
+// p-bits of the block: word whose low bits are the first subset's.
+__device__ inline uint32_t bc7_pbits(const Bc7Head &h, uint32_t w1, uint32_t w2, uint32_t w3)
+{
+    const bool six = h.m == 6u;
+    const uint32_t w = funnel(six ? w2 : w3, six ? w1 : w2, GSBC_BY_MODE(l.pbits & 31));
+    return h.hp ? w : 0u;
+}
+
+// p-bits of a subset whose bits start at q's low bit, in the halves of a word.
+__device__ inline uint32_t bc7_pair(const Bc7Head &h, uint32_t q)
+{
+    return (q & 1u) | ((q << GSBC_BY_MODE(d.pb == 1 ? 16 : 15)) & 0x00010000u);
+}
+
+// The texel of endpoints (pairs of r, g, b, a) at indices i1 and i2:
+// interp64 of each channel, as weights times 4 and >> 8.
+__device__ inline uint32_t bc7_mix(const Bc7Head &h, uint32_t r, uint32_t g, uint32_t b, uint32_t a, uint32_t i1,
+                                   uint32_t i2)
+{
+    const uint32_t ci = h.swap ? i2 : i1, cs = h.swap ? h.step2 : h.step;
+    const uint32_t ai = h.second ? i2 : i1, as = h.second ? h.step2 : h.step;
+    // (256 - 4 w) | 4 w << 16
+    const uint32_t wc = __umul24((__umul24(ci, cs) + 128u) >> 8, 0x3FFFCu) + 256u;
+    const uint32_t wa = __umul24((__umul24(ai, as) + 128u) >> 8, 0x3FFFCu) + 256u;
+    const uint32_t rg = bytes(dot2(g, wc, 128u), dot2(r, wc, 128u), 0x0C0C0501u);
+    const uint32_t ba = bytes(dot2(a, wa, 128u), dot2(b, wc, 128u), 0x0C0C0501u);
+    return bytes(ba, rg, h.rot);
+}
+
 // Texel i of a BC7 block, RGBA packed in a uint32 (R in the low byte).
 template <class Lut>
 __device__ inline uint32_t bc7_texel(const Blk128 &b, int i, const Lut &lut)
 {
-    uint32_t b0 = (uint32_t)b.lo & 0xFF;
-    if (b0 == 0) return 0;  // reserved mode: all zero
-    int m = __ffs(b0) - 1;
-    Bc7Mode md = bc7_mode(m);
-    int pos = m + 1;
-    int part = md.partbits ? (int)get_field(b, pos, md.partbits) : 0;
-    pos += md.partbits;
-    int rot = md.rotbits ? (int)get_field(b, pos, md.rotbits) : 0;
-    pos += md.rotbits;
-    int sel = md.selbits ? (int)get_field(b, pos, 1) : 0;
-    pos += md.selbits;
-    int ns = md.ns, ne = 2 * ns;
-    int s = bc7_subset(ns, part, i, lut);
-    int e0[4], e1[4];
-    int cpos = pos;
-    pos += 3 * ne * md.cb;
-    int apos = pos;
-    pos += ne * md.ab;
-    int p0 = 0, p1 = 0;
-    if (md.pb == 2) { p0 = (int)get_field(b, pos + 2 * s, 1); p1 = (int)get_field(b, pos + 2 * s + 1, 1); pos += ne; }
-    else if (md.pb == 1) { p0 = p1 = (int)get_field(b, pos + s, 1); pos += ns; }
-    int nbits = md.cb + (md.pb ? 1 : 0);
-    for (int c = 0; c < 3; c++) {
-        int v0 = (int)get_field(b, cpos + (c * ne + 2 * s) * md.cb, md.cb);
-        int v1 = (int)get_field(b, cpos + (c * ne + 2 * s + 1) * md.cb, md.cb);
-        if (md.pb) { v0 = (v0 << 1) | p0; v1 = (v1 << 1) | p1; }
-        e0[c] = expand_bits(v0, nbits);
-        e1[c] = expand_bits(v1, nbits);
-    }
-    if (md.ab) {
-        int abits = md.ab + (md.pb ? 1 : 0);
-        int v0 = (int)get_field(b, apos + 2 * s * md.ab, md.ab);
-        int v1 = (int)get_field(b, apos + (2 * s + 1) * md.ab, md.ab);
-        if (md.pb) { v0 = (v0 << 1) | p0; v1 = (v1 << 1) | p1; }
-        e0[3] = expand_bits(v0, abits);
-        e1[3] = expand_bits(v1, abits);
-    } else {
-        e0[3] = e1[3] = 255;
-    }
-    // primary index: one bit less for each anchor texel before i and for i itself
-    int a1 = ns >= 2 ? bc7_anchor(ns, part, 1, lut) : 99;
-    int a2 = ns == 3 ? bc7_anchor(ns, part, 2, lut) : 99;
-    int before = (i > 0) + (a1 < i) + (a2 < i);
-    int anchored = (i == 0) || (i == a1) || (i == a2);
-    int i1 = (int)get_field(b, pos + i * md.ib - before, md.ib - anchored);
-    pos += 16 * md.ib - ns;
-    int i2 = 0;
-    if (md.ib2) i2 = (int)get_field(b, pos + i * md.ib2 - (i > 0), md.ib2 - (i == 0));
-    int ci = i1, cn = md.ib, ai = i1, an = md.ib;
-    if (md.ib2) {
-        if (sel == 0) { ai = i2; an = md.ib2; }
-        else { ci = i2; cn = md.ib2; ai = i1; an = md.ib; }
-    }
-    int wc = bc7_weight_packed(cn, ci), wa = bc7_weight_packed(an, ai);
-    int px[4];
-    for (int c = 0; c < 3; c++) px[c] = interp64(e0[c], e1[c], wc);
-    px[3] = interp64(e0[3], e1[3], wa);
-    if (rot) { int t = px[3]; px[3] = px[rot - 1]; px[rot - 1] = t; }
-    return (uint32_t)px[0] | ((uint32_t)px[1] << 8) | ((uint32_t)px[2] << 16) | ((uint32_t)px[3] << 24);
+    const uint32_t w0 = (uint32_t)b.lo, w1 = (uint32_t)(b.lo >> 32), w2 = (uint32_t)b.hi, w3 = (uint32_t)(b.hi >> 32);
+    const Bc7Head h = bc7_head(w0, w1, w2, w3, lut);
+    const uint32_t s = bits(h.part.map, 2u * i, 2u);
+    // the subset's red at the low end of S, green and blue one stride up each
+    const uint32_t at = GSBC_BY_MODE(l.colour) + 2u * s * h.cb, stride = GSBC_BY_MODE(2 * d.ns * d.cb);
+    const uint32_t S0 = funnel(w1, w0, at), S1 = funnel(w2, w1, at), S2 = funnel(w3, w2, at);
+    const uint32_t T0 = funnel(S1, S0, stride), T1 = funnel(S2, S1, stride), U0 = funnel(T1, T0, stride);
+    const uint32_t pp = bc7_pair(h, bc7_pbits(h, w1, w2, w3) >> (s * GSBC_BY_MODE(d.pb)));
+    const uint32_t r = bc7_endpoints(bits(S0, 0u, h.cb), bits(S0, h.cb, h.cb), pp, h.hp, h.up, h.down);
+    const uint32_t g = bc7_endpoints(bits(T0, 0u, h.cb), bits(T0, h.cb, h.cb), pp, h.hp, h.up, h.down);
+    const uint32_t bl = bc7_endpoints(bits(U0, 0u, h.cb), bits(U0, h.cb, h.cb), pp, h.hp, h.up, h.down);
+    const bool seven = h.m == 7u;
+    const uint32_t A = funnel(seven ? w3 : w2, seven ? w2 : w1, GSBC_BY_MODE(l.alpha & 31) + 2u * s * h.ab);
+    const uint32_t a = bc7_endpoints(bits(A, 0u, h.ab), bits(A, h.ab, h.ab), pp, h.hp, h.aup, h.adown) | h.amask;
+    // indices: one bit less for each anchor texel before i and for i itself
+    const uint32_t before = (uint32_t)__popc(h.part.anchors & ((1u << i) - 1u)), own = (h.part.anchors >> i) & 1u;
+    const uint64_t iw = (uint64_t)h.iw << 32 | h.iv, jw = (uint64_t)w3 << 32 | w2;
+    const uint32_t i1 = bits((uint32_t)(iw >> (h.ibase + i * h.ib - before)), 0u, h.ib - own);
+    const uint32_t i2 = bits((uint32_t)(jw >> ((h.ibase2 + i * h.ib2 - (i > 0)) & 63u)), 0u, h.ib2 - (i == 0));
+    return bc7_mix(h, r, g, bl, a, i1, i2);
 }
 __device__ inline uint32_t bc7_texel(const Blk128 &b, int i) { return bc7_texel(b, i, Bc7ConstLut{}); }
+
+// All 16 texels: the fields and endpoints are taken once, the index bits are
+// given their anchors' missing top bits so that every texel's are h.ib wide.
+template <class Lut>
+__device__ inline void bc7_block(const Blk128 &b, uint32_t (&px)[16], const Lut &lut)
+{
+    const uint32_t w0 = (uint32_t)b.lo, w1 = (uint32_t)(b.lo >> 32), w2 = (uint32_t)b.hi, w3 = (uint32_t)(b.hi >> 32);
+    const Bc7Head h = bc7_head(w0, w1, w2, w3, lut);
+    const uint32_t at = GSBC_BY_MODE(l.colour), stride = GSBC_BY_MODE(2 * d.ns * d.cb);
+    const uint32_t S0 = funnel(w1, w0, at), S1 = funnel(w2, w1, at), S2 = funnel(w3, w2, at);
+    const uint32_t T0 = funnel(S1, S0, stride), T1 = funnel(S2, S1, stride), U0 = funnel(T1, T0, stride);
+    const bool seven = h.m == 7u;
+    const uint32_t A = funnel(seven ? w3 : w2, seven ? w2 : w1, GSBC_BY_MODE(l.alpha & 31));
+    const uint32_t P = bc7_pbits(h, w1, w2, w3), pstep = GSBC_BY_MODE(d.pb);
+    uint32_t r[3], g[3], bl[3], a[3];
+#pragma unroll
+    for (uint32_t s = 0; s < 3; s++) {   // (a subset that the mode has not is never chosen below)
+        const uint32_t c0 = 2u * s * h.cb, c1 = c0 + h.cb, a0 = 2u * s * h.ab, a1 = a0 + h.ab;
+        const uint32_t pp = bc7_pair(h, P >> (s * pstep));
+        r[s] = bc7_endpoints(bits(S0, c0, h.cb), bits(S0, c1, h.cb), pp, h.hp, h.up, h.down);
+        g[s] = bc7_endpoints(bits(T0, c0, h.cb), bits(T0, c1, h.cb), pp, h.hp, h.up, h.down);
+        bl[s] = bc7_endpoints(bits(U0, c0, h.cb), bits(U0, c1, h.cb), pp, h.hp, h.up, h.down);
+        a[s] = bc7_endpoints(bits(A, a0, h.ab), bits(A, a1, h.ab), pp, h.hp, h.aup, h.adown) | h.amask;
+    }
+    uint64_t iw = ((uint64_t)h.iw << 32 | h.iv) >> h.ibase, jw = ((uint64_t)w3 << 32 | w2) >> h.ibase2;
+    uint32_t left = h.part.anchors;
+#pragma unroll
+    for (int s = 0; s < 3; s++) {        // anchors in texel order: bit p and what is above move up by one
+        const uint32_t p = ((uint32_t)__builtin_ctz(left | 0x10000u) + 1u) * h.ib - 1u;
+        iw += left ? iw & (~0ull << (p & 63u)) : 0ull;
+        left &= left - 1u;
+    }
+    jw += jw & (~0ull << ((h.ib2 - 1u) & 63u));
+    const uint32_t ilo = (uint32_t)iw, ihi = (uint32_t)(iw >> (8u * h.ib));
+    const uint32_t jlo = (uint32_t)jw, jhi = (uint32_t)(jw >> (8u * h.ib2));
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const uint32_t s = bits(h.part.map, 2u * i, 2u);
+        const bool s1 = s == 1u, s2 = s == 2u;
+        const uint32_t i1 = bits(i < 8 ? ilo : ihi, (i & 7) * h.ib, h.ib);
+        const uint32_t i2 = bits(i < 8 ? jlo : jhi, (i & 7) * h.ib2, h.ib2);
+        px[i] = bc7_mix(h, s2 ? r[2] : s1 ? r[1] : r[0], s2 ? g[2] : s1 ? g[1] : g[0], s2 ? bl[2] : s1 ? bl[1] : bl[0],
+                        s2 ? a[2] : s1 ? a[1] : a[0], i1, i2);
+    }
+}
+
+#undef GSBC_BY_MODE
 
 }  // namespace gsbc
