@@ -178,7 +178,7 @@ __device__ __forceinline__ Bc7LdsLut stage_parts(Bc7Part *rows)
 // of 16 texels found one by one, and hands them over in LDS: row `band`, slot
 // t at t + 4 (t / 16) (16-byte pieces, spread over the banks).  1,048,576
 // slots x 64 directions 182 -> 145 us, all of a 3,145,728-slot scene from one
-// view position 0.26 -> 0.11 ms (half of each gain from the texel decoder).
+// view position 0.26 -> 0.09 ms (part of each gain is the texel decoder's).
 constexpr int kTileRow = 320;
 constexpr int kTileWords = 16 * kTileRow;
 

@@ -29,9 +29,8 @@ constexpr int kSortTile = 256 * kSortKPT;      // keys per tile (one workgroup)
 constexpr int kMaxDigitBits = 9;
 constexpr int kMaxBins = 1 << kMaxDigitBits;
 constexpr int kMaxPasses = 7;                  // 56-bit keys (grid 10 bits, degree class) in 9-bit digits
-constexpr int kRangeBlock = 384;               // coverage histogram block: a multiple of 12 and 3
+constexpr int kCovBlock = 1024;                // coverage histogram and selection block
 constexpr int kMinMaxBlock = 768;              // min/max pass block (measured faster than 384 or 192)
-static_assert(kRangeBlock % 12 == 0, "a block-size run of float4 chunks must hold whole primitives");
 
 // Digits of each pass, low to high: ceil(bits / 9) passes of near-equal width.
 struct SortPlan {
@@ -707,69 +706,102 @@ __global__ __launch_bounds__(256) void k_gather_pack(const float *sh, const floa
 // 14..7 and 6..0, each a histogram of the next digit among the values that
 // match the prefix chosen so far, then a scan that picks the digit holding
 // the remaining rank.
-constexpr int kCovWG = 256;
-constexpr uint64_t kCoverNum = 995, kCoverDen = 1000;   // 99.5 % of each band inside [-t, t]                    // workgroups of the histogram pass
+constexpr int kCovWG = 256;                             // workgroups of the histogram pass
+constexpr uint64_t kCoverNum = 995, kCoverDen = 1000;   // 99.5 % of each band inside [-t, t]
 constexpr int kCovShift[4] = {23, 15, 7, 0};
 constexpr int kCovWidth[4] = {8, 8, 8, 7};
+// A band's row of counters: values of all bands share a few digits, which
+// rows 4 words longer than the 256 counters spread over the 64 banks.
+constexpr uint32_t kCovRow = 260;
 
 // part[wg][band][256]: this workgroup's digit counts; state[band] = prefix,
 // state[16 + band] = remaining rank.
-__global__ __launch_bounds__(kRangeBlock) void k_cov_hist(const float4 *sh4, const float *opacity, uint64_t n,
-                                                          int pass, const uint32_t *state, uint32_t *part)
+// Bound by reading the rows: a wave takes 32 primitives a step, as the range
+// pass does (six 16-byte loads per lane in flight together, chunk u * 64 +
+// lane at place (lane + 4u) mod 12 of its primitive), so a lane's 12 counter
+// rows and prefixes stay in registers.  One load at a time with the prefix
+// read per value took 50 us a pass at 500,009 primitives with opacity, this
+// 18.
+template <int PASS>
+__global__ __launch_bounds__(kCovBlock) void k_cov_hist(const float4 *sh4, const float *opacity, uint64_t n,
+                                                        const uint32_t *state, uint32_t *part)
 {
-    __shared__ uint32_t h[16][256];
-    for (int e = threadIdx.x; e < 16 * 256; e += kRangeBlock) h[e >> 8][e & 255] = 0;
-    __syncthreads();
-    const int shift = kCovShift[pass], width = kCovWidth[pass];
-    const uint64_t T = (uint64_t)gridDim.x * blockDim.x;
-    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int j = (int)(t % 12);
-    const uint64_t nq = n * 12;
-    for (uint64_t q = t; q < nq; q += T) {
-        float4 v = sh4[q];
-        float f[4] = {v.x, v.y, v.z, v.w};
-        const float mu = opacity ? opacity[q / 12] : 1.0f;
+    __shared__ uint32_t h[16 * kCovRow];
+    constexpr int shift = kCovShift[PASS], width = kCovWidth[PASS];
+    const uint32_t t = threadIdx.x, lane = t & 63u;
+    for (uint32_t e = t; e < 16 * kCovRow; e += kCovBlock) h[e] = 0;
+    uint32_t row[3][4], want[3][4];
 #pragma unroll
-        for (int c = 0; c < 4; c++) {
-            const int band = (4 * j + c) / 3;
-            const uint32_t u = __float_as_uint(opacity ? mu * f[c] : f[c]) & 0x7FFFFFFFu;
-            if (pass > 0 && (u >> (shift + width)) != state[band]) continue;
-            atomicAdd(&h[band][(u >> shift) & ((1u << width) - 1u)], 1u);
+    for (uint32_t k = 0; k < 3; k++)
+#pragma unroll
+        for (uint32_t c = 0; c < 4; c++) {
+            const uint32_t band = (4 * ((lane + 4 * k) % 12) + c) / 3;
+            row[k][c] = band * kCovRow;
+            want[k][c] = PASS > 0 ? state[band] : 0u;
+        }
+    __syncthreads();
+    const uint64_t waves = (uint64_t)gridDim.x * (kCovBlock / 64);
+    const uint64_t wave = (uint64_t)blockIdx.x * (kCovBlock / 64) + __builtin_amdgcn_readfirstlane(t >> 6);
+    const uint64_t steps = (n + kStepPrims - 1) / kStepPrims;
+    for (uint64_t step = wave; step < steps; step += waves) {
+        const uint64_t p0 = step * kStepPrims;
+        const uint32_t chunks = 12 * (uint32_t)min((uint64_t)kStepPrims, n - p0);
+        const float4 *src = sh4 + p0 * 12;
+        float4 v[kStepLoads];
+        float mu[kStepLoads];
+#pragma unroll
+        for (uint32_t u = 0; u < kStepLoads; u++) {   // (the last step's missing chunks load its last one)
+            const uint32_t q = min(u * 64 + lane, chunks - 1);
+            v[u] = src[q];
+            mu[u] = opacity ? opacity[p0 + q / 12] : 1.0f;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kStepLoads; u++) {
+            const float f[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+            for (uint32_t c = 0; c < 4; c++) {
+                const uint32_t x = __float_as_uint(opacity ? mu[u] * f[c] : f[c]) & 0x7FFFFFFFu;
+                bool mine = u * 64 + lane < chunks;
+                if (PASS > 0) mine = mine && (x >> (shift + width)) == want[u % 3][c];
+                if (mine) atomicAdd(&h[row[u % 3][c] + ((x >> shift) & ((1u << width) - 1u))], 1u);
+            }
         }
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < 16 * 256; e += kRangeBlock)
-        part[(uint64_t)blockIdx.x * 4096 + e] = h[e >> 8][e & 255];
+    for (uint32_t e = t; e < 16 * 256; e += kCovBlock)
+        part[(uint64_t)blockIdx.x * 4096 + e] = h[(e >> 8) * kCovRow + (e & 255u)];
 }
 
-// One workgroup per band, one thread per digit: total the partial counts,
-// scan, and keep the digit whose cumulative count reaches the rank.
-__global__ __launch_bounds__(256) void k_cov_select(const uint32_t *part, uint32_t nwg, int pass, uint32_t *state)
+// One workgroup per band, four threads per digit: total the partial counts
+// (a quarter of the workgroups' each, eight loads in flight: one thread a
+// digit took 74 us over 256 of them, this 6), scan, and keep the digit
+// whose cumulative count reaches the rank (rank0 in the first pass, whose
+// prefix is empty).
+__global__ __launch_bounds__(kCovBlock) void k_cov_select(const uint32_t *part, uint32_t nwg, int pass, uint32_t rank0,
+                                                          uint32_t *state)
 {
-    __shared__ uint32_t scan[256];
-    const int band = blockIdx.x, d = threadIdx.x;
+    __shared__ uint32_t sum[4][256], scan[256];
+    const uint32_t band = blockIdx.x, d = threadIdx.x & 255u, g = threadIdx.x >> 8;
     uint32_t c = 0;
-    for (uint32_t w = 0; w < nwg; w++) c += part[(uint64_t)w * 4096 + band * 256 + d];
-    scan[d] = c;
+#pragma unroll 8
+    for (uint32_t w = g; w < nwg; w += 4) c += part[(uint64_t)w * 4096 + band * 256 + d];
+    sum[g][d] = c;
     __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {   // inclusive scan
+    c = sum[0][d] + sum[1][d] + sum[2][d] + sum[3][d];
+    if (g == 0) scan[d] = c;
+    __syncthreads();
+    for (uint32_t off = 1; off < 256; off <<= 1) {   // inclusive scan
         const uint32_t x = d >= off ? scan[d - off] : 0u;
         __syncthreads();
-        scan[d] += x;
+        if (g == 0) scan[d] += x;
         __syncthreads();
     }
-    const uint32_t rank = state[16 + band], incl = scan[d], excl = incl - c;
-    if (c > 0 && excl < rank && rank <= incl) {
-        state[band] = (state[band] << kCovWidth[pass]) | (uint32_t)d;
+    const uint32_t prefix = pass ? state[band] : 0u, rank = pass ? state[16 + band] : rank0;
+    const uint32_t incl = scan[d], excl = incl - c;
+    __syncthreads();   // every thread has read the state
+    if (g == 0 && c > 0 && excl < rank && rank <= incl) {
+        state[band] = (prefix << kCovWidth[pass]) | d;
         state[16 + band] = rank - excl;
-    }
-}
-
-__global__ void k_cov_init(uint32_t *state, uint32_t rank)
-{
-    if (threadIdx.x < 16) {
-        state[threadIdx.x] = 0;
-        state[16 + threadIdx.x] = rank;
     }
 }
 
@@ -884,7 +916,6 @@ void enqueue_range(const float *pos, const float *sh, const float *opacity, uint
                    uint32_t quantiser, bool keys_finish, float deg_tau, const Layout &L, char *s, RangeRec *range_dev,
                    hipStream_t st)
 {
-    uint64_t want = (n * 12 + kRangeBlock - 1) / kRangeBlock;
     // at most 512 workgroups of 768 (two per CU, each one contiguous span)
     const uint32_t nb = (uint32_t)std::min<uint64_t>(std::max<uint64_t>((n * 12 + kMinMaxBlock - 1) / kMinMaxBlock, 1), 512);
     const bool stream = n * 192 > kStreamRowBytes;
@@ -904,12 +935,13 @@ void enqueue_range(const float *pos, const float *sh, const float *opacity, uint
         uint32_t *part = reinterpret_cast<uint32_t *>(s + L.cov_part);
         // 1-based rank of the covering magnitude among the 3n per band
         const uint32_t rank = (uint32_t)((3 * n * kCoverNum + kCoverDen - 1) / kCoverDen);
-        GSBC_LAUNCH("cov_init", k_cov_init, dim3(1), dim3(64), 0, st, cov, rank);
-        const uint32_t ncw = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(want, 1), kCovWG);
+        const uint64_t steps = (n + kStepPrims - 1) / kStepPrims;
+        const uint32_t ncw = (uint32_t)std::min<uint64_t>((steps + kCovBlock / 64 - 1) / (kCovBlock / 64), kCovWG);
         for (int pass = 0; pass < 4; pass++) {
-            GSBC_LAUNCH("cov_hist", k_cov_hist, dim3(ncw), dim3(kRangeBlock), 0, st,
-                        reinterpret_cast<const float4 *>(sh), opacity, n, pass, cov, part);
-            GSBC_LAUNCH("cov_select", k_cov_select, dim3(16), dim3(256), 0, st, part, ncw, pass, cov);
+            auto hist = pass == 0 ? k_cov_hist<0> : pass == 1 ? k_cov_hist<1> : pass == 2 ? k_cov_hist<2> : k_cov_hist<3>;
+            GSBC_LAUNCH("cov_hist", hist, dim3(ncw), dim3(kCovBlock), 0, st, reinterpret_cast<const float4 *>(sh),
+                        opacity, n, cov, part);
+            GSBC_LAUNCH("cov_select", k_cov_select, dim3(16), dim3(kCovBlock), 0, st, part, ncw, pass, rank, cov);
         }
     }
     if (quantiser == 1 || !keys_finish)
