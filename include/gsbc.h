@@ -400,9 +400,14 @@ GSBC_API gsbc_status gsbc_decode_eval_view(gsbc_ctx *ctx, const uint8_t *blocks,
  *     a += g_i ctilde_i T,   then T *= 1 - mu_i g_i,   T starting at 1,
  * with ctilde_i = Htilde_i w(f - p_i) the primitive's colour decoded from the
  * bitstreams and evaluated towards the view position (as
- * gsbc_decode_eval_view, never written to memory) and
+ * gsbc_decode_eval_view) and
  * g_i = exp(-(a dx^2 + 2 b dx dy + c dy^2)/2) its footprint at the pixel.
- * FP32 throughout; no early termination.
+ * FP32 throughout; no early termination.  Lists of more than one entry per
+ * three slots have all slots' colours computed first, into the scratch arena
+ * (12 bytes a slot; gsbc_reserve's size holds them); where the arena does not
+ * hold them and cannot grow (a failed allocation, a stream being captured)
+ * and for shorter lists each entry is decoded in the blend, with no colour
+ * in memory.  Both give the same bits.
  *   blocks, desc     as gsbc_decode_eval (a coded scene)
  *   pos, perm        as gsbc_decode_eval_view
  *   view             host float[3], the view position f
@@ -424,8 +429,7 @@ GSBC_API gsbc_status gsbc_blend_tiles(gsbc_ctx *ctx, const uint8_t *blocks, cons
                                       float *transmittance);
 
 /* The same colour stage with each primitive's colour computed beforehand,
- * once per primitive, instead of decoded from the bitstreams for every list
- * entry (a primitive sits in several tiles' lists): the two-pass form of
+ * by the caller, e.g. for several images of one view: the two-pass form of
  * Sec. II eq. preblend.  With colours from gsbc_decode_eval_view over all
  * slots (prim_idx NULL) for the same blocks, desc, pos, perm and view, the
  * image and transmittance equal gsbc_blend_tiles' bit for bit.

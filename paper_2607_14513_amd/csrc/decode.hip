@@ -560,18 +560,17 @@ __device__ __forceinline__ void colour_sum(const BandArgs &b, const uint32_t (&p
 template <class Lut>
 __device__ __forceinline__ void view_colour(const uint8_t *blocks, const BandArgs &b, uint32_t s, const float *pos,
                                             const uint32_t *perm, float fx, float fy, float fz, float c[3],
-                                            const Lut &lut)
+                                            const Lut &lut, bool batched = false)
 {
     float Y[16];
     view_basis(s, pos, perm, fx, fy, fz, Y);
     uint32_t px[16];
-    slot_texels(blocks, b, s, px, lut);
+    if (batched) slot_texels_batched(blocks, b, s, px, lut);
+    else slot_texels(blocks, b, s, px, lut);
     colour_sum(b, px, Y, c);
 }
 
-// One lane per listed slot; out-of-range slot ids give NaN.  The BC7
-// tables are read from the workgroup's LDS copy (the colour stage keeps
-// them in constant memory: there the LDS copy measured slower).
+// One lane per listed slot; out-of-range slot ids give NaN.
 __global__ __launch_bounds__(256) void k_decode_eval_view(const uint8_t *blocks, BandArgs b, const uint32_t *prim_idx,
                                                           uint64_t m, uint64_t n_prims, const float *pos,
                                                           const uint32_t *perm, float fx, float fy, float fz,
@@ -633,15 +632,21 @@ __global__ __launch_bounds__(1024) void k_tile_order(const uint32_t *tile_start,
 // Colour stage of a tile rasteriser (Sec. II, eq. preblend with the
 // premultiplied coefficients of eq. premult), one workgroup per 16x16 tile,
 // one lane per pixel.  The tile's list is taken 256 entries at a time: lane t
-// decodes entry t's colour c~ = Htilde w(f - p) from the bitstreams (no
-// colour buffer in HBM) and stages it in LDS with the primitive's footprint
-// and opacity mu, the conic turned into base-2 exponent coefficients
-// (A, B, C) = -log2(e) (a/2, b, c/2); then every pixel walks the staged
-// entries front to back: g = 2^(A dx^2 + B dx dy + C dy^2) at its centre,
-// a += (g T) c~, T -= (T mu) g.  A list entry past n_prims gives NaN colour.
-// Once every pixel of a wave (or of the tile) has T exactly 0, the remaining
-// entries change nothing (g T = 0 and T stays 0 for finite colours) and are
-// skipped.
+// stages entry t in LDS with its colour c~ = Htilde w(f - p) (read where it
+// was computed beforehand, else decoded here from the bitstreams), the
+// primitive's footprint and opacity mu, the conic turned into base-2 exponent
+// coefficients (A, B, C) = -log2(e) (a/2, b, c/2); then every pixel walks the
+// staged entries front to back: g = 2^(A dx^2 + B dx dy + C dy^2) at its
+// centre, w = g T, a += w c~, T -= mu w.  A list entry past n_prims gives NaN
+// colour.  Once every pixel of a wave (or of the tile) has T exactly 0, the
+// remaining entries change nothing (w = 0 and T stays 0 for finite colours)
+// and are skipped.
+// Bound by the issue of the walk's instructions.  Apart from the decode's
+// registers and with T mu not formed by itself, colours and blend of a
+// 1920 x 1088 frame (16.5 M entries) 1,293 -> 1,270 us.  Two and four pixels
+// per lane, which share dx and the LDS reads, took 1,326 and 1,545: a tile's
+// waves are then fewer and its walk longer.
+template <bool COLOURS>
 __global__ __launch_bounds__(256) void k_blend_tiles(const uint8_t *blocks, BandArgs b, uint64_t n_prims,
                                                      const float *pos, const uint32_t *perm, float fx, float fy,
                                                      float fz, const float *mu, const float *foot,
@@ -653,7 +658,12 @@ __global__ __launch_bounds__(256) void k_blend_tiles(const uint8_t *blocks, Band
     // (rows of 12 floats: three 16-byte LDS reads per entry, all lanes
     // reading the same row)
     __shared__ __align__(16) float s_par[256][12];
+    __shared__ __align__(8) Bc7Part s_rows[COLOURS ? 1 : kBc7PartRows];
     const uint32_t t = threadIdx.x, tile = order[blockIdx.x];
+    if constexpr (!COLOURS) {
+        stage_parts(s_rows);
+        __syncthreads();
+    }
     const uint32_t tx = tile % tiles_x, ty = tile / tiles_x;
     const float x = (float)(16 * tx + (t & 15u)) + 0.5f, y = (float)(16 * ty + (t >> 4)) + 0.5f;
     const uint64_t b1 = min((uint64_t)tile_start[tile + 1], list_len);
@@ -667,12 +677,12 @@ __global__ __launch_bounds__(256) void k_blend_tiles(const uint8_t *blocks, Band
             float c[3] = {__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
             uint64_t i = 0;
             if (s < n_prims) {
-                if (colours) {   // the colour computed beforehand, once per primitive
+                if constexpr (COLOURS) {   // the colour computed beforehand, once per primitive
                     c[0] = colours[3 * (uint64_t)s];
                     c[1] = colours[3 * (uint64_t)s + 1];
                     c[2] = colours[3 * (uint64_t)s + 2];
                 } else {
-                    view_colour(blocks, b, s, pos, perm, fx, fy, fz, c, Bc7ConstLut{});
+                    view_colour(blocks, b, s, pos, perm, fx, fy, fz, c, Bc7LdsLut{s_rows}, true);
                 }
                 i = perm[s];
             }
@@ -696,15 +706,15 @@ __global__ __launch_bounds__(256) void k_blend_tiles(const uint8_t *blocks, Band
             for (uint32_t j = j0; j < j1; j++) {
                 const float4 pa = *reinterpret_cast<const float4 *>(&s_par[j][0]);
                 const float4 pb = *reinterpret_cast<const float4 *>(&s_par[j][4]);
-                const float4 pc = *reinterpret_cast<const float4 *>(&s_par[j][8]);
+                const float blue = s_par[j][8];
                 const float dx = x - pa.x, dy = y - pa.y;
                 const float ex = fmaf(dx, fmaf(pa.z, dx, pa.w * dy), pb.x * dy * dy);
                 const float g = __builtin_amdgcn_exp2f(ex);
-                const float w = g * T, m = T * pb.y;
+                const float w = g * T;
                 a0 = fmaf(w, pb.z, a0);
                 a1 = fmaf(w, pb.w, a1);
-                a2 = fmaf(w, pc.x, a2);
-                T = fmaf(-m, g, T);
+                a2 = fmaf(w, blue, a2);
+                T = fmaf(-pb.y, w, T);
             }
         }
         if (__syncthreads_and(T == 0.0f)) break;   // every pixel of the tile is covered
@@ -728,8 +738,9 @@ hipError_t launch_blend_tiles(const uint8_t *blocks, const BandArgs &b, uint64_t
     const uint64_t tiles = (uint64_t)tiles_x * tiles_y;
     if (tiles == 0) return hipSuccess;
     GSBC_LAUNCH("tile_order", k_tile_order, dim3(1), dim3(1024), 0, st, tile_start, list_len, (uint32_t)tiles, order);
-    GSBC_LAUNCH("blend_tiles", k_blend_tiles, dim3((uint32_t)tiles), dim3(256), 0, st, blocks, b, n_prims, pos, perm,
-                view[0], view[1], view[2], mu, foot, tile_start, list, list_len, order, tiles_x, colours, image, trans);
+    GSBC_LAUNCH("blend_tiles", colours ? k_blend_tiles<true> : k_blend_tiles<false>, dim3((uint32_t)tiles), dim3(256), 0,
+                st, blocks, b, n_prims, pos, perm, view[0], view[1], view[2], mu, foot, tile_start, list, list_len, order,
+                tiles_x, colours, image, trans);
     return hipGetLastError();
 }
 
