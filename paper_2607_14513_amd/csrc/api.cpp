@@ -718,36 +718,40 @@ gsbc_status gsbc_encode(gsbc_ctx *ctx, const uint8_t *textures, gsbc_stream_desc
     a.keys = reinterpret_cast<uint32_t *>(arena + front + 2 * kRunTableBytes);
     const WorkSplit w3[3] = {kPlainSplit, kPlainSplit, kPlainSplit};
     // With both formats the BC1 encoder runs on a side stream beside the BC7
-    // kernels, from the start: each kernel's last, nearly empty wave of
-    // workgroups is then filled by the other format's work.  Joined before
-    // anything reads either format's results.  While kernel timing is on,
-    // everything stays on the context's stream, one kernel after another, so
-    // each timed kernel has the GPU to itself.
+    // kernels: the waves that those leave idle as each of them ends are then
+    // filled with the other format's work.  It starts when the (first chunk's)
+    // bounds are done, not with them: they fill the chip by themselves, and
+    // the BC7 kernels after them are the longer chain (both formats of
+    // 4,101 / 65,536 / 200,003 / 1,048,576 primitives: 290 / 555 / 1,550 /
+    // 6,178 us from the start, 257 / 518 / 1,468 / 6,181 after the bounds, 259
+    // / 538 / 1,405 / 6,225 after the seeds, 305 / 571 / 1,572 / 6,225 after
+    // the search).  Joined before anything reads either format's results.
+    // While kernel timing is on, everything stays on the context's stream, one
+    // kernel after another, so each timed kernel has the GPU to itself.
     hipStream_t s1 = ctx->stream;
     if (have1 && have7 && !ctx->profiling) {
         if ((s = ensure_side(ctx))) return s;
         s1 = ctx->side;
-        HIP_TRY(ctx, hipEventRecord(ctx->fork, ctx->stream), "fork");
-        HIP_TRY(ctx, hipStreamWaitEvent(s1, ctx->fork, 0), "fork");
     }
     hipError_t e1 = hipSuccess, e7 = hipSuccess;
     unsigned long long *hist = reinterpret_cast<unsigned long long *>(arena + hist_off);
-    if (format == GSBC_FMT_AUTO_ZERO) {   // the code histograms need the textures only
+    if (have7) {
+        a.run = druns7;
+        a.nrun = (uint32_t)r7.v.size();
+        a.total = r7.total;
+        e7 = launch_bc7_encode(a, w3, kPlainBc7Split, ctx->stream, s1 != ctx->stream ? ctx->fork : nullptr);
+        if (e7 == hipSuccess && s1 != ctx->stream) e1 = hipStreamWaitEvent(s1, ctx->fork, 0);
+    }
+    if (format == GSBC_FMT_AUTO_ZERO && e7 == hipSuccess && e1 == hipSuccess) {   // the histograms need the textures only
         e1 = launch_fill_u64(hist, 16 * 256, 0, s1);
         if (e1 == hipSuccess) e1 = launch_band_hist(textures, S, nblk, hist, s1);
     }
-    if (have1 && e1 == hipSuccess) {
+    if (have1 && e7 == hipSuccess && e1 == hipSuccess) {
         EncodeArgs a1 = a;
         a1.run = druns1;
         a1.nrun = (uint32_t)r1.v.size();
         a1.total = r1.total;
         e1 = launch_bc1_encode(a1, kPlainSplit, kPlainBc1Lanes, s1);
-    }
-    if (have7 && e1 == hipSuccess) {
-        a.run = druns7;
-        a.nrun = (uint32_t)r7.v.size();
-        a.total = r7.total;
-        e7 = launch_bc7_encode(a, w3, kPlainBc7Split, ctx->stream);
     }
     if (s1 != ctx->stream) {   // also after a failed launch: the side stream's work reads this call's buffers
         HIP_TRY(ctx, hipEventRecord(ctx->join, s1), "join");

@@ -1809,7 +1809,8 @@ hipError_t upload_bc7_tables(int device, hipStream_t st)
     return hipSuccess;
 }
 
-hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t split, hipStream_t st)
+hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t split, hipStream_t st,
+                             hipEvent_t bounded)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -1869,6 +1870,7 @@ hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t 
         Q.slices = (uint32_t)(left / 64);
         const uint32_t per = left >= (1u << 17) ? kWG : 64;
         GSBC_LAUNCH("bc7_bounds", k_bc7_bounds, dim3((uint32_t)(left / per)), dim3(kWG), 0, st, Q, per);
+        if (bounded && first == 0 && (e = hipEventRecord(bounded, st)) != hipSuccess) return e;
         const bool pairs = left < (1u << 17);
         GSBC_LAUNCH("bc7_seed", k_bc7_seed, dim3((uint32_t)(left / (pairs ? kWG / 2 : kWG))), dim3(kWG), 0, st, Q, pairs);
         if (split == 0) {
