@@ -253,6 +253,8 @@ class Context:
     may still write it goes to its own later calls only, not to another
     context's."""
 
+    _own, _pool = None, None   # that stream's handle, and the stream as torch sees it
+
     def __init__(self, device=0, stream=None):
         lib = load()
         if not torch.cuda.is_available():
@@ -262,7 +264,6 @@ class Context:
             stream = torch.cuda.current_stream(self.device)
         self.stream = stream
         h = ctypes.c_void_p()
-        self._own, self._pool = None, None
         if not stream.cuda_stream and 0 <= int(device) < torch.cuda.device_count():
             self._own = _take_stream(int(device))
             self._pool = torch.cuda.ExternalStream(self._own, device=self.device)
