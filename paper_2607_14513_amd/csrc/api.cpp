@@ -572,30 +572,23 @@ gsbc_status gsbc_reorder_degrees(gsbc_ctx *ctx, const float *pos, const float *s
     ctx->reordered = false;   // the range record is this call's now
     HIP_TRY(ctx, launch_degree_sort(pos, sh, opacity, n, p.grid_bits, p.quantiser, tau, perm, ctx->arena, range, cls,
                                     ctx->stream), "degree sort launch");
+    // the pack finds the classes' places from the device's counts, and its
+    // first workgroup hands the range and the counts over: one wait a call
     char *stage = static_cast<char *>(ctx->pinned);
-    HIP_TRY(ctx, hipMemcpyAsync(stage, range, sizeof(RangeRec), hipMemcpyDeviceToHost, ctx->stream), "range read-back");
-    HIP_TRY(ctx, hipMemcpyAsync(stage + 512, cls, 4 * sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream),
-            "class counts");
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream), "degree sort");
+    HIP_TRY(ctx, launch_pack_degrees(sh, opacity, perm, n, cls, setup_c, range, textures, reinterpret_cast<RangeRec *>(stage),
+                                     reinterpret_cast<uint32_t *>(stage + kClassOff), ctx->stream), "degree pack launch");
+    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream), "degree pack");
     RangeRec r;
     memcpy(&r, stage, sizeof r);
     uint32_t c32[4];
-    memcpy(c32, stage + 512, sizeof c32);
-    DegreeLayout lay;
-    lay.slot_start[0] = lay.pad_start[0] = 0;
+    memcpy(c32, stage + kClassOff, sizeof c32);
+    if ((uint64_t)c32[0] + c32[1] + c32[2] + c32[3] != n) return fail(ctx, GSBC_E_DEVICE, "class counts do not add up to n");
     uint64_t word = 0;
     for (int L = 0; L < 4; L++) {
         counts[L] = c32[L];
-        lay.slot_start[L + 1] = lay.slot_start[L] + c32[L];
-        lay.pad_start[L + 1] = lay.pad_start[L] + pad16(c32[L]);
-        lay.tex_word[L] = word;
         tex_offset[L] = word * 4;
         word += (uint64_t)(L + 1) * (L + 1) * pad16(c32[L]);    // (L+1)^2 streams of pad16/16 blocks x 16 words
     }
-    if (lay.slot_start[4] != n) return fail(ctx, GSBC_E_DEVICE, "class counts do not add up to n");
-    lay.quad1 = setup_c ? 1u : 0u;
-    HIP_TRY(ctx, launch_pack_degrees(sh, opacity, perm, lay, range, textures, ctx->stream), "degree pack launch");
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream), "degree pack");
     for (int L = 0; L < 4; L++) {
         gsbc_stream_desc &d = descs[L];
         memset(&d, 0, sizeof d);

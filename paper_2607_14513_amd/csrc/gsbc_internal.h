@@ -104,15 +104,18 @@ struct DegreeLayout {
     uint64_t slot_start[5];
     uint64_t pad_start[5];
     uint64_t tex_word[4];
-    uint32_t quad1;   // 1: the degree-1 class in Fig. SetupC (one stream, four primitives per block)
 };
 // Range, keys with the degree class above the cell and colour fields, class
 // counts (device uint32[4]) and the sort into perm.
 hipError_t launch_degree_sort(const float *pos, const float *sh, const float *opacity, uint64_t n, uint32_t grid_bits,
                               uint32_t quantiser, float tau, uint32_t *perm, void *scratch, RangeRec *range_dev,
                               uint32_t *class_count, hipStream_t st);
-hipError_t launch_pack_degrees(const float *sh, const float *opacity, const uint32_t *perm, const DegreeLayout &lay,
-                               const RangeRec *range_dev, uint8_t *textures, hipStream_t st);
+// quad1: the degree-1 class in Fig. SetupC (one stream, four primitives per
+// block).  host_range, host_count: pinned memory for the range record and the
+// counts.
+hipError_t launch_pack_degrees(const float *sh, const float *opacity, const uint32_t *perm, uint64_t n,
+                               const uint32_t *class_count, bool quad1, const RangeRec *range_dev, uint8_t *textures,
+                               RangeRec *host_range, uint32_t *host_count, hipStream_t st);
 
 // ---- encoders (bc1_encode.hip, bc7_encode.hip)
 // The encoders work on runs: a run is the consecutive blocks of one band of

@@ -119,15 +119,17 @@ template <bool DEG>
 __global__ __launch_bounds__(kMinMaxBlock) void k_range_partial(const float4 *sh4, const float *opacity,
                                                                 const float *pos, uint64_t n, uint32_t *acc,
                                                                 float *dc, uint32_t *meta, uint32_t meta_words,
-                                                                float tau, uint8_t *deg, bool stream)
+                                                                float tau, uint8_t *deg, uint32_t *class_count, bool stream)
 {
     __shared__ uint32_t s_acc[kAccWords];
     __shared__ float stage[kMinMaxBlock / 64][kStepPrims * 3];
     __shared__ uint8_t s_deg[DEG ? kMinMaxBlock / 64 : 1][kStepChunks];   // degree masks of the step's chunks
     const uint32_t tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     if (tid < kAccWords) s_acc[tid] = acc_is_min((int)tid) ? 0xFFFFFFFFu : 0u;
-    if (blockIdx.x == 0)   // the sort's digit totals, for the key pass that follows
+    if (blockIdx.x == 0) {   // the sort's digit totals and the class counts, for the key pass that follows
         for (uint32_t e = tid; e < meta_words; e += kMinMaxBlock) meta[e] = 0u;
+        if (DEG && tid < 4) class_count[tid] = 0u;
+    }
     __syncthreads();
     const uint64_t waves = (uint64_t)gridDim.x * (kMinMaxBlock / 64), wg = (uint64_t)blockIdx.x * (kMinMaxBlock / 64) + wv;
     float mn[3][4], mx[3][4];
@@ -266,9 +268,7 @@ __global__ __launch_bounds__(kMinMaxBlock) void k_range_partial(const float4 *sh
 __device__ __forceinline__ float canon_zero(float x) { return x == 0.0f ? 0.0f : x; }
 
 // The range record's fields from the extremes acc: lane k < 16 band k,
-// lane k < 3 also axis k.  cov: null for the min/max range, else the
-// coverage state (prefix[16] = bit pattern of t per band after the last
-// selection pass) for [-t, t].
+// lane k < 3 also axis k.
 __device__ __forceinline__ void band_range(const uint32_t *acc, int k, float &lo, float &hi, float &scale)
 {
     lo = canon_zero(float_of(acc[k]));
@@ -284,29 +284,25 @@ __device__ __forceinline__ void axis_range(const uint32_t *acc, int a, uint32_t 
     const float ext = hi - lo;
     cell_scale = ext > 0.0f ? (float)(1u << grid_bits) / ext : 0.0f;
 }
-__device__ void finish_range(const uint32_t *acc, const uint32_t *cov, uint32_t grid_bits, RangeRec *r, int k)
+__device__ __forceinline__ void finish_axis(const uint32_t *acc, uint32_t grid_bits, RangeRec *r, int a)
+{
+    axis_range(acc, a, grid_bits, r->lo[a], r->hi[a], r->cell_scale[a]);
+}
+__device__ void finish_range(const uint32_t *acc, uint32_t grid_bits, RangeRec *r, int k)
 {
     if (k < 16) {
         float lo, hi, scale;
         band_range(acc, k, lo, hi, scale);
-        if (cov) {
-            const float t = __uint_as_float(cov[k]);
-            lo = canon_zero(-t);
-            hi = t;
-            const float range = hi - lo;
-            scale = range > 0.0f ? 255.0f / range : 0.0f;
-        }
         r->vmin[k] = lo;
         r->vmax[k] = hi;
         r->scale[k] = scale;
     }
-    if (k < 3) axis_range(acc, k, grid_bits, r->lo[k], r->hi[k], r->cell_scale[k]);
+    if (k < 3) finish_axis(acc, grid_bits, r, k);
 }
 
-// The range record from r->acc (and cov), then r->acc back to neutral; for
-// calls whose key pass does not finish the range itself (an identity order,
-// or the coverage range).
-__global__ __launch_bounds__(64) void k_range_final(const uint32_t *cov, uint32_t grid_bits, RangeRec *r)
+// The range record from r->acc, then r->acc back to neutral; for calls with
+// no key pass to finish the range (an identity order).
+__global__ __launch_bounds__(64) void k_range_final(uint32_t grid_bits, RangeRec *r)
 {
     __shared__ uint32_t acc[kAccWords];
     const int k = threadIdx.x;
@@ -315,7 +311,7 @@ __global__ __launch_bounds__(64) void k_range_final(const uint32_t *cov, uint32_
         r->acc[k] = acc_is_min(k) ? 0xFFFFFFFFu : 0u;
     }
     __syncthreads();
-    finish_range(acc, cov, grid_bits, r, k);
+    finish_range(acc, grid_bits, r, k);
 }
 
 // Keys, 4,096 per workgroup: (Morton cell << 24) | colour interleave, and
@@ -348,7 +344,7 @@ __global__ __launch_bounds__(kKeysThreads) void k_keys(const float *pos, const f
         band_range(r->acc, 0, vmin0, hi, scale0);
 #pragma unroll
         for (int a = 0; a < 3; a++) axis_range(r->acc, a, grid_bits, lo[a], hi, cell_scale[a]);
-        if (blockIdx.x == 0 && threadIdx.x < 16) finish_range(r->acc, nullptr, grid_bits, r, (int)threadIdx.x);
+        if (blockIdx.x == 0 && threadIdx.x < 16) finish_range(r->acc, grid_bits, r, (int)threadIdx.x);
     } else {
         vmin0 = r->vmin[0];
         scale0 = r->scale[0];
@@ -776,9 +772,11 @@ __global__ __launch_bounds__(kCovBlock) void k_cov_hist(const float4 *sh4, const
 // (a quarter of the workgroups' each, eight loads in flight: one thread a
 // digit took 74 us over 256 of them, this 6), scan, and keep the digit
 // whose cumulative count reaches the rank (rank0 in the first pass, whose
-// prefix is empty).
+// prefix is empty).  The last pass has the magnitude t: it writes the band's
+// range [-t, t], workgroups 0..2 also an axis each, and puts their extremes
+// back to neutral.
 __global__ __launch_bounds__(kCovBlock) void k_cov_select(const uint32_t *part, uint32_t nwg, int pass, uint32_t rank0,
-                                                          uint32_t *state)
+                                                          uint32_t *state, uint32_t grid_bits, RangeRec *r)
 {
     __shared__ uint32_t sum[4][256], scan[256];
     const uint32_t band = blockIdx.x, d = threadIdx.x & 255u, g = threadIdx.x >> 8;
@@ -800,68 +798,105 @@ __global__ __launch_bounds__(kCovBlock) void k_cov_select(const uint32_t *part, 
     const uint32_t incl = scan[d], excl = incl - c;
     __syncthreads();   // every thread has read the state
     if (g == 0 && c > 0 && excl < rank && rank <= incl) {
-        state[band] = (prefix << kCovWidth[pass]) | d;
+        const uint32_t found = (prefix << kCovWidth[pass]) | d;
+        state[band] = found;
         state[16 + band] = rank - excl;
+        if (pass == 3) {
+            const float hi = __uint_as_float(found), lo = canon_zero(-hi), range = hi - lo;
+            r->vmin[band] = lo;
+            r->vmax[band] = hi;
+            r->scale[band] = range > 0.0f ? 255.0f / range : 0.0f;
+        }
+    }
+    if (pass == 3 && threadIdx.x == 0) {
+        if (band < 3) finish_axis(r->acc, grid_bits, r, (int)band);
+        for (uint32_t e = band; e < (uint32_t)kAccWords; e += 16)
+            if (e < 32) r->acc[e] = acc_is_min((int)e) ? 0xFFFFFFFFu : 0u;
+        if (band < 3) {
+            r->acc[32 + band] = 0xFFFFFFFFu;
+            r->acc[35 + band] = 0u;
+        }
     }
 }
 
-__global__ void k_zero4(uint32_t *c)
+// The classes' places, from their counts (device memory: the pack follows the
+// sort without the host in between).
+__device__ __forceinline__ DegreeLayout degree_layout(const uint32_t *count)
 {
-    if (threadIdx.x < 4) c[threadIdx.x] = 0;
+    DegreeLayout lay;
+    lay.slot_start[0] = lay.pad_start[0] = 0;
+    uint64_t word = 0;
+#pragma unroll
+    for (int L = 0; L < 4; L++) {
+        const uint64_t c = count[L], pad = (c + 15) / 16 * 16;
+        lay.slot_start[L + 1] = lay.slot_start[L] + c;
+        lay.pad_start[L + 1] = lay.pad_start[L] + pad;
+        lay.tex_word[L] = word;
+        word += (uint64_t)(L + 1) * (L + 1) * pad;   // (L+1)^2 streams of pad/16 blocks x 16 words
+    }
+    return lay;
 }
 
-// One thread per padded slot of every class: thread t of class L (t in
-// [pad_start[L], pad_start[L+1])) is class slot j = t - pad_start[L], the
-// dense slot slot_start[L] + min(j, count[L] - 1); its (L+1)^2 kept bands go
-// to stream k of the class, block j/16, zigzag texel of j%16 -- or, for the
-// degree-1 class in Fig. SetupC, bands 0..3 to texels 4 (j%4) + k of block
-// j/4 of the class's one stream.
-__global__ __launch_bounds__(256) void k_pack_degrees(const float *sh, const float *opacity, const uint32_t *perm,
-                                                      DegreeLayout lay, const RangeRec *r, uint32_t *tex)
+// Class slot j of class L, its (L+1)^2 bands: only the chunks of the row that
+// hold them are read.
+template <int L>
+__device__ __forceinline__ void pack_class(const float *sh, const float *opacity, uint32_t src, uint64_t j, uint64_t pad,
+                                           bool quad, const RangeRec *r, uint32_t *tex)
 {
-    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= lay.pad_start[4]) return;
-    int L = 0;
-    while (L < 3 && t >= lay.pad_start[L + 1]) L++;
-    const uint64_t j = t - lay.pad_start[L];
-    const uint64_t cnt = lay.slot_start[L + 1] - lay.slot_start[L];
-    const uint32_t src = perm[lay.slot_start[L] + (j < cnt ? j : cnt - 1)];
+    constexpr int nb = (L + 1) * (L + 1), chunks = (3 * nb + 3) / 4;
     const float4 *p = reinterpret_cast<const float4 *>(sh + (uint64_t)src * 48);
-    float f[48];
+    float f[4 * chunks];
 #pragma unroll
-    for (int c = 0; c < 12; c++) {
+    for (int c = 0; c < chunks; c++) {
         const float4 v = p[c];
         f[4 * c] = v.x; f[4 * c + 1] = v.y; f[4 * c + 2] = v.z; f[4 * c + 3] = v.w;
     }
     if (opacity) {
         const float mu = opacity[src];
 #pragma unroll
-        for (int e = 0; e < 48; e++) f[e] = mu * f[e];
+        for (int e = 0; e < 3 * nb; e++) f[e] = mu * f[e];
     }
-    const int nb = (L + 1) * (L + 1);
-    if (L == 1 && lay.quad1) {
-        uint32_t *blk = tex + lay.tex_word[1] + (j >> 2) * 16 + 4 * (j & 3);
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const float vm = r->vmin[k], sc = r->scale[k];
-            blk[k] = quant8(f[3 * k], vm, sc) | (quant8(f[3 * k + 1], vm, sc) << 8) |
-                     (quant8(f[3 * k + 2], vm, sc) << 16) | 0xFF000000u;
-        }
-        return;
-    }
-    const uint64_t nblk = (lay.pad_start[L + 1] - lay.pad_start[L]) / 16;
     const uint32_t jj = (uint32_t)(j & 15);
     const uint32_t x = (jj & 1u) | (((jj >> 2) & 1u) << 1);
     const uint32_t y = ((jj >> 1) & 1u) | (((jj >> 3) & 1u) << 1);
-    uint32_t *base = tex + lay.tex_word[L] + (j >> 4) * 16 + 4 * y + x;
+    uint32_t *base = L == 1 && quad ? tex + (j >> 2) * 16 + 4 * (j & 3) : tex + (j >> 4) * 16 + 4 * y + x;
+    const uint64_t step = L == 1 && quad ? 1 : pad;
 #pragma unroll
-    for (int k = 0; k < 16; k++) {
-        if (k < nb) {
-            const float vm = r->vmin[k], sc = r->scale[k];
-            base[(uint64_t)k * nblk * 16] = quant8(f[3 * k], vm, sc) | (quant8(f[3 * k + 1], vm, sc) << 8) |
-                                            (quant8(f[3 * k + 2], vm, sc) << 16) | 0xFF000000u;
-        }
+    for (int k = 0; k < nb; k++) {
+        const float vm = r->vmin[k], sc = r->scale[k];
+        base[(uint64_t)k * step] = quant8(f[3 * k], vm, sc) | (quant8(f[3 * k + 1], vm, sc) << 8) |
+                                   (quant8(f[3 * k + 2], vm, sc) << 16) | 0xFF000000u;
     }
+}
+
+// One thread per padded slot of every class: thread t of class L (t in
+// [pad_start[L], pad_start[L+1])) is class slot j = t - pad_start[L], the
+// dense slot slot_start[L] + min(j, count[L] - 1); its (L+1)^2 kept bands go
+// to stream k of the class, block j/16, zigzag texel of j%16 -- or, for the
+// degree-1 class in Fig. SetupC (quad1), bands 0..3 to texels 4 (j%4) + k of
+// block j/4 of the class's one stream.  Workgroup 0 also copies the range
+// record and the counts to the host.  Bound by the gathered rows: reading the
+// class's chunks only, 500,009 primitives (35/20/15/30 % of degree 0..3)
+// take 20 us, all twelve of every row 28.
+__global__ __launch_bounds__(256) void k_pack_degrees(const float *sh, const float *opacity, const uint32_t *perm,
+                                                      uint64_t n, const uint32_t *count, bool quad1, const RangeRec *r,
+                                                      uint32_t *tex, RangeRec *host_range, uint32_t *host_count)
+{
+    if (blockIdx.x == 0 && threadIdx.x < sizeof(RangeRec) / 4)
+        reinterpret_cast<uint32_t *>(host_range)[threadIdx.x] = reinterpret_cast<const uint32_t *>(r)[threadIdx.x];
+    if (blockIdx.x == 0 && threadIdx.x < 4) host_count[threadIdx.x] = count[threadIdx.x];
+    const DegreeLayout lay = degree_layout(count);
+    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= lay.pad_start[4] || lay.slot_start[4] != n) return;
+    const int L = (t >= lay.pad_start[1]) + (t >= lay.pad_start[2]) + (t >= lay.pad_start[3]);
+    auto start = [&](const uint64_t (&a)[5], int l) { return l == 0 ? a[0] : l == 1 ? a[1] : l == 2 ? a[2] : l == 3 ? a[3] : a[4]; };
+    const uint64_t j = t - start(lay.pad_start, L), first = start(lay.slot_start, L), cnt = start(lay.slot_start, L + 1) - first;
+    const uint64_t pad = (cnt + 15) / 16 * 16;
+    const uint32_t src = perm[first + (j < cnt ? j : cnt - 1)];
+    if (L == 0) pack_class<0>(sh, opacity, src, j, pad, false, r, tex + lay.tex_word[0]);
+    else if (L == 1) pack_class<1>(sh, opacity, src, j, pad, quad1, r, tex + lay.tex_word[1]);
+    else if (L == 2) pack_class<2>(sh, opacity, src, j, pad, false, r, tex + lay.tex_word[2]);
+    else pack_class<3>(sh, opacity, src, j, pad, false, r, tex + lay.tex_word[3]);
 }
 
 struct Layout {
@@ -913,8 +948,8 @@ namespace {
 // deg_tau >= 0: also each primitive's degree class (threshold deg_tau) into
 // the arena's deg bytes, for the degree-class key pass.
 void enqueue_range(const float *pos, const float *sh, const float *opacity, uint64_t n, uint32_t grid_bits,
-                   uint32_t quantiser, bool keys_finish, float deg_tau, const Layout &L, char *s, RangeRec *range_dev,
-                   hipStream_t st)
+                   uint32_t quantiser, bool keys_finish, float deg_tau, uint32_t *class_count, const Layout &L, char *s,
+                   RangeRec *range_dev, hipStream_t st)
 {
     // at most 512 workgroups of 768 (two per CU, each one contiguous span)
     const uint32_t nb = (uint32_t)std::min<uint64_t>(std::max<uint64_t>((n * 12 + kMinMaxBlock - 1) / kMinMaxBlock, 1), 512);
@@ -923,15 +958,14 @@ void enqueue_range(const float *pos, const float *sh, const float *opacity, uint
         GSBC_LAUNCH("range_partial", k_range_partial<true>, dim3(nb), dim3(kMinMaxBlock), 0, st,
                     reinterpret_cast<const float4 *>(sh), opacity, pos, n, range_dev->acc,
                     reinterpret_cast<float *>(s + L.dc), reinterpret_cast<uint32_t *>(s + L.meta), kMetaWords, deg_tau,
-                    reinterpret_cast<uint8_t *>(s + L.deg), stream);
+                    reinterpret_cast<uint8_t *>(s + L.deg), class_count, stream);
     else
         GSBC_LAUNCH("range_partial", k_range_partial<false>, dim3(nb), dim3(kMinMaxBlock), 0, st,
                     reinterpret_cast<const float4 *>(sh), opacity, pos, n, range_dev->acc,
                     reinterpret_cast<float *>(s + L.dc), reinterpret_cast<uint32_t *>(s + L.meta), kMetaWords, 0.0f,
-                    nullptr, stream);
-    uint32_t *cov = nullptr;
+                    nullptr, nullptr, stream);
     if (quantiser == 1) {
-        cov = reinterpret_cast<uint32_t *>(s + L.cov_state);
+        uint32_t *cov = reinterpret_cast<uint32_t *>(s + L.cov_state);
         uint32_t *part = reinterpret_cast<uint32_t *>(s + L.cov_part);
         // 1-based rank of the covering magnitude among the 3n per band
         const uint32_t rank = (uint32_t)((3 * n * kCoverNum + kCoverDen - 1) / kCoverDen);
@@ -941,11 +975,12 @@ void enqueue_range(const float *pos, const float *sh, const float *opacity, uint
             auto hist = pass == 0 ? k_cov_hist<0> : pass == 1 ? k_cov_hist<1> : pass == 2 ? k_cov_hist<2> : k_cov_hist<3>;
             GSBC_LAUNCH("cov_hist", hist, dim3(ncw), dim3(kCovBlock), 0, st, reinterpret_cast<const float4 *>(sh),
                         opacity, n, cov, part);
-            GSBC_LAUNCH("cov_select", k_cov_select, dim3(16), dim3(kCovBlock), 0, st, part, ncw, pass, rank, cov);
+            GSBC_LAUNCH("cov_select", k_cov_select, dim3(16), dim3(kCovBlock), 0, st, part, ncw, pass, rank, cov,
+                        grid_bits, range_dev);
         }
     }
-    if (quantiser == 1 || !keys_finish)
-        GSBC_LAUNCH("range_final", k_range_final, dim3(1), dim3(64), 0, st, cov, grid_bits, range_dev);
+    if (quantiser != 1 && !keys_finish)
+        GSBC_LAUNCH("range_final", k_range_final, dim3(1), dim3(64), 0, st, grid_bits, range_dev);
 }
 
 // The keys in keys_a with their digit totals and the first pass's tile
@@ -1005,7 +1040,7 @@ hipError_t launch_reorder(const float *pos, const float *sh, const float *opacit
 {
     Layout L = layout(n);
     char *s = static_cast<char *>(scratch);
-    enqueue_range(pos, sh, opacity, n, grid_bits, quantiser, !identity, -1.0f, L, s, range_dev, st);
+    enqueue_range(pos, sh, opacity, n, grid_bits, quantiser, !identity, -1.0f, nullptr, L, s, range_dev, st);
     if (identity) {
         GSBC_LAUNCH("iota", k_iota, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, st, perm, n);
     } else {
@@ -1024,19 +1059,18 @@ hipError_t launch_degree_sort(const float *pos, const float *sh, const float *op
 {
     Layout L = layout(n);
     char *s = static_cast<char *>(scratch);
-    enqueue_range(pos, sh, opacity, n, grid_bits, quantiser, true, tau, L, s, range_dev, st);
-    GSBC_LAUNCH("fill_count", k_zero4, dim3(1), dim3(64), 0, st, class_count);
+    enqueue_range(pos, sh, opacity, n, grid_bits, quantiser, true, tau, class_count, L, s, range_dev, st);
     enqueue_keys_and_sort<true>(pos, n, grid_bits, quantiser != 1, L, s, range_dev, class_count, perm, st);
     return hipGetLastError();
 }
 
-hipError_t launch_pack_degrees(const float *sh, const float *opacity, const uint32_t *perm, const DegreeLayout &lay,
-                               const RangeRec *range_dev, uint8_t *textures, hipStream_t st)
+hipError_t launch_pack_degrees(const float *sh, const float *opacity, const uint32_t *perm, uint64_t n,
+                               const uint32_t *class_count, bool quad1, const RangeRec *range_dev, uint8_t *textures,
+                               RangeRec *host_range, uint32_t *host_count, hipStream_t st)
 {
-    const uint64_t threads = lay.pad_start[4];
-    if (threads == 0) return hipSuccess;
-    GSBC_LAUNCH("pack_degrees", k_pack_degrees, dim3((uint32_t)((threads + 255) / 256)), dim3(256), 0, st,
-                       sh, opacity, perm, lay, range_dev, reinterpret_cast<uint32_t *>(textures));
+    const uint64_t threads = n + 4 * 15;   // at least every class's padded slots
+    GSBC_LAUNCH("pack_degrees", k_pack_degrees, dim3((uint32_t)((threads + 255) / 256)), dim3(256), 0, st, sh, opacity,
+                perm, n, class_count, quad1, range_dev, reinterpret_cast<uint32_t *>(textures), host_range, host_count);
     return hipGetLastError();
 }
 
