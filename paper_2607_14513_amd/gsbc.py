@@ -188,6 +188,10 @@ def _dev_tensor(t, dtype, name, shape=None, min_numel=None):
     return t
 
 
+# stream counts that an arrangement can have
+_STREAM_COUNTS = {ARR_BANDS: (1, 4, 9, 16), ARR_PRIM: (1,), ARR_QUAD: (1, 4)}
+
+
 def _desc_numbers(desc):
     """(n_streams, blocks_per_stream, payload_bytes, n_prims) of a descriptor
     whose sizes agree with each other, else None: the library rejects such a
@@ -195,13 +199,10 @@ def _desc_numbers(desc):
     derived from it are not checked here."""
     if not isinstance(desc, StreamDesc):
         raise TypeError("desc must be a StreamDesc")
-    S, nblk, n, npad = int(desc.n_streams), int(desc.blocks_per_stream), int(desc.n_prims), int(desc.n_pad)
-    arr = int(desc.arrangement)
-    allowed = {ARR_BANDS: (1, 4, 9, 16), ARR_PRIM: (1,), ARR_QUAD: (1, 4)}.get(arr, ())
-    per_block = {ARR_BANDS: 16, ARR_PRIM: 1, ARR_QUAD: 4}.get(arr, 0)
-    if S not in allowed or n < 1 or npad != (n + 15) // 16 * 16 or nblk * N_STREAMS[arr] != npad or per_block == 0:
+    S, nblk, n, npad, arr = desc.n_streams, desc.blocks_per_stream, desc.n_prims, desc.n_pad, desc.arrangement
+    if S not in _STREAM_COUNTS.get(arr, ()) or n < 1 or npad != (n + 15) // 16 * 16 or nblk * N_STREAMS[arr] != npad:
         return None
-    return S, nblk, int(desc.payload_bytes), n
+    return S, nblk, desc.payload_bytes, n
 
 
 def _sizes(desc):
@@ -267,6 +268,7 @@ class Context:
         if not stream.cuda_stream and 0 <= int(device) < torch.cuda.device_count():
             self._own = _take_stream(int(device))
             self._pool = torch.cuda.ExternalStream(self._own, device=self.device)
+            self._pool_at = (self._pool.stream_id, self._pool.device_index, self._pool.device_type)
         st = lib.gsbc_create(ctypes.byref(h), int(device), ctypes.c_void_p(self._own or stream.cuda_stream))
         if st != OK:
             if self._own:
@@ -298,12 +300,13 @@ class Context:
         """A new output tensor, from the pool of the stream that writes it."""
         if self._pool is None:
             return torch.empty(shape, dtype=dtype, device=self.device)
-        if torch._C._cuda_getDevice() != self.device.index:
+        at = self._pool_at
+        if torch._C._cuda_getDevice() != at[1]:
             with torch.cuda.stream(self._pool):
                 return torch.empty(shape, dtype=dtype, device=self.device)
         # the same without the context manager's 6 us a call
-        now = torch._C._cuda_getCurrentStream(self.device.index)
-        torch._C._cuda_setStream(self._pool.stream_id, self._pool.device_index, self._pool.device_type)
+        now = torch._C._cuda_getCurrentStream(at[1])
+        torch._C._cuda_setStream(*at)
         try:
             return torch.empty(shape, dtype=dtype, device=self.device)
         finally:
