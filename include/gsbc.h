@@ -403,7 +403,7 @@ GSBC_API gsbc_status gsbc_decode_eval_view(gsbc_ctx *ctx, const uint8_t *blocks,
  * gsbc_decode_eval_view) and
  * g_i = exp(-(a dx^2 + 2 b dx dy + c dy^2)/2) its footprint at the pixel.
  * FP32 throughout; no early termination.  Lists of more than one entry per
- * three slots have all slots' colours computed first, into the scratch arena
+ * four slots have all slots' colours computed first, into the scratch arena
  * (12 bytes a slot; gsbc_reserve's size holds them); where the arena does not
  * hold them and cannot grow (a failed allocation, a stream being captured)
  * and for shorter lists each entry is decoded in the blend, with no colour

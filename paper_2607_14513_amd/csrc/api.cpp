@@ -1173,13 +1173,13 @@ gsbc_status gsbc_blend_tiles(gsbc_ctx *ctx, const uint8_t *blocks, const gsbc_st
     // Colours of all slots first, into scratch, or of each list entry in the
     // blend: a primitive sits in several tiles' lists, and slots in order
     // decode whole blocks.  At 5.3 entries a slot colours first take 530 us
-    // against 815 (786,432 slots; 220 against 360 at 49,152 and 1,221 against
-    // 2,251 at 3,145,728), at 0.35 88 against 99 (31 : 40, 203 : 259), at 0.2
-    // 69 against 63 (31 : 27, 163 : 183): the line is one entry in three slots.
+    // against 875 (786,432 slots; 219 at 49,152 and 1,225 at 3,145,728), at 0.35
+    // 88 (30, 205), where the entries alone take 100 (37, 211) at 0.3; at 0.2 69
+    // against 74 (31 : 26, 163 : 170): the line is one entry in four slots.
     // Without room for them (12 bytes a slot) the entries are decoded in the
     // blend; the image is the same bit for bit.
     const float *colours = nullptr;
-    if (list_len >= desc->n_prims / 3 + 1 && try_arena(ctx, order_bytes + desc->n_prims * 3 * sizeof(float))) {
+    if (list_len >= desc->n_prims / 4 + 1 && try_arena(ctx, order_bytes + desc->n_prims * 3 * sizeof(float))) {
         float *c = reinterpret_cast<float *>(static_cast<char *>(ctx->arena) + order_bytes);
         HIP_TRY(ctx, launch_decode_eval_view(blocks, band_args(desc), desc->n_prims, pos, perm, f, nullptr, desc->n_prims,
                                              c, ctx->stream), "decode_eval_view launch");

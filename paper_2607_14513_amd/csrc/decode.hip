@@ -560,13 +560,12 @@ __device__ __forceinline__ void colour_sum(const BandArgs &b, const uint32_t (&p
 template <class Lut>
 __device__ __forceinline__ void view_colour(const uint8_t *blocks, const BandArgs &b, uint32_t s, const float *pos,
                                             const uint32_t *perm, float fx, float fy, float fz, float c[3],
-                                            const Lut &lut, bool batched = false)
+                                            const Lut &lut)
 {
     float Y[16];
     view_basis(s, pos, perm, fx, fy, fz, Y);
     uint32_t px[16];
-    if (batched) slot_texels_batched(blocks, b, s, px, lut);
-    else slot_texels(blocks, b, s, px, lut);
+    slot_texels(blocks, b, s, px, lut);
     colour_sum(b, px, Y, c);
 }
 
@@ -645,7 +644,10 @@ __global__ __launch_bounds__(1024) void k_tile_order(const uint32_t *tile_start,
 // registers and with T mu not formed by itself, colours and blend of a
 // 1920 x 1088 frame (16.5 M entries) 1,293 -> 1,270 us.  Two and four pixels
 // per lane, which share dx and the LDS reads, took 1,326 and 1,545: a tile's
-// waves are then fewer and its walk longer.
+// waves are then fewer and its walk longer.  The decoding kernel takes short
+// lists only: blocks decoded as they arrive and the partition table in constant
+// memory start sooner than 16 loads ahead and a copy in LDS (lists of 0.02
+// entries a slot, 786,432 slots: 28 against 42 us).
 template <bool COLOURS>
 __global__ __launch_bounds__(256) void k_blend_tiles(const uint8_t *blocks, BandArgs b, uint64_t n_prims,
                                                      const float *pos, const uint32_t *perm, float fx, float fy,
@@ -658,12 +660,7 @@ __global__ __launch_bounds__(256) void k_blend_tiles(const uint8_t *blocks, Band
     // (rows of 12 floats: three 16-byte LDS reads per entry, all lanes
     // reading the same row)
     __shared__ __align__(16) float s_par[256][12];
-    __shared__ __align__(8) Bc7Part s_rows[COLOURS ? 1 : kBc7PartRows];
     const uint32_t t = threadIdx.x, tile = order[blockIdx.x];
-    if constexpr (!COLOURS) {
-        stage_parts(s_rows);
-        __syncthreads();
-    }
     const uint32_t tx = tile % tiles_x, ty = tile / tiles_x;
     const float x = (float)(16 * tx + (t & 15u)) + 0.5f, y = (float)(16 * ty + (t >> 4)) + 0.5f;
     const uint64_t b1 = min((uint64_t)tile_start[tile + 1], list_len);
@@ -682,7 +679,7 @@ __global__ __launch_bounds__(256) void k_blend_tiles(const uint8_t *blocks, Band
                     c[1] = colours[3 * (uint64_t)s + 1];
                     c[2] = colours[3 * (uint64_t)s + 2];
                 } else {
-                    view_colour(blocks, b, s, pos, perm, fx, fy, fz, c, Bc7LdsLut{s_rows}, true);
+                    view_colour(blocks, b, s, pos, perm, fx, fy, fz, c, Bc7ConstLut{});
                 }
                 i = perm[s];
             }

@@ -1,4 +1,4 @@
-"""GPU: the two routes of blend_tiles.  Lists of at least one entry per three
+"""GPU: the two routes of blend_tiles.  Lists of at least one entry per four
 slots have every slot's colour computed first, shorter ones are decoded entry
 by entry; a capture whose scratch has no room for the colours takes the second
 route too.  All give the same image and transmittance bit for bit."""
@@ -40,8 +40,8 @@ def test_short_and_padded_lists(n, arrangement):
     from paper_2607_14513_amd import gsbc
     with gsbc.Context(0) as ctx:
         blocks, d, pos, perm, mu, foot, ts, lst = _inputs(ctx, gsbc, n, 5, 4, 11, arrangement)
-        ts, lst = _shorter(ts, lst, n // 3)
-        assert len(lst) <= n // 3
+        ts, lst = _shorter(ts, lst, n // 4)
+        assert len(lst) <= n // 4
         args = (blocks, d, pos, perm, VIEW, mu, foot, dev(ts.astype(np.int32)))
         for bad in (False, True):
             if bad:
