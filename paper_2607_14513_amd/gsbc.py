@@ -169,7 +169,7 @@ def _check(t, dtype, name, shape=None, min_numel=None):
         raise TypeError(f"{name} must be a torch tensor")
     if t.dtype != dtype or not t.is_contiguous():
         raise TypeError(f"{name} must be a contiguous {dtype} tensor")
-    if shape is not None and tuple(t.shape) != tuple(int(x) for x in shape):
+    if shape is not None and tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(int(x) for x in shape)}")
     if min_numel is not None and t.numel() < int(min_numel):
         raise ValueError(f"{name} holds {t.numel()} elements, needs at least {int(min_numel)}")
@@ -296,21 +296,22 @@ class Context:
     def __exit__(self, *a):
         self.close()
 
-    def _empty(self, shape, dtype):
-        """A new output tensor, from the pool of the stream that writes it."""
+    def _empty(self, *specs):
+        """New output tensors, one per (shape, dtype), from the pool of the
+        stream that writes them; a single one comes by itself."""
         if self._pool is None:
-            return torch.empty(shape, dtype=dtype, device=self.device)
-        at = self._pool_at
-        if torch._C._cuda_getDevice() != at[1]:
+            out = [torch.empty(shape, dtype=dtype, device=self.device) for shape, dtype in specs]
+        elif torch._C._cuda_getDevice() != self._pool_at[1]:
             with torch.cuda.stream(self._pool):
-                return torch.empty(shape, dtype=dtype, device=self.device)
-        # the same without the context manager's 6 us a call
-        now = torch._C._cuda_getCurrentStream(at[1])
-        torch._C._cuda_setStream(*at)
-        try:
-            return torch.empty(shape, dtype=dtype, device=self.device)
-        finally:
-            torch._C._cuda_setStream(*now)
+                out = [torch.empty(shape, dtype=dtype, device=self.device) for shape, dtype in specs]
+        else:   # the same without the context manager's 6 us a call
+            now = torch._C._cuda_getCurrentStream(self._pool_at[1])
+            torch._C._cuda_setStream(*self._pool_at)
+            try:
+                out = [torch.empty(shape, dtype=dtype, device=self.device) for shape, dtype in specs]
+            finally:
+                torch._C._cuda_setStream(*now)
+        return out[0] if len(out) == 1 else out
 
     def _check(self, st):
         if st != OK:
@@ -354,7 +355,8 @@ class Context:
         want_desc False: only enqueue (no wait; desc None, see reorder_desc)."""
         _check(pos, torch.float32, "pos")
         n = pos.shape[0] if pos.dim() == 2 else -1
-        _check(pos, torch.float32, "pos", shape=(n, 3))
+        if tuple(pos.shape) != (n, 3):
+            raise ValueError(f"pos has shape {tuple(pos.shape)}, expected {(n, 3)}")
         _check(sh, torch.float32, "sh", shape=(n, 16, 3))
         if opacity is not None:
             _check(opacity, torch.float32, "opacity", shape=(n,))
@@ -362,8 +364,7 @@ class Context:
         S = N_STREAMS.get(int(p.arrangement), 16)
         npad = (n + 15) // 16 * 16
         if out is None:
-            perm = self._empty(n, torch.int32)
-            tex = self._empty((S, npad // S, 16, 4), torch.uint8)
+            perm, tex = self._empty((n, torch.int32), ((S, npad // S, 16, 4), torch.uint8))
         else:
             perm, tex = out
             _check(perm, torch.int32, "perm", shape=(n,))
@@ -389,15 +390,15 @@ class Context:
         empty class, descs: list of 4 StreamDesc)."""
         _check(pos, torch.float32, "pos")
         n = pos.shape[0] if pos.dim() == 2 else -1
-        _check(pos, torch.float32, "pos", shape=(n, 3))
+        if tuple(pos.shape) != (n, 3):
+            raise ValueError(f"pos has shape {tuple(pos.shape)}, expected {(n, 3)}")
         _check(sh, torch.float32, "sh", shape=(n, 16, 3))
         if opacity is not None:
             _check(opacity, torch.float32, "opacity", shape=(n,))
         _on_device(("pos", pos), ("sh", sh), ("opacity", opacity))
         p = params if params is not None else default_params()
         cap = (n + 15) // 16 * 16 * 64 + 1800
-        buf = self._empty(cap, torch.uint8)
-        perm = self._empty(n, torch.int32)
+        buf, perm = self._empty((cap, torch.uint8), (n, torch.int32))
         counts = (ctypes.c_uint64 * 4)()
         offs = (ctypes.c_uint64 * 4)()
         descs = (StreamDesc * 4)()
@@ -426,7 +427,7 @@ class Context:
         desc = desc.copy()
         if blocks is None:
             _, cap, _ = query_sizes(desc.n_prims)
-            blocks = self._empty(cap, torch.uint8)
+            blocks = self._empty((cap, torch.uint8))
         _check(blocks, torch.uint8, "blocks")
         _on_device(("textures", textures), ("blocks", blocks))
         sse = np.zeros(32, np.int64) if want_sse else None
@@ -478,7 +479,7 @@ class Context:
         if prim_idx is not None:
             _check(prim_idx, torch.int32, "prim_idx", shape=(m,))
         if out is None:
-            out = self._empty((m, 3), torch.float32)
+            out = self._empty(((m, 3), torch.float32))
         _check(out, torch.float32, "out", shape=(m, 3))
         _on_device(("blocks", blocks), ("pos", pos), ("perm", perm), ("prim_idx", prim_idx), ("out", out))
         f = (ctypes.c_float * 3)(*[float(x) for x in view])
@@ -507,10 +508,10 @@ class Context:
         _check(lst, torch.int32, "lst")
         H, W = 16 * int(tiles_y), 16 * int(tiles_x)
         if image is None:
-            image = self._empty((H, W, 3), torch.float32)
+            image = self._empty(((H, W, 3), torch.float32))
         _check(image, torch.float32, "image", shape=(H, W, 3))
         if transmittance is None and want_transmittance:
-            transmittance = self._empty((H, W), torch.float32)
+            transmittance = self._empty(((H, W), torch.float32))
         if transmittance is not None:
             _check(transmittance, torch.float32, "transmittance", shape=(H, W))
         _on_device(("blocks", blocks), ("pos", pos), ("perm", perm), ("opacity", opacity), ("footprint", footprint),
@@ -541,10 +542,10 @@ class Context:
         _check(lst, torch.int32, "lst")
         H, W = 16 * int(tiles_y), 16 * int(tiles_x)
         if image is None:
-            image = self._empty((H, W, 3), torch.float32)
+            image = self._empty(((H, W, 3), torch.float32))
         _check(image, torch.float32, "image", shape=(H, W, 3))
         if transmittance is None and want_transmittance:
-            transmittance = self._empty((H, W), torch.float32)
+            transmittance = self._empty(((H, W), torch.float32))
         if transmittance is not None:
             _check(transmittance, torch.float32, "transmittance", shape=(H, W))
         _on_device(("colours", colours), ("perm", perm), ("opacity", opacity), ("footprint", footprint),
@@ -562,7 +563,7 @@ class Context:
     def load(self, path):
         """Read a container file -> (device blocks tensor, desc)."""
         d = load_header(path)
-        blocks = self._empty(d.payload_bytes, torch.uint8)
+        blocks = self._empty((d.payload_bytes, torch.uint8))
         self._check(load().gsbc_load(self._h, os.fsencode(path), ctypes.byref(d), _ptr(blocks), blocks.numel()))
         return blocks, d
 
@@ -571,7 +572,7 @@ class Context:
         S, nblk, payload, _ = _sizes(desc)
         _check(blocks, torch.uint8, "blocks", min_numel=payload)
         if out is None:
-            out = self._empty((int(desc.n_streams), int(desc.blocks_per_stream), 16, 4), torch.uint8)
+            out = self._empty(((int(desc.n_streams), int(desc.blocks_per_stream), 16, 4), torch.uint8))
         _check(out, torch.uint8, "out", shape=(S, nblk, 16, 4) if S else None)
         _on_device(("blocks", blocks), ("out", out))
         self._check(load().gsbc_decode(self._h, _ptr(blocks), ctypes.byref(desc), _ptr(out)))
@@ -591,7 +592,7 @@ class Context:
         if prim_idx is not None:
             _check(prim_idx, torch.int32, "prim_idx", shape=(m,))
         if out is None:
-            out = self._empty((V, m, 3), torch.float32)
+            out = self._empty(((V, m, 3), torch.float32))
         _check(out, torch.float32, "out", shape=(V, m, 3))
         _on_device(("blocks", blocks), ("dirs", dirs), ("prim_idx", prim_idx), ("out", out))
         fn = load().gsbc_decode_eval_noalloc if noalloc else load().gsbc_decode_eval
