@@ -313,6 +313,20 @@ class Context:
                 torch._C._cuda_setStream(*now)
         return out[0] if len(out) == 1 else out
 
+    def _frame(self, H, W, image, transmittance, want_transmittance):
+        """A blend's outputs: the caller's, checked, or new ones."""
+        if image is None and transmittance is None and want_transmittance:
+            return self._empty(((H, W, 3), torch.float32), ((H, W), torch.float32))
+        if image is None:
+            image = self._empty(((H, W, 3), torch.float32))
+        else:
+            _check(image, torch.float32, "image", shape=(H, W, 3))
+        if transmittance is None and want_transmittance:
+            transmittance = self._empty(((H, W), torch.float32))
+        elif transmittance is not None:
+            _check(transmittance, torch.float32, "transmittance", shape=(H, W))
+        return image, transmittance
+
     def _check(self, st):
         if st != OK:
             raise GsbcError(st, load().gsbc_last_error(self._h).decode())
@@ -507,13 +521,7 @@ class Context:
         _check(tile_start, torch.int32, "tile_start", shape=(tiles + 1,))
         _check(lst, torch.int32, "lst")
         H, W = 16 * int(tiles_y), 16 * int(tiles_x)
-        if image is None:
-            image = self._empty(((H, W, 3), torch.float32))
-        _check(image, torch.float32, "image", shape=(H, W, 3))
-        if transmittance is None and want_transmittance:
-            transmittance = self._empty(((H, W), torch.float32))
-        if transmittance is not None:
-            _check(transmittance, torch.float32, "transmittance", shape=(H, W))
+        image, transmittance = self._frame(H, W, image, transmittance, want_transmittance)
         _on_device(("blocks", blocks), ("pos", pos), ("perm", perm), ("opacity", opacity), ("footprint", footprint),
                    ("tile_start", tile_start), ("lst", lst), ("image", image), ("transmittance", transmittance))
         f = (ctypes.c_float * 3)(*[float(x) for x in view])
@@ -535,19 +543,14 @@ class Context:
         _check(perm, torch.int32, "perm", shape=(n,))
         _check(opacity, torch.float32, "opacity")
         N = opacity.shape[0] if opacity.dim() == 1 else -1
-        _check(opacity, torch.float32, "opacity", shape=(N,))
+        if N < 0:
+            raise ValueError(f"opacity has shape {tuple(opacity.shape)}, expected {(N,)}")
         _check(footprint, torch.float32, "footprint", shape=(N, 5))
         tiles = int(tiles_x) * int(tiles_y)
         _check(tile_start, torch.int32, "tile_start", shape=(tiles + 1,))
         _check(lst, torch.int32, "lst")
         H, W = 16 * int(tiles_y), 16 * int(tiles_x)
-        if image is None:
-            image = self._empty(((H, W, 3), torch.float32))
-        _check(image, torch.float32, "image", shape=(H, W, 3))
-        if transmittance is None and want_transmittance:
-            transmittance = self._empty(((H, W), torch.float32))
-        if transmittance is not None:
-            _check(transmittance, torch.float32, "transmittance", shape=(H, W))
+        image, transmittance = self._frame(H, W, image, transmittance, want_transmittance)
         _on_device(("colours", colours), ("perm", perm), ("opacity", opacity), ("footprint", footprint),
                    ("tile_start", tile_start), ("lst", lst), ("image", image), ("transmittance", transmittance))
         self._check(load().gsbc_blend_tiles_colours(self._h, _ptr(colours), n, _ptr(perm), _ptr(opacity),
