@@ -10,14 +10,17 @@ mixture, Laplacian higher bands; seed 2), i.e. 1,048,576 blocks per format.
 
 Prints one JSON line.  `value` = blocks encoded per step (both formats) /
 step time, in Mblocks/s.  Also reported:
-  roofline            the step's dominant kernel (a BC7 search kernel):
-                      algorithmic integer ops per launch / its average launch
-                      time (HIP events the library records on its stream),
-                      against the VALU peak;
+  roofline            the step's dominant kernel (the BC7 search): VALU
+                      lane-instructions per launch (SQ_INSTS_VALU of the
+                      committed rocprofv3 pass) / its average launch time (HIP
+                      events the library records on its stream), against the
+                      VALU peak; beside it the distance evaluations of an
+                      exhaustive search over the same time, which passes the
+                      peak because bounds rule most candidates out unfitted;
   kernels_ms_per_step per-kernel device times of the same step from extra
                       passes with the library's kernel timing on, which runs
                       the encoder's kernels one after another (the timed steps
-                      overlap BC1 with the BC7 bucketing and emit kernels);
+                      overlap BC1 with the BC7 kernels);
   valu_issue          the BC7 search and BC1 encoders' VALU instructions per
                       launch (SQ_INSTS_VALU of the committed rocprofv3 pass)
                       over the live launch time, against one wave64
@@ -49,13 +52,11 @@ HBM_PEAK = 8.0e12                        # bytes/s
 # distance comparison needs at the least on gfx950: one v_dot2 for two
 # channels, one 24-bit multiply-add for the third channel plus the entry's
 # constant, and half a v_min3 for the running minimum.  A plain scalar form
-# takes about 8 (3 sub, 3 mul, 2 add); the issue-slot floor is what bounds
-# the kernel, so the fraction below is the share of peak VALU issue spent on
-# that irreducible work.
+# takes about 8 (3 sub, 3 mul, 2 add).
 OPS_PER_EVAL = 2.5
-# Algorithmic work per block of the BC7 search kernels: texel x palette-entry
-# distance evaluations of the candidates each kernel covers (initial fit and
-# least-squares refit, every p-bit choice) x OPS_PER_EVAL.
+# Work per block of an exhaustive BC7 search: texel x palette-entry distance
+# evaluations of the candidates of each group (initial fit and least-squares
+# refit, every p-bit choice) x OPS_PER_EVAL.
 ALGO_OPS = {
     "bc7_search_2subset": 3 * 32_768 * OPS_PER_EVAL,            # modes 1, 3, 7
     "bc7_search_3subset": (16_384 + 8_192) * OPS_PER_EVAL,     # modes 0, 2
@@ -63,11 +64,9 @@ ALGO_OPS = {
 }
 # one launch over every group (work items per group, or all groups per block)
 ALGO_OPS["bc7_search_items"] = ALGO_OPS["bc7_search_all"] = sum(ALGO_OPS.values())
-# The evaluations the search actually executes: a 3-subset mask that recurs
-# across partitions is fitted once per mode and its SSE reused, so mode 2
-# fits 140 distinct masks of its 192 (5,984 of 8,192 evaluations) and mode 0
-# 36 of 48 (12,288 of 16,384).  The refit's evaluation is also skipped when
-# its normal equations are singular (data-dependent, not counted here).
+# The same with every 3-subset mask that recurs across partitions fitted once
+# per mode: mode 2 has 140 distinct masks of 192 (5,984 of 8,192 evaluations),
+# mode 0 36 of 48 (12,288 of 16,384).
 EXECUTED_EVALS = 3 * 32_768 + 12_288 + 5_984 + 3_072 + 1_024 + 2_048
 TRAFFIC = os.path.join(ROOT, "profiles", "traffic_encode_step_1M_and_decode_eval_3M.json")
 
@@ -225,19 +224,21 @@ def main():
         launches = kern[dom][0] / nprof
         dom_s = per_step[dom] / launches * 1e-3                     # average launch, s
         dom_launch_ms = [r[dom][1] / r[dom][0] for r in per_run if dom in r]
-        units = 16 * nblk                                           # blocks per launch
+        units = 16 * nblk / launches                                # blocks per launch
         work = ALGO_OPS.get(dom)
         traffic = traffic_bytes(dom)
-        roof = {"kernel": dom, "bound": "alu", "achieved": work * units / dom_s / 1e12 if work else None,
+        insts = profiled(dom, "valu_insts")
+        roof = {"kernel": dom, "bound": "alu", "achieved": 64 * insts / dom_s / 1e12 if insts else None,
                 "peak": VALU_PEAK / 1e12, "unit": "Tops/s",
-                "frac": work * units / dom_s / VALU_PEAK if work else None, "traffic": traffic,
+                "frac": 64 * insts / dom_s / VALU_PEAK if insts else None, "traffic": traffic,
                 "launch_ms": round(dom_s * 1e3, 4), "launch_ms_median": round(float(np.median(dom_launch_ms)), 4),
-                "launch_ms_min": round(float(np.min(dom_launch_ms)), 4),
-                "algorithmic_ops_per_block": work, "blocks_per_launch": units}
-        if dom in ("bc7_search_items", "bc7_search_all"):
-            # the same floor over the evaluations the kernel executes
-            roof["executed_ops_per_block"] = EXECUTED_EVALS * OPS_PER_EVAL
-            roof["frac_executed"] = EXECUTED_EVALS * OPS_PER_EVAL * units / dom_s / VALU_PEAK
+                "launch_ms_min": round(float(np.min(dom_launch_ms)), 4), "blocks_per_launch": units}
+        if work:
+            # an exhaustive search's evaluations in the same time, all of them
+            # and with recurring 3-subset masks fitted once
+            roof["exhaustive_ops_per_block"] = work
+            roof["exhaustive_equivalent_tops"] = round(work * units / dom_s / 1e12, 3)
+            roof["exhaustive_distinct_equivalent_tops"] = round(EXECUTED_EVALS * OPS_PER_EVAL * units / dom_s / 1e12, 3)
 
         # ---- counter-measured VALU issue utilisation of the encoders: the
         # committed SQ_INSTS_VALU count of a launch over the live launch time
@@ -477,10 +478,9 @@ def main():
                         "ms": med_min(t_view), "gslots_s": round(c3["n"] / view_s / 1e9, 3),
                         "bytes": int(dd2.payload_bytes + c3["n"] * (12 + 4 + 12))}
             view_leg["gb_s"] = round(view_leg["bytes"] / view_s / 1e9, 1)
-            # the fused colour stage: a 1920 x 1088 image of 16 x 16 tiles whose
-            # front-to-back lists come from projecting the scene from the same
-            # view position (footprints 0.7-6 px); every entry's colour decoded
-            # in the tile's workgroup, nothing per primitive written to memory
+            # the colour stage from the bitstreams: a 1920 x 1088 image of
+            # 16 x 16 tiles whose front-to-back lists come from projecting the
+            # scene from the same view position (footprints 0.7-6 px)
             mu3 = synth.make_opacity(c3["n"], seed=c3["seed"])
             foot3, ts3, lst3 = synth.make_tiles(pos3, view, 120, 68, seed=c3["seed"], sigma=(0.7, 6.0))
             slot3 = np.argsort(p3.cpu().numpy().view(np.uint32)).astype(np.int32)
@@ -488,9 +488,9 @@ def main():
             ts3d = torch.from_numpy(ts3.astype(np.int32)).to(dev)
             lst3d = torch.from_numpy(slot3[lst3]).to(dev)
             img3, tr3 = ctx.blend_tiles(b3, dd2, pos3d, p3, view, mu3d, foot3d, ts3d, lst3d, 120, 68)
-            t_bl = kernel_ms(ctx, ("tile_order", "blend_tiles"), lambda: ctx.blend_tiles(b3, dd2, pos3d, p3, view, mu3d, foot3d, ts3d,
-                                                                         lst3d, 120, 68, image=img3,
-                                                                         transmittance=tr3), 3)
+            t_bl = kernel_ms(ctx, ("decode_eval_view", "tile_order", "blend_tiles"),
+                             lambda: ctx.blend_tiles(b3, dd2, pos3d, p3, view, mu3d, foot3d, ts3d, lst3d, 120, 68,
+                                                     image=img3, transmittance=tr3), 3)
             bl_s = float(np.median(t_bl)) * 1e-3
             entries = int(ts3[-1])
             colour_leg = {"workload": "1920x1088 image (120x68 tiles of 16x16), 3,145,728 primitives projected from "
@@ -499,12 +499,12 @@ def main():
                           "max_entries_per_tile": int(np.diff(ts3.astype(np.int64)).max()),
                           "gentries_s": round(entries / bl_s / 1e9, 3),
                           "listed_pixel_pairs_gs": round(256 * entries / bl_s / 1e9, 1),
-                          # 18 issue slots per pixel-entry pair at least (footprint 7, exp 4,
-                          # weights and transmittance 4, colour 3); tiles stop at T = 0 exactly,
+                          # 13 instructions per pixel-entry pair at least (footprint 7, exp2,
+                          # weight and transmittance 2, colour 3); tiles stop at T = 0 exactly,
                           # so this counts listed pairs, not executed ones
-                          "alu_frac_listed_pairs": round(18 * 256 * entries / bl_s / VALU_PEAK, 4)}
-            # the two-pass form: every primitive's colour decoded once (the
-            # view decode), then the blend reads those colours (bit-identical)
+                          "alu_frac_listed_pairs": round(13 * 256 * entries / bl_s / VALU_PEAK, 4)}
+            # the two-pass form: the caller's view decode of every primitive,
+            # then the blend reads those colours (bit-identical)
             cols3 = ctx.decode_eval_view(b3, dd2, pos3d, p3, view)
             ctx.blend_tiles_colours(cols3, p3, mu3d, foot3d, ts3d, lst3d, 120, 68, image=img3, transmittance=tr3)
             t_bl2 = kernel_ms(ctx, ("decode_eval_view", "tile_order", "blend_tiles"),
