@@ -713,12 +713,12 @@ gsbc_status gsbc_encode(gsbc_ctx *ctx, const uint8_t *textures, gsbc_stream_desc
     // With both formats the BC1 encoder runs on a side stream beside the BC7
     // kernels: the waves that those leave idle as each of them ends are then
     // filled with the other format's work.  It starts when the (first chunk's)
-    // bounds are done, not with them: they fill the chip by themselves, and
-    // the BC7 kernels after them are the longer chain (both formats of
-    // 4,101 / 65,536 / 200,003 / 1,048,576 primitives: 290 / 555 / 1,550 /
-    // 6,178 us from the start, 257 / 518 / 1,468 / 6,181 after the bounds, 259
-    // / 538 / 1,405 / 6,225 after the seeds, 305 / 571 / 1,572 / 6,225 after
-    // the search).  Joined before anything reads either format's results.
+    // bounds, in larger scenes the seeds too, are done, not with them: they
+    // fill the chip by themselves, and the BC7 kernels after them are the
+    // longer chain (both formats of 4,101 / 65,536 / 262,144 / 1,048,576
+    // primitives: 257 / 514 / 1,760 / 6,140 us; from the start, then with the
+    // search not yet sorted by XCD, 290 / 555 / - / 6,178; after the search 305 /
+    // 571 / - / 6,225).  Joined before anything reads either format's results.
     // While kernel timing is on, everything stays on the context's stream, one
     // kernel after another, so each timed kernel has the GPU to itself.
     hipStream_t s1 = ctx->stream;

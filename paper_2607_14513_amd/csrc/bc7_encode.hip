@@ -1829,7 +1829,7 @@ hipError_t upload_bc7_tables(int device, hipStream_t st)
 }
 
 hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t split, hipStream_t st,
-                             hipEvent_t bounded)
+                             hipEvent_t alone)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -1883,15 +1883,22 @@ hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t 
         return hipGetLastError();
     };
     constexpr uint32_t kType2 = 1u << kTwo, kType3 = 1u << kThree0 | 1u << kThree2, kType1 = 1u << kRot | 1u << kSix;
+    // Up to which kernel the (first chunk's) launches want the chip to
+    // themselves: the bounds fill it from few blocks on, the seeds from about
+    // 196,608 (both formats, other work after the bounds / after the seeds:
+    // 131,072 primitives 923 / 972 us, 200,003 1,466 / 1,436, 262,144 1,995 /
+    // 1,760, 524,288 3,262 / 3,180, 1,048,576 6,139 / 6,140).
+    const bool seeds_fill = a.total >= (3u << 16);
     for (uint64_t first = 0; first < a.total; first += nc) {
         const uint64_t left = a.total - first < nc ? a.total - first : nc;
         Q.first = first;
         Q.slices = (uint32_t)(left / 64);
         const uint32_t per = left >= (1u << 17) ? kWG : 64;
         GSBC_LAUNCH("bc7_bounds", k_bc7_bounds, dim3((uint32_t)(left / per)), dim3(kWG), 0, st, Q, per);
-        if (bounded && first == 0 && (e = hipEventRecord(bounded, st)) != hipSuccess) return e;
+        if (alone && !seeds_fill && first == 0 && (e = hipEventRecord(alone, st)) != hipSuccess) return e;
         const bool pairs = left < (1u << 17);
         GSBC_LAUNCH("bc7_seed", k_bc7_seed, dim3((uint32_t)(left / (pairs ? kWG / 2 : kWG))), dim3(kWG), 0, st, Q, pairs);
+        if (alone && seeds_fill && first == 0 && (e = hipEventRecord(alone, st)) != hipSuccess) return e;
         if (split == 0) {
             if ((e = launch(0, kType3, "bc7_search_3subset")) != hipSuccess) return e;
             if ((e = launch(1, kType1, "bc7_search_1subset")) != hipSuccess) return e;

@@ -180,9 +180,10 @@ inline size_t bc7_scratch_bytes(uint64_t blocks)
 // split gives the same bits (the winner is a minimum over a total order,
 // combined with atomic minima).
 hipError_t launch_bc1_encode(const EncodeArgs &a, const WorkSplit &w, uint32_t lanes, hipStream_t st);
-// bounded: recorded on st after the first chunk's bounds, if given.
+// alone: recorded on st, if given, where work on another stream is better
+// started: after the first chunk's bounds or seeds.
 hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t split, hipStream_t st,
-                             hipEvent_t bounded = nullptr);
+                             hipEvent_t alone = nullptr);
 hipError_t upload_bc1_tables(int device, hipStream_t st);
 hipError_t upload_bc7_tables(int device, hipStream_t st);
 
