@@ -403,11 +403,14 @@ GSBC_API gsbc_status gsbc_decode_eval_view(gsbc_ctx *ctx, const uint8_t *blocks,
  * gsbc_decode_eval_view) and
  * g_i = exp(-(a dx^2 + 2 b dx dy + c dy^2)/2) its footprint at the pixel.
  * FP32 throughout; no early termination.  Lists of more than one entry per
- * four slots have all slots' colours computed first, into the scratch arena
- * (12 bytes a slot; gsbc_reserve's size holds them); where the arena does not
- * hold them and cannot grow (a failed allocation, a stream being captured)
- * and for shorter lists each entry is decoded in the blend, with no colour
- * in memory.  Both give the same bits.
+ * four slots, and 32,768 at least, have the colours of all slots that a tile
+ * lists computed first, into the scratch arena (13 bytes a slot; gsbc_reserve's
+ * size holds them); where the arena does not hold them and cannot grow (a
+ * failed allocation, a stream being captured) and for shorter lists each entry
+ * is decoded in the blend, with no colour in memory.  Both give the same bits,
+ * and neither reads anything of slots that no tile lists (their perm entries,
+ * positions and blocks).  list_len is the buffer's length: entries that no tile
+ * uses are not read either.
  *   blocks, desc     as gsbc_decode_eval (a coded scene)
  *   pos, perm        as gsbc_decode_eval_view
  *   view             host float[3], the view position f

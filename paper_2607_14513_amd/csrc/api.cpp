@@ -1170,25 +1170,29 @@ gsbc_status gsbc_blend_tiles(gsbc_ctx *ctx, const uint8_t *blocks, const gsbc_st
     const float f[3] = {view[0], view[1], view[2]};
     if (!(isfinite(f[0]) && isfinite(f[1]) && isfinite(f[2]))) return fail(ctx, GSBC_E_ARG, "view position not finite");
     const size_t order_bytes = ((size_t)tiles * sizeof(uint32_t) + 255) & ~(size_t)255;   // the tile schedule
-    // Colours of all slots first, into scratch, or of each list entry in the
-    // blend: a primitive sits in several tiles' lists, and slots in order
-    // decode whole blocks.  At 5.3 entries a slot colours first take 530 us
-    // against 875 (786,432 slots; 219 at 49,152 and 1,225 at 3,145,728), at 0.35
-    // 88 (30, 205), where the entries alone take 100 (37, 211) at 0.3; at 0.2 69
-    // against 74 (31 : 26, 163 : 170): the line is one entry in four slots.
-    // Without room for them (12 bytes a slot) the entries are decoded in the
-    // blend; the image is the same bit for bit.
-    const float *colours = nullptr;
-    if (list_len >= desc->n_prims / 4 + 1 && try_arena(ctx, order_bytes + desc->n_prims * 3 * sizeof(float))) {
-        float *c = reinterpret_cast<float *>(static_cast<char *>(ctx->arena) + order_bytes);
-        HIP_TRY(ctx, launch_decode_eval_view(blocks, band_args(desc), desc->n_prims, pos, perm, f, nullptr, desc->n_prims,
-                                             c, ctx->stream), "decode_eval_view launch");
-        colours = c;
+    // Colours of all listed slots first, into scratch, or of each list entry in
+    // the blend: a primitive sits in several tiles' lists, and slots in order
+    // decode whole blocks.  At 3.6 entries a slot colours first take 320 us
+    // against 451 (786,432 slots; 142 : 183 at 300,000 and 1,038 : 1,568 at
+    // 3,145,728), at 0.27 54 : 57 (36 : 42, 150 : 150).  The line is one entry in
+    // four slots, though marks make fewer gain too in large scenes (0.01 a slot
+    // 26 : 35, 64 : 94): of few entries, which slots they are costs more than it
+    // saves (14,000 entries of 30,000 slots 22 : 18, 113,000 43 : 55; 12,000 of
+    // 3,000 28 : 24), so lists are 2^15 long at least.
+    // Without room for them (13 bytes a slot) the entries are decoded in the
+    // blend; the image is the same bit for bit.  Nothing is read of slots that
+    // no tile lists, on either way.
+    float *colours = nullptr;
+    uint8_t *marks = nullptr;
+    const uint64_t n = desc->n_prims;
+    if (list_len >= std::max<uint64_t>(n / 4 + 1, 1u << 15) && try_arena(ctx, order_bytes + pad16(n) * (3 * sizeof(float) + 1))) {
+        marks = static_cast<uint8_t *>(ctx->arena) + order_bytes;
+        colours = reinterpret_cast<float *>(marks + pad16(n));
     }
     if ((s = ensure_arena(ctx, order_bytes))) return s;
-    HIP_TRY(ctx, launch_blend_tiles(blocks, band_args(desc), desc->n_prims, pos, perm, f, opacity, footprint, tile_start,
-                                    list, list_len, tiles_x, tiles_y, colours, image, transmittance,
-                                    static_cast<uint32_t *>(ctx->arena), ctx->stream),
+    HIP_TRY(ctx, launch_blend_tiles(blocks, band_args(desc), n, pos, perm, f, opacity, footprint, tile_start, list, list_len,
+                                    tiles_x, tiles_y, nullptr, image, transmittance, static_cast<uint32_t *>(ctx->arena),
+                                    colours, marks, ctx->stream),
             "blend_tiles launch");
     return GSBC_OK;
 }
@@ -1214,7 +1218,7 @@ gsbc_status gsbc_blend_tiles_colours(gsbc_ctx *ctx, const float *colours, uint64
     const float f[3] = {0.0f, 0.0f, 0.0f};   // unused: the colours are given
     HIP_TRY(ctx, launch_blend_tiles(nullptr, BandArgs{}, n_prims, nullptr, perm, f, opacity, footprint, tile_start,
                                     list, list_len, tiles_x, tiles_y, colours, image, transmittance,
-                                    static_cast<uint32_t *>(ctx->arena), ctx->stream),
+                                    static_cast<uint32_t *>(ctx->arena), nullptr, nullptr, ctx->stream),
             "blend_tiles launch");
     return GSBC_OK;
 }

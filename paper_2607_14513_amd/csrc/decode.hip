@@ -179,23 +179,26 @@ __device__ __forceinline__ Bc7LdsLut stage_parts(Bc7Part *rows)
 // t at t + 4 (t / 16) (16-byte pieces, spread over the banks).  1,048,576
 // slots x 64 directions 182 -> 145 us, all of a 3,145,728-slot scene from one
 // view position 0.26 -> 0.09 ms (part of each gain is the texel decoder's).
+// wanted(i, k): whether any of the k slots from s0 + i on is asked for; the
+// blocks of others are not read.
 constexpr int kTileRow = 320;
 constexpr int kTileWords = 16 * kTileRow;
 
-template <class Lut>
+template <class Lut, class Wanted>
 __device__ __forceinline__ void slot_texels_tile(const uint8_t *blocks, const BandArgs &b, uint64_t s0, uint32_t *tile,
-                                                 uint32_t (&px)[16], const Lut &lut)
+                                                 uint32_t (&px)[16], const Lut &lut, Wanted wanted)
 {
     const uint32_t t = threadIdx.x, lane = t & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
     uint2 lo, hi;
     if (b.arrangement == 1) {         // block s holds slot s's bands
+        if (!wanted(t, 1)) return;
         load_block(blocks + b.offset[0], b.format[0], s0 + t, lo, hi);
         block_texels(b.format[0], lo, hi, px, lut);
         return;
     }
     if (b.arrangement == 2) {         // a wave's 64 blocks of stream `wave`: 4 slots x 4 bands each
-        if (wave < b.n_streams) {
+        if (wave < b.n_streams && wanted(4 * lane, 4)) {
             load_block(blocks + b.offset[wave], b.format[wave], (s0 >> 2) + lane, lo, hi);
             block_texels(b.format[wave], lo, hi, px, lut);
 #pragma unroll
@@ -209,7 +212,7 @@ __device__ __forceinline__ void slot_texels_tile(const uint8_t *blocks, const Ba
         uint64_t offset = 0;
 #pragma unroll
         for (uint32_t q = 0; q < 4; q++)
-            if ((lane >> 4) == q && 4 * wave + q < b.n_streams) {
+            if ((lane >> 4) == q && 4 * wave + q < b.n_streams && wanted(16 * (lane & 15u), 16)) {
                 format = b.format[4 * wave + q];
                 offset = b.offset[4 * wave + q];
             }
@@ -338,7 +341,7 @@ __device__ __forceinline__ void decode_eval_body(const uint8_t *blocks, const Ba
         const bool whole = !prim_idx && j0 + kSlots <= min(m, n_prims);
         uint32_t px[16];
         if (whole) {
-            slot_texels_tile(blocks, b, j0, reinterpret_cast<uint32_t *>(lds), px, lut);
+            slot_texels_tile(blocks, b, j0, reinterpret_cast<uint32_t *>(lds), px, lut, [](uint32_t, int) { return true; });
             __syncthreads();
         }
         float h[16][3];
@@ -569,29 +572,43 @@ __device__ __forceinline__ void view_colour(const uint8_t *blocks, const BandArg
     colour_sum(b, px, Y, c);
 }
 
-// One lane per listed slot; out-of-range slot ids give NaN.
+// One lane per listed slot; out-of-range slot ids give NaN.  MARKED: all slots,
+// of which only those with a mark (a byte each) are asked for: nothing of the
+// others is read, neither their blocks nor their perm entries and positions,
+// and their colours are left as they are or NaN.
+template <bool MARKED>
 __global__ __launch_bounds__(256) void k_decode_eval_view(const uint8_t *blocks, BandArgs b, const uint32_t *prim_idx,
-                                                          uint64_t m, uint64_t n_prims, const float *pos,
+                                                          const uint8_t *mark, uint64_t m, uint64_t n_prims, const float *pos,
                                                           const uint32_t *perm, float fx, float fy, float fz,
                                                           float *out)
 {
     __shared__ __align__(16) uint32_t s_tile[kTileWords];
     __shared__ __align__(8) Bc7Part s_rows[kBc7PartRows];
+    __shared__ uint64_t s_marks[4];
+    const uint64_t j0 = (uint64_t)blockIdx.x * 256, j = j0 + threadIdx.x;
+    bool mine = j < m;
+    if (MARKED) {
+        mine = mine && mark[j] != 0;
+        const uint64_t marks = __ballot(mine);
+        if ((threadIdx.x & 63u) == 0) s_marks[threadIdx.x >> 6] = marks;
+        if (!__syncthreads_or(mine)) return;
+    }
     const Bc7LdsLut lut = stage_parts(s_rows);
     __syncthreads();
-    const uint64_t j0 = (uint64_t)blockIdx.x * 256, j = j0 + threadIdx.x;
     float c[3] = {__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
     if (!prim_idx && j0 + 256 <= min(m, n_prims)) {   // 256 slots in a row: whole blocks
         float Y[16];
-        view_basis((uint32_t)j, pos, perm, fx, fy, fz, Y);
+        if (mine) view_basis((uint32_t)j, pos, perm, fx, fy, fz, Y);
         uint32_t px[16];
-        slot_texels_tile(blocks, b, j0, s_tile, px, lut);
-        colour_sum(b, px, Y, c);
-    } else {
-        if (j >= m) return;
+        slot_texels_tile(blocks, b, j0, s_tile, px, lut, [&](uint32_t i, int k) {
+            return !MARKED || ((s_marks[i >> 6] >> (i & 63u)) & ((1ull << k) - 1u)) != 0;
+        });
+        if (mine) colour_sum(b, px, Y, c);
+    } else if (mine) {
         const uint32_t s = prim_idx ? prim_idx[j] : (uint32_t)j;
         if (s < n_prims) view_colour(blocks, b, s, pos, perm, fx, fy, fz, c, lut);
     }
+    if (j >= m || (MARKED && __ballot(mine) == 0)) return;
     out[3 * j] = c[0];
     out[3 * j + 1] = c[1];
     out[3 * j + 2] = c[2];
@@ -601,12 +618,18 @@ __global__ __launch_bounds__(256) void k_decode_eval_view(const uint8_t *blocks,
 // last): one workgroup counts, scans and scatters.  The blend takes tiles
 // in this order so that the longest lists start first instead of ending
 // the launch alone; the order within a bucket does not matter (each tile is
-// computed on its own).
+// computed on its own).  Workgroup 0; the others clear the slots' marks, where
+// there are any (n_marks bytes, a multiple of 16).
 __global__ __launch_bounds__(1024) void k_tile_order(const uint32_t *tile_start, uint64_t list_len, uint32_t tiles,
-                                                    uint32_t *order)
+                                                    uint32_t *order, uint4 *marks, uint64_t n_marks)
 {
     __shared__ uint32_t cnt[33];
     const uint32_t t = threadIdx.x;
+    if (blockIdx.x) {
+        const uint64_t e = (uint64_t)(blockIdx.x - 1) * 1024 + t;
+        if (e < n_marks / 16) marks[e] = make_uint4(0u, 0u, 0u, 0u);
+        return;
+    }
     if (t < 33) cnt[t] = 0u;
     __syncthreads();
     auto key = [&](uint32_t i) {
@@ -626,6 +649,24 @@ __global__ __launch_bounds__(1024) void k_tile_order(const uint32_t *tile_start,
     }
     __syncthreads();
     for (uint32_t i = t; i < tiles; i += 1024) order[atomicAdd(&cnt[key(i)], 1u)] = i;
+}
+
+// A mark on every slot that a tile's list names (ids past the scene have none):
+// one workgroup per tile, the longest lists first.  What colours first read is
+// then what decoding entry by entry reads, whatever the rest of perm, pos and
+// blocks holds.  Marks cost a frame of 786,432 slots and 2.8 M entries 15 of 318
+// us, one of 3,145,728 and 10.7 M 21 of 1,038.
+__global__ __launch_bounds__(256) void k_mark_slots(const uint32_t *tile_start, const uint32_t *list, uint64_t list_len,
+                                                    const uint32_t *order, uint64_t n_prims, uint8_t *mark)
+{
+    const uint32_t tile = order[blockIdx.x];
+    const uint64_t b1 = min((uint64_t)tile_start[tile + 1], list_len);
+    const uint64_t b0 = min((uint64_t)tile_start[tile], b1);
+#pragma unroll 4
+    for (uint64_t e = b0 + threadIdx.x; e < b1; e += 256) {
+        const uint32_t s = list[e];
+        if (s < n_prims) mark[s] = 1;
+    }
 }
 
 // Colour stage of a tile rasteriser (Sec. II, eq. preblend with the
@@ -730,11 +771,20 @@ hipError_t launch_blend_tiles(const uint8_t *blocks, const BandArgs &b, uint64_t
                               const uint32_t *perm, const float view[3], const float *mu, const float *foot,
                               const uint32_t *tile_start, const uint32_t *list, uint64_t list_len, uint32_t tiles_x,
                               uint32_t tiles_y, const float *colours, float *image, float *trans, uint32_t *order,
-                              hipStream_t st)
+                              float *fill_colours, uint8_t *marks, hipStream_t st)
 {
     const uint64_t tiles = (uint64_t)tiles_x * tiles_y;
     if (tiles == 0) return hipSuccess;
-    GSBC_LAUNCH("tile_order", k_tile_order, dim3(1), dim3(1024), 0, st, tile_start, list_len, (uint32_t)tiles, order);
+    const uint64_t n_marks = fill_colours ? (n_prims + 15) / 16 * 16 : 0;
+    GSBC_LAUNCH("tile_order", k_tile_order, dim3(1 + (uint32_t)((n_marks / 16 + 1023) / 1024)), dim3(1024), 0, st, tile_start,
+                list_len, (uint32_t)tiles, order, reinterpret_cast<uint4 *>(marks), n_marks);
+    if (fill_colours) {
+        GSBC_LAUNCH("mark_slots", k_mark_slots, dim3((uint32_t)tiles), dim3(256), 0, st, tile_start, list, list_len, order,
+                    n_prims, marks);
+        GSBC_LAUNCH("decode_eval_view", k_decode_eval_view<true>, dim3((uint32_t)((n_prims + 255) / 256)), dim3(256), 0, st,
+                    blocks, b, nullptr, marks, n_prims, n_prims, pos, perm, view[0], view[1], view[2], fill_colours);
+        colours = fill_colours;
+    }
     GSBC_LAUNCH("blend_tiles", colours ? k_blend_tiles<true> : k_blend_tiles<false>, dim3((uint32_t)tiles), dim3(256), 0,
                 st, blocks, b, n_prims, pos, perm, view[0], view[1], view[2], mu, foot, tile_start, list, list_len, order,
                 tiles_x, colours, image, trans);
@@ -746,8 +796,8 @@ hipError_t launch_decode_eval_view(const uint8_t *blocks, const BandArgs &b, uin
                                    float *out, hipStream_t st)
 {
     if (m == 0) return hipSuccess;
-    GSBC_LAUNCH("decode_eval_view", k_decode_eval_view, dim3((uint32_t)((m + 255) / 256)), dim3(256), 0, st, blocks, b,
-                prim_idx, m, n_prims, pos, perm, view[0], view[1], view[2], out);
+    GSBC_LAUNCH("decode_eval_view", k_decode_eval_view<false>, dim3((uint32_t)((m + 255) / 256)), dim3(256), 0, st, blocks, b,
+                prim_idx, nullptr, m, n_prims, pos, perm, view[0], view[1], view[2], out);
     return hipGetLastError();
 }
 
