@@ -44,6 +44,9 @@ __device__ void write_selection(uint32_t fmt, uint32_t S, uint64_t nblk, const u
 // One wave, lane q = band q.  A band is BC7 if fewer than k bands come before
 // it (larger gain, the lower band on ties).  Gains are ranked by their bits
 // (ordered as the values are), so exactly k bands are BC7 whatever they hold.
+// A gain that is no number (a band whose range is infinite or NaN) has no rank:
+// then the bands are picked one by one, the first one left against the others,
+// as the rule is written (a NaN is passed by nothing and passes nothing).
 __global__ __launch_bounds__(64) void k_rate_select(const unsigned long long *sse, BandArgs b, uint32_t S, uint32_t k,
                                                     uint64_t nblk, RateSel *sel, RateSel *host_sel,
                                                     unsigned long long *host_sse)
@@ -58,7 +61,20 @@ __global__ __launch_bounds__(64) void k_rate_select(const unsigned long long *ss
         const uint64_t other = __shfl(key, (int)o);
         before += o != q && (other > key || (other == key && o < q)) ? 1u : 0u;
     }
-    write_selection(q == 0 || before < k ? GSBC_FMT_BC7 : GSBC_FMT_BC1, S, nblk, sse, sel, host_sel, host_sse);
+    bool wide = q == 0 || before < k;
+    if (__any(q >= 1 && q < S && gain != gain)) {
+        wide = q == 0;
+        for (uint32_t pick = 0; pick < k; pick++) {
+            const uint32_t left = ~(uint32_t)__ballot(wide) & ((1u << S) - 1u);   // (lanes 0..15 hold the bands)
+            uint32_t best = (uint32_t)__ffs(left) - 1;
+            for (uint32_t rest = left & (left - 1); rest; rest &= rest - 1) {
+                const uint32_t o = (uint32_t)__ffs(rest) - 1;
+                if (__shfl(gain, (int)o) > __shfl(gain, (int)best)) best = o;
+            }
+            wide |= q == best;
+        }
+    }
+    write_selection(wide ? GSBC_FMT_BC7 : GSBC_FMT_BC1, S, nblk, sse, sel, host_sel, host_sse);
 }
 
 // Code histogram of every band's R, G and B texel channels: one workgroup
