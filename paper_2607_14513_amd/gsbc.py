@@ -249,12 +249,14 @@ class Context:
 
     On torch's default stream a context works on a blocking stream of its own,
     which HIP keeps in order with the default stream but not with the streams
-    of other contexts.  The outputs that it makes therefore come from that
-    stream's pool of torch's allocator: memory that is freed while the context
-    may still write it goes to its own later calls only, not to another
-    context's."""
+    of other contexts.  The outputs that a context makes come from the pool
+    that torch's allocator keeps for the stream they are written on: memory
+    that is freed while the context may still write it goes to its own later
+    calls only, not to another context's.  A call made while another stream is
+    torch's current one marks them as used there, too: they are not written
+    again before what that stream had to do when they were freed is done."""
 
-    _own, _pool = None, None   # that stream's handle, and the stream as torch sees it
+    _own, _pool = None, None   # the handle of a stream of its own; the stream that it works on
 
     def __init__(self, device=0, stream=None):
         lib = load()
@@ -268,6 +270,9 @@ class Context:
         if not stream.cuda_stream and 0 <= int(device) < torch.cuda.device_count():
             self._own = _take_stream(int(device))
             self._pool = torch.cuda.ExternalStream(self._own, device=self.device)
+        elif stream.cuda_stream and stream.device == self.device:
+            self._pool = stream
+        if self._pool is not None:
             self._pool_at = (self._pool.stream_id, self._pool.device_index, self._pool.device_type)
         st = lib.gsbc_create(ctypes.byref(h), int(device), ctypes.c_void_p(self._own or stream.cuda_stream))
         if st != OK:
@@ -299,18 +304,23 @@ class Context:
     def _empty(self, *specs):
         """New output tensors, one per (shape, dtype), from the pool of the
         stream that writes them; a single one comes by itself."""
-        if self._pool is None:
+        now = None if self._pool is None else torch._C._cuda_getCurrentStream(self._pool_at[1])
+        if now is None or now == self._pool_at:
             out = [torch.empty(shape, dtype=dtype, device=self.device) for shape, dtype in specs]
-        elif torch._C._cuda_getDevice() != self._pool_at[1]:
-            with torch.cuda.stream(self._pool):
-                out = [torch.empty(shape, dtype=dtype, device=self.device) for shape, dtype in specs]
-        else:   # the same without the context manager's 6 us a call
-            now = torch._C._cuda_getCurrentStream(self._pool_at[1])
-            torch._C._cuda_setStream(*self._pool_at)
-            try:
-                out = [torch.empty(shape, dtype=dtype, device=self.device) for shape, dtype in specs]
-            finally:
-                torch._C._cuda_setStream(*now)
+        else:
+            if torch._C._cuda_getDevice() != self._pool_at[1]:
+                with torch.cuda.stream(self._pool):
+                    out = [torch.empty(shape, dtype=dtype, device=self.device) for shape, dtype in specs]
+            else:   # the same without the context manager's 6 us a call
+                torch._C._cuda_setStream(*self._pool_at)
+                try:
+                    out = [torch.empty(shape, dtype=dtype, device=self.device) for shape, dtype in specs]
+                finally:
+                    torch._C._cuda_setStream(*now)
+            if now[0] != 0 or not self._own:   # (HIP orders a stream of its own and the default stream, whose id is 0)
+                user = torch.cuda.Stream(stream_id=now[0], device_index=now[1], device_type=now[2])
+                for t in out:
+                    t.record_stream(user)
         return out[0] if len(out) == 1 else out
 
     def _frame(self, H, W, image, transmittance, want_transmittance):

@@ -1,0 +1,62 @@
+"""GPU: outputs come from the pool of the stream that writes them, whatever
+stream is torch's current one, and are kept from being written again while that
+one may still read them."""
+import pytest
+
+from paper_2607_14513_amd import synth
+from test_gpu_two_contexts import _scene
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+SLEEP = 100_000_000   # cycles: some 50 ms
+
+
+def test_contexts_on_streams_of_the_caller():
+    """A dropped output does not become another context's, nor a torch
+    tensor's of the current stream, while its kernel may still write it."""
+    from paper_2607_14513_amd import gsbc
+    sa, sb = torch.cuda.Stream(), torch.cuda.Stream()
+    dirs = torch.from_numpy(synth.make_dirs(64, seed=7)).cuda()
+    torch.cuda.synchronize()
+    with gsbc.Context(0, stream=sa) as a, gsbc.Context(0, stream=sb) as b:
+        xa, xb = _scene(a, gsbc, 20_011, 5), _scene(b, gsbc, 20_011, 6)
+        torch.cuda.synchronize()
+        ref = b.decode_eval(*xb, dirs)
+        b.sync()
+        ref = ref.clone()
+        torch.cuda.synchronize()
+        for _ in range(4):
+            p = a.decode_eval(*xa, dirs).data_ptr()   # dropped at once, its kernel still running
+            t = torch.empty_like(ref)
+            out = b.decode_eval(*xb, dirs)
+            assert p not in (out.data_ptr(), t.data_ptr())
+            b.sync()
+            assert torch.equal(out, ref)
+        torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("own", [True, False])
+def test_output_read_on_another_stream(own):
+    """An output made and read under stream t, dropped while t still reads."""
+    from paper_2607_14513_amd import gsbc
+    t, s = torch.cuda.Stream(), None if own else torch.cuda.Stream()
+    d0, d1 = (torch.from_numpy(synth.make_dirs(64, seed=k)).cuda() for k in (8, 9))
+    torch.cuda.synchronize()
+    with gsbc.Context(0, stream=s) as ctx:
+        x = _scene(ctx, gsbc, 20_011, 5)
+        torch.cuda.synchronize()
+        ref = ctx.decode_eval(*x, d0)
+        ctx.sync()
+        ref = ref.cpu()
+        with torch.cuda.stream(t):
+            out = ctx.decode_eval(*x, d0)
+            ctx.sync()
+            torch.cuda._sleep(SLEEP)
+            got = out.clone()
+        p = out.data_ptr()
+        del out
+        again = ctx.decode_eval(*x, d1)
+        assert again.data_ptr() != p
+        torch.cuda.synchronize()
+        assert torch.equal(got.cpu(), ref)
