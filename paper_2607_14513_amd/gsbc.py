@@ -216,7 +216,7 @@ def _sizes(desc):
 # those pools few).  At most _SPARE_STREAMS a device; the others are destroyed.
 _SPARE_STREAMS = 8
 _spare_streams = {}
-_spare_lock = threading.Lock()
+_spare_lock = threading.RLock()   # (a collection while it is held may close a context)
 
 
 def _take_stream(device):

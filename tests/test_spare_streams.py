@@ -1,0 +1,42 @@
+"""The streams of closed contexts: a context collected while their lock is held
+closes without waiting for it.  CPU only (made-up handles)."""
+import threading
+
+import pytest
+
+torch = pytest.importorskip("torch")
+from paper_2607_14513_amd import gsbc  # noqa: E402
+
+
+class _Lib:
+    def __init__(self, status):
+        self.status = status
+
+    def gsbc_destroy(self, h):
+        return self.status
+
+
+def _context(handle):
+    c = object.__new__(gsbc.Context)
+    c._h, c._own, c.device = 1, handle, torch.device("cuda", 0)
+    return c
+
+
+def test_closing_a_context_inside_the_lock(monkeypatch):
+    monkeypatch.setattr(gsbc, "load", lambda: _Lib(gsbc.OK))
+
+    class Collects(dict):
+        def setdefault(self, key, value):          # as a collection here would
+            spare = super().setdefault(key, value)
+            if not spare:
+                spare.append(0)
+                _context(11).close()
+            return spare
+
+    monkeypatch.setattr(gsbc, "_spare_streams", Collects())
+    t = threading.Thread(target=lambda: _context(12).close(), daemon=True)
+    t.start()
+    t.join(20)
+    assert not t.is_alive()
+    assert sorted(gsbc._spare_streams[0]) == [0, 11, 12]
+
