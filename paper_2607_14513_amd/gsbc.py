@@ -283,11 +283,11 @@ class Context:
 
     def close(self):
         if getattr(self, "_h", None):
-            load().gsbc_destroy(self._h)
+            st = load().gsbc_destroy(self._h)
             self._h = None
-            if self._own:
+            if self._own and st == OK:   # (one that could not be waited for goes to no other context)
                 _give_stream(self.device.index, self._own)
-                self._own = None
+            self._own = None
 
     def __del__(self):
         try:

@@ -1,5 +1,6 @@
 """The streams of closed contexts: a context collected while their lock is held
-closes without waiting for it.  CPU only (made-up handles)."""
+closes without waiting for it, and a stream that could not be waited for is not
+handed on.  CPU only (made-up handles)."""
 import threading
 
 import pytest
@@ -40,3 +41,12 @@ def test_closing_a_context_inside_the_lock(monkeypatch):
     assert not t.is_alive()
     assert sorted(gsbc._spare_streams[0]) == [0, 11, 12]
 
+
+@pytest.mark.parametrize("status,spare", [(gsbc.OK, [21]), (gsbc.E_DEVICE, [])])
+def test_only_streams_that_were_waited_for(monkeypatch, status, spare):
+    monkeypatch.setattr(gsbc, "load", lambda: _Lib(status))
+    monkeypatch.setattr(gsbc, "_spare_streams", {})
+    c = _context(21)
+    c.close()
+    assert gsbc._spare_streams.get(0, []) == spare
+    assert c._h is None and c._own is None
