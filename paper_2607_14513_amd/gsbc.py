@@ -213,18 +213,21 @@ def _sizes(desc):
 
 # Blocking HIP streams of closed contexts, per device, for the next ones (a
 # stream's handle names a pool of torch's allocator: reusing handles keeps
-# those pools few).  At most _SPARE_STREAMS a device; the others are destroyed.
+# those pools few).  At most _SPARE_STREAMS a device; the others are destroyed,
+# each once no output in its pool is alive: its handle may then name another
+# stream, which would take memory that the default stream still reads.
 _SPARE_STREAMS = 8
 _spare_streams = {}
+_held_streams = {}   # to be destroyed
 _spare_lock = threading.RLock()   # (a collection while it is held may close a context)
 
 
 def _take_stream(device):
     """A blocking stream of `device` that no open context uses."""
     with _spare_lock:
-        spare = _spare_streams.get(device)
-        if spare:
-            return spare.pop()
+        for streams in (_spare_streams, _held_streams):
+            if streams.get(device):
+                return streams[device].pop()
     h = ctypes.c_void_p()
     with torch.cuda.device(device):
         st = load().hipStreamCreate(ctypes.byref(h))
@@ -237,10 +240,27 @@ def _give_stream(device, handle):
     """The stream of a closed context (idle: gsbc_destroy waits for it)."""
     with _spare_lock:
         spare = _spare_streams.setdefault(device, [])
+        held = _held_streams.setdefault(device, [])
         if len(spare) < _SPARE_STREAMS:
             spare.append(handle)
+        else:
+            held.append(handle)
+        if not held:
             return
-    load().hipStreamDestroy(ctypes.c_void_p(handle))
+    alive = _pools_alive(device)
+    with _spare_lock:
+        drop = [h for h in held if h not in alive]
+        held[:] = [h for h in held if h in alive]
+    if drop:
+        torch.cuda.default_stream(device).synchronize()   # what was freed may still be read there
+    for h in drop:
+        load().hipStreamDestroy(ctypes.c_void_p(h))
+
+
+def _pools_alive(device):
+    """Handles of the streams of `device` in whose pools of torch's allocator a tensor is alive."""
+    return {seg["stream"] for seg in torch.cuda.memory_snapshot()
+            if seg["device"] == device and any(b["state"] != "inactive" for b in seg["blocks"])}
 
 
 class Context:

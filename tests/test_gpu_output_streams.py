@@ -60,3 +60,25 @@ def test_output_read_on_another_stream(own):
         assert again.data_ptr() != p
         torch.cuda.synchronize()
         assert torch.equal(got.cpu(), ref)
+
+
+def test_streams_of_living_outputs():
+    """More contexts than the spare streams, closed while their outputs live:
+    no stream is destroyed before its outputs are gone."""
+    from paper_2607_14513_amd import gsbc
+    dirs = torch.from_numpy(synth.make_dirs(3, seed=8)).cuda()
+    many = [gsbc.Context(0) for _ in range(gsbc._SPARE_STREAMS + 3)]
+    x = _scene(many[0], gsbc, 1_003, 9)
+    outs = {c._own: c.decode_eval(*x, dirs) for c in many}
+    for c in many:
+        c.close()
+    assert set(outs) <= set(gsbc._spare_streams[0]) | set(gsbc._held_streams[0])
+    assert gsbc._held_streams[0] and set(gsbc._held_streams[0]) <= gsbc._pools_alive(0)
+    ref = outs.popitem()[1].cpu()
+    assert all(torch.equal(o.cpu(), ref) for o in outs.values())
+    held = set(gsbc._held_streams[0])
+    del outs, x
+    more = [gsbc.Context(0) for _ in range(gsbc._SPARE_STREAMS)]   # the spare ones
+    for c in more + [gsbc.Context(0)]:
+        c.close()
+    assert held and not held & set(gsbc._held_streams[0]) - gsbc._pools_alive(0)

@@ -1,6 +1,7 @@
 """The streams of closed contexts: a context collected while their lock is held
-closes without waiting for it, and a stream that could not be waited for is not
-handed on.  CPU only (made-up handles)."""
+closes without waiting for it, a stream that could not be waited for is not
+handed on, and one whose outputs are alive is not destroyed.  CPU only (made-up
+handles)."""
 import threading
 
 import pytest
@@ -13,8 +14,13 @@ class _Lib:
     def __init__(self, status):
         self.status = status
 
+        self.destroyed = []
+
     def gsbc_destroy(self, h):
         return self.status
+
+    def hipStreamDestroy(self, h):
+        self.destroyed.append(h.value)
 
 
 def _context(handle):
@@ -50,3 +56,24 @@ def test_only_streams_that_were_waited_for(monkeypatch, status, spare):
     c.close()
     assert gsbc._spare_streams.get(0, []) == spare
     assert c._h is None and c._own is None
+
+
+def test_stream_of_a_living_output_is_kept(monkeypatch):
+    lib, waited = _Lib(gsbc.OK), []
+    most = gsbc._SPARE_STREAMS
+    segments = [{"stream": 100 + k, "device": 0, "blocks": [{"state": "active_allocated"}, {"state": "inactive"}]}
+                for k in range(most + 3)]
+    monkeypatch.setattr(gsbc, "load", lambda: lib)
+    monkeypatch.setattr(gsbc, "_spare_streams", {})
+    monkeypatch.setattr(gsbc, "_held_streams", {}, raising=False)
+    monkeypatch.setattr(torch.cuda, "memory_snapshot", lambda: segments)
+    monkeypatch.setattr(torch.cuda, "default_stream",
+                        lambda d: type("S", (), {"synchronize": lambda self: waited.append(list(lib.destroyed))})())
+    for k in range(most + 2):
+        _context(100 + k).close()
+    assert lib.destroyed == [] and len(gsbc._spare_streams[0]) == most
+    segments[most]["blocks"] = [{"state": "inactive"}]       # its outputs are gone
+    _context(100 + most + 2).close()
+    assert lib.destroyed == [100 + most] and waited == [[]]
+    kept = {gsbc._take_stream(0) for _ in range(most + 2)}   # the others go to the next contexts
+    assert kept == {100 + k for k in range(most + 3)} - {100 + most}
