@@ -1139,7 +1139,21 @@ __device__ __forceinline__ uint32_t tile_mask(int t, int i)
     return 0xFFFFu;
 }
 
-// Bounds of every candidate.  A wave takes 16 blocks at a time: with
+// Where a block's first fits come from, by the modes that are on.  Usually the
+// best-bounded 3-subset partition in mode 2 and the best-bounded rotation.
+// Without modes 2, 4 and 5 the best-bounded 2-subset partition, or mode 0's.
+// With one-subset modes only, every candidate is fitted and nothing bounded:
+// 13 at most, and the bounds cost as much as a few (1,048,576 blocks in mode 6
+// alone: 1,999 us bounded and gathered, 544 fitted; without a first fit that
+// rules others out mode 0 alone takes 4,390 us, with one 1,117; mode 1 8,650 and
+// 1,141; exhaustive 2,213 and 5,408).
+enum { kSeedUsual, kSeedOther, kSeedEvery };
+__host__ __device__ inline int seed_kind(uint32_t mode_mask)
+{
+    return !(mode_mask & 0x8F) ? kSeedEvery : mode_mask & 0x34 ? kSeedUsual : kSeedOther;
+}
+
+// Bounds of every candidate of the modes that are on.  A wave takes 16 blocks at a time: with
 // v_mfma_f32_16x16x32_bf16, lane l supplies row l%16 of A (a mask) and
 // column l%16 of B (a block's texel feature) for k = 8 (l/16) .. + 7, and
 // receives rows 4 (l/16) .. + 3 of column l%16: four subsets of one block,
@@ -1167,6 +1181,8 @@ __global__ __launch_bounds__(kWG) void k_bc7_bounds(Bc7Search L, uint32_t per)
     }
     __syncthreads();
     const EncodeArgs &a = L.a;
+    const bool on2 = a.mode_mask & 0x8A, other = seed_kind(a.mode_mask) == kSeedOther;
+    const int tiles3 = a.mode_mask & 0x04 ? 8 : a.mode_mask & 0x01 ? 2 : 0;   // mode 0 has 16 partitions
     const int lane = threadIdx.x & 63, grp = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t c0 = (uint64_t)blockIdx.x * per, g0 = L.first + c0;   // a workgroup lies in one run
@@ -1232,8 +1248,9 @@ __global__ __launch_bounds__(kWG) void k_bc7_bounds(Bc7Search L, uint32_t per)
             if (grp == 0) L.B.seed[c] = (least & 255u) << 8 | lb6 << 16;
         }
         // 2-subset partitions: rows are subset 1, the total less them subset 0
+        uint32_t least = ~0u;
 #pragma unroll 1
-        for (int t = 0; t < 4; t++) {
+        for (int t = 0; t < (on2 ? 4 : 0); t++) {
             sums(t, D);
             const uint32_t cnt = count[t][grp];
             uint32_t lb[4];
@@ -1247,11 +1264,13 @@ __global__ __launch_bounds__(kWG) void k_bc7_bounds(Bc7Search L, uint32_t per)
                                 bound_term(residual_root(n0, s0), n0, __builtin_amdgcn_rcpf(n0), kSlack3));
             }
             L.B.b2[(uint64_t)(4 * t + grp) * L.B.nc + c] = make_uint2(lb[0] | lb[1] << 16, lb[2] | lb[3] << 16);
+            if (other)
+#pragma unroll
+                for (int r = 0; r < 4; r++) least = min(least, lb[r] << 8 | (uint32_t)(16 * t + 4 * grp + r));
         }
         // 3-subset partitions: two rows each
-        uint32_t least = ~0u;
 #pragma unroll 1
-        for (int t = 0; t < 8; t++) {
+        for (int t = 0; t < tiles3; t++) {
             sums(4 + t, D);
             const uint32_t cnt = count[4 + t][grp];
             uint32_t lb[2], lb0[2];
@@ -1266,7 +1285,7 @@ __global__ __launch_bounds__(kWG) void k_bc7_bounds(Bc7Search L, uint32_t per)
                 const float q0 = __builtin_amdgcn_rcpf(n0), q1 = __builtin_amdgcn_rcpf(n1), q2 = __builtin_amdgcn_rcpf(n2);
                 lb[h] = bound16(bound_term(r0, n0, q0, kSlack2) + bound_term(r1, n1, q1, kSlack2) + bound_term(r2, n2, q2, kSlack2));
                 lb0[h] = bound16(bound_term(r0, n0, q0, kSlack3) + bound_term(r1, n1, q1, kSlack3) + bound_term(r2, n2, q2, kSlack3));
-                least = min(least, lb[h] << 8 | (uint32_t)(8 * t + 2 * grp + h));
+                if (!(other && on2)) least = min(least, (other ? lb0[h] : lb[h]) << 8 | (uint32_t)(8 * t + 2 * grp + h));
             }
             L.B.b3[(uint64_t)(4 * t + grp) * L.B.nc + c] = lb[0] | lb[1] << 16;
             if (t < 2) L.B.b0[(uint64_t)(4 * t + grp) * L.B.nc + c] = lb0[0] | lb0[1] << 16;
@@ -1282,8 +1301,9 @@ __global__ __launch_bounds__(kWG) void k_bc7_bounds(Bc7Search L, uint32_t per)
 // fits the 3-subset seed and writes the words of the 3-subset partitions, the
 // other the rotation seed and the other words (4,112 blocks: 76 -> 57 us;
 // 524,288 blocks: 205 -> 250 us, where a wave does both).  The seeds' own bits
-// are cleared (they are fitted here).
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k_bc7_seed(Bc7Search L, bool pairs)
+// are cleared (they are fitted here).  SEEDS: see seed_kind.
+template <int SEEDS>
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(SEEDS == kSeedUsual ? 4 : 3))) void k_bc7_seed(Bc7Search L, bool pairs)
 {
     __shared__ TexLds S;
     __shared__ uint32_t s_key[4][64];
@@ -1303,10 +1323,40 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
     bool one = live;
 #pragma unroll
     for (int i = 1; i < 16; i++) one &= S.rg[i][threadIdx.x] == S.rg[0][threadIdx.x] && S.bx[i][threadIdx.x] == S.bx[0][threadIdx.x];
-    const uint32_t seed = L.B.seed[c];
-    const int p3 = one ? 0 : (int)(seed & 255u), rot = (int)((seed >> 8) & 255u);
+    const bool on2 = a.mode_mask & 0x8A;
+    const uint32_t seed = SEEDS == kSeedEvery ? 0u : L.B.seed[c];
+    // the seeds: a 3-subset partition, a 2-subset partition, a rotation (-1: none)
+    const int p = one ? 0 : (int)(seed & 255u);
+    const int p3 = SEEDS == kSeedUsual || !on2 ? p : -1, p2 = SEEDS == kSeedOther && on2 ? p : -1;
+    const int rot = SEEDS == kSeedUsual ? (int)((seed >> 8) & 255u) : -1;
     uint32_t key = ~0u;
-    if (live) {
+    if (SEEDS == kSeedEvery && live) {
+        if (a.mode_mask & 0x30)
+#pragma unroll 1
+            for (int r = parts ? 0 : 2; r < (others ? 4 : 2); r++) key = min(key, search_rotation(S, r, a.mode_mask, L.T.sv));
+        if (others && (a.mode_mask & 0x40)) key = min(key, search_mode6(S, L.T.sv));
+    }
+    if (SEEDS == kSeedOther && live) {
+        uint32_t e[3] = {a.mode_mask & 0x02 ? 0u : kGone, a.mode_mask & 0x08 ? 0u : kGone, a.mode_mask & 0x80 ? 0u : kGone};
+        if (on2 && others) {
+#pragma unroll 1
+            for (int s = 0; s < 2; s++) {
+                const uint32_t m = mask2(p2, s);
+                add_subset<kTwo>(S, m, subset_sums(S, m, 0), L.T.sv, e);
+            }
+            key = partition_key<kTwo>(p2, e);
+        }
+        if (!on2 && parts) {
+            e[0] = 0;
+#pragma unroll 1
+            for (int s = 0; s < 3; s++) {
+                const uint32_t m = mask3(p3, s);
+                add_subset<kThree0>(S, m, subset_sums(S, m, 0), L.T.sv, e);
+            }
+            key = partition_key<kThree0>(p3, e);
+        }
+    }
+    if (SEEDS == kSeedUsual && live) {
         if (parts) {
             if (a.mode_mask & 0x04) {
                 uint32_t e[3] = {0, 0, 0};
@@ -1326,6 +1376,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
         key = min(key, s_key[wave ^ 1][lane]);
     }
     if (parts) a.keys[g] = key;
+    if (SEEDS == kSeedEvery) return;
     // 0 .. thr: bounds that may still win (with no seed, all of them; past the
     // run, none; only partition 0 of a block of one colour)
     const int thr = !live ? -1 : key == ~0u ? 0xFFFF : (int)bound16((float)(key >> 9));
@@ -1336,37 +1387,44 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
         if (lane == at) w = m;
     };
     uint64_t *words = L.words + (c >> 6) * kWords;
-    if (parts) {
+    // (only the words of modes that are on: their bounds are there, and the search reads no others)
+    const int p0 = SEEDS == kSeedOther ? p3 : -1;   // mode 0's seed
+    if (SEEDS == kSeedUsual && parts && (a.mode_mask & 0x04)) {
 #pragma unroll 4
         for (int q = 0; q < 32; q++) {
             const uint32_t v = L.B.b3[q * L.B.nc + c];
             put(w0, 2 * q, (int)(v & 0xFFFFu) <= (q ? thrp : thr) && p3 != 2 * q);
             put(w0, 2 * q + 1, (int)(v >> 16) <= thrp && p3 != 2 * q + 1);
         }
+        words[kWordAt[kThree2] + lane] = w0;
+    }
+    if (parts && (a.mode_mask & 0x01)) {
 #pragma unroll 4
         for (int q = 0; q < 8; q++) {
             const uint32_t v = L.B.b0[q * L.B.nc + c];
-            put(w1, 2 * q, (int)(v & 0xFFFFu) <= (q ? thrp : thr));
-            put(w1, 2 * q + 1, (int)(v >> 16) <= thrp);
+            put(w1, 2 * q, (int)(v & 0xFFFFu) <= (q ? thrp : thr) && (SEEDS == kSeedUsual || p0 != 2 * q));
+            put(w1, 2 * q + 1, (int)(v >> 16) <= thrp && (SEEDS == kSeedUsual || p0 != 2 * q + 1));
         }
-        words[kWordAt[kThree2] + lane] = w0;
         if (lane < 16) words[kWordAt[kThree0] + lane] = w1;
     }
     if (others) {
+        if (on2) {
 #pragma unroll 4
-        for (int q = 0; q < 16; q++) {
-            const uint2 v = L.B.b2[q * L.B.nc + c];
-            put(w0, 4 * q, (int)(v.x & 0xFFFFu) <= (q ? thrp : thr));
-            put(w0, 4 * q + 1, (int)(v.x >> 16) <= thrp);
-            put(w0, 4 * q + 2, (int)(v.y & 0xFFFFu) <= thrp);
-            put(w0, 4 * q + 3, (int)(v.y >> 16) <= thrp);
+            for (int q = 0; q < 16; q++) {
+                const uint2 v = L.B.b2[q * L.B.nc + c];
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    const uint32_t lb = ((r < 2 ? v.x : v.y) >> (16 * (r & 1))) & 0xFFFFu;
+                    put(w0, 4 * q + r, (int)lb <= (q + r ? thrp : thr) && (SEEDS == kSeedUsual || p2 != 4 * q + r));
+                }
+            }
+            words[kWordAt[kTwo] + lane] = w0;
         }
         const uint2 vr = L.B.br[c];
 #pragma unroll
         for (int r = 0; r < 4; r++)
             put(w1, r, (int)(((r < 2 ? vr.x : vr.y) >> (16 * (r & 1))) & 0xFFFFu) <= thr && rot != r);
         put(w1, 4, (int)(seed >> 16) <= thr);
-        words[kWordAt[kTwo] + lane] = w0;
         if (lane < 5) words[kWordAt[kRot] + lane] = w1;
     }
 }
@@ -1894,11 +1952,14 @@ hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t 
         Q.first = first;
         Q.slices = (uint32_t)(left / 64);
         const uint32_t per = left >= (1u << 17) ? kWG : 64;
-        GSBC_LAUNCH("bc7_bounds", k_bc7_bounds, dim3((uint32_t)(left / per)), dim3(kWG), 0, st, Q, per);
+        const int seeds = seed_kind(a.mode_mask);
+        if (seeds != kSeedEvery) GSBC_LAUNCH("bc7_bounds", k_bc7_bounds, dim3((uint32_t)(left / per)), dim3(kWG), 0, st, Q, per);
         if (alone && !seeds_fill && first == 0 && (e = hipEventRecord(alone, st)) != hipSuccess) return e;
         const bool pairs = left < (1u << 17);
-        GSBC_LAUNCH("bc7_seed", k_bc7_seed, dim3((uint32_t)(left / (pairs ? kWG / 2 : kWG))), dim3(kWG), 0, st, Q, pairs);
+        auto seed = seeds == kSeedUsual ? k_bc7_seed<kSeedUsual> : seeds == kSeedOther ? k_bc7_seed<kSeedOther> : k_bc7_seed<kSeedEvery>;
+        GSBC_LAUNCH("bc7_seed", seed, dim3((uint32_t)(left / (pairs ? kWG / 2 : kWG))), dim3(kWG), 0, st, Q, pairs);
         if (alone && seeds_fill && first == 0 && (e = hipEventRecord(alone, st)) != hipSuccess) return e;
+        if (seeds == kSeedEvery) continue;
         if (split == 0) {
             if ((e = launch(0, kType3, "bc7_search_3subset")) != hipSuccess) return e;
             if ((e = launch(1, kType1, "bc7_search_1subset")) != hipSuccess) return e;
