@@ -793,6 +793,133 @@ __device__ __forceinline__ uint32_t partition_key(int p, const uint32_t (&e)[3])
 // member loops and keeps all texels in registers, which spill.
 __device__ __forceinline__ uint32_t all_texels() { return 0xFFFFu + g_bc7_opaque_zero; }
 
+// ---- visiting order of the 3-subset partitions, where every one is fitted
+//
+// Of the 192 subset masks of the 64 three-subset partitions only 140 differ
+// (36 of the 48 of partitions 0..15, the ones mode 0 also uses).  They are
+// visited in the order below; a mask that recurs is fitted once and its SSE
+// kept in an LDS slot of its lane until its last use.  This order (found
+// offline by a local search) needs at most kSlots2 slots for mode 2 and kSlots0
+// for mode 0; a static check below recomputes both.
+constexpr int kOrder3[64] = {62, 9,  2,  0,  60, 42, 61, 27, 38, 18, 46, 33, 51, 47, 55, 41,
+                             31, 17, 63, 15, 23, 10, 36, 22, 8,  56, 29, 4,  3,  24, 6,  32,
+                             25, 19, 14, 37, 34, 7,  26, 43, 52, 5,  54, 50, 20, 48, 1,  39,
+                             58, 13, 35, 57, 53, 30, 21, 59, 49, 40, 28, 45, 16, 11, 44, 12};
+constexpr int kSlots2 = 6, kSlots0 = 4;
+
+// What is done at visit t (partition kOrder3[t]), subset s, per mode:
+//   kFit           fit the subset
+//   kKeep | slot   fit it and keep the SSE in the slot (the mask recurs)
+//   kTake | slot   take the SSE from the slot (fitted at an earlier visit)
+constexpr uint8_t kFit = 0, kKeep = 0x40, kTake = 0x80;
+struct Plan3 {
+    uint8_t act[2][64][3];   // [0]: mode 2 (all partitions), [1]: mode 0 (partitions 0..15)
+    int slots[2];            // slots each mode needs
+};
+
+constexpr Plan3 make_plan3()
+{
+    Plan3 P{};
+    for (int mode = 0; mode < 2; mode++) {
+        // each visit's mask, then its last visit
+        uint32_t mk[192] = {};
+        int pos[192] = {}, n = 0;
+        for (int t = 0; t < 64; t++)
+            for (int s = 0; s < 3; s++)
+                if (mode == 0 || kOrder3[t] < 16) { mk[n] = mask3_of(kPart3[kOrder3[t]], s); pos[n] = t * 3 + s; n++; }
+        bool used[8] = {};
+        uint32_t held[8] = {};
+        int most = 0;
+        for (int q = 0; q < n; q++) {
+            int later = -1, slot = -1;
+            for (int r = q + 1; r < n; r++)
+                if (mk[r] == mk[q]) { later = r; break; }
+            for (int z = 0; z < 8; z++)
+                if (used[z] && held[z] == mk[q]) slot = z;
+            uint8_t a = kFit;
+            if (slot >= 0) {
+                a = (uint8_t)(kTake | slot);
+                if (later < 0) used[slot] = false;   // last use
+            } else if (later >= 0) {
+                int z = 0;
+                while (used[z]) z++;
+                used[z] = true;
+                held[z] = mk[q];
+                a = (uint8_t)(kKeep | z);
+                int live = 0;
+                for (int y = 0; y < 8; y++) live += used[y] ? 1 : 0;
+                most = live > most ? live : most;
+            }
+            P.act[mode][pos[q] / 3][pos[q] % 3] = a;
+        }
+        P.slots[mode] = most;
+    }
+    return P;
+}
+constexpr Plan3 kPlan3 = make_plan3();
+static_assert(kPlan3.slots[0] <= kSlots2 && kPlan3.slots[1] <= kSlots0, "3-subset visiting order needs more slots");
+
+// Per-lane SSE slots (kSlots2 for mode 2, then kSlots0 for mode 0), one column
+// per lane.
+typedef uint32_t Cache3[kSlots2 + kSlots0][kWG];
+
+// The best key over every 2-subset partition (THREE: 3-subset partition).
+template <bool THREE>
+__device__ __forceinline__ uint32_t search_every(const TexLds &S, Cache3 &cache, uint32_t mode_mask, const uint32_t *sv)
+{
+    uint32_t best = 0xFFFFFFFFu;
+    if (!THREE) {
+        const Sums tot = subset_sums(S, all_texels(), 0);
+        for (int p = 0; p < 64; p++) {
+            const uint32_t m0 = mask2(p, 0), m1 = mask2(p, 1);
+            const Sums s0 = subset_sums(S, m0, 0);
+            const Prep P0 = prep_subset(S, m0, 0, s0), P1 = prep_subset(S, m1, 0, sums_minus(tot, s0));
+            if (mode_mask & 0x02)
+                consider(fit_colour<6, 1, 3, true>(S, m0, 0, P0, sv).sse + fit_colour<6, 1, 3, true>(S, m1, 0, P1, sv).sse,
+                         16 + p, best);
+            if (mode_mask & 0x08)
+                consider(fit_colour<7, 2, 2, true>(S, m0, 0, P0, sv).sse + fit_colour<7, 2, 2, true>(S, m1, 0, P1, sv).sse,
+                         144 + p, best);
+            if (mode_mask & 0x80)
+                consider(fit_colour<5, 2, 2, true>(S, m0, 0, P0, sv).sse + fit_colour<5, 2, 2, true>(S, m1, 0, P1, sv).sse,
+                         221 + p, best);
+        }
+    } else {
+        const bool on2 = mode_mask & 0x04, on0 = mode_mask & 0x01;
+        for (int t = 0; t < 64; t++) {
+            const int p = kOrder3[t];
+            if (!on2 && p >= 16) continue;
+            const bool with0 = on0 && p < 16;
+            uint32_t e2 = 0, e0 = 0;
+#pragma unroll 1
+            for (int s = 0; s < 3; s++) {
+                const uint32_t msk = mask3(p, s);
+                const int a2 = kPlan3.act[0][t][s], a0 = kPlan3.act[1][t][s];
+                const bool fit2 = on2 && !(a2 & kTake), fit0 = with0 && !(a0 & kTake);
+                uint32_t v2 = 0, v0 = 0;
+                if (on2 && (a2 & kTake)) v2 = cache[a2 & 15][threadIdx.x];
+                if (with0 && (a0 & kTake)) v0 = cache[kSlots2 + (a0 & 15)][threadIdx.x];
+                if (fit2 || fit0) {
+                    const Prep P = prep_subset(S, msk, 0);
+                    if (fit2) {
+                        v2 = fit_colour<5, 0, 2, true>(S, msk, 0, P, sv).sse;
+                        if (a2 & kKeep) cache[a2 & 15][threadIdx.x] = v2;
+                    }
+                    if (fit0) {
+                        v0 = fit_colour<4, 2, 3, true>(S, msk, 0, P, sv).sse;
+                        if (a0 & kKeep) cache[kSlots2 + (a0 & 15)][threadIdx.x] = v0;
+                    }
+                }
+                e2 += v2;
+                e0 += v0;
+            }
+            if (on2) consider(e2, 80 + p, best);
+            if (with0) consider(e0, p, best);
+        }
+    }
+    return best;
+}
+
 // rotation r: modes 4 (both index selections) and 5
 __device__ __forceinline__ uint32_t search_rotation(const TexLds &S, int r, uint32_t mode_mask, const uint32_t *sv)
 {
@@ -1083,6 +1210,7 @@ struct Bc7Search {
     uint32_t slices;            // slices of the chunk
     Bounds B;
     uint64_t *words;            // [slice][kWords]
+    uint32_t *dense;            // slices that k_bc7_every takes: their number, then a list; or null
     const uint8_t **src;        // [slice] texels of the slice's first block
     uint32_t win[kTypes];       // search: slices per window, per type
     uint32_t types;             // search: candidate types of this launch, bit per type
@@ -1159,8 +1287,16 @@ __host__ __device__ inline int seed_kind(uint32_t mode_mask)
     return !(mode_mask & 0x8F) ? kSeedEvery : mode_mask & 0x34 ? kSeedUsual : kSeedOther;
 }
 
-// Bounds of every candidate of the modes that are on.  A wave takes 16 blocks at a time: with
-// v_mfma_f32_16x16x32_bf16, lane l supplies row l%16 of A (a mask) and
+// With partitions of one shape only, slices whose blocks keep this share (%) of
+// the candidates after the first fits have them all fitted in order instead: the
+// gathers and the masks fitted more than once cost more than the little that is
+// ruled out saves (1,048,576 blocks along gradients in mode 2 5.6 -> 4.1 ms, in
+// mode 1 7.7 -> 6.3; exhaustive 3.2 and 5.4).  With both shapes the second test
+// rules out more than that (all modes 16.6 -> 18.7 ms).
+constexpr uint32_t kDense = 85;
+
+// Bounds of every candidate of the modes that are on.  A wave takes 16 blocks
+// at a time: with v_mfma_f32_16x16x32_bf16, lane l supplies row l%16 of A (a mask) and
 // column l%16 of B (a block's texel feature) for k = 8 (l/16) .. + 7, and
 // receives rows 4 (l/16) .. + 3 of column l%16: four subsets of one block,
 // every feature of them in the same lane.  k < 16 are the texels' values or
@@ -1195,6 +1331,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
     const BlockRun run = a.run[find_run(a.run, a.nrun, g0)];
     const uint64_t b0 = g0 - run.gbase;
     if (threadIdx.x < per / 64) L.src[(c0 >> 6) + threadIdx.x] = run.src + (b0 + 64 * threadIdx.x) * 64;
+    if (L.dense && blockIdx.x == 0 && threadIdx.x == 0) L.dense[0] = 0;
     const uint32_t sh = lane < 32 ? 0u : 8u, lin = lane < 32 ? 0xFFu : 0u;
     for (uint32_t sb = wave; sb < per / 16; sb += kWG / 64) {
         const uint64_t b = b0 + 16 * sb + (lane & 15), c = c0 + 16 * sb + (lane & 15);
@@ -1412,7 +1549,6 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(SEEDS == kS
             put(w0, 2 * q, (int)(v & 0xFFFFu) <= (q ? thrp : thr) && p3 != 2 * q);
             put(w0, 2 * q + 1, (int)(v >> 16) <= thrp && p3 != 2 * q + 1);
         }
-        words[kWordAt[kThree2] + lane] = w0;
     }
     if (parts && (a.mode_mask & 0x01)) {
 #pragma unroll 4
@@ -1421,7 +1557,22 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(SEEDS == kS
             put(w1, 2 * q, (int)(v & 0xFFFFu) <= (q ? thrp : thr) && (SEEDS == kSeedUsual || p0 != 2 * q));
             put(w1, 2 * q + 1, (int)(v >> 16) <= thrp && (SEEDS == kSeedUsual || p0 != 2 * q + 1));
         }
-        if (lane < 16) words[kWordAt[kThree0] + lane] = w1;
+    }
+    // slices most of whose blocks keep most partitions go to k_bc7_every
+    auto is_dense = [&](uint64_t u, uint64_t v, uint32_t cands) {
+        if (!L.dense) return false;
+        uint32_t n = (uint32_t)__popcll(u) + (uint32_t)__popcll(v);
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) n += (uint32_t)__shfl_xor((int)n, d);
+        if (n * 100u < 64u * cands * kDense) return false;
+        if (lane == 0) L.dense[4 + atomicAdd(L.dense, 1u)] = (uint32_t)(c >> 6);
+        return true;
+    };
+    if (parts && (a.mode_mask & 0x05)) {
+        const uint32_t cands = (a.mode_mask & 0x04 ? 64u : 0u) + (a.mode_mask & 0x01 ? 16u : 0u);
+        if (is_dense(w0, w1, cands)) w0 = w1 = 0;
+        if (SEEDS == kSeedUsual && (a.mode_mask & 0x04)) words[kWordAt[kThree2] + lane] = w0;
+        if ((a.mode_mask & 0x01) && lane < 16) words[kWordAt[kThree0] + lane] = w1;
     }
     if (others) {
         if (on2) {
@@ -1434,6 +1585,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(SEEDS == kS
                     put(w0, 4 * q + r, (int)lb <= (q + r ? thrp : thr) && (SEEDS == kSeedUsual || p2 != 4 * q + r));
                 }
             }
+            if (is_dense(w0, 0, 64)) w0 = 0;
             words[kWordAt[kTwo] + lane] = w0;
         }
         const uint2 vr = L.B.br[c];
@@ -1443,6 +1595,27 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(SEEDS == kS
         put(w1, 4, (int)(seed >> 16) <= thr);
         if (lane < 5) words[kWordAt[kRot] + lane] = w1;
     }
+}
+
+// Slices that the seeds found dense, where one shape of partition is on: every
+// partition, one lane per block, the texels staged once.
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k_bc7_every(Bc7Search L)
+{
+    __shared__ TexLds S;
+    __shared__ Cache3 cache;
+    const uint32_t n = L.dense[0], at = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (blockIdx.x * 4 >= n) return;
+    stage_table(S, L.T.near64);
+    const uint32_t slice = L.dense[4 + min(at, n - 1)];
+    const uint64_t g0 = L.first + (uint64_t)slice * 64, g = g0 + (threadIdx.x & 63u);
+    const BlockRun run = L.a.run[find_run(L.a.run, L.a.nrun, g0)];
+    const uint64_t b = g - run.gbase;
+    const bool live = at < n && b < run.nblk;
+    stage_texels(S, run.src + b * 64, live);
+    __syncthreads();
+    if (live)
+        atomicMin(L.a.keys + g, L.a.mode_mask & 0x8A ? search_every<false>(S, cache, L.a.mode_mask, L.T.sv)
+                                                     : search_every<true>(S, cache, L.a.mode_mask, L.T.sv));
 }
 
 // Bit k (from 0) among the set bits of w.
@@ -1930,6 +2103,7 @@ hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t 
     const uint64_t nc = a.total < kBc7Chunk ? a.total : kBc7Chunk;
     Q.src = reinterpret_cast<const uint8_t **>(take(8 * (nc / 64)));
     Q.words = reinterpret_cast<uint64_t *>(take(8 * kWords * (nc / 64)));
+    uint32_t *const dense = reinterpret_cast<uint32_t *>(take(4 * (nc / 64) + 16));
     Q.B.nc = nc;
     Q.B.b2 = reinterpret_cast<uint2 *>(take(16 * 8 * nc));
     Q.B.b3 = reinterpret_cast<uint32_t *>(take(32 * 4 * nc));
@@ -1973,14 +2147,17 @@ hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t 
         Q.first = first;
         Q.slices = (uint32_t)(left / 64);
         const uint32_t per = left >= (1u << 17) ? kWG : 64;
+        const bool pairs = left < (1u << 17);
+        // (one shape of partition only: with both, what the other one reaches rules more out)
+        Q.dense = !pairs && !(a.mode_mask & 0x8A) != !(a.mode_mask & 0x05) ? dense : nullptr;
         const int seeds = seed_kind(a.mode_mask);
         if (seeds != kSeedEvery) GSBC_LAUNCH("bc7_bounds", k_bc7_bounds, dim3((uint32_t)(left / per)), dim3(kWG), 0, st, Q, per);
         if (alone && !seeds_fill && first == 0 && (e = hipEventRecord(alone, st)) != hipSuccess) return e;
-        const bool pairs = left < (1u << 17);
         auto seed = seeds == kSeedUsual ? k_bc7_seed<kSeedUsual> : seeds == kSeedOther ? k_bc7_seed<kSeedOther> : k_bc7_seed<kSeedEvery>;
         GSBC_LAUNCH("bc7_seed", seed, dim3((uint32_t)(left / (pairs ? kWG / 2 : kWG))), dim3(kWG), 0, st, Q, pairs);
         if (alone && seeds_fill && first == 0 && (e = hipEventRecord(alone, st)) != hipSuccess) return e;
         if (seeds == kSeedEvery) continue;
+        if (Q.dense) GSBC_LAUNCH("bc7_every", k_bc7_every, dim3((uint32_t)(left / kWG)), dim3(kWG), 0, st, Q);
         if (split == 0) {
             if ((e = launch(0, kType3, "bc7_search_3subset")) != hipSuccess) return e;
             if ((e = launch(1, kType1, "bc7_search_1subset")) != hipSuccess) return e;

@@ -166,13 +166,13 @@ struct EncodeArgs {
 };
 // Scratch bytes the BC7 encoder needs for `blocks` global indices (a
 // multiple of 256): a key per index, and for the indices of one chunk 300
-// bytes of candidate bounds each, a texel pointer and 149 candidate words
-// per 64.
+// bytes of candidate bounds each, a texel pointer, 149 candidate words and a
+// list entry per 64.
 constexpr uint64_t kBc7Chunk = 1u << 19;
 inline size_t bc7_scratch_bytes(uint64_t blocks)
 {
     const uint64_t nc = blocks < kBc7Chunk ? blocks : kBc7Chunk;
-    return (size_t)blocks * 4 + (nc / 64) * 150 * 8 + nc * 300 + 128;
+    return (size_t)blocks * 4 + (nc / 64) * (150 * 8 + 4) + nc * 300 + 160;
 }
 // How the BC7 candidate search is split over kernels: 0 -> three kernels
 // (2-subset, 3-subset, 1-subset modes), 1 -> two (the 1-subset modes folded

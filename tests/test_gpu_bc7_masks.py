@@ -46,3 +46,22 @@ def test_modes_in_large_encodes(mask):
                                params=gsbc.default_params(bc7_mode_mask=mask))
     got = out.cpu().numpy()[:16 * nblk].reshape(-1, 16)
     assert np.array_equal(got, np.tile(want.reshape(-1, 16), (-(-nblk // 336), 1))[:nblk])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mask", [0x01, 0x02, 0x04, 0x05, 0x42, 0x8A])
+def test_slices_that_keep_their_candidates(mask):
+    """Slices of 64 blocks that bounds rule little out of, among others, in two
+    chunks of the scratch and a ragged end; partitions of one shape."""
+    import torch
+    from paper_2607_14513_amd import gsbc
+    kinds = ["gradient", "random", "near_constant", "constant", "gradient", "two_level"]
+    unit = np.concatenate([_blocks(k, 64, 40 + i) for i, k in enumerate(kinds)])
+    nblk = (1 << 19) + (1 << 17) + 272
+    want, _ = O.bc7_encode(unit, mode_mask=mask)
+    with gsbc.Context(0) as ctx:
+        tex = torch.from_numpy(unit).cuda().repeat(-(-nblk // len(unit)), 1, 1)[:nblk].contiguous()
+        out, _, _ = ctx.encode(tex[None], _prim_desc(gsbc, nblk), fmt=gsbc.FMT_BC7, params=gsbc.default_params(bc7_mode_mask=mask))
+        ref = torch.from_numpy(want.reshape(-1, 16)).cuda().repeat(-(-nblk // len(unit)), 1)[:nblk]
+        ctx.sync()
+        assert torch.equal(out[:16 * nblk].view(-1, 16), ref)
