@@ -9,9 +9,8 @@ own with fixed integer decisions), so the tuner only compares times.
 
 The search is coordinate descent from the defaults: each knob in turn is
 set to the value with the least median time while the others stay fixed;
-two sweeps.  Results are cached in a JSON file keyed by device name,
-compute-unit count and a hash of the workload shape (block counts and band
-formats per scene).
+two sweeps.  Results are cached in a JSON file keyed by device name, compute-unit count and a hash of the
+library and the workload shape (block counts and band formats per scene).
 """
 import hashlib
 import json
@@ -35,9 +34,23 @@ def cache_path():
     return os.environ.get("GSBC_TUNE_CACHE", os.path.join(os.path.expanduser("~"), ".cache", "gsbc", "autotune.json"))
 
 
+_lib_hash = {}
+
+
+def _library_hash():
+    """Hash of the library's file: another build's kernels may want other settings."""
+    st = os.stat(gsbc.LIB_PATH)
+    key = (gsbc.LIB_PATH, st.st_mtime_ns, st.st_size)
+    if key not in _lib_hash:
+        with open(gsbc.LIB_PATH, "rb") as f:
+            _lib_hash[key] = hashlib.sha1(f.read()).digest()
+    return _lib_hash[key]
+
+
 def workload_key(descs, params=None):
     p = params if params is not None else gsbc.default_params()
     h = hashlib.sha1()
+    h.update(_library_hash())
     h.update(f"{p.refine_steps},{p.bc7_mode_mask}".encode())
     for d in descs:
         h.update(f"{d.blocks_per_stream}:{''.join(str(int(f)) for f in d.formats())};".encode())
