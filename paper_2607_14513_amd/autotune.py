@@ -9,7 +9,8 @@ own with fixed integer decisions), so the tuner only compares times.
 
 The search is coordinate descent from the defaults: each knob in turn is
 set to the value with the least median time while the others stay fixed;
-two sweeps.  Results are cached in a JSON file keyed by device name, compute-unit count and a hash of the
+two sweeps.  Settings that launch the same kernels are timed once.  Results are
+cached in a JSON file keyed by device name, compute-unit count and a hash of the
 library and the workload shape (block counts and band formats per scene).
 """
 import hashlib
@@ -25,7 +26,7 @@ SPACE = {
     "item_rounds": [1, 2, 4, 8],
     "wgs_per_cu": [0, 2, 4, 8, 12],
     "bc1_lanes": [64, 128, 256],
-    "bc7_split": [0, 1, 2, 3],
+    "bc7_split": [0, 1, 3],          # (2 is 3)
     "concurrent": [0, 1],
 }
 
@@ -45,6 +46,22 @@ def _library_hash():
         with open(gsbc.LIB_PATH, "rb") as f:
             _lib_hash[key] = hashlib.sha1(f.read()).digest()
     return _lib_hash[key]
+
+
+# Fewer BC1 blocks than this, in a plain grid of one round per item, are shared
+# by four waves each whatever bc1_lanes says (include/gsbc.h).
+SHARED_BC1_BELOW = 1 << 19
+
+
+def same_launch(cfg, descs):
+    """The setting of the knobs that launches what `cfg` does, for this batch."""
+    cfg = dict(cfg)
+    bc1 = sum(-(-int(d.blocks_per_stream) // 256) * 256 for d in descs for f in d.formats() if int(f) == gsbc.FMT_BC1)
+    if cfg["bc7_split"] == 2:
+        cfg["bc7_split"] = 3
+    if cfg["item_rounds"] == 1 and cfg["wgs_per_cu"] == 0 and bc1 < SHARED_BC1_BELOW:
+        cfg["bc1_lanes"] = gsbc.default_batch_tuning().bc1_lanes
+    return cfg
 
 
 def workload_key(descs, params=None):
@@ -103,7 +120,7 @@ def tune(ctx, textures, descs, blocks, params=None, repeats=3, sweeps=2, use_cac
     seen = {}
 
     def measure(cfg):
-        k = tuple(sorted(cfg.items()))
+        k = tuple(sorted(same_launch(cfg, descs).items()))
         if k not in seen:
             seen[k] = time_batch(ctx, textures, descs, blocks, gsbc.default_batch_tuning(**cfg), params, repeats)
             if log:

@@ -1,5 +1,5 @@
 """The tuner's host side: a cached tuning belongs to the library that it was
-timed with.  CPU only."""
+timed with, and settings that launch the same kernels are timed once.  CPU only."""
 import types
 
 import pytest
@@ -28,3 +28,23 @@ def test_key_names_the_library(monkeypatch, tmp_path):
         monkeypatch.setattr(gsbc, "LIB_PATH", str(p))
         keys.append(autotune.workload_key(_descs(100, [1, 7])))
     assert keys[0] == keys[2] != keys[1]
+
+
+@pytest.mark.parametrize("nblk,shared", [(1000, True), (70_000, False)])
+def test_same_launches_are_timed_once(monkeypatch, nblk, shared):
+    timed = []
+
+    def time_batch(ctx, textures, descs, blocks, tuning, params, repeats):
+        timed.append(tuning.as_dict())
+        return 1.0 + 0.001 * (len(timed) * 7919 % 13)     # noise
+
+    monkeypatch.setattr(autotune, "time_batch", time_batch)
+    monkeypatch.setattr(autotune, "workload_key", lambda *a: "k")
+    autotune.tune(None, None, _descs(nblk, [1, 1, 7]), None, use_cache=False)
+
+    def launches(t):
+        plain = t["item_rounds"] == 1 and t["wgs_per_cu"] == 0
+        return (t["item_rounds"], t["wgs_per_cu"], 0 if plain and shared else t["bc1_lanes"],
+                min(t["bc7_split"], 2), t["concurrent"])
+
+    assert len({launches(t) for t in timed}) == len(timed) > 5
