@@ -140,6 +140,16 @@ gsbc_status ensure_arena(gsbc_ctx *ctx, size_t bytes)
     return GSBC_OK;
 }
 
+// The next smaller chunk of the BC7 encoder that needs less scratch; false if none is.
+bool smaller_chunk(uint64_t total, uint64_t *chunk)
+{
+    do {
+        if (*chunk <= kBc7LeastChunk) return false;
+        *chunk >>= 2;
+    } while (*chunk >= total);
+    return true;
+}
+
 // The arena holds `bytes`, or could be grown to: false, with no error and
 // nothing changed, where it could not, or where the stream is being captured
 // (memory is not allocated in a capture).  For scratch that a call can do without.
@@ -154,6 +164,18 @@ bool try_arena(gsbc_ctx *ctx, size_t bytes)
     if (ensure_arena(ctx, bytes) == GSBC_OK) return true;
     ctx->err[0] = 0;
     return false;
+}
+
+// The arena holds `rest` bytes and the BC7 encoder's scratch for `total` block
+// indices, in chunks as large as memory allows (*chunk).
+gsbc_status ensure_bc7_arena(gsbc_ctx *ctx, size_t rest, uint64_t total, uint64_t *chunk)
+{
+    *chunk = kBc7Chunk;
+    while (true) {
+        const gsbc_status s = ensure_arena(ctx, rest + bc7_scratch_bytes(total, *chunk));
+        if (s == GSBC_OK) ctx->err[0] = 0;
+        if (s != GSBC_E_NOMEM || !smaller_chunk(total, chunk)) return s;
+    }
 }
 
 uint64_t pad16(uint64_t n) { return (n + 15) / 16 * 16; }
@@ -452,11 +474,11 @@ gsbc_status gsbc_reserve(gsbc_ctx *ctx, uint64_t n_max, uint32_t n_dirs_max)
     if (n_max == 0 || n_max > 0x7FFFFFFFull) return fail(ctx, GSBC_E_ARG, "n_max = %llu not in 1..2^31-1",
                                                          (unsigned long long)n_max);
     const uint64_t nblk = pad16(n_max) / 16;
-    size_t need = reorder_scratch_bytes(n_max, 3);
-    need = std::max(need, encode_front_bytes(nblk) + 2 * kRunTableBytes + bc7_scratch_bytes(16 * run_span(nblk)) +
-                              kHistBytes);
+    const size_t need = reorder_scratch_bytes(n_max, 3);
     (void)n_dirs_max;   // decode_eval needs no scratch
-    return ensure_arena(ctx, need);
+    if ((s = ensure_arena(ctx, need))) return s;
+    uint64_t chunk;
+    return ensure_bc7_arena(ctx, encode_front_bytes(nblk) + 2 * kRunTableBytes + kHistBytes, 16 * run_span(nblk), &chunk);
 }
 
 gsbc_status gsbc_arena_info(const gsbc_ctx *ctx, uint64_t *bytes, uint64_t *growths)
@@ -684,8 +706,10 @@ gsbc_status gsbc_encode(gsbc_ctx *ctx, const uint8_t *textures, gsbc_stream_desc
     }
     // arena: [candidate payloads (AUTO)] [BC7 runs] [BC1 runs] [BC7 key scratch] [band histograms (AUTO_ZERO)]
     const uint64_t total7 = autoc ? (uint64_t)S * run_span(nblk) : r7.total;
-    const size_t hist_off = front + 2 * kRunTableBytes + bc7_scratch_bytes(total7);
-    if ((s = ensure_arena(ctx, hist_off + (format == GSBC_FMT_AUTO_ZERO ? kHistBytes : 0)))) return s;
+    uint64_t chunk = kBc7Chunk;
+    if ((s = ensure_bc7_arena(ctx, front + 2 * kRunTableBytes + (format == GSBC_FMT_AUTO_ZERO ? kHistBytes : 0), total7, &chunk)))
+        return s;
+    const size_t hist_off = front + 2 * kRunTableBytes + bc7_scratch_bytes(total7, chunk);
     uint8_t *arena = static_cast<uint8_t *>(ctx->arena);
     if (autoc) {
         buf1 = arena;
@@ -709,6 +733,7 @@ gsbc_status gsbc_encode(gsbc_ctx *ctx, const uint8_t *textures, gsbc_stream_desc
     a.refine_steps = p.refine_steps;
     a.mode_mask = p.bc7_mode_mask;
     a.keys = reinterpret_cast<uint32_t *>(arena + front + 2 * kRunTableBytes);
+    a.chunk = chunk;
     const WorkSplit w3[3] = {kPlainSplit, kPlainSplit, kPlainSplit};
     // With both formats the BC1 encoder runs on a side stream beside the BC7
     // kernels: the waves that those leave idle as each of them ends are then
@@ -869,13 +894,16 @@ gsbc_status gsbc_encode_batch(gsbc_ctx *ctx, uint32_t n_scenes, const uint8_t *c
         // plan memory: [runs7][runs1][sse n_scenes x 16][queues 4 x u64][BC7 keys]
         const size_t b7 = align16(r7.v.size() * sizeof(BlockRun)), b1 = align16(r1.v.size() * sizeof(BlockRun));
         const size_t bs = 16 * (size_t)n_scenes * 8, bq = 64;
-        const size_t bytes = b7 + b1 + bs + bq + bc7_scratch_bytes(r7.total);
-        if (injected_alloc_failure()) return fail(ctx, GSBC_E_NOMEM, "plan allocation of %zu bytes failed (injected)", bytes);
-        hipError_t e = hipMalloc(&ctx->plan_mem, bytes);
-        if (e != hipSuccess) {
+        uint64_t chunk = kBc7Chunk;
+        hipError_t e = hipSuccess;
+        while (true) {
+            const size_t bytes = b7 + b1 + bs + bq + bc7_scratch_bytes(r7.total, chunk);
+            e = injected_alloc_failure() ? hipErrorOutOfMemory : hipMalloc(&ctx->plan_mem, bytes);
+            if (e == hipSuccess) break;
             ctx->plan_mem = nullptr;
             (void)hipGetLastError();
-            return fail(ctx, GSBC_E_NOMEM, "plan allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
+            if (!smaller_chunk(r7.total, &chunk))
+                return fail(ctx, GSBC_E_NOMEM, "plan allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
         }
         uint8_t *pm = static_cast<uint8_t *>(ctx->plan_mem);
         BlockRun *d7 = reinterpret_cast<BlockRun *>(pm), *d1 = reinterpret_cast<BlockRun *>(pm + b7);
@@ -901,6 +929,7 @@ gsbc_status gsbc_encode_batch(gsbc_ctx *ctx, uint32_t n_scenes, const uint8_t *c
         a.refine_steps = p.refine_steps;
         a.mode_mask = p.bc7_mode_mask;
         a.keys = keys;
+        a.chunk = chunk;
         WorkSplit w3[3], w1;
         for (int q = 0; q < 3; q++)
             w3[q] = {t.item_rounds, (uint32_t)cus * t.wgs_per_cu, t.wgs_per_cu ? queues + 2 * q : nullptr};

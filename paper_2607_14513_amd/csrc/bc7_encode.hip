@@ -2088,7 +2088,7 @@ hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t 
     if (e != hipSuccess) return e;
     if (!g_tab[dev]) return hipErrorNotInitialized;
     if (a.total == 0) return hipSuccess;
-    if (split > 3) return hipErrorInvalidValue;
+    if (split > 3 || a.chunk == 0 || a.chunk % kRunAlign) return hipErrorInvalidValue;
     Bc7Launch L;
     L.a = a;
     L.T.nearest = static_cast<const uint16_t *>(g_tab[dev]);
@@ -2100,7 +2100,7 @@ hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t 
     Q.T = L.T;
     uint8_t *s = reinterpret_cast<uint8_t *>(a.keys) + 4 * a.total;
     auto take = [&](size_t bytes) { uint8_t *r = s; s += (bytes + 15) & ~(size_t)15; return r; };
-    const uint64_t nc = a.total < kBc7Chunk ? a.total : kBc7Chunk;
+    const uint64_t nc = a.total < a.chunk ? a.total : a.chunk;
     Q.src = reinterpret_cast<const uint8_t **>(take(8 * (nc / 64)));
     Q.words = reinterpret_cast<uint64_t *>(take(8 * kWords * (nc / 64)));
     uint32_t *const dense = reinterpret_cast<uint32_t *>(take(4 * (nc / 64) + 16));

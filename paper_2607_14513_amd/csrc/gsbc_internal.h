@@ -162,16 +162,18 @@ struct EncodeArgs {
     uint64_t total;                 // end of the global index space (multiple of 256)
     uint32_t refine_steps;
     uint32_t mode_mask;
-    uint32_t *keys;                 // BC7 only: scratch of bc7_scratch_bytes(total)
+    uint32_t *keys;                 // BC7 only: scratch of bc7_scratch_bytes(total, chunk)
+    uint64_t chunk;                 // BC7 only: blocks bounded and searched at a time (a multiple of 256)
 };
 // Scratch bytes the BC7 encoder needs for `blocks` global indices (a
 // multiple of 256): a key per index, and for the indices of one chunk 300
 // bytes of candidate bounds each, a texel pointer, 149 candidate words and a
 // list entry per 64.
-constexpr uint64_t kBc7Chunk = 1u << 19;
-inline size_t bc7_scratch_bytes(uint64_t blocks)
+// Chunks of 2^19 (167 MB); where memory does not allow that, of down to 2^13.
+constexpr uint64_t kBc7Chunk = 1u << 19, kBc7LeastChunk = 1u << 13;
+inline size_t bc7_scratch_bytes(uint64_t blocks, uint64_t chunk)
 {
-    const uint64_t nc = blocks < kBc7Chunk ? blocks : kBc7Chunk;
+    const uint64_t nc = blocks < chunk ? blocks : chunk;
     return (size_t)blocks * 4 + (nc / 64) * (150 * 8 + 4) + nc * 300 + 160;
 }
 // How the BC7 candidate search is split over kernels: 0 -> three kernels
