@@ -1182,7 +1182,7 @@ constexpr float kSlackRot = 0.6328f;
 // sqrt of 16 R of a block whose texels lie so near a line (R up to 12) that its
 // bounds come out below 1 (coded as 0) or little above: sixteen such blocks go
 // without.  What bounds and gathers do not have to do on blocks of two adjacent
-// levels: 1,048,576 of them 18.97 -> 17.63 ms (17.19 exhaustive).
+// levels: 1,048,576 of them 18.97 -> 17.84 ms (17.19 exhaustive).
 constexpr float kFlatRoot = 13.86f;
 
 // Candidate words of a slice (64 blocks), per type.
@@ -1454,8 +1454,9 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
 // fits the 3-subset seed and writes the words of the 3-subset partitions, the
 // other the rotation seed and the other words (4,112 blocks: 76 -> 57 us;
 // 524,288 blocks: 205 -> 250 us, where a wave does both).  The seeds' own bits
-// are cleared (they are fitted here).  SEEDS: see seed_kind.
-template <int SEEDS>
+// are cleared (they are fitted here).  SEEDS: see seed_kind.  DENSE: slices to be
+// fitted in order are listed.
+template <int SEEDS, bool DENSE>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(SEEDS == kSeedUsual ? 4 : 3))) void k_bc7_seed(Bc7Search L, bool pairs)
 {
     __shared__ TexLds S;
@@ -1560,7 +1561,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(SEEDS == kS
     }
     // slices most of whose blocks keep most partitions go to k_bc7_every
     auto is_dense = [&](uint64_t u, uint64_t v, uint32_t cands) {
-        if (!L.dense) return false;
+        if (!DENSE) return false;
         uint32_t n = (uint32_t)__popcll(u) + (uint32_t)__popcll(v);
 #pragma unroll
         for (int d = 32; d > 0; d >>= 1) n += (uint32_t)__shfl_xor((int)n, d);
@@ -1767,17 +1768,17 @@ __device__ __forceinline__ void search_item(const Bc7Search &L, TexLds &S, WaveL
         // gather 64 blocks whose best so far still leaves the candidate a chance
         while (q1 < 64 && t < n) {
             const uint32_t i = t + lane;
+            uint32_t lo = 0, hi = n == 64 * ns ? 0 : ns - 1;   // (all of the window's blocks: i itself)
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (W.end[mid] > i) hi = mid;
+                else lo = mid + 1;
+            }
             bool keep = i < n;
             uint32_t at = i;
-            if (n != 64 * ns) {   // not all of them
-                uint32_t lo = 0, hi = ns - 1;
-                while (lo < hi) {
-                    const uint32_t mid = (lo + hi) >> 1;
-                    if (W.end[mid] > i) hi = mid;
-                    else lo = mid + 1;
-                }
+            if (keep && n != 64 * ns) {
                 const uint64_t x = W.word[lo];
-                at = lo * 64 + (uint32_t)nth_bit(x, keep ? (int)(i - ((uint32_t)W.end[lo] - (uint32_t)__popcll(x))) : 0);
+                at = lo * 64 + (uint32_t)nth_bit(x, (int)(i - ((uint32_t)W.end[lo] - (uint32_t)__popcll(x))));
             }
             if (keep) {
                 const uint32_t key = keys[at];
@@ -1801,14 +1802,11 @@ __device__ __forceinline__ void search_item(const Bc7Search &L, TexLds &S, WaveL
             if (TYPE == kSix) key = search_mode6(S, L.T.sv);
             if (kParts) {
                 const Sums sums = subset_sums(S, first, 0);
+                const float f[9] = {(float)sums.nSx[0], (float)sums.nSx[1], (float)sums.nSx[2], (float)sums.XX[0], (float)sums.XX[1],
+                                    (float)sums.XX[2], (float)sums.XX[3], (float)sums.XX[4], (float)sums.XX[5]};
                 // what the bounds leave for the other subsets (the same arithmetic as the bounds')
-                const uint32_t bound = lb[(uint64_t)at * kStep];
-                float rest = 0.0f;
-                if (bound) {
-                    const float f[9] = {(float)sums.nSx[0], (float)sums.nSx[1], (float)sums.nSx[2], (float)sums.XX[0], (float)sums.XX[1],
-                                        (float)sums.XX[2], (float)sums.XX[3], (float)sums.XX[4], (float)sums.XX[5]};
-                    rest = fmaf(bound_value(bound), 1.0f - 2e-6f, -bound_term(residual_root(members, f), members, inv, kSlack));
-                }
+                const float rest = fmaf(bound_value(lb[(uint64_t)at * kStep]), 1.0f - 2e-6f,
+                                        -bound_term(residual_root(members, f), members, inv, kSlack));
                 if (TYPE == kTwo) {
                     if (a.mode_mask & 0x02) e[0] = 0;
                     if (a.mode_mask & 0x08) e[1] = 0;
@@ -2153,7 +2151,9 @@ hipError_t launch_bc7_encode(const EncodeArgs &a, const WorkSplit *w3, uint32_t 
         const int seeds = seed_kind(a.mode_mask);
         if (seeds != kSeedEvery) GSBC_LAUNCH("bc7_bounds", k_bc7_bounds, dim3((uint32_t)(left / per)), dim3(kWG), 0, st, Q, per);
         if (alone && !seeds_fill && first == 0 && (e = hipEventRecord(alone, st)) != hipSuccess) return e;
-        auto seed = seeds == kSeedUsual ? k_bc7_seed<kSeedUsual> : seeds == kSeedOther ? k_bc7_seed<kSeedOther> : k_bc7_seed<kSeedEvery>;
+        auto seed = seeds == kSeedUsual ? (Q.dense ? k_bc7_seed<kSeedUsual, true> : k_bc7_seed<kSeedUsual, false>)
+                  : seeds == kSeedOther ? (Q.dense ? k_bc7_seed<kSeedOther, true> : k_bc7_seed<kSeedOther, false>)
+                                        : k_bc7_seed<kSeedEvery, false>;
         GSBC_LAUNCH("bc7_seed", seed, dim3((uint32_t)(left / (pairs ? kWG / 2 : kWG))), dim3(kWG), 0, st, Q, pairs);
         if (alone && seeds_fill && first == 0 && (e = hipEventRecord(alone, st)) != hipSuccess) return e;
         if (seeds == kSeedEvery) continue;

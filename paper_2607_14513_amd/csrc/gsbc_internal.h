@@ -174,7 +174,8 @@ constexpr uint64_t kBc7Chunk = 1u << 19, kBc7LeastChunk = 1u << 13;
 inline size_t bc7_scratch_bytes(uint64_t blocks, uint64_t chunk)
 {
     const uint64_t nc = blocks < chunk ? blocks : chunk;
-    return (size_t)blocks * 4 + (nc / 64) * (150 * 8 + 4) + nc * 300 + 160;
+    // (whole 256-byte lines: what follows starts on one)
+    return ((size_t)blocks * 4 + (nc / 64) * (150 * 8 + 4) + nc * 300 + 160 + 255) & ~(size_t)255;
 }
 // How the BC7 candidate search is split over kernels: 0 -> three kernels
 // (2-subset, 3-subset, 1-subset modes), 1 -> two (the 1-subset modes folded
