@@ -167,12 +167,13 @@ bool try_arena(gsbc_ctx *ctx, size_t bytes)
 }
 
 // The arena holds `rest` bytes and the BC7 encoder's scratch for `total` block
-// indices, in chunks as large as memory allows (*chunk).
-gsbc_status ensure_bc7_arena(gsbc_ctx *ctx, size_t rest, uint64_t total, uint64_t *chunk)
+// indices, in chunks as large as memory allows (*chunk), and `least` bytes at
+// the least.
+gsbc_status ensure_bc7_arena(gsbc_ctx *ctx, size_t least, size_t rest, uint64_t total, uint64_t *chunk)
 {
     *chunk = kBc7Chunk;
     while (true) {
-        const gsbc_status s = ensure_arena(ctx, rest + bc7_scratch_bytes(total, *chunk));
+        const gsbc_status s = ensure_arena(ctx, std::max(least, rest + bc7_scratch_bytes(total, *chunk)));
         if (s == GSBC_OK) ctx->err[0] = 0;
         if (s != GSBC_E_NOMEM || !smaller_chunk(total, chunk)) return s;
     }
@@ -474,11 +475,10 @@ gsbc_status gsbc_reserve(gsbc_ctx *ctx, uint64_t n_max, uint32_t n_dirs_max)
     if (n_max == 0 || n_max > 0x7FFFFFFFull) return fail(ctx, GSBC_E_ARG, "n_max = %llu not in 1..2^31-1",
                                                          (unsigned long long)n_max);
     const uint64_t nblk = pad16(n_max) / 16;
-    const size_t need = reorder_scratch_bytes(n_max, 3);
     (void)n_dirs_max;   // decode_eval needs no scratch
-    if ((s = ensure_arena(ctx, need))) return s;
     uint64_t chunk;
-    return ensure_bc7_arena(ctx, encode_front_bytes(nblk) + 2 * kRunTableBytes + kHistBytes, 16 * run_span(nblk), &chunk);
+    return ensure_bc7_arena(ctx, reorder_scratch_bytes(n_max, 3), encode_front_bytes(nblk) + 2 * kRunTableBytes + kHistBytes,
+                            16 * run_span(nblk), &chunk);
 }
 
 gsbc_status gsbc_arena_info(const gsbc_ctx *ctx, uint64_t *bytes, uint64_t *growths)
@@ -707,7 +707,7 @@ gsbc_status gsbc_encode(gsbc_ctx *ctx, const uint8_t *textures, gsbc_stream_desc
     // arena: [candidate payloads (AUTO)] [BC7 runs] [BC1 runs] [BC7 key scratch] [band histograms (AUTO_ZERO)]
     const uint64_t total7 = autoc ? (uint64_t)S * run_span(nblk) : r7.total;
     uint64_t chunk = kBc7Chunk;
-    if ((s = ensure_bc7_arena(ctx, front + 2 * kRunTableBytes + (format == GSBC_FMT_AUTO_ZERO ? kHistBytes : 0), total7, &chunk)))
+    if ((s = ensure_bc7_arena(ctx, 0, front + 2 * kRunTableBytes + (format == GSBC_FMT_AUTO_ZERO ? kHistBytes : 0), total7, &chunk)))
         return s;
     const size_t hist_off = front + 2 * kRunTableBytes + bc7_scratch_bytes(total7, chunk);
     uint8_t *arena = static_cast<uint8_t *>(ctx->arena);

@@ -48,3 +48,14 @@ def test_smaller_chunks(call):
     env = dict(os.environ, GSBC_FAULT="alloc:1", PYTHONPATH=root)
     r = subprocess.run([sys.executable, "-c", CODE, call], env=env, cwd=root, capture_output=True, text=True, timeout=100)
     assert r.returncode == 0 and "SAME" in r.stdout, r.stderr[-2000:]
+
+
+@pytest.mark.parametrize("n", [100, 5_000, 3_000_000])
+def test_reserve_allocates_once(n):
+    from paper_2607_14513_amd import gsbc
+    with gsbc.Context(0) as ctx:
+        ctx.reserve(n)
+        size, growths = ctx.arena_info()
+        assert growths == 1
+        ctx.reserve(n)
+        assert ctx.arena_info() == (size, 1)
