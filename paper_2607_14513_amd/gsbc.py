@@ -290,7 +290,7 @@ class Context:
         if not stream.cuda_stream and 0 <= int(device) < torch.cuda.device_count():
             self._own = _take_stream(int(device))
             self._pool = torch.cuda.ExternalStream(self._own, device=self.device)
-        elif stream.cuda_stream and stream.device == self.device:
+        elif stream.cuda_stream and isinstance(stream, torch.cuda.Stream) and stream.device == self.device:
             self._pool = stream
         if self._pool is not None:
             self._pool_at = (self._pool.stream_id, self._pool.device_index, self._pool.device_type)

@@ -82,3 +82,16 @@ def test_streams_of_living_outputs():
     for c in more + [gsbc.Context(0)]:
         c.close()
     assert held and not held & set(gsbc._held_streams[0]) - gsbc._pools_alive(0)
+
+
+def test_stream_of_another_kind():
+    """Anything with a `cuda_stream` serves as a stream; outputs then come from the current stream's pool."""
+    from paper_2607_14513_amd import gsbc
+    st = torch.cuda.Stream()
+    handle = type("Handle", (), {"cuda_stream": st.cuda_stream})()
+    with torch.cuda.stream(st):
+        dirs = torch.from_numpy(synth.make_dirs(3, seed=8)).cuda()
+        with gsbc.Context(0, stream=handle) as ctx:
+            out = ctx.decode_eval(*_scene(ctx, gsbc, 1_003, 9), dirs)
+            ctx.sync()
+    assert out.shape == (3, 1_003, 3)
