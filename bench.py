@@ -488,7 +488,7 @@ def main():
             ts3d = torch.from_numpy(ts3.astype(np.int32)).to(dev)
             lst3d = torch.from_numpy(slot3[lst3]).to(dev)
             img3, tr3 = ctx.blend_tiles(b3, dd2, pos3d, p3, view, mu3d, foot3d, ts3d, lst3d, 120, 68)
-            t_bl = kernel_ms(ctx, ("tile_order", "mark_slots", "decode_eval_view", "blend_tiles"),
+            t_bl = kernel_ms(ctx, ("clear_marks", "tile_order", "decode_eval_view", "blend_tiles"),
                              lambda: ctx.blend_tiles(b3, dd2, pos3d, p3, view, mu3d, foot3d, ts3d, lst3d, 120, 68,
                                                      image=img3, transmittance=tr3), 3)
             bl_s = float(np.median(t_bl)) * 1e-3

@@ -138,9 +138,12 @@ GSBC_API const char *gsbc_last_error(const gsbc_ctx *ctx);
 GSBC_API gsbc_status gsbc_sync(gsbc_ctx *ctx);
 
 /* Size the context's scratch arena once for scenes of up to n_max primitives
- * (decode_eval needs no scratch, whatever n_dirs_max is), so that calls within those
- * sizes allocate nothing (a serving slot reserves its largest admissible
- * request up front instead of growing mid-stream).  Outgrown arenas are kept
+ * (decode_eval needs no scratch, whatever n_dirs_max is; the colour stage's 13
+ * bytes a slot and 4 a tile are covered up to n_max tiles), so that calls within
+ * those sizes allocate nothing (a serving slot reserves its largest admissible
+ * request up front instead of growing mid-stream).  Where memory does not allow
+ * the BC7 encoder's scratch for a whole chunk of blocks (up to 167 MB), a smaller
+ * one's is taken, as the encode calls do.  Outgrown arenas are kept
  * until gsbc_destroy, since queued kernels may still read them and freeing
  * device memory waits for the whole device.
  * GSBC_E_ARG for n_max outside 1..2^31-1, GSBC_E_NOMEM if it cannot grow. */
@@ -408,9 +411,10 @@ GSBC_API gsbc_status gsbc_decode_eval_view(gsbc_ctx *ctx, const uint8_t *blocks,
  * size holds them); where the arena does not hold them and cannot grow (a
  * failed allocation, a stream being captured) and for shorter lists each entry
  * is decoded in the blend, with no colour in memory.  Both give the same bits,
- * and neither reads anything of slots that no tile lists (their perm entries,
- * positions and blocks).  list_len is the buffer's length: entries that no tile
- * uses are not read either.
+ * and what perm, pos and blocks hold for slots that no tile lists does not
+ * matter (a perm entry that names none of n_prims primitives is followed for
+ * listed slots only).  list_len is the buffer's length: entries that no tile
+ * uses are not read.
  *   blocks, desc     as gsbc_decode_eval (a coded scene)
  *   pos, perm        as gsbc_decode_eval_view
  *   view             host float[3], the view position f
@@ -479,8 +483,8 @@ GSBC_API gsbc_status gsbc_load(gsbc_ctx *ctx, const char *path, gsbc_stream_desc
 /* Kernel timing, a tracing aid.  While enabled, every kernel this context
  * launches is bracketed by HIP events on the context's stream (so the times
  * are device times of that stream), and gsbc_encode runs its kernels one
- * after another there (without timing, its BC1 kernel overlaps the BC7
- * bucketing and emit kernels on a second stream).  gsbc_profile_read waits for the stream,
+ * after another there (without timing, its BC1 kernel runs beside the BC7
+ * kernels on a second stream).  gsbc_profile_read waits for the stream,
  * then returns per kernel name (at most max_entries of them, in first-launch
  * order) the number of launches and their total milliseconds since the
  * previous read, and forgets them.

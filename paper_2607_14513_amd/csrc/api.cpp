@@ -66,6 +66,7 @@ constexpr size_t kSelOff = 512;                  // RateSel
 constexpr size_t kSse1Off = 1024;                // 16 x u64
 constexpr size_t kSse7Off = 1152;                // 16 x u64
 constexpr size_t kClassOff = 1536;               // 4 x u32 degree-class counts
+constexpr size_t kOddOff = 1600;                 // u32, zero between colour stages
 constexpr size_t kSmallBytes = 2048;
 static_assert(sizeof(gsbc::RangeRec) <= kSelOff, "RangeRec must fit before RateSel (and before the class counts read back beside it)");
 
@@ -1199,18 +1200,18 @@ gsbc_status gsbc_blend_tiles(gsbc_ctx *ctx, const uint8_t *blocks, const gsbc_st
     const float f[3] = {view[0], view[1], view[2]};
     if (!(isfinite(f[0]) && isfinite(f[1]) && isfinite(f[2]))) return fail(ctx, GSBC_E_ARG, "view position not finite");
     const size_t order_bytes = ((size_t)tiles * sizeof(uint32_t) + 255) & ~(size_t)255;   // the tile schedule
-    // Colours of all listed slots first, into scratch, or of each list entry in
-    // the blend: a primitive sits in several tiles' lists, and slots in order
-    // decode whole blocks.  At 3.6 entries a slot colours first take 320 us
-    // against 451 (786,432 slots; 142 : 183 at 300,000 and 1,038 : 1,568 at
-    // 3,145,728), at 0.27 54 : 57 (36 : 42, 150 : 150).  The line is one entry in
-    // four slots, though marks make fewer gain too in large scenes (0.01 a slot
-    // 26 : 35, 64 : 94): of few entries, which slots they are costs more than it
-    // saves (14,000 entries of 30,000 slots 22 : 18, 113,000 43 : 55; 12,000 of
-    // 3,000 28 : 24), so lists are 2^15 long at least.
+    // Colours first, of every slot or of those that a tile lists (the kernels
+    // decide), into scratch, or of each list entry in the blend: a primitive sits
+    // in several tiles' lists, and slots in order decode whole blocks.  At 3.6
+    // entries a slot colours first take 309 us against 451 (786,432 slots; 138 :
+    // 183 at 300,000 and 994 : 1,568 at 3,145,728), at 0.27 59 : 57 (42 : 42, 150 :
+    // 150).  The line is one entry in four slots, though fewer gain too in large
+    // scenes (0.01 a slot 29 : 35, 69 : 94): of few entries, which slots they are
+    // costs more than it saves (14,000 entries of 30,000 slots 22 : 18, 113,000 44 :
+    // 55; 12,000 of 3,000 28 : 24), so lists are 2^15 long at least.
     // Without room for them (13 bytes a slot) the entries are decoded in the
-    // blend; the image is the same bit for bit.  Nothing is read of slots that
-    // no tile lists, on either way.
+    // blend; the image is the same bit for bit.  Neither way leaves its arrays
+    // through what perm holds for slots that no tile lists.
     float *colours = nullptr;
     uint8_t *marks = nullptr;
     const uint64_t n = desc->n_prims;
@@ -1221,7 +1222,7 @@ gsbc_status gsbc_blend_tiles(gsbc_ctx *ctx, const uint8_t *blocks, const gsbc_st
     if ((s = ensure_arena(ctx, order_bytes))) return s;
     HIP_TRY(ctx, launch_blend_tiles(blocks, band_args(desc), n, pos, perm, f, opacity, footprint, tile_start, list, list_len,
                                     tiles_x, tiles_y, nullptr, image, transmittance, static_cast<uint32_t *>(ctx->arena),
-                                    colours, marks, ctx->stream),
+                                    colours, marks, reinterpret_cast<uint32_t *>(small_ptr(ctx, kOddOff)), ctx->stream),
             "blend_tiles launch");
     return GSBC_OK;
 }
@@ -1247,7 +1248,7 @@ gsbc_status gsbc_blend_tiles_colours(gsbc_ctx *ctx, const float *colours, uint64
     const float f[3] = {0.0f, 0.0f, 0.0f};   // unused: the colours are given
     HIP_TRY(ctx, launch_blend_tiles(nullptr, BandArgs{}, n_prims, nullptr, perm, f, opacity, footprint, tile_start,
                                     list, list_len, tiles_x, tiles_y, colours, image, transmittance,
-                                    static_cast<uint32_t *>(ctx->arena), nullptr, nullptr, ctx->stream),
+                                    static_cast<uint32_t *>(ctx->arena), nullptr, nullptr, nullptr, ctx->stream),
             "blend_tiles launch");
     return GSBC_OK;
 }

@@ -267,7 +267,8 @@ __device__ __forceinline__ void split_list(const Lds &L, int lane, const int (&t
 //     SSE >= (max(0, sqrt(E) - sqrt(3)))^2
 // over 16 texels of three channels.  A split whose bound exceeds an SSE
 // already reached cannot win: |u|^2 >= V (Q' - (sqrt(best) + sqrt(3))^2) is
-// the test, eight instructions where scoring a split takes about 85.
+// the test, eight instructions (ten with its row's set-up) where scoring a split
+// takes 85 in uniform order and 140 queued.
 //
 // The splits that pass are queued with their block's lane and scored 64 at a
 // time, any lane for any block, so that scoring runs on full waves; the
@@ -277,7 +278,7 @@ __device__ __forceinline__ void split_list(const Lds &L, int lane, const int (&t
 // the final SSE.  About 190 of the 1,122 splits of a block of synthetic SH
 // bands are scored; a wave issues 57 k VALU instructions where scoring every
 // split took 105 k, and 1,048,576 blocks take 1.77 ms (2.95 before).  Bound by
-// VALU issue (85 %): scoring 27 k, the tests 11 k, refinement 7 k.
+// VALU issue (85 %): scoring 27 k (queued), the tests 11 k, refinement 7 k.
 
 // Score the queued splits e (lane: one entry, or none).  The same arithmetic
 // as split_list, with the split per lane.

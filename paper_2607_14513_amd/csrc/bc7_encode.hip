@@ -311,10 +311,6 @@ struct PairFit {
 template <int NB>
 constexpr int idx_width() { return NB == 2 ? 2 : 4; }
 
-// Zero, read from memory: added to a constant whose low bits the compiler
-// can prove clear of the product it joins, it keeps the sum an addition, so
-// product and sum fuse into one v_mad_u32_u24 instead of a multiply and an or.
-
 // Palette entry constant C = 256 |p|^2 + k from the 64-scaled entry:
 // (64 p) . (64 p) + 16 k = 16 C, exactly.  The opaque zero keeps 16 k an
 // addition (its bits are provably clear of the product's, which would turn

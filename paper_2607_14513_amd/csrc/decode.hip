@@ -572,13 +572,45 @@ __device__ __forceinline__ void view_colour(const uint8_t *blocks, const BandArg
     colour_sum(b, px, Y, c);
 }
 
+// The blend's colours first: all slots or the marked ones only (a byte each).
+// All are decoded where most will be read and each slot's primitive is known to
+// be one of pos (perm below n_prims, which pos holds at least); else only marked
+// ones, of which alone the caller answers for perm: lists with less than an entry
+// a slot in use (786,432 slots, 0.27 entries each: 59 us against 69), and scenes
+// that hold a part of pos's primitives.  From there on marks cost more than
+// unlisted slots (3.6 entries each: 319 us against 309; 16.6 M entries of
+// 3,145,728 slots 1,525 against 1,393).
+__device__ __forceinline__ bool all_slots(const uint32_t *tile_start, uint32_t tiles, uint64_t list_len, uint64_t n_prims,
+                                          const uint32_t *odd)
+{
+    return *odd == 0 && min((uint64_t)tile_start[tiles], list_len) >= n_prims;
+}
+
+// Marks (n_marks bytes, a multiple of 16) cleared; *odd is set where a perm entry
+// is no number below n_prims.
+__global__ __launch_bounds__(256) void k_clear_marks(uint4 *mark, uint64_t n_marks, const uint32_t *perm, uint64_t n_prims,
+                                                     uint32_t *odd)
+{
+    const uint64_t e0 = (uint64_t)blockIdx.x * 256;
+    if (e0 + threadIdx.x < n_marks / 16) mark[e0 + threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
+    bool bad = false;
+#pragma unroll
+    for (uint32_t q = 0; q < 16; q++) {
+        const uint64_t s = 16 * e0 + 256 * q + threadIdx.x;
+        bad |= s < n_prims && perm[min(s, n_prims - 1)] >= n_prims;
+    }
+    if (bad) *odd = 1;
+}
+
 // One lane per listed slot; out-of-range slot ids give NaN.  MARKED: all slots,
-// of which only those with a mark (a byte each) are asked for: nothing of the
-// others is read, neither their blocks nor their perm entries and positions,
-// and their colours are left as they are or NaN.
+// or those with a mark (see all_slots): then nothing of the others is read,
+// neither their blocks nor their perm entries and positions, and their colours
+// are left as they are or NaN.
 template <bool MARKED>
 __global__ __launch_bounds__(256) void k_decode_eval_view(const uint8_t *blocks, BandArgs b, const uint32_t *prim_idx,
-                                                          const uint8_t *mark, uint64_t m, uint64_t n_prims, const float *pos,
+                                                          const uint8_t *mark, const uint32_t *odd,
+                                                          const uint32_t *tile_start, uint32_t tiles, uint64_t list_len,
+                                                          uint64_t m, uint64_t n_prims, const float *pos,
                                                           const uint32_t *perm, float fx, float fy, float fz,
                                                           float *out)
 {
@@ -588,7 +620,7 @@ __global__ __launch_bounds__(256) void k_decode_eval_view(const uint8_t *blocks,
     const uint64_t j0 = (uint64_t)blockIdx.x * 256, j = j0 + threadIdx.x;
     bool mine = j < m;
     if (MARKED) {
-        mine = mine && mark[j] != 0;
+        mine = mine && (all_slots(tile_start, tiles, list_len, n_prims, odd) || mark[j] != 0);
         const uint64_t marks = __ballot(mine);
         if ((threadIdx.x & 63u) == 0) s_marks[threadIdx.x >> 6] = marks;
         if (!__syncthreads_or(mine)) return;
@@ -618,16 +650,31 @@ __global__ __launch_bounds__(256) void k_decode_eval_view(const uint8_t *blocks,
 // last): one workgroup counts, scans and scatters.  The blend takes tiles
 // in this order so that the longest lists start first instead of ending
 // the launch alone; the order within a bucket does not matter (each tile is
-// computed on its own).  Workgroup 0; the others clear the slots' marks, where
-// there are any (n_marks bytes, a multiple of 16).
-__global__ __launch_bounds__(1024) void k_tile_order(const uint32_t *tile_start, uint64_t list_len, uint32_t tiles,
-                                                    uint32_t *order, uint4 *marks, uint64_t n_marks)
+// computed on its own).  Workgroup 0 does that.  The others, where there are
+// any, set a mark on every slot that their tile's list names (ids past the scene
+// have none) unless all slots' colours are wanted.  Bound by the marks' scattered
+// byte stores (16.6 M entries 121 us with eight loads of the list in flight per
+// lane, 180 with one and 256 lanes a tile).
+__global__ __launch_bounds__(1024) void k_tile_order(const uint32_t *tile_start, const uint32_t *list, uint64_t list_len,
+                                                    uint32_t tiles, uint32_t *order, uint64_t n_prims, uint8_t *mark,
+                                                    const uint32_t *odd)
 {
     __shared__ uint32_t cnt[33];
     const uint32_t t = threadIdx.x;
     if (blockIdx.x) {
-        const uint64_t e = (uint64_t)(blockIdx.x - 1) * 1024 + t;
-        if (e < n_marks / 16) marks[e] = make_uint4(0u, 0u, 0u, 0u);
+        if (all_slots(tile_start, tiles, list_len, n_prims, odd)) return;
+        const uint32_t tile = blockIdx.x - 1;
+        const uint64_t b1 = min((uint64_t)tile_start[tile + 1], list_len);
+        const uint64_t b0 = min((uint64_t)tile_start[tile], b1);
+        constexpr int kLoads = 8;   // in flight per lane
+        for (uint64_t base = b0 + t; base < b1; base += 1024 * kLoads) {
+            uint32_t s[kLoads];
+#pragma unroll
+            for (int q = 0; q < kLoads; q++) s[q] = list[min(base + 1024 * q, b1 - 1)];
+#pragma unroll
+            for (int q = 0; q < kLoads; q++)
+                if (s[q] < n_prims) mark[s[q]] = 1;
+        }
         return;
     }
     if (t < 33) cnt[t] = 0u;
@@ -649,24 +696,6 @@ __global__ __launch_bounds__(1024) void k_tile_order(const uint32_t *tile_start,
     }
     __syncthreads();
     for (uint32_t i = t; i < tiles; i += 1024) order[atomicAdd(&cnt[key(i)], 1u)] = i;
-}
-
-// A mark on every slot that a tile's list names (ids past the scene have none):
-// one workgroup per tile, the longest lists first.  What colours first read is
-// then what decoding entry by entry reads, whatever the rest of perm, pos and
-// blocks holds.  Marks cost a frame of 786,432 slots and 2.8 M entries 15 of 318
-// us, one of 3,145,728 and 10.7 M 21 of 1,038.
-__global__ __launch_bounds__(256) void k_mark_slots(const uint32_t *tile_start, const uint32_t *list, uint64_t list_len,
-                                                    const uint32_t *order, uint64_t n_prims, uint8_t *mark)
-{
-    const uint32_t tile = order[blockIdx.x];
-    const uint64_t b1 = min((uint64_t)tile_start[tile + 1], list_len);
-    const uint64_t b0 = min((uint64_t)tile_start[tile], b1);
-#pragma unroll 4
-    for (uint64_t e = b0 + threadIdx.x; e < b1; e += 256) {
-        const uint32_t s = list[e];
-        if (s < n_prims) mark[s] = 1;
-    }
 }
 
 // Colour stage of a tile rasteriser (Sec. II, eq. preblend with the
@@ -695,8 +724,9 @@ __global__ __launch_bounds__(256) void k_blend_tiles(const uint8_t *blocks, Band
                                                      float fz, const float *mu, const float *foot,
                                                      const uint32_t *tile_start, const uint32_t *list,
                                                      uint64_t list_len, const uint32_t *order, uint32_t tiles_x,
-                                                     const float *colours, float *image, float *trans)
+                                                     const float *colours, uint32_t *odd, float *image, float *trans)
 {
+    if (COLOURS && odd && blockIdx.x == 0 && threadIdx.x == 0) *odd = 0;   // for the next call
     // per staged entry: mean x, mean y, A, B | C, mu, colour r, g | colour b
     // (rows of 12 floats: three 16-byte LDS reads per entry, all lanes
     // reading the same row)
@@ -771,23 +801,25 @@ hipError_t launch_blend_tiles(const uint8_t *blocks, const BandArgs &b, uint64_t
                               const uint32_t *perm, const float view[3], const float *mu, const float *foot,
                               const uint32_t *tile_start, const uint32_t *list, uint64_t list_len, uint32_t tiles_x,
                               uint32_t tiles_y, const float *colours, float *image, float *trans, uint32_t *order,
-                              float *fill_colours, uint8_t *marks, hipStream_t st)
+                              float *fill_colours, uint8_t *marks, uint32_t *odd, hipStream_t st)
 {
     const uint64_t tiles = (uint64_t)tiles_x * tiles_y;
     if (tiles == 0) return hipSuccess;
-    const uint64_t n_marks = fill_colours ? (n_prims + 15) / 16 * 16 : 0;
-    GSBC_LAUNCH("tile_order", k_tile_order, dim3(1 + (uint32_t)((n_marks / 16 + 1023) / 1024)), dim3(1024), 0, st, tile_start,
-                list_len, (uint32_t)tiles, order, reinterpret_cast<uint4 *>(marks), n_marks);
+    const uint64_t n_marks = (n_prims + 15) / 16 * 16;
+    if (fill_colours)
+        GSBC_LAUNCH("clear_marks", k_clear_marks, dim3((uint32_t)((n_marks / 16 + 255) / 256)), dim3(256), 0, st,
+                    reinterpret_cast<uint4 *>(marks), n_marks, perm, n_prims, odd);
+    GSBC_LAUNCH("tile_order", k_tile_order, dim3(fill_colours ? 1 + (uint32_t)tiles : 1), dim3(1024), 0, st, tile_start, list,
+                list_len, (uint32_t)tiles, order, n_prims, marks, odd);
     if (fill_colours) {
-        GSBC_LAUNCH("mark_slots", k_mark_slots, dim3((uint32_t)tiles), dim3(256), 0, st, tile_start, list, list_len, order,
-                    n_prims, marks);
         GSBC_LAUNCH("decode_eval_view", k_decode_eval_view<true>, dim3((uint32_t)((n_prims + 255) / 256)), dim3(256), 0, st,
-                    blocks, b, nullptr, marks, n_prims, n_prims, pos, perm, view[0], view[1], view[2], fill_colours);
+                    blocks, b, nullptr, marks, odd, tile_start, (uint32_t)tiles, list_len, n_prims, n_prims, pos, perm, view[0],
+                    view[1], view[2], fill_colours);
         colours = fill_colours;
     }
     GSBC_LAUNCH("blend_tiles", colours ? k_blend_tiles<true> : k_blend_tiles<false>, dim3((uint32_t)tiles), dim3(256), 0,
                 st, blocks, b, n_prims, pos, perm, view[0], view[1], view[2], mu, foot, tile_start, list, list_len, order,
-                tiles_x, colours, image, trans);
+                tiles_x, colours, fill_colours ? odd : nullptr, image, trans);
     return hipGetLastError();
 }
 
@@ -797,7 +829,7 @@ hipError_t launch_decode_eval_view(const uint8_t *blocks, const BandArgs &b, uin
 {
     if (m == 0) return hipSuccess;
     GSBC_LAUNCH("decode_eval_view", k_decode_eval_view<false>, dim3((uint32_t)((m + 255) / 256)), dim3(256), 0, st, blocks, b,
-                prim_idx, nullptr, m, n_prims, pos, perm, view[0], view[1], view[2], out);
+                prim_idx, nullptr, nullptr, nullptr, 0u, 0ull, m, n_prims, pos, perm, view[0], view[1], view[2], out);
     return hipGetLastError();
 }
 

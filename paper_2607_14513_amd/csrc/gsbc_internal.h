@@ -233,14 +233,15 @@ hipError_t launch_decode_eval(const uint8_t *blocks, const BandArgs &b, uint64_t
 // direction from its primitive (pos[perm[slot]]) towards `view`.
 // Colour stage over per-tile front-to-back lists (Sec. II, eq. preblend);
 // order: device scratch of tiles_x * tiles_y words (the tile schedule).
-// colours: every slot's, given beforehand, or null.  fill_colours, marks: null,
-// or scratch of 3 floats and a byte a slot (n_prims padded to 16) where the
-// listed slots' colours are computed before the blend.
+// colours: every slot's, given beforehand, or null.  fill_colours, marks, odd:
+// null, or scratch of 3 floats and a byte a slot (n_prims padded to 16) and a word
+// that is zero before and after the call, where colours are computed before the
+// blend.
 hipError_t launch_blend_tiles(const uint8_t *blocks, const BandArgs &b, uint64_t n_prims, const float *pos,
                               const uint32_t *perm, const float view[3], const float *mu, const float *foot,
                               const uint32_t *tile_start, const uint32_t *list, uint64_t list_len, uint32_t tiles_x,
                               uint32_t tiles_y, const float *colours, float *image, float *trans, uint32_t *order,
-                              float *fill_colours, uint8_t *marks, hipStream_t st);
+                              float *fill_colours, uint8_t *marks, uint32_t *odd, hipStream_t st);
 hipError_t launch_decode_eval_view(const uint8_t *blocks, const BandArgs &b, uint64_t n_prims, const float *pos,
                                    const uint32_t *perm, const float view[3], const uint32_t *prim_idx, uint64_t m,
                                    float *out, hipStream_t st);

@@ -1,6 +1,6 @@
-"""GPU: blend_tiles reads nothing of slots that no tile lists.  Their perm
-entries may name no primitive, their primitives' positions and blocks may hold
-anything, on the route that computes the colours first too, which a list
+"""GPU: what slots that no tile lists hold does not matter to blend_tiles.  Their
+perm entries may name no primitive, their primitives' positions and blocks may
+hold anything, on the route that computes the colours first too, which a list
 buffer longer than the entries in use also takes; the image is that of the
 whole scene bit for bit."""
 import numpy as np
@@ -51,3 +51,29 @@ def test_only_listed_slots_are_read(n, arrangement, share):
         ctx.sync()
     for a, b in ((img, ref), (T, refT), (got, ref), (gotT, refT)):
         assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+
+
+@pytest.mark.parametrize("rows", ["own", "more"])
+def test_all_slots_or_marked_ones(rows):
+    """Long lists over a scene whose perm names its own primitives (every slot is
+    decoded) and over a part of a larger set (perm beyond n_prims: the listed
+    ones only), in turn on one context."""
+    from paper_2607_14513_amd import gsbc
+    n, tx, ty = 20_011, 6, 4
+    with gsbc.Context(0) as ctx:
+        blocks, d, pos, perm, mu, foot, ts, lst = _inputs(ctx, gsbc, n, tx, ty, 23, 0)
+        lst = np.concatenate([lst, np.full(1 << 15, 7, np.int32)])
+        if rows == "more":          # the same primitives behind n others
+            pos, mu, foot = (torch.cat([torch.full_like(t, float("nan")), t]) for t in (pos, mu, foot))
+            perm = perm + n
+        tail = (mu, foot, dev(ts.astype(np.int32)), dev(lst), tx, ty)
+        colours = ctx.decode_eval_view(blocks, d, pos, perm, VIEW)
+        ref, refT = ctx.blend_tiles_colours(colours, perm, *tail)
+        used = np.unique(lst[:ts[-1]])
+        off = np.setdiff1d(np.arange(n), used)
+        wild = perm.clone()
+        wild[torch.from_numpy(off).cuda()] = 0x7FFFFFFF
+        for p in (perm, wild, perm):
+            got, gotT = ctx.blend_tiles(blocks, d, pos, p, VIEW, *tail)
+            assert torch.equal(got.view(torch.int32), ref.view(torch.int32))
+            assert torch.equal(gotT.view(torch.int32), refT.view(torch.int32))
